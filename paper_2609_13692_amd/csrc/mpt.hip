@@ -2131,69 +2131,296 @@ constexpr Subsets make_subsets() {
 }
 __constant__ Subsets c_subsets = make_subsets();
 
-// Row 0: the DP over the L requests of the in-row part alone (S_H empty),
-// level by level in |S_L|, a group of lanes per subset; the key of a candidate is
-// C'(A) + C'(S ^ A) + A's mask, with A holding lowbit(S). Writes row 0 to the
-// plain table (it is only ever a B row; NARROW: to the narrow plain table as
-// well, for the self pairs) and its splits.
+// The DP over the requests of one row alone (row 0 of the row-blocked DP,
+// and whole instances of at most L requests), by one workgroup in LDS.
+//
+// A mask X = X2 << CB | X1 has r2 middle bits X2 and CB low bits X1; blocks
+// of NB entries share X2 (as in the rows above). An entry is C(X) << L | X
+// (tagged); a candidate's key is a tagged entry of the part holding
+// lowbit(S) plus the other part's entry without its tag, so the least key
+// is the least cost and, among equal costs, the smallest such part. Levels
+// k = |S2| run in order:
+//   pairs   A2 (+) B2 = S2, both non-empty, A2 holding lowbit(S2): both
+//           blocks are complete. lowbit(S) lies in S1 when S1 is not empty,
+//           so for S1 != 0 either block may hold it (two candidates per A1
+//           that holds lowbit(S1)), and for S1 = 0 block A2 does: 27
+//           candidates per pair from two block loads. 2^glog lanes share one
+//           S2 (row_group_log: the most that keep a level within one pass of
+//           the workgroup, so a level's chain is at most four pairs);
+//   blocks  S2 with the empty set, one thread per block: the entries of S2
+//           by popcount of S1, against block 0 on either side.
+// What bounds it: a chain of ten levels, each two barriers, a few LDS round
+// trips and one block's dependent chain; the arithmetic is 0.27M candidates.
+// Before, a lane group per subset gathered two entries per candidate: row 0
+// took 71 us (72 us inside the m = 25 step) and an m = 12 instance 16
+// launches of one popcount layer each (81 us of kernels, 160 us with gaps).
+constexpr int row_group_log(int k) {     // k = 2 .. R2: log2 of the lanes that share one S2
+    constexpr int g[10] = {0, 0, 1, 2, 3, 3, 3, 4, 6, 8};
+    return g[k];
+}
+constexpr bool row_groups_fit() {
+    for (int k = 2; k <= R2; ++k)
+        if ((int)kBinom.v[R2][k] << row_group_log(k) > THREADS || row_group_log(k) > k - 1) return false;
+    return true;
+}
+static_assert(R2 == 9 && row_groups_fit(), "every level's pairs run in one pass of the workgroup");
+
+template <class E> __device__ inline uint32_t row_pos(uint32_t slot, int x) {
+    return sizeof(E) == 4 ? npos(slot, x) : lpos(slot, x);
+}
+template <class E> __device__ inline E row_plain(E t) { return t & ~(E)(ROW - 1); }
+
+// the candidates of one pair of complete blocks (a: A2, which holds
+// lowbit(S2); b: B2), both tagged
+template <class E>
+__device__ inline void row_conv(const E (&a)[NB], const E (&b)[NB], E (&best)[NB]) {
+    auto take = [&](int s1, E key) { best[s1] = key < best[s1] ? key : best[s1]; };
+    take(0, a[0] + row_plain(b[0]));
+#pragma unroll
+    for (int s1 = 1; s1 < NB; ++s1) {
+        const int low = s1 & -s1;
+#pragma unroll
+        for (int a1 = 1; a1 < NB; ++a1) {
+            if ((a1 & ~s1) || !(a1 & low)) continue;
+            take(s1, a[a1] + row_plain(b[s1 ^ a1]));
+            take(s1, b[a1] + row_plain(a[s1 ^ a1]));
+        }
+    }
+}
+
+// One row's DP over r2 <= R2 middle bits. w: W of this thread's block (the
+// threads take the blocks in order of popcount: row_block); t receives the
+// tagged entries (block layout of the rows), acc the split of every entry
+// (plain mask order; 0 for at most one request). Ends with a barrier.
+template <class E>
+__device__ inline void row_dp(int r2, int own_k, uint32_t own_s2, const E (&w)[NB], E *t, E *acc) {
+    const uint32_t tid = threadIdx.x;
+    for (uint32_t e = tid; e < (uint32_t)NB << r2; e += THREADS) acc[e] = ~(E)0;
+    auto finish_block = [&](bool first, const E (&b0)[NB], const E (&key)[NB]) {
+        // S1 in order of popcount, so that every smaller entry is ready
+        E out[NB], sp[NB];
+        const uint32_t tag = own_s2 << CB;
+        const bool single = (own_s2 & (own_s2 - 1u)) == 0;
+#pragma unroll
+        for (int pc = 0; pc <= CB; ++pc) {
+#pragma unroll
+            for (int s1 = 0; s1 < NB; ++s1) {
+                if (cpop(s1) != pc) continue;
+                const int low = s1 & -s1;
+                E k = key[s1];
+#pragma unroll
+                for (int a1 = 1; a1 < NB; ++a1) {
+                    if ((a1 & ~s1) || !(a1 & low)) continue;
+                    if (a1 != s1) {
+                        const E c = out[a1] + row_plain(first ? out[s1 ^ a1] : b0[s1 ^ a1]);
+                        k = c < k ? c : k;
+                    }
+                    if (!first) {
+                        const E c = b0[a1] + row_plain(out[s1 ^ a1]);
+                        k = c < k ? c : k;
+                    }
+                }
+                const bool leaf = first ? pc <= 1 : (s1 == 0 && single);
+                const E c = leaf ? (first && s1 == 0 ? (E)0 : w[s1]) : (k >> L) - w[s1];
+                out[s1] = (c << L) | tag | (E)s1;
+                sp[s1] = leaf ? (E)0 : k & (E)(ROW - 1);
+            }
+        }
+        const uint32_t sl = slot_of(own_s2);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+            t[row_pos<E>(sl, x)] = out[x];
+            acc[tag | (uint32_t)x] = sp[x];
+        }
+    };
+    lds_barrier();      // acc is set before any block or pair writes it
+    if (own_k == 0) {
+        E none[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) none[x] = ~(E)0;
+        finish_block(true, none, none);
+    }
+    lds_barrier();
+    for (int k = 1; k <= r2; ++k) {
+        const int glog = row_group_log(k);
+        const uint32_t n_blk = c_binom.v[r2][k];
+        const uint32_t gi = tid >> glog, j = tid & ((1u << glog) - 1u);
+        if (k >= 2 && gi < n_blk) {
+            // (masks below 2^r2 come first among the masks of a popcount)
+            const uint32_t s2 = c_blocks.v[c_blocks.begin[k] + (int)gi];
+            const uint32_t low = s2 & (0u - s2), rest = s2 ^ low;
+            const uint32_t n = (1u << (k - 1)) - 1u;          // proper submasks of rest
+            const uint32_t step = deposit(1u << glog, rest);
+            const uint32_t slot_s2 = slot_of(s2);
+            uint32_t ap = deposit(j, rest);
+            E best[NB];
+#pragma unroll
+            for (int x = 0; x < NB; ++x) best[x] = ~(E)0;
+            for (uint32_t q = j; q < n; q += 1u << glog) {
+                const uint32_t sa = slot_of(low | ap);
+                E a[NB], b[NB];
+                load_blk(t, sa, a);
+                load_blk(t, slot_s2 ^ sa, b);
+                row_conv<E>(a, b, best);
+                ap = ((ap | ~rest) + step) & rest;
+            }
+            const uint32_t seg = glog < 4 ? 1u << glog : 16u;
+            if constexpr (sizeof(E) == 4) {
+                const uint32_t lane = tid & (kWave - 1);
+#pragma unroll
+                for (int x = 0; x < NB; ++x) {
+                    const uint32_t g = group_min32((uint32_t)best[x], seg);
+                    if ((lane & (seg - 1u)) == 0) atomicMin((uint32_t *)&acc[(s2 << CB) | (uint32_t)x], g);
+                }
+            } else {
+                flush_group<uint64_t>(best, s2, seg, acc);
+            }
+        }
+        lds_barrier();
+        if (own_k == k) {
+            E b0[NB], key[NB];
+            load_blk(t, 0u, b0);
+#pragma unroll
+            for (int x = 0; x < NB; ++x) key[x] = acc[(own_s2 << CB) | (uint32_t)x];
+            finish_block(false, b0, key);
+        }
+        lds_barrier();
+    }
+}
+
+// the block of thread tid among the 2^r2 middle masks in order of popcount:
+// its level (-1: none) and middle mask
+__device__ inline void row_block(int r2, int &k, uint32_t &s2) {
+    int at = (int)threadIdx.x;
+    k = -1;
+    s2 = 0;
+    for (int q = 0; q <= r2; ++q) {
+        const int n = (int)c_binom.v[r2][q];
+        if (at >= 0 && at < n) { k = q; s2 = c_blocks.v[c_blocks.begin[q] + at]; }
+        at -= n;
+    }
+}
+
+// Row 0 of the row-blocked DP (S_H empty). Writes it to the plain table (it
+// is only ever a B row; NARROW: to the narrow plain table as well, for the
+// self pairs) and its splits.
 template <class K, bool NARROW>
 __global__ __launch_bounds__(THREADS) void k_rb_row0(int m, const int64_t *__restrict__ Wr,
                                                      uint64_t *__restrict__ Pt, uint32_t *__restrict__ Pn,
                                                      uint32_t *__restrict__ Sr) {
-    __shared__ uint64_t c[ROW];
-    __shared__ int64_t wrow[ROW];          // W of row 0, read once
-    __shared__ uint32_t spl[ROW];
+    typedef typename std::conditional<NARROW, uint32_t, uint64_t>::type E;
+    __shared__ __align__(16) E t[ROW];
+    __shared__ __align__(16) E acc[ROW];
     const int H = m - L;
-    const uint64_t mask = ((uint64_t)1 << m) - 1u;
-    for (int e = threadIdx.x; e < ROW; e += THREADS) {
-        const int64_t w = Wr[e];
-        wrow[e] = w;
-        c[e] = __popc((uint32_t)e) == 1 ? (uint64_t)w << m : 0u;         // C(empty) = 0 is never a part
-        spl[e] = 0u;
+    int own_k;
+    uint32_t own_s2;
+    row_block(R2, own_k, own_s2);
+    E w[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) w[x] = (E)Wr[(own_s2 << CB) | (uint32_t)x];
+    row_dp<E>(R2, own_k, own_s2, w, t, acc);
+    // in stored order: two entries (16 bytes) of the wide plain row at a time
+    for (uint32_t p = threadIdx.x; p < (uint32_t)ROW / 2; p += THREADS) {
+        const uint32_t slot = p % (uint32_t)NS2;
+        const int x = 2 * (int)(p / (uint32_t)NS2);
+        const uint64_t c0 = (uint64_t)(t[row_pos<E>(slot, x)] >> L), c1 = (uint64_t)(t[row_pos<E>(slot, x + 1)] >> L);
+        *reinterpret_cast<ulonglong2 *>(Pt + lpos(slot, x)) =
+            make_ulonglong2(Key<K>::store(c0 << m), Key<K>::store(c1 << m));
     }
-    __syncthreads();
-    const int wv = (int)(threadIdx.x / kWave), lane = (int)(threadIdx.x & (kWave - 1));
-    for (int p = 2; p <= L; ++p) {
-        // one thread per subset while a subset has at most 63 candidates,
-        // two at |S| = 8 (each level is then one round of the workgroup), a
-        // wave per subset above; lane li of a group takes candidates li,
-        // li + G, ..., its A' stepping by a masked add of G
-        const int G = p <= 7 ? 1 : p == 8 ? 2 : kWave;
-        const uint32_t n_sub = (uint32_t)(c_subsets.begin[p + 1] - c_subsets.begin[p]);
-        const uint32_t per_wave = (uint32_t)(kWave / G);
-        const uint32_t gl = (uint32_t)(lane / G), li = (uint32_t)(lane % G);
-        for (uint32_t r0 = (uint32_t)wv * per_wave; r0 < n_sub; r0 += (uint32_t)(THREADS / kWave) * per_wave) {
-            const uint32_t r = r0 + gl;
-            uint64_t kb = ~0ull;
-            uint32_t S = 0;
-            if (r < n_sub) {
-                S = c_subsets.v[c_subsets.begin[p] + (int)r];
-                const uint32_t lb = S & (0u - S), rest = S ^ lb;
-                const uint32_t n_a = (1u << (p - 1)) - 1u;   // A = lb | A', A' a proper subset of rest
-                const uint32_t step = deposit((uint32_t)G, rest);
-                uint32_t ap = deposit(li, rest);
-                for (uint32_t t = li; t < n_a; t += (uint32_t)G) {
-                    const uint32_t A = lb | ap;
-                    const uint64_t key = c[A] + c[S ^ A] + ((uint64_t)A << H);
-                    kb = key < kb ? key : kb;
-                    ap = ((ap | ~rest) + step) & rest;
+    for (uint32_t e = threadIdx.x; e < (uint32_t)ROW; e += THREADS) {
+        if constexpr (NARROW) Pn[e] = row_plain<E>(t[e]);      // (t has the narrow rows' layout)
+        Sr[e] = (uint32_t)acc[e] << H;
+    }
+}
+
+// Whole instances of m <= L requests: the row DP on W, C and split in mask
+// order, in one launch. The total sum_i w(R_i) picks the width inside the
+// kernel, so that nothing is read back: 32-bit keys below 2^20 - 1 (C(A) +
+// C(B) <= total, shifted by L = 12 bits), 64-bit keys below 2^50; above, (cost,
+// part) pairs by lane groups per subset. For m < CB the block's missing requests hold
+// nothing: they cost 0 and reach no subset that is written.
+__global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__restrict__ W, int64_t *__restrict__ C,
+                                                      uint32_t *__restrict__ split) {
+    __shared__ __align__(16) uint64_t t64[ROW];
+    __shared__ __align__(16) uint64_t acc64[ROW];
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const uint32_t n = 1u << m;
+    const int r2 = m > CB ? m - CB : 0;
+    int own_k;
+    uint32_t own_s2;
+    row_block(r2, own_k, own_s2);
+    int64_t w[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) {
+        const uint32_t e = (own_s2 << CB) | (uint32_t)x;
+        w[x] = e < n ? W[e] : 0;
+    }
+    // every wave sums the m request weights; one past 2^50 counts as 2^50
+    constexpr int64_t kWide = (int64_t)1 << 50;
+    int64_t total = lane < m ? W[1u << lane] : 0;
+    if (total < 0 || total > kWide) total = kWide;
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) total += __shfl_xor(total, off, kWave);
+    if (total < kNarrowTotal - 1) {
+        uint32_t w32[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) w32[x] = (uint32_t)w[x];
+        uint32_t *t = reinterpret_cast<uint32_t *>(t64), *acc = reinterpret_cast<uint32_t *>(acc64);
+        row_dp<uint32_t>(r2, own_k, own_s2, w32, t, acc);
+        for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
+            C[e] = e ? (int64_t)(t[npos(slot_of(e >> CB), (int)(e & (NB - 1u)))] >> L) : kInf;
+            split[e] = acc[e];
+        }
+    } else if (total < kWide) {
+        uint64_t w64[NB];
+#pragma unroll
+        for (int x = 0; x < NB; ++x) w64[x] = (uint64_t)w[x];
+        row_dp<uint64_t>(r2, own_k, own_s2, w64, t64, acc64);
+        for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
+            C[e] = e ? (int64_t)(t64[lpos(slot_of(e >> CB), (int)(e & (NB - 1u)))] >> L) : kInf;
+            split[e] = (uint32_t)acc64[e];
+        }
+    } else {
+        int64_t *c = reinterpret_cast<int64_t *>(t64);
+        uint32_t *spl = reinterpret_cast<uint32_t *>(acc64);
+        for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
+            c[e] = (e & (e - 1u)) == 0 && e ? W[e] : 0;
+            spl[e] = 0u;
+        }
+        lds_barrier();
+        const uint32_t wv = threadIdx.x / kWave;
+        for (int p = 2; p <= m; ++p) {
+            // one lane per subset while it has at most 63 candidates, a wave
+            // above; lane li takes candidates li, li + G, ... in ascending A
+            const uint32_t G = p <= 7 ? 1u : (uint32_t)kWave, per_wave = (uint32_t)kWave / G;
+            const uint32_t n_sub = c_binom.v[m][p], gl = (uint32_t)lane / G, li = (uint32_t)lane % G;
+            for (uint32_t r0 = wv * per_wave; r0 < n_sub; r0 += (uint32_t)(THREADS / kWave) * per_wave) {
+                const uint32_t r = r0 + gl;
+                int64_t best = INT64_MAX;
+                uint32_t best_a = ~0u, S = 0;
+                if (r < n_sub) {
+                    S = c_subsets.v[c_subsets.begin[p] + (int)r];
+                    const uint32_t lb = S & (0u - S), rest = S ^ lb;
+                    const uint32_t n_a = (1u << (p - 1)) - 1u;
+                    const uint32_t step = deposit(G, rest);
+                    uint32_t ap = deposit(li, rest);
+                    for (uint32_t q = li; q < n_a; q += G) {
+                        lex_min(best, best_a, c[lb | ap] + c[S ^ (lb | ap)], lb | ap);
+                        ap = ((ap | ~rest) + step) & rest;
+                    }
+                }
+                if (G > 1u) wave_lex_min(best, best_a);
+                if (r < n_sub && li == 0) {
+                    c[S] = best - W[S];
+                    spl[S] = best_a;
                 }
             }
-            for (int off = G / 2; off > 0; off >>= 1) {
-                const uint64_t o = __shfl_xor(kb, off, kWave);
-                kb = o < kb ? o : kb;
-            }
-            if (r < n_sub && li == 0) {
-                c[S] = ((kb >> m) - (uint64_t)wrow[S]) << m;
-                spl[S] = (uint32_t)(kb & mask);
-            }
+            lds_barrier();
         }
-        __syncthreads();
-    }
-    for (int e = threadIdx.x; e < ROW; e += THREADS) {
-        Pt[lpos(slot_of((uint32_t)e >> CB), e & (NB - 1))] = Key<K>::store(c[e]);
-        if (NARROW) Pn[npos(slot_of((uint32_t)e >> CB), e & (NB - 1))] = (uint32_t)(c[e] >> m) << L;
-        Sr[e] = spl[e];
+        for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
+            C[e] = e ? c[e] : kInf;
+            split[e] = spl[e];
+        }
     }
 }
 
@@ -2814,6 +3041,18 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             return MPT_OK;
         }
     }
+    if (m < kRbMinM) {
+        // at most one row of requests: one launch, which picks its key width
+        LaunchScope ls("dp_small", (std::pow(3.0, m) + 1.0) / 2.0 - (double)n, s);
+        rb::k_dp_small<<<1, rb::THREADS, 0, s>>>(m, W, C, split);
+        MPT_HIP_TRY(hipGetLastError());
+        if (opt_cost) {
+            MPT_HIP_TRY(hipMemcpyAsync(opt_cost, C + (n - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s));
+            MPT_HIP_TRY(hipStreamSynchronize(s));
+        }
+        return MPT_OK;
+    }
+    // costs too large to pack: the plain kernels, one launch per popcount layer
     {
         LaunchScope ls("dp_init", 8.0 * n, s);
         k_dp_init<<<grid_for(n, 256, 16384), 256, 0, s>>>(m, W, C, split);
