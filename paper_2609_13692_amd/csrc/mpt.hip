@@ -2151,9 +2151,10 @@ __constant__ Subsets c_subsets = make_subsets();
 //           by popcount of S1, against block 0 on either side.
 // What bounds it: a chain of ten levels, each two barriers, a few LDS round
 // trips and one block's dependent chain; the arithmetic is 0.27M candidates.
-// Before, a lane group per subset gathered two entries per candidate: row 0
-// took 71 us (72 us inside the m = 25 step) and an m = 12 instance 16
-// launches of one popcount layer each (81 us of kernels, 160 us with gaps).
+// Row 0 takes 23 us and an m = 12 instance 25 us. Before, a lane group per
+// subset gathered two entries per candidate: row 0 took 71 us, and an m = 12
+// instance 16 launches of one popcount layer each (81 us of kernels, 160 us
+// with gaps).
 constexpr int row_group_log(int k) {     // k = 2 .. R2: log2 of the lanes that share one S2
     constexpr int g[10] = {0, 0, 1, 2, 3, 3, 3, 4, 6, 8};
     return g[k];
@@ -2561,6 +2562,113 @@ __global__ __launch_bounds__(256) void k_extract(int m, int64_t n_chunks, int64_
         }
         keys[j] = key;
     }
+}
+
+// Up to kShortOrders request slots, in one launch: a workgroup per request
+// takes its keys to LDS, orders them there and writes the request's range.
+// With VALIDATE every workgroup checks the whole input (offsets, one lane per
+// request walking its path, all chunk ids), so that none writes before all of
+// it is known to be sound; workgroup 0 reports the error bits. Positions by
+// counting smaller keys (ties by slot) up to kRankOrders chunks, a bitonic
+// sort in LDS above.
+// Bound by latency: the walk is up to m - 1 dependent reads of split. The
+// sort of all nnz keys that it replaces for these sizes padded them to one
+// tile of 4096 keys and took four launches: 33 us in the tile sort whatever
+// nnz was and 12 us in the others, against 7 us here (m = 16, 128 slots). A limit on nnz and not on the longest request, because
+// only nnz is known on the host.
+constexpr int kShortOrders = 4096;
+constexpr int kRankOrders = 512;      // 512^2 comparisons on one CU take about 7 us, the sort's 45 stages as long
+constexpr int kOrderThreads = 256;
+template <bool VALIDATE>
+__global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t n_chunks, int64_t nnz,
+                                                                 const int64_t *__restrict__ req_off,
+                                                                 const int32_t *__restrict__ req_chunks,
+                                                                 const uint32_t *__restrict__ sig,
+                                                                 const uint32_t *__restrict__ split,
+                                                                 int32_t *__restrict__ order_chunks, WsHeader *h) {
+    __shared__ uint64_t keys[kShortOrders];
+    __shared__ int64_t off[32];
+    __shared__ uint32_t path[32];
+    __shared__ int depth_n;
+    __shared__ uint32_t err;
+    const int tid = (int)threadIdx.x, own = (int)blockIdx.x;
+    if (tid <= m) off[tid] = req_off[tid];
+    if (tid == 0) err = 0;
+    __syncthreads();
+    if (VALIDATE) {
+        bool ok = off[0] == 0 && off[m] == nnz;
+        for (int i = 0; i < m; ++i) ok = ok && off[i] <= off[i + 1];
+        if (!ok) {                                    // (the same for every thread of every workgroup)
+            if (own == 0 && tid == 0) h->err = ERR_INVALID;
+            return;
+        }
+    }
+    // request tid's path (VALIDATE), or the own request's only
+    if (VALIDATE ? tid < m : tid == own) {
+        const uint32_t full = (1u << m) - 1u;
+        uint32_t node = full;
+        int d = 0;
+        bool bad = false;
+        if (tid == own) path[0] = node;
+        while (__popc(node) > 1 && d < 31) {
+            const uint32_t a = split[node];
+            const uint32_t low = node & (0u - node);
+            if ((a & ~node) || a == 0 || a == node || !(a & low)) { bad = true; break; }
+            node = ((a >> tid) & 1u) ? a : (node ^ a);
+            ++d;
+            if (tid == own) path[d] = node;
+        }
+        if (tid == own) depth_n = d + 1;
+        if (bad) atomicOr(&err, (uint32_t)ERR_INVALID);
+    }
+    if (VALIDATE)
+        for (int64_t j = tid; j < nnz; j += kOrderThreads) {
+            const int32_t x = req_chunks[j];
+            if (x < 0 || (int64_t)x >= n_chunks) atomicOr(&err, (uint32_t)ERR_RANGE);
+        }
+    __syncthreads();
+    const uint32_t e_all = err;
+    if (VALIDATE && own == 0 && tid == 0) h->err = e_all;
+    if (e_all) return;
+    const int64_t lo = off[own];
+    const int len = (int)(off[own + 1] - lo);
+    const int dn = depth_n;
+    int n2 = 1;
+    while (n2 < len) n2 <<= 1;
+    for (int e = tid; e < n2; e += kOrderThreads) {
+        uint64_t key = ~0ull;                         // padding of the sort
+        if (e < len) {
+            const uint32_t x = (uint32_t)req_chunks[lo + e];
+            const uint32_t s = sig[x];
+            int d = 0;
+            while (d < dn - 1 && (path[d] & ~s)) ++d;
+            key = ((uint64_t)d << 32) | x;
+        }
+        keys[e] = key;
+    }
+    __syncthreads();
+    if (len <= kRankOrders) {
+        for (int e = tid; e < len; e += kOrderThreads) {
+            const uint64_t key = keys[e];
+            int pos = 0;
+            for (int f = 0; f < len; ++f) {
+                const uint64_t o = keys[f];
+                pos += (o < key || (o == key && f < e)) ? 1 : 0;
+            }
+            order_chunks[lo + pos] = (int32_t)(key & 0xffffffffu);
+        }
+        return;
+    }
+    for (int k = 2; k <= n2; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int p = tid; p < n2 / 2; p += kOrderThreads) {
+                const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), l = i + j;
+                const uint64_t x = keys[i], y = keys[l];
+                if ((x > y) == ((i & k) == 0)) { keys[i] = y; keys[l] = x; }
+            }
+            __syncthreads();
+        }
+    for (int e = tid; e < len; e += kOrderThreads) order_chunks[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
 }
 
 __global__ void k_fill_u64(uint64_t *p, int64_t from, int64_t to, uint64_t v) {
@@ -3098,6 +3206,17 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
     if ((rc = check_ws(workspace, workspace_bytes, L.extract_end))) return rc;
     char *ws = (char *)workspace;
     WsHeader *h = (WsHeader *)ws;
+    if (nnz <= kShortOrders) {
+        LaunchScope ls("extract", (double)nnz, s);
+        if (validate)
+            k_extract_short<true><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
+                                                              order_chunks, h);
+        else
+            k_extract_short<false><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
+                                                               order_chunks, h);
+        MPT_HIP_TRY(hipGetLastError());
+        return validate ? read_errors(h, s) : MPT_OK;
+    }
     if (validate) {
         k_header_init<<<1, 64, 0, s>>>(h);
         k_check_offsets<<<1, 64, 0, s>>>(m, nnz, req_off, h);
