@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <cstring>
 #include <new>
 
 #include "common.h"
@@ -91,6 +92,30 @@ struct mpt_ctx {
 };
 
 namespace {
+
+constexpr size_t kHostImage = 16384;    // bytes of a host instance that goes over in one copy
+
+// where memory lies, as the runtime knows it (an address it does not know is
+// ordinary host memory)
+hipMemoryType memory_type(const void *p, int *device) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return hipMemoryTypeUnregistered;
+    }
+    *device = at.device;
+    return at.type;
+}
+bool on_device(const void *p, int device) {
+    int d = -1;
+    return memory_type(p, &d) == hipMemoryTypeDevice && d == device;
+}
+// (pinned memory stays with stream-ordered copies: work on the stream may
+// still be writing it)
+bool on_host(const void *p) {
+    int d = -1;
+    return memory_type(p, &d) == hipMemoryTypeUnregistered;
+}
 
 int table_info(const mpt_ctx *c, int which, size_t *off, size_t *bytes) {
     const size_t n = (size_t)1 << c->m;
@@ -194,15 +219,45 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
         ctx->n_chunks = n_chunks;
         ctx->nnz = nnz;
         hipStream_t s = ctx->stream;
-        MPT_HIP_TRY(hipMemcpyAsync(ctx->at<void>(L.req_off), req_off, 8 * (size_t)(m + 1), hipMemcpyDefault, s));
-        if (nnz > 0)
-            MPT_HIP_TRY(hipMemcpyAsync(ctx->at<void>(L.req_chunks), req_chunks, 4 * (size_t)nnz, hipMemcpyDefault, s));
-        if (n_chunks > 0)
-            MPT_HIP_TRY(hipMemcpyAsync(ctx->at<void>(L.chunk_w), chunk_w, 8 * (size_t)n_chunks, hipMemcpyDefault, s));
+        int64_t *d_off = ctx->at<int64_t>(L.req_off), *d_w = ctx->at<int64_t>(L.chunk_w);
+        int32_t *d_chunks = ctx->at<int32_t>(L.req_chunks);
+        const size_t b_off = 8 * (size_t)(m + 1), b_chunks = 4 * (size_t)nnz, b_w = 8 * (size_t)n_chunks;
+        // Inputs in this device's memory, outside the workspace: the build's
+        // first kernel reads them in place and leaves the copies. Otherwise
+        // they are copied first; the three arrays lie one after the other in
+        // the workspace (sig follows), so a small instance in host memory goes
+        // over in one copy, from an image of that stretch.
+        mptcore::InputCopy copy{};
+        const int64_t *in_off = d_off, *in_w = d_w;
+        const int32_t *in_chunks = d_chunks;
+        char image[kHostImage];
+        bool staged = false;
+        auto in_place = [&](const void *p) {
+            const char *q = (const char *)p;
+            return on_device(p, ctx->device) && (q < ctx->ws || q >= ctx->ws + ctx->ws_bytes);
+        };
+        if (in_place(req_off) && (nnz == 0 || in_place(req_chunks)) && (n_chunks == 0 || in_place(chunk_w))) {
+            copy = {d_w, d_off, d_chunks};
+            in_off = req_off;
+            in_w = chunk_w;
+            in_chunks = req_chunks;
+        } else if (L.sig - L.req_off <= sizeof image && on_host(req_off) && (nnz == 0 || on_host(req_chunks)) &&
+                   (n_chunks == 0 || on_host(chunk_w))) {
+            std::memcpy(image, req_off, b_off);
+            if (nnz > 0) std::memcpy(image + (L.req_chunks - L.req_off), req_chunks, b_chunks);
+            if (n_chunks > 0) std::memcpy(image + (L.chunk_w - L.req_off), chunk_w, b_w);
+            staged = true;
+            MPT_HIP_TRY(hipMemcpyAsync(d_off, image, L.chunk_w - L.req_off + b_w, hipMemcpyHostToDevice, s));
+        } else {
+            MPT_HIP_TRY(hipMemcpyAsync(d_off, req_off, b_off, hipMemcpyDefault, s));
+            if (nnz > 0) MPT_HIP_TRY(hipMemcpyAsync(d_chunks, req_chunks, b_chunks, hipMemcpyDefault, s));
+            if (n_chunks > 0) MPT_HIP_TRY(hipMemcpyAsync(d_w, chunk_w, b_w, hipMemcpyDefault, s));
+        }
         int64_t total = 0;
-        const int rc = mptcore::build(m, n_chunks, nnz, ctx->at<int64_t>(L.chunk_w), ctx->at<int64_t>(L.req_off),
-                                      ctx->at<int32_t>(L.req_chunks), ctx->at<uint32_t>(L.sig), ctx->at<int64_t>(L.W),
-                                      ctx->ws + L.core, L.core_bytes, s, &total, ctx->route);
+        const int rc = mptcore::build(m, n_chunks, nnz, in_w, in_off, in_chunks, ctx->at<uint32_t>(L.sig),
+                                      ctx->at<int64_t>(L.W), ctx->ws + L.core, L.core_bytes, s, &total, ctx->route,
+                                      copy);
+        if (rc && staged) (void)hipStreamSynchronize(s);     // (a build that succeeds has synchronised it)
         if (rc) return rc;
         ctx->total = total;
         ctx->state = BUILT;

@@ -56,7 +56,7 @@ __constant__ BinomTable c_binom = make_binom();
 
 // error bits set by device-side validation
 enum : uint32_t {
-    ERR_INVALID = 1u, ERR_RANGE = 2u, ERR_DUP = 4u, ERR_WEIGHT = 8u, ERR_OVERFLOW = 16u
+    ERR_INVALID = 1u, ERR_RANGE = 2u, ERR_DUP = 4u, ERR_WEIGHT = 8u
 };
 
 // workspace header (first 256 bytes of the caller's workspace)
@@ -119,11 +119,6 @@ __device__ inline void wave_lex_min(int64_t &v, uint32_t &a) {
 // ---------------------------------------------------------------------------
 // phase 1 kernels
 
-__global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 __global__ void k_header_init(WsHeader *h) {
     if (threadIdx.x == 0) { h->err = 0; h->n_list = 0; h->zero_weight = 0; h->total = 0; }
 }
@@ -134,6 +129,20 @@ __global__ void k_check_offsets(int m, int64_t nnz, const int64_t *req_off, WsHe
     bool ok = req_off[0] == 0 && req_off[m] == nnz;
     for (int i = 0; i < m; ++i) ok = ok && req_off[i] <= req_off[i + 1];
     if (!ok) atomicOr(&h->err, ERR_INVALID);
+}
+
+// The start of a build: the header (with the offsets' check, one lane per
+// request: m < 32) by block 0, zeroed masks by all.
+__global__ void k_build_init(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, uint32_t *sig, WsHeader *h) {
+    if (blockIdx.x == 0 && threadIdx.x < (uint32_t)kWave) {
+        const int i = (int)threadIdx.x;
+        bool bad = i < m && req_off[i] > req_off[i + 1];
+        if (i == 0) bad = bad || req_off[0] != 0 || req_off[m] != nnz;
+        const bool any = __any(bad);
+        if (i == 0) { h->err = any ? ERR_INVALID : 0u; h->n_list = 0; h->zero_weight = 0; h->total = 0; }
+    }
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n_chunks; i += (int64_t)gridDim.x * blockDim.x)
+        sig[i] = 0u;
 }
 
 // S_x: every request slot sets bit i of its chunk's mask; a bit that was
@@ -155,126 +164,92 @@ __global__ void k_demand_sets(int m, int64_t n_chunks, int64_t nnz, const int64_
     }
 }
 
-// weight check and compaction of the chunks that some request holds into a
-// (S_x, w(x)) list, in chunk order; the others only reach W(empty) and are
-// summed apart. Three passes without contended atomics: each block counts
-// its contiguous range, one workgroup scans the counts (and sums the
-// unrequested weight), each block writes its range at its offset.
+// Weight check and compaction of the chunks that some request holds into a
+// (S_x, w(x)) list, in one pass: a workgroup keeps a tile of kCompactTile
+// chunks in registers, counts, reserves its part of the list with one atomic
+// and writes it. The list's order depends on the order of the atomics; it is
+// only ever summed over, in integers. The chunks that nobody holds reach only
+// W(empty) and are summed apart; sum_i w(R_i) = sum_x |S_x| w(x) is summed
+// here too (below 2^63: at most 2^31 slots of 2^32).
+// Counting, scanning and writing took three launches, and reading the total
+// off W a fourth: 12 us of kernels and three more gaps at m = 16, 37 us of
+// kernels at 2^20 chunks against 16 us here (256 atomics on each counter;
+// one atomic per wave and address was 0.39 ms there).
 constexpr int kCompactThreads = 256;
+constexpr int kCompactPer = 16;
+constexpr int kCompactTile = kCompactThreads * kCompactPer;
 constexpr int kCompactMaxBlocks = 4096;
 
-struct CompactPlan {
-    int64_t per;     // chunks per block (a multiple of the block size)
-    uint32_t blocks;
-};
-
-inline CompactPlan compact_plan(int64_t n_chunks) {
-    const int64_t want = (n_chunks + 4095) / 4096;
-    const uint32_t blocks = (uint32_t)std::max<int64_t>(1, std::min<int64_t>(want, kCompactMaxBlocks));
-    int64_t per = (n_chunks + blocks - 1) / blocks;
-    per = (per + kCompactThreads - 1) / kCompactThreads * kCompactThreads;
-    return {std::max<int64_t>(per, kCompactThreads), blocks};
-}
-
-__device__ inline int64_t block_sum_i64(int64_t v, int64_t *red) {
+__device__ inline uint64_t wave_sum_u64(uint64_t v) {
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
-    __syncthreads();
-    int64_t s = 0;
-    for (int i = 0; i < kCompactThreads / kWave; ++i) s += red[i];
-    return s;
+    return v;
 }
 
-__global__ __launch_bounds__(kCompactThreads) void k_compact_count(int64_t n_chunks, int64_t per, const int64_t *w,
-                                                                    const uint32_t *sig, uint32_t *bcount,
-                                                                    int64_t *bzero, WsHeader *h) {
-    __shared__ int64_t red[2][kCompactThreads / kWave];
-    const int64_t lo = blockIdx.x * per, hi = min(n_chunks, lo + per);
-    int64_t taken = 0, zw = 0;
-    bool bad = false;
-    for (int64_t x = lo + threadIdx.x; x < hi; x += kCompactThreads) {
-        const int64_t wx = w[x];
-        const uint32_t sx = sig[x];
-        if (wx <= 0 || wx > MPT_MAX_CHUNK_WEIGHT) { bad = true; continue; }
-        if (sx) ++taken; else zw += wx;
-    }
-    if (bad) atomicOr(&h->err, ERR_WEIGHT);
-    taken = block_sum_i64(taken, red[0]);
-    zw = block_sum_i64(zw, red[1]);
-    if (threadIdx.x == 0) { bcount[blockIdx.x] = (uint32_t)taken; bzero[blockIdx.x] = zw; }
-}
-
-// exclusive scan of the block counts, the list length and the unrequested
-// weight into the header; one workgroup
-constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void k_compact_scan(uint32_t blocks, const uint32_t *bcount,
-                                                               const int64_t *bzero, uint32_t *boff, WsHeader *h) {
-    __shared__ uint64_t part[kScanThreads];
-    __shared__ int64_t zpart[kScanThreads];
-    const uint32_t t = threadIdx.x;
-    const uint32_t per = (blocks + kScanThreads - 1) / kScanThreads;
-    const uint32_t lo = min(blocks, t * per), hi = min(blocks, lo + per);
-    uint64_t sum = 0;
-    int64_t zs = 0;
-    for (uint32_t i = lo; i < hi; ++i) { sum += bcount[i]; zs += bzero[i]; }
-    part[t] = sum;
-    zpart[t] = zs;
-    __syncthreads();
-    for (uint32_t off = 1; off < kScanThreads; off <<= 1) {
-        const uint64_t v = t >= off ? part[t - off] : 0u;
-        const int64_t z = t >= off ? zpart[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        zpart[t] += z;
-        __syncthreads();
-    }
-    uint64_t run = t ? part[t - 1] : 0u;
-    for (uint32_t i = lo; i < hi; ++i) {
-        boff[i] = (uint32_t)run;
-        run += bcount[i];
-    }
-    if (t == kScanThreads - 1) {
-        h->n_list = (uint32_t)part[t];
-        h->zero_weight = zpart[t];
-    }
-}
-
-__global__ __launch_bounds__(kCompactThreads) void k_compact_write(int64_t n_chunks, int64_t per, int64_t cap,
-                                                                    const int64_t *w, const uint32_t *sig,
-                                                                    const uint32_t *boff, uint32_t *list_sig,
-                                                                    int64_t *list_w, WsHeader *h) {
+__global__ __launch_bounds__(kCompactThreads) void k_compact(int64_t n_chunks, int64_t cap,
+                                                             const int64_t *__restrict__ w,
+                                                             const uint32_t *__restrict__ sig,
+                                                             uint32_t *__restrict__ list_sig,
+                                                             int64_t *__restrict__ list_w, WsHeader *h) {
     constexpr int kWaves = kCompactThreads / kWave;
     __shared__ uint32_t wcount[kWaves];
+    __shared__ uint64_t wzero[kWaves], wtotal[kWaves];
+    __shared__ uint32_t at;
     const int lane = (int)(threadIdx.x & (kWave - 1)), wv = (int)(threadIdx.x / kWave);
-    const uint64_t below = lane ? (~0ull >> (kWave - lane)) : 0ull;     // lanes under this one
-    const int64_t lo = blockIdx.x * per, hi = min(n_chunks, lo + per);
-    uint32_t base = boff[blockIdx.x];
-    bool over = false;
-    // every thread of the block runs the same iterations (out-of-range lanes idle)
-    for (int64_t x0 = lo; x0 < hi; x0 += kCompactThreads) {
-        const int64_t x = x0 + threadIdx.x;
-        const int64_t wx = x < hi ? w[x] : 0;
-        const uint32_t sx = x < hi ? sig[x] : 0u;
-        const bool take = sx != 0 && wx > 0 && wx <= MPT_MAX_CHUNK_WEIGHT;
-        const uint64_t mask = __ballot(take);
-        if (lane == 0) wcount[wv] = (uint32_t)__popcll(mask);
-        __syncthreads();
-        uint32_t before = 0, all = 0;
+    const uint64_t below = (1ull << lane) - 1ull;               // lanes under this one
+    for (int64_t lo = (int64_t)blockIdx.x * kCompactTile; lo < n_chunks; lo += (int64_t)gridDim.x * kCompactTile) {
+        int64_t wx[kCompactPer];
+        uint32_t sx[kCompactPer];
+        // the last tile's missing chunks read as unheld chunks of weight 0
 #pragma unroll
-        for (int i = 0; i < kWaves; ++i) {
-            before += i < wv ? wcount[i] : 0u;
-            all += wcount[i];
+        for (int i = 0; i < kCompactPer; ++i) {
+            const int64_t x = lo + i * kCompactThreads + threadIdx.x;
+            wx[i] = x < n_chunks ? w[x] : 0;
+            sx[i] = x < n_chunks ? sig[x] : 0u;
         }
-        if (take) {
-            const uint32_t idx = base + before + (uint32_t)__popcll(mask & below);
-            if ((int64_t)idx < cap) { list_sig[idx] = sx; list_w[idx] = wx; }
-            else over = true;
+        uint64_t zero = 0, total = 0;
+        uint32_t mine = 0;                                       // entries of this wave
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < kCompactPer; ++i) {
+            const int64_t x = lo + i * kCompactThreads + threadIdx.x;
+            if (x < n_chunks && (wx[i] <= 0 || wx[i] > MPT_MAX_CHUNK_WEIGHT)) { bad = true; wx[i] = 0; sx[i] = 0u; }
+            if (sx[i]) total += (uint64_t)__popc(sx[i]) * (uint64_t)wx[i];
+            else zero += (uint64_t)wx[i];
+            mine += (uint32_t)__popcll(__ballot(sx[i] != 0u));
         }
-        base += all;
+        if (bad) atomicOr(&h->err, (uint32_t)ERR_WEIGHT);
+        zero = wave_sum_u64(zero);
+        total = wave_sum_u64(total);
+        if (lane == 0) { wcount[wv] = mine; wzero[wv] = zero; wtotal[wv] = total; }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t n = 0;
+            uint64_t z = 0, t = 0;
+#pragma unroll
+            for (int i = 0; i < kWaves; ++i) { n += wcount[i]; z += wzero[i]; t += wtotal[i]; }
+            at = n ? atomicAdd(&h->n_list, n) : 0u;
+            if (z) atomicAdd((unsigned long long *)&h->zero_weight, (unsigned long long)z);
+            if (t) atomicAdd((unsigned long long *)&h->total, (unsigned long long)t);
+        }
+        __syncthreads();
+        uint32_t base = at;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) base += i < wv ? wcount[i] : 0u;
+        bool over = false;
+#pragma unroll
+        for (int i = 0; i < kCompactPer; ++i) {
+            const uint64_t mask = __ballot(sx[i] != 0u);
+            const uint32_t idx = base + (uint32_t)__popcll(mask & below);
+            if (sx[i]) {
+                if ((int64_t)idx < cap) { list_sig[idx] = sx[i]; list_w[idx] = wx[i]; }
+                else over = true;                                // cannot happen: each entry has a slot
+            }
+            base += (uint32_t)__popcll(mask);
+        }
+        if (over) atomicOr(&h->err, (uint32_t)ERR_INVALID);
         __syncthreads();
     }
-    if (over) atomicOr(&h->err, ERR_INVALID);
 }
 
 // W table, one workgroup per tile of 2^13 consecutive subsets that share the
@@ -578,18 +553,104 @@ void dense_zeta_high(int m, int j, int K, int64_t *W, hipStream_t s) {
     }
 }
 
-// every C(S) is at most sum_{i in S} w(R_i) = sum_{i in S} W({i}); the DP
-// needs that total below 2^61
-__global__ void k_check_total(int m, const int64_t *W, WsHeader *h) {
-    if (threadIdx.x != 0) return;
-    int64_t tot = 0;
-    bool over = false;
-    for (int i = 0; i < m; ++i) {
-        int64_t v = W[(int64_t)1 << i];
-        if (v >= kCostLimit - tot) over = true; else tot += v;
+// Small instances (n_chunks and nnz up to kSmallBuild): the checks, the
+// demand sets, the compaction and, FULL (m <= 12), the W table itself, by one
+// workgroup in one launch; the masks live in LDS. off_dst, chunks_dst and
+// w_dst, where given, receive copies of the inputs (the context keeps them),
+// which saves three copies between launches.
+// Bound by latency: launches and a few dependent round trips. 4.4 us at m = 9
+// (36 slots, 64 chunks, with W) and at m = 16 (128 slots, 1000 chunks), where
+// the separate kernels took 15 us and up to eight more launches. The limit is
+// the LDS for the masks (64 KiB).
+constexpr int kSmallBuild = 16384;
+constexpr int kSmallThreads = 1024;
+template <bool FULL>
+__global__ __launch_bounds__(kSmallThreads) void k_build_small(
+        int m, int n_chunks, int nnz, const int64_t *__restrict__ w, const int64_t *__restrict__ req_off,
+        const int32_t *__restrict__ req_chunks, int64_t *__restrict__ w_dst, int64_t *__restrict__ off_dst,
+        int32_t *__restrict__ chunks_dst, uint32_t *__restrict__ sig, uint32_t *__restrict__ list_sig,
+        int64_t *__restrict__ list_w, int64_t *__restrict__ W, WsHeader *h) {
+    __shared__ uint32_t sg[kSmallBuild];
+    __shared__ __align__(16) int64_t tile[FULL ? kZetaN + kZetaN / 8 : 1];
+    __shared__ int64_t off[32];
+    __shared__ uint32_t err, n_list;
+    __shared__ unsigned long long zero_weight, total;
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1);
+    for (int x = tid; x < n_chunks; x += kSmallThreads) sg[x] = 0u;
+    if (FULL)
+        for (int e = tid; e < kZetaN + kZetaN / 8; e += kSmallThreads) tile[e] = 0;
+    if (tid <= m) {
+        off[tid] = req_off[tid];
+        if (off_dst) off_dst[tid] = off[tid];
     }
-    h->total = over ? kCostLimit : tot;
-    if (over) atomicOr(&h->err, ERR_OVERFLOW);
+    if (tid == 0) { err = 0u; n_list = 0u; zero_weight = 0ull; total = 0ull; }
+    __syncthreads();
+    if (tid < m && off[tid] > off[tid + 1]) atomicOr(&err, (uint32_t)ERR_INVALID);
+    if (tid == 0 && (off[0] != 0 || off[m] != nnz)) atomicOr(&err, (uint32_t)ERR_INVALID);
+    for (int j = tid; j < nnz; j += kSmallThreads) {
+        int lo = 0, hi = m - 1;                     // request of slot j: the last i with off[i] <= j
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (off[mid] <= j) lo = mid; else hi = mid - 1;
+        }
+        const int32_t x = req_chunks[j];
+        if (chunks_dst) chunks_dst[j] = x;
+        if (x < 0 || x >= n_chunks) { atomicOr(&err, (uint32_t)ERR_RANGE); continue; }
+        const uint32_t bit = 1u << lo;
+        if (atomicOr(&sg[x], bit) & bit) atomicOr(&err, (uint32_t)ERR_DUP);
+    }
+    __syncthreads();
+    uint64_t z = 0, tot = 0;
+    // whole waves walk the chunks (the list positions come from ballots)
+    for (int x0 = tid - lane; x0 < n_chunks; x0 += kSmallThreads) {
+        const int x = x0 + lane;
+        int64_t wx = x < n_chunks ? w[x] : 0;
+        uint32_t sx = x < n_chunks ? sg[x] : 0u;
+        if (x < n_chunks) {
+            if (w_dst) w_dst[x] = wx;
+            sig[x] = sx;
+            if (wx <= 0 || wx > MPT_MAX_CHUNK_WEIGHT) { atomicOr(&err, (uint32_t)ERR_WEIGHT); wx = 0; sx = 0u; }
+        }
+        if (sx) tot += (uint64_t)__popc(sx) * (uint64_t)wx;
+        else z += (uint64_t)wx;
+        if constexpr (FULL) {
+            if (sx) zeta_scatter(tile, sx, wx);
+        } else {
+            const uint64_t mask = __ballot(sx != 0u);
+            uint32_t at = 0;
+            if (lane == 0 && mask) at = atomicAdd(&n_list, (uint32_t)__popcll(mask));
+            at = __shfl(at, 0, kWave) + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+            // (at most nnz chunks are held, so the list has room)
+            if (sx) { list_sig[at] = sx; list_w[at] = wx; }
+        }
+    }
+    z = wave_sum_u64(z);
+    tot = wave_sum_u64(tot);
+    if (lane == 0) {
+        if (z) atomicAdd(&zero_weight, (unsigned long long)z);
+        if (tot) atomicAdd(&total, (unsigned long long)tot);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        h->err = err;
+        h->n_list = n_list;
+        h->zero_weight = (int64_t)zero_weight;
+        h->total = (int64_t)total;
+        if (FULL) tile[0] += (int64_t)zero_weight;
+    }
+    if constexpr (FULL) {
+        // bits 0 .. 4 are done (zeta_scatter); the others in place. A chunk's
+        // set only has bits below m.
+        __syncthreads();
+        for (int b = 5; b < m; ++b) {
+            for (int p = tid; p < 1 << (m - 1); p += kSmallThreads) {
+                const int e = ((p >> b) << (b + 1)) | (p & ((1 << b) - 1));
+                tile[zpos(e)] += tile[zpos(e | (1 << b))];
+            }
+            __syncthreads();
+        }
+        for (int e = tid; e < 1 << m; e += kSmallThreads) W[e] = tile[zpos(e)];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -2574,8 +2635,9 @@ __global__ __launch_bounds__(256) void k_extract(int m, int64_t n_chunks, int64_
 // Bound by latency: the walk is up to m - 1 dependent reads of split. The
 // sort of all nnz keys that it replaces for these sizes padded them to one
 // tile of 4096 keys and took four launches: 33 us in the tile sort whatever
-// nnz was and 12 us in the others, against 7 us here (m = 16, 128 slots). A limit on nnz and not on the longest request, because
-// only nnz is known on the host.
+// nnz was and 12 us in the others, against 7 us here (m = 16, 128 slots). A
+// limit on nnz and not on the longest request, because only nnz is known on
+// the host.
 constexpr int kShortOrders = 4096;
 constexpr int kRankOrders = 512;      // 512^2 comparisons on one CU take about 7 us, the sort's 45 stages as long
 constexpr int kOrderThreads = 256;
@@ -2831,7 +2893,6 @@ size_t rb_partial_entries(int m, int64_t chunk_pairs) {
 
 struct WsLayout {
     size_t list_sig, list_w, part_v, part_a, keys, rb_part, rb_tagged, rb_plain, rb_wrow, rb_srow;
-    size_t compact_count, compact_zero, compact_off;
     size_t build_end, extract_end;   // bytes the build and the extraction use
     size_t total;                    // bytes every phase fits in
 };
@@ -2853,11 +2914,6 @@ WsLayout ws_layout(int m, int64_t nnz, int64_t chunk_pairs) {
     L.list_sig = off;
     L.list_w = off + align256(nz * 4);
     size_t build_end = L.list_w + align256(nz * 8);
-    // the compaction's per-block counts, unrequested weights and offsets
-    L.compact_count = build_end;
-    L.compact_zero = L.compact_count + align256((size_t)kCompactMaxBlocks * 4);
-    L.compact_off = L.compact_zero + align256((size_t)kCompactMaxBlocks * 8);
-    build_end = L.compact_off + align256((size_t)kCompactMaxBlocks * 4);
     L.part_v = off;
     L.part_a = off + align256(P * 8);
     size_t dp_end = L.part_a + align256(P * 4);
@@ -2903,7 +2959,8 @@ int read_errors(WsHeader *h, hipStream_t s, int64_t *total = nullptr) {
     if (err & ERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
     if (err & ERR_DUP) return fail(MPT_E_DUP, "a chunk is repeated inside one request");
     if (err & ERR_WEIGHT) return fail(MPT_E_WEIGHT, "a chunk weight is <= 0 or > 2^32");
-    if (err & ERR_OVERFLOW) return fail(MPT_E_OVERFLOW, "sum of request weights reaches 2^61");
+    // (the total is below 2^63: see k_compact; only a build leaves one)
+    if (total && hh.total >= kCostLimit) return fail(MPT_E_OVERFLOW, "sum of request weights reaches 2^61");
     if (total) *total = hh.total;
     return MPT_OK;
 }
@@ -3041,7 +3098,7 @@ size_t workspace_bytes(int m, int64_t nnz, int64_t chunk_pairs) {
 
 int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const int64_t *req_off,
           const int32_t *req_chunks, uint32_t *sig, int64_t *W, void *workspace, size_t workspace_bytes,
-          hipStream_t s, int64_t *total, int route) {
+          hipStream_t s, int64_t *total, int route, const InputCopy &copy) {
     mptlib::Range range("mpt build_weights");
     int rc = check_common(m, n_chunks, nnz);
     if (rc) return rc;
@@ -3056,30 +3113,46 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
     uint32_t *list_sig = (uint32_t *)(ws + L.list_sig);
     int64_t *list_w = (int64_t *)(ws + L.list_w);
 
-    k_header_init<<<1, 64, 0, s>>>(h);
-    k_check_offsets<<<1, 64, 0, s>>>(m, nnz, req_off, h);
-    if (n_chunks > 0) {
-        {
-            LaunchScope ls("fill_sig", 4.0 * n_chunks, s);
-            k_fill_u32<<<grid_for(n_chunks, 256), 256, 0, s>>>(sig, n_chunks, 0u);
+    const bool dense = route == MPT_ROUTE_DENSE || (route == MPT_ROUTE_AUTO && dense_route_pays(m, nnz));
+    const bool small = n_chunks <= kSmallBuild && nnz <= kSmallBuild;
+    const bool full = small && m <= kZetaBits && !dense;       // the whole build in one launch
+    if (full) {
+        LaunchScope ls("weights_tile", 8.0 * (double)(1ull << m), s);
+        k_build_small<true><<<1, kSmallThreads, 0, s>>>(m, (int)n_chunks, (int)nnz, chunk_w, req_off, req_chunks,
+                                                       copy.w, copy.off, copy.chunks, sig, nullptr, nullptr, W, h);
+        MPT_HIP_TRY(hipGetLastError());
+        return read_errors(h, s, total);
+    }
+    if (small) {
+        LaunchScope ls("build_small", (double)nnz, s);
+        k_build_small<false><<<1, kSmallThreads, 0, s>>>(m, (int)n_chunks, (int)nnz, chunk_w, req_off, req_chunks,
+                                                        copy.w, copy.off, copy.chunks, sig, list_sig, list_w, W, h);
+    } else {
+        if (copy.off) {
+            MPT_HIP_TRY(hipMemcpyAsync(copy.off, req_off, 8 * (size_t)(m + 1), hipMemcpyDeviceToDevice, s));
+            if (nnz > 0)
+                MPT_HIP_TRY(hipMemcpyAsync(copy.chunks, req_chunks, 4 * (size_t)nnz, hipMemcpyDeviceToDevice, s));
+            if (n_chunks > 0)
+                MPT_HIP_TRY(hipMemcpyAsync(copy.w, chunk_w, 8 * (size_t)n_chunks, hipMemcpyDeviceToDevice, s));
+            req_off = copy.off;
+            req_chunks = copy.chunks;
+            chunk_w = copy.w;
         }
-        if (nnz > 0) {
-            LaunchScope ls("demand_sets", (double)nnz, s);
-            k_demand_sets<<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, h);
-        }
         {
+            LaunchScope ls("build_init", 4.0 * n_chunks, s);
+            k_build_init<<<grid_for(n_chunks, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, sig, h);
+        }
+        if (n_chunks > 0) {
+            if (nnz > 0) {
+                LaunchScope ls("demand_sets", (double)nnz, s);
+                k_demand_sets<<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, h);
+            }
             LaunchScope ls("compact", (double)n_chunks, s);
-            const CompactPlan cp = compact_plan(n_chunks);
-            uint32_t *bcount = (uint32_t *)(ws + L.compact_count), *boff = (uint32_t *)(ws + L.compact_off);
-            int64_t *bzero = (int64_t *)(ws + L.compact_zero);
-            k_compact_count<<<cp.blocks, kCompactThreads, 0, s>>>(n_chunks, cp.per, chunk_w, sig, bcount, bzero, h);
-            k_compact_scan<<<1, kScanThreads, 0, s>>>(cp.blocks, bcount, bzero, boff, h);
-            k_compact_write<<<cp.blocks, kCompactThreads, 0, s>>>(n_chunks, cp.per, std::max<int64_t>(nnz, 1), chunk_w,
-                                                                 sig, boff, list_sig, list_w, h);
+            k_compact<<<grid_for(n_chunks, kCompactTile, kCompactMaxBlocks), kCompactThreads, 0, s>>>(
+                n_chunks, std::max<int64_t>(nnz, 1), chunk_w, sig, list_sig, list_w, h);
         }
     }
     const uint32_t tiles = m > kZetaBits ? 1u << (m - kZetaBits) : 1u;
-    const bool dense = route == MPT_ROUTE_DENSE || (route == MPT_ROUTE_AUTO && dense_route_pays(m, nnz));
     if (!dense) {
         LaunchScope ls("weights_tile", 8.0 * (double)(1ull << m), s);
         k_weights_tile<<<std::min(tiles, 1024u), kZetaThreads, 0, s>>>(m, (uint32_t)std::max<int64_t>(nnz, 1), tiles,
@@ -3103,7 +3176,6 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
             }
         }
     }
-    k_check_total<<<1, 64, 0, s>>>(m, W, h);
     MPT_HIP_TRY(hipGetLastError());
     return read_errors(h, s, total);
 }
@@ -3276,8 +3348,9 @@ extern "C" int mpt_build_weights(int m, int64_t n_chunks, int64_t nnz, const int
                                  int64_t *W, void *workspace, size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
     return mptlib::guarded(__func__, [&]() -> int {
+        int64_t total = 0;
         return mptcore::build(m, n_chunks, nnz, chunk_w, req_off, req_chunks, sig, W, workspace, workspace_bytes,
-                              (hipStream_t)stream, nullptr, MPT_ROUTE_AUTO);
+                              (hipStream_t)stream, &total, MPT_ROUTE_AUTO, mptcore::InputCopy{});
     });
 }
 
