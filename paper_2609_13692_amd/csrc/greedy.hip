@@ -24,8 +24,8 @@
 #include <cstdint>
 #include <cstring>
 
-#include "bitonic.h"
 #include "common.h"
+#include "keysort.h"
 #include "mpt.h"
 
 namespace {
@@ -35,7 +35,6 @@ using mptlib::fail;
 using mptlib::grid_for;
 using mptlib::LaunchScope;
 using mptlib::kSegMax;
-using mptlib::kSortTile;
 using mptlib::seg_rank;
 using mptlib::sort_keys;
 
@@ -59,16 +58,9 @@ struct GHeader {
 };
 static_assert(sizeof(GHeader) == 256, "header is one 256-byte block");
 
-inline int64_t pow2_at_least(int64_t n) {
-    int64_t p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
-
 struct GLayout {
-    size_t keys1, keys2, sig, sig_len, dem, dem_off, V, best_v, best_p, active, last, touched, resc, dbuf, d_off,
+    size_t keys1, keys2, keys3, sig, sig_len, dem, dem_off, V, best_v, best_p, active, last, touched, resc, dbuf, d_off,
         d_len, rec32, rec64, total;
-    int64_t npad;
 };
 constexpr int kRec32 = 7;    // int32 arrays of the merge records
 constexpr int kRec64 = 3;    // int64 arrays of the merge records
@@ -76,11 +68,11 @@ constexpr int kRec64 = 3;    // int64 arrays of the merge records
 GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     GLayout L{};
     const size_t mm = (size_t)m;
-    L.npad = std::max<int64_t>(pow2_at_least(std::max<int64_t>(nnz, 1)), kSortTile);
     size_t o = align256(sizeof(GHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
-    L.keys1 = take(8 * (size_t)L.npad);
-    L.keys2 = take(8 * (size_t)L.npad);
+    L.keys1 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
+    L.keys2 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
+    L.keys3 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig_len = take(4 * mm);
     L.dem = take(4 * (size_t)std::max<int64_t>(nnz, 1));
@@ -175,12 +167,10 @@ __global__ void k_g_check_weights(int64_t n_chunks, const int64_t *w, GHeader *h
         if (w[x] <= 0 || w[x] > MPT_MAX_CHUNK_WEIGHT) atomicOr(&h->err, GERR_WEIGHT);
 }
 
-// (request, chunk) and (chunk, request) keys of every slot; keys past nnz
-// are padding that sorts last
-__global__ void k_g_keys(int m, int64_t n_chunks, int64_t nnz, int64_t npad, const int64_t *req_off,
+// (request, chunk) and (chunk, request) keys of every slot
+__global__ void k_g_keys(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off,
                          const int32_t *req_chunks, const int64_t *w, uint64_t *keys1, uint64_t *keys2, GHeader *h) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < npad; j += (int64_t)gridDim.x * blockDim.x) {
-        if (j >= nnz) { keys1[j] = ~0ull; keys2[j] = ~0ull; continue; }
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         int lo = 0, hi = m - 1;                     // request of slot j: last i with req_off[i] <= j
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -824,8 +814,7 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
     if (n_chunks > 0) k_g_check_weights<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, chunk_w, h);
     {
         LaunchScope ls("g_keys", (double)nnz, s);
-        k_g_keys<<<grid_for(L.npad, 256), 256, 0, s>>>(m, n_chunks, nnz, L.npad, req_off, req_chunks, chunk_w, keys1,
-                                                      keys2, h);
+        k_g_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, chunk_w, keys1, keys2, h);
     }
     MPT_HIP_TRY(hipGetLastError());
     int64_t max_len = 0;
@@ -837,10 +826,14 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
     // (request, chunk) keys unsorted and unused
     const bool short_lists = max_len <= kSegMax;
     {
-        LaunchScope ls("g_sort", 2.0 * (double)L.npad, s);
+        LaunchScope ls("g_sort", 2.0 * (double)nnz, s);
+        uint64_t *tmp = (uint64_t *)(ws + L.keys3), *free1 = tmp;
         if (short_lists) k_g_sig_short<<<std::max(1, (m + 3) / 4), 4 * kWave, 0, s>>>(m, req_off, req_chunks, sig, h);
-        else if ((rc = sort_keys(keys1, L.npad, s))) return rc;
-        if ((rc = sort_keys(keys2, L.npad, s))) return rc;
+        else if ((rc = sort_keys(keys1, tmp, nnz, s, &free1))) return rc;
+        // (the buffer that the first sort did not end in)
+        uint64_t *tmp2 = free1 == tmp ? keys1 : tmp;
+        if (!short_lists) keys1 = free1; else tmp2 = tmp;
+        if ((rc = sort_keys(keys2, tmp2, nnz, s, &keys2))) return rc;
     }
     k_g_lists<<<grid_for(std::max<int64_t>(nnz, m), 256), 256, 0, s>>>(m, nnz, short_lists ? nullptr : keys1, keys2, sig,
                                                                         sig_len, dem, req_off, h);

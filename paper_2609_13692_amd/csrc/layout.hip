@@ -31,8 +31,8 @@
 #include <cstdint>
 #include <vector>
 
-#include "bitonic.h"
 #include "common.h"
+#include "keysort.h"
 #include "mpt.h"
 #include "seqsort.h"
 
@@ -42,7 +42,6 @@ using mptlib::align256;
 using mptlib::fail;
 using mptlib::grid_for;
 using mptlib::kSegMax;
-using mptlib::kSortTile;
 using mptlib::LaunchScope;
 using mptlib::seg_rank;
 using mptlib::sort_keys;
@@ -70,9 +69,9 @@ inline int64_t pow2_at_least(int64_t n) {
 }
 
 struct LLayout {
-    size_t ord, rank, lcp, base, pn, nw, mtree, crank, cinv, keys, sched, log_off, logs, acc_start, prev, next, accw,
+    size_t ord, rank, lcp, base, pn, nw, mtree, crank, cinv, keys, keys2, sched, log_off, logs, acc_start, prev, next, accw,
         bnext, bsum, cfg_win, cfg_cap, cfg_off, cfg_list, costs, total;
-    int64_t mpad, kpad;
+    int64_t mpad;
 };
 
 // nnz bounds the trie's node count
@@ -80,8 +79,8 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     LLayout L{};
     const size_t mm = (size_t)m, nz = (size_t)std::max<int64_t>(nnz, 1), nc = (size_t)std::max(n_cfg, 0);
     L.mpad = std::max<int64_t>(pow2_at_least(m), kSeqSortTile);
-    L.kpad = std::max<int64_t>(
-        pow2_at_least(std::max(std::max<int64_t>(nnz, n_chunks), (int64_t)nc * std::max<int64_t>(m, nnz))), kSortTile);
+    // the most keys of one sort (two buffers)
+    const size_t kn = (size_t)std::max(std::max<int64_t>(nnz, n_chunks), (int64_t)nc * std::max<int64_t>(m, nnz));
     const size_t nblk = (nz + 255) / 256;       // sorted blocks of the access logs (kStackBlock entries)
     size_t o = align256(sizeof(LHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
@@ -94,7 +93,8 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     L.mtree = take(8 * (size_t)L.mpad);          // min segment tree over the LCPs
     L.crank = take(4 * (size_t)n_chunks);
     L.cinv = take(4 * (size_t)n_chunks);
-    L.keys = take(8 * (size_t)L.kpad);
+    L.keys = take(8 * kn);
+    L.keys2 = take(8 * kn);
     L.sched = take(4 * nc * mm);
     L.log_off = take(8 * nc * mm);
     L.logs = take(4 * nc * nz);
@@ -188,10 +188,9 @@ __global__ void k_l_pop_rank(int64_t n_chunks, const uint64_t *keys, int32_t *ra
 
 // key of slot j: its request in the high 32 bits, the chunk's position in
 // the order in the low 32 bits (for the id order the position is the id)
-__global__ void k_l_layout_keys(int m, int64_t nnz, int64_t npad, const int64_t *req_off, const int32_t *chunks,
+__global__ void k_l_layout_keys(int m, int64_t nnz, const int64_t *req_off, const int32_t *chunks,
                                 const int32_t *rank, int kind, uint64_t *keys) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < npad; j += (int64_t)gridDim.x * blockDim.x) {
-        if (j >= nnz) { keys[j] = ~0ull; continue; }
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         int lo = 0, hi = m - 1;                 // request of slot j
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -376,10 +375,9 @@ __global__ void k_l_paths(int m, int64_t nnz, int64_t mpad, const int64_t *off, 
 
 // key of request i under configuration c: window index, then the request's
 // position in the DFS order (windowed DFS = sort inside every window)
-__global__ void k_l_sched_keys(int m, int n_cfg, int64_t npad, const int64_t *windows, const int32_t *rank,
-                               uint64_t *keys) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < npad; e += (int64_t)gridDim.x * blockDim.x) {
-        if (e >= (int64_t)n_cfg * m) { keys[e] = ~0ull; continue; }
+__global__ void k_l_sched_keys(int m, int n_cfg, const int64_t *windows, const int32_t *rank, uint64_t *keys) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < (int64_t)n_cfg * m;
+         e += (int64_t)gridDim.x * blockDim.x) {
         const int c = (int)(e / m), i = (int)(e % m);
         const int64_t W = windows[c];
         const uint64_t win = (uint64_t)(i / W);
@@ -470,11 +468,10 @@ constexpr int kStackBlock = 256;               // log entries per sorted block
 static_assert(kStackBlock == 256, "the lockstep searches of k_l_bill take 9 halvings");
 
 // sort keys of the access logs of schedules d0 .. d0 + nd - 1: (schedule,
-// node, log position); the padding sorts last
-__global__ void k_l_acc_keys(int64_t nnz, int d0, int nd, int be, int bn, int64_t npad, const int32_t *logs,
-                             uint64_t *keys) {
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < npad; k += (int64_t)gridDim.x * blockDim.x) {
-        if (k >= (int64_t)nd * nnz) { keys[k] = ~0ull; continue; }
+// node, log position)
+__global__ void k_l_acc_keys(int64_t nnz, int d0, int nd, int be, int bn, const int32_t *logs, uint64_t *keys) {
+    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < (int64_t)nd * nnz;
+         k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t dl = k / nnz, e = k % nnz;
         const uint64_t v = (uint64_t)logs[(d0 + dl) * nnz + e];
         keys[k] = ((uint64_t)dl << (bn + be)) | (v << be) | (uint64_t)e;
@@ -728,19 +725,16 @@ extern "C" int mpt_global_order_layout(int m, int64_t n_chunks, int64_t nnz, con
     int64_t max_len = 0;
     if ((rc = l_read_errors(h, s, &max_len))) return rc;
     if (nnz == 0) return MPT_OK;
-    uint64_t *keys = (uint64_t *)(ws + L.keys);
+    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
     int32_t *rank = (int32_t *)(ws + L.crank), *inv = (int32_t *)(ws + L.cinv);
-    const int64_t kpad = L.kpad;
     LaunchScope ls("l_global_order", (double)nnz, s);
     if (order_kind == MPT_ORDER_POPULARITY) {
-        // (count, id) keys of the chunks, padded to a power of two
-        const int64_t cpad = std::max<int64_t>(pow2_at_least(n_chunks), kSortTile);
+        // (count, id) keys of the chunks
         k_l_fill_i32<<<grid_for(n_chunks, 256), 256, 0, s>>>(rank, n_chunks, 0);
         k_l_count<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, req_chunks, rank);
-        k_l_fill_u64<<<grid_for(cpad, 256), 256, 0, s>>>(keys, cpad, ~0ull);
         k_l_pop_keys<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, keys);
-        if ((rc = sort_keys(keys, cpad, s))) return rc;
-        k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, keys, rank);
+        if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
+        k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
         if (max_len > kSegMax) k_l_inverse<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, inv);
     }
     if (max_len <= kSegMax) {
@@ -748,9 +742,9 @@ extern "C" int mpt_global_order_layout(int m, int64_t n_chunks, int64_t nnz, con
         MPT_HIP_TRY(hipGetLastError());
         return MPT_OK;
     }
-    k_l_layout_keys<<<grid_for(kpad, 256), 256, 0, s>>>(m, nnz, kpad, req_off, req_chunks, rank, order_kind, keys);
-    if ((rc = sort_keys(keys, kpad, s))) return rc;
-    k_l_layout_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, keys, inv, order_kind, seqs);
+    k_l_layout_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, rank, order_kind, keys);
+    if ((rc = sort_keys(keys, keys2, nnz, s, &sorted))) return rc;
+    k_l_layout_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, inv, order_kind, seqs);
     MPT_HIP_TRY(hipGetLastError());
     return MPT_OK;
 }
@@ -821,17 +815,17 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
     MPT_HIP_TRY(hipMemcpyAsync(dev_capacity, capv.data(), sizeof(int64_t) * n_configs, hipMemcpyHostToDevice, s));
     MPT_HIP_TRY(hipMemcpyAsync(dev_cfg_off, cfg_off.data(), sizeof(int32_t) * (n_sched + 1), hipMemcpyHostToDevice, s));
     MPT_HIP_TRY(hipMemcpyAsync(dev_cfg_list, cfg_list.data(), sizeof(int32_t) * n_configs, hipMemcpyHostToDevice, s));
-    uint64_t *keys = (uint64_t *)(ws + L.keys);
+    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
     int32_t *sched = (int32_t *)(ws + L.sched), *logs = (int32_t *)(ws + L.logs);
     int32_t *acc_start = (int32_t *)(ws + L.acc_start), *prev = (int32_t *)(ws + L.prev), *next = (int32_t *)(ws + L.next);
     int64_t *log_off = (int64_t *)(ws + L.log_off), *accw = (int64_t *)(ws + L.accw);
     const int32_t *ord = (const int32_t *)(ws + L.ord), *rank = (const int32_t *)(ws + L.rank);
     {
         LaunchScope ls("l_schedules", (double)n_sched * m, s);
-        const int64_t spad = std::max<int64_t>(pow2_at_least((int64_t)n_sched * m), kSortTile);
-        k_l_sched_keys<<<grid_for(spad, 256), 256, 0, s>>>(m, n_sched, spad, dev_win, rank, keys);
-        if ((rc = sort_keys(keys, spad, s))) return rc;
-        k_l_sched_out<<<grid_for((int64_t)n_sched * m, 256), 256, 0, s>>>(m, n_sched, keys, ord, seq_off, sched,
+        const int64_t sn = (int64_t)n_sched * m;
+        k_l_sched_keys<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, dev_win, rank, keys);
+        if ((rc = sort_keys(keys, keys2, sn, s, &sorted))) return rc;
+        k_l_sched_out<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, sorted, ord, seq_off, sched,
                                                                           log_off);
         k_l_log_scan<<<n_sched, 1024, 0, s>>>(m, log_off);
         if (nnz > 0)
@@ -853,10 +847,10 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
             const int group = gb >= 8 ? n_sched : std::min(n_sched, 1 << gb);
             for (int d0 = 0; d0 < n_sched; d0 += group) {
                 const int nd = std::min(group, n_sched - d0);
-                const int64_t npad = std::max<int64_t>(pow2_at_least((int64_t)nd * nnz), kSortTile);
-                k_l_acc_keys<<<grid_for(npad, 256), 256, 0, s>>>(nnz, d0, nd, be, bn, npad, logs, keys);
-                if ((rc = sort_keys(keys, npad, s))) return rc;
-                k_l_prev_next<<<grid_for((int64_t)nd * nnz, 256), 256, 0, s>>>(nnz, d0, nd, be, keys, prev, next);
+                const int64_t an = (int64_t)nd * nnz;
+                k_l_acc_keys<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, bn, logs, keys);
+                if ((rc = sort_keys(keys, keys2, an, s, &sorted))) return rc;
+                k_l_prev_next<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, sorted, prev, next);
             }
         }
         LaunchScope ls("l_simulate", (double)n_configs * nnz, s);

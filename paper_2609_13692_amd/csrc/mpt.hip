@@ -24,9 +24,9 @@
 #include <type_traits>
 #include <vector>
 
-#include "bitonic.h"
 #include "common.h"
 #include "core.h"
+#include "keysort.h"
 #include "mpt.h"
 
 namespace {
@@ -2733,11 +2733,6 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
     for (int e = tid; e < len; e += kOrderThreads) order_chunks[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
 }
 
-__global__ void k_fill_u64(uint64_t *p, int64_t from, int64_t to, uint64_t v) {
-    for (int64_t i = from + blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < to; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 __global__ void k_extract_out(int64_t nnz, const uint64_t *keys, int32_t *order_chunks) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x)
         order_chunks[j] = (int32_t)(keys[j] & 0xffffffffu);
@@ -2892,17 +2887,10 @@ size_t rb_partial_entries(int m, int64_t chunk_pairs) {
 }
 
 struct WsLayout {
-    size_t list_sig, list_w, part_v, part_a, keys, rb_part, rb_tagged, rb_plain, rb_wrow, rb_srow;
+    size_t list_sig, list_w, part_v, part_a, keys, keys2, rb_part, rb_tagged, rb_plain, rb_wrow, rb_srow;
     size_t build_end, extract_end;   // bytes the build and the extraction use
     size_t total;                    // bytes every phase fits in
 };
-
-// keys sorted by the extraction: a power of two, at least one sort tile
-inline size_t extract_keys(int64_t nnz) {
-    size_t n = (size_t)mptlib::kSortTile;
-    while (n < (size_t)nnz) n <<= 1;
-    return n;
-}
 
 WsLayout ws_layout(int m, int64_t nnz, int64_t chunk_pairs) {
     WsLayout L{};
@@ -2918,7 +2906,10 @@ WsLayout ws_layout(int m, int64_t nnz, int64_t chunk_pairs) {
     L.part_a = off + align256(P * 8);
     size_t dp_end = L.part_a + align256(P * 4);
     L.keys = off;
-    size_t ex_end = L.keys + align256(extract_keys(nnz) * 8);
+    // (the read-off of more slots sorts keys between two buffers)
+    const size_t kn = nnz > kShortOrders ? nz : 1;
+    L.keys2 = L.keys + align256(kn * 8);
+    size_t ex_end = L.keys2 + align256(kn * 8);
     L.rb_part = off;
     size_t rb_end = L.rb_part + align256(rb_partial_entries(m, chunk_pairs) * 8);
     if (m >= kRbMinM) {
@@ -3296,17 +3287,14 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
     {
         LaunchScope ls("extract", (double)nnz, s);
         uint64_t *keys = (uint64_t *)(ws + L.keys);
-        const int64_t nk = (int64_t)extract_keys(nnz);
-        k_fill_u64<<<grid_for(nk - nnz, 256), 256, 0, s>>>(keys, nnz, nk, ~0ull);
         k_extract<<<m, 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split, keys, h);
         MPT_HIP_TRY(hipGetLastError());
         // offsets and the hierarchy are checked before the sort (inputs that
         // the library produced itself need no check)
         if (validate && (rc = read_errors(h, s))) return rc;
-        if (nnz > 0) {
-            if ((rc = mptlib::sort_keys(keys, nk, s))) return rc;
-            k_extract_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, keys, order_chunks);
-        }
+        uint64_t *sorted = nullptr;
+        if ((rc = mptlib::sort_keys(keys, (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
+        k_extract_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, order_chunks);
     }
     MPT_HIP_TRY(hipGetLastError());
     return MPT_OK;

@@ -14,8 +14,8 @@
 #include <algorithm>
 #include <cstdint>
 
-#include "bitonic.h"
 #include "common.h"
+#include "keysort.h"
 #include "mpt.h"
 #include "seqsort.h"
 
@@ -25,7 +25,6 @@ using mptlib::align256;
 using mptlib::fail;
 using mptlib::grid_for;
 using mptlib::kSeqSortTile;
-using mptlib::kSortTile;
 using mptlib::LaunchScope;
 using mptlib::sort_keys;
 using mptlib::sort_requests;
@@ -48,18 +47,18 @@ inline int64_t pow2_at_least(int64_t n) {
 }
 
 struct PLayout {
-    size_t keys, rf_off, rf_chunks, ord, gstart, lead, rep, roff, total;
-    int64_t kpad, mpad;
+    size_t keys, keys2, rf_off, rf_chunks, ord, gstart, lead, rep, roff, total;
+    int64_t mpad;
 };
 
 PLayout p_layout(int m, int64_t nnz) {
     PLayout L{};
     const size_t mm = (size_t)m, nz = (size_t)std::max<int64_t>(nnz, 1);
-    L.kpad = std::max<int64_t>(pow2_at_least(std::max<int64_t>(nnz, 1)), kSortTile);
     L.mpad = std::max<int64_t>(pow2_at_least(m), kSeqSortTile);
     size_t o = align256(sizeof(PHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
-    L.keys = take(8 * (size_t)L.kpad);
+    L.keys = take(8 * nz);
+    L.keys2 = take(8 * nz);
     L.rf_off = take(8 * (mm + 1));
     L.rf_chunks = take(4 * nz);
     L.ord = take(4 * (size_t)L.mpad);
@@ -146,11 +145,9 @@ __global__ __launch_bounds__(1024) void k_p_max_scan(int n, int32_t *a) {
     }
 }
 
-// (request, chunk) keys of the free slots; pinned slots are padding
-__global__ void k_p_keys(int m, int t, int64_t nnz, int64_t npad, const int64_t *off, const int32_t *chunks,
-                         uint64_t *keys) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < npad; j += (int64_t)gridDim.x * blockDim.x) {
-        if (j >= nnz) { keys[j] = ~0ull; continue; }
+// (request, chunk) keys of the free slots; pinned slots sort last
+__global__ void k_p_keys(int m, int t, int64_t nnz, const int64_t *off, const int32_t *chunks, uint64_t *keys) {
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         int lo = 0, hi = m - 1;                 // request of slot j
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -285,9 +282,12 @@ extern "C" int mpt_pinned_split(int m, int64_t n_chunks, int64_t nnz, const int6
         LaunchScope ls("p_split", (double)nnz, s);
         k_p_counts<<<grid_for(m, 256), 256, 0, s>>>(m, t, req_off, rf_off);
         k_p_scan<<<1, 1024, 0, s>>>(m, rf_off);
-        k_p_keys<<<grid_for(L.kpad, 256), 256, 0, s>>>(m, t, nnz, L.kpad, req_off, req_chunks, keys);
-        if ((rc = sort_keys(keys, L.kpad, s))) return rc;
-        k_p_free_chunks<<<grid_for(std::max<int64_t>(nnz, 1), 256), 256, 0, s>>>(m, rf_off, keys, rf_chunks);
+        if (nnz > 0) {
+            uint64_t *sorted = nullptr;
+            k_p_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, t, nnz, req_off, req_chunks, keys);
+            if ((rc = sort_keys(keys, (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
+            k_p_free_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(m, rf_off, sorted, rf_chunks);
+        }
         // (gstart, written after the sort, is its scratch)
         if ((rc = sort_requests(ord, gstart, m, L.mpad, rf_off, rf_chunks, s))) return rc;
         k_p_group_starts<<<grid_for(m, 256), 256, 0, s>>>(m, ord, rf_off, rf_chunks, gstart);
