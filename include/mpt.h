@@ -270,7 +270,7 @@ int mpt_table_device(const mpt_ctx *ctx, int which, const void **dev_ptr, size_t
  *
  * These calls take any m in [1, MPT_GREEDY_MAX_M]; requests are identified
  * by index. Same conventions as above; they share one workspace of
- * mpt_greedy_workspace_bytes(m, n_chunks, nnz) bytes (about 8 m^2 + 44 nnz
+ * mpt_greedy_workspace_bytes(m, n_chunks, nnz) bytes (about 8 m^2 + 32 nnz
  * + 8 n_chunks + 110 m bytes). Instances are validated as for
  * mpt_build_weights.
  */
@@ -288,7 +288,8 @@ size_t mpt_greedy_workspace_bytes(int m, int64_t n_chunks, int64_t nnz);
  * Cost: one write of P plus sum_x |S_x|^2 additions, in on-chip memory,
  * one per pair of requests sharing a chunk -- meant for sparse demand
  * (small |S_x|).
- * Synchronises `stream` (twice) to report validation errors.
+ * Synchronises `stream` once to report validation errors (twice when a
+ * request has more than 512 chunks).
  */
 int mpt_pair_weights(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w,
                      const int64_t *req_off, const int32_t *req_chunks, int64_t *P,

@@ -6,8 +6,8 @@
 //   mpt_spanning_tree_bound  the maximum spanning tree of P, whence
 //                            OPT_free >= sum_i w(R_i) - MST (Section 6.3)
 //
-// Requests are sorted once (a bitonic sort of (request, chunk) keys); the
-// transposed (chunk, request) keys give the demand list S_x of every chunk.
+// Every request's chunks are put in ascending order once; a counting sort of
+// the slots by chunk gives the demand list S_x of every chunk.
 // Pair weights are a scatter over the pairs of every demand list: request
 // families of retrieval shape have small |S_x|, so this touches
 // sum_x |S_x|^2 entries instead of a dense m x m x u contraction.
@@ -34,7 +34,10 @@ using mptlib::align256;
 using mptlib::fail;
 using mptlib::grid_for;
 using mptlib::LaunchScope;
+using mptlib::kListMax;
+using mptlib::kListThreads;
 using mptlib::kSegMax;
+using mptlib::list_ranks;
 using mptlib::seg_rank;
 using mptlib::sort_keys;
 
@@ -54,12 +57,13 @@ struct GHeader {
     int32_t bv_done;             // spanning tree: 1 once one component is left
     unsigned long long dcursor;  // next free slot of the packed D lists
     int64_t max_len;             // longest request list
-    int64_t pad[25];
+    unsigned long long dem_at;   // next free slot of the demand lists
+    int64_t pad[24];
 };
 static_assert(sizeof(GHeader) == 256, "header is one 256-byte block");
 
 struct GLayout {
-    size_t keys1, keys2, keys3, sig, sig_len, dem, dem_off, V, best_v, best_p, active, last, touched, resc, dbuf, d_off,
+    size_t keys1, keys2, rank, sig, sig_len, dem, dem_seg, V, best_v, best_p, active, last, touched, resc, dbuf, d_off,
         d_len, rec32, rec64, total;
 };
 constexpr int kRec32 = 7;    // int32 arrays of the merge records
@@ -72,11 +76,11 @@ GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
     L.keys1 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
     L.keys2 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
-    L.keys3 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
+    L.rank = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig_len = take(4 * mm);
     L.dem = take(4 * (size_t)std::max<int64_t>(nnz, 1));
-    L.dem_off = take(8 * ((size_t)n_chunks + 1));
+    L.dem_seg = take(8 * (size_t)std::max<int64_t>(n_chunks, 1));
     L.V = take(8 * mm * mm);
     L.best_v = take(8 * mm);
     L.best_p = take(4 * mm);
@@ -143,101 +147,199 @@ __device__ inline int64_t find_sorted(const int32_t *a, int64_t n, int32_t x) {
 }
 
 // ---------------------------------------------------------------------------
-// validation and keys
+// validation and lists
+//
+// Demand lists by a counting sort of the slots, in three launches: the first
+// counts every chunk's slots (and leaves each slot its place among its
+// chunk's), the second gives every chunk a stretch of dem, the third writes.
+// The stretches follow the order of their atomics and a list's requests come
+// in no order: the lists are only summed over. A sort of (chunk, request) keys
+// took two launches of 25 us and two more to read them (before that ten
+// bitonic ones), and the total one atomic per slot on one address.
 
-__global__ void k_g_header(GHeader *h) {
-    if (threadIdx.x == 0) { h->err = 0; h->total = 0; h->max_len = 0; }
-}
-
-__global__ void k_g_check_offsets(int m, int64_t nnz, const int64_t *req_off, GHeader *h) {
-    bool ok = true;
-    int64_t mx = 0;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
-        const int64_t len = req_off[i + 1] - req_off[i];
-        ok = ok && len >= 0;
-        mx = len > mx ? len : mx;
-    }
-    if (threadIdx.x == 0) ok = ok && req_off[0] == 0 && req_off[m] == nnz;
-    if (!ok) atomicOr(&h->err, GERR_INVALID);
-    if (mx > 0) atomicMax((long long *)&h->max_len, (long long)mx);
-}
-
-__global__ void k_g_check_weights(int64_t n_chunks, const int64_t *w, GHeader *h) {
+__global__ void k_g_begin(int64_t n_chunks, uint64_t *dem_seg, GHeader *h) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) { h->err = 0; h->total = 0; h->max_len = 0; h->dem_at = 0; }
     for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n_chunks; x += (int64_t)gridDim.x * blockDim.x)
-        if (w[x] <= 0 || w[x] > MPT_MAX_CHUNK_WEIGHT) atomicOr(&h->err, GERR_WEIGHT);
+        dem_seg[x] = 0;
 }
 
-// (request, chunk) and (chunk, request) keys of every slot
-__global__ void k_g_keys(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off,
-                         const int32_t *req_chunks, const int64_t *w, uint64_t *keys1, uint64_t *keys2, GHeader *h) {
+// Offsets, weights, chunk ids, sum_i w(R_i), the longest request, and the
+// slots of every chunk counted into dem_seg[x]; rank[j]: slot j's place among
+// its chunk's. Popular chunks are in a quarter of all requests, and atomics on
+// one address serialise device-wide, so each workgroup counts its slice of the
+// slots in an LDS hash table first (linear probing; a slot that finds no entry
+// counts in memory directly) and adds each entry once.
+constexpr int kCountThreads = 256;
+constexpr int kCountSlice = 1024;              // slots per workgroup pass
+constexpr int kCountBits = 11;
+constexpr int kCountEntries = 1 << kCountBits;
+constexpr int kCountProbes = 16;
+__global__ __launch_bounds__(kCountThreads) void k_g_check(int m, int64_t n_chunks, int64_t nnz,
+                                                           const int64_t *__restrict__ req_off,
+                                                           const int32_t *__restrict__ req_chunks,
+                                                           const int64_t *__restrict__ w, uint64_t *dem_seg,
+                                                           uint32_t *__restrict__ rank, GHeader *h) {
+    constexpr int PER = kCountSlice / kCountThreads;
+    __shared__ uint32_t key[kCountEntries];    // chunk + 1; 0: empty
+    __shared__ uint32_t cnt[kCountEntries];    // its slots here, then its slots before this workgroup's
+    __shared__ uint64_t red[kCountThreads / kWave];
+    const int64_t t0 = blockIdx.x * (int64_t)kCountThreads + threadIdx.x, stride = (int64_t)gridDim.x * kCountThreads;
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    uint32_t err = 0;
+    int64_t longest = 0;
+    for (int64_t i = t0; i < m; i += stride) {
+        const int64_t len = req_off[i + 1] - req_off[i];
+        if (len < 0) err |= GERR_INVALID;
+        longest = len > longest ? len : longest;
+    }
+    if (t0 == 0 && (req_off[0] != 0 || req_off[m] != nnz)) err |= GERR_INVALID;
+    for (int64_t x = t0; x < n_chunks; x += stride)
+        if (w[x] <= 0 || w[x] > MPT_MAX_CHUNK_WEIGHT) err |= GERR_WEIGHT;
+    uint64_t total = 0;
+    for (int64_t s0 = (int64_t)blockIdx.x * kCountSlice; s0 < nnz; s0 += (int64_t)gridDim.x * kCountSlice) {
+        for (int e = (int)threadIdx.x; e < kCountEntries; e += kCountThreads) { key[e] = 0u; cnt[e] = 0u; }
+        __syncthreads();
+        int at[PER];                           // the slot's entry; -1: counted in memory or no slot
+        uint32_t place[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t j = s0 + q * kCountThreads + threadIdx.x;
+            at[q] = -1;
+            place[q] = 0;
+            if (j >= nnz) continue;
+            const int32_t x = req_chunks[j];
+            if (x < 0 || (int64_t)x >= n_chunks) { err |= GERR_RANGE; continue; }
+            const int64_t wx = w[x];
+            if (wx > 0 && wx <= MPT_MAX_CHUNK_WEIGHT) total += (uint64_t)wx;
+            uint32_t slot = ((uint32_t)x * 2654435761u) >> (32 - kCountBits);
+            for (int p = 0; p < kCountProbes && at[q] < 0; ++p) {
+                const uint32_t k = atomicCAS(&key[slot], 0u, (uint32_t)x + 1u);
+                if (k == 0u || k == (uint32_t)x + 1u) {
+                    at[q] = (int)slot;
+                    place[q] = atomicAdd(&cnt[slot], 1u);
+                }
+                slot = (slot + 1u) & (kCountEntries - 1u);
+            }
+            if (at[q] < 0) rank[j] = (uint32_t)atomicAdd((unsigned long long *)&dem_seg[x], 1ull);
+        }
+        __syncthreads();
+        for (int e = (int)threadIdx.x; e < kCountEntries; e += kCountThreads)
+            if (key[e]) cnt[e] = (uint32_t)atomicAdd((unsigned long long *)&dem_seg[key[e] - 1u], (unsigned long long)cnt[e]);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            if (at[q] >= 0) rank[s0 + q * kCountThreads + threadIdx.x] = cnt[at[q]] + place[q];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        total += __shfl_xor(total, off, kWave);
+        const int64_t o = __shfl_xor(longest, off, kWave);
+        longest = o > longest ? o : longest;
+        err |= (uint32_t)__shfl_xor((int)err, off, kWave);
+    }
+    if (lane == 0) {
+        red[threadIdx.x / kWave] = total;
+        if (err) atomicOr(&h->err, err);
+        if (longest > 0) atomicMax((long long *)&h->max_len, (long long)longest);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        uint64_t sum = 0;
+        for (int k = 0; k < kCountThreads / kWave; ++k) sum += red[k];
+        if (sum) atomicAdd(&h->total, (unsigned long long)sum);
+    }
+}
+
+// a stretch of dem for every chunk: dem_seg[x] = start << 32 | count
+__global__ __launch_bounds__(kCountThreads) void k_g_stretches(int64_t n_chunks, uint64_t *dem_seg, GHeader *h) {
+    __shared__ int sw[kCountThreads / kWave];
+    __shared__ unsigned long long start;
+    for (int64_t x0 = (int64_t)blockIdx.x * kCountThreads; x0 < n_chunks; x0 += (int64_t)gridDim.x * kCountThreads) {
+        const int64_t x = x0 + threadIdx.x;
+        const uint64_t c = x < n_chunks ? dem_seg[x] : 0;
+        int total;
+        const int before = block_scan((int)c, &total, sw);
+        if (threadIdx.x == 0) start = total ? atomicAdd(&h->dem_at, (unsigned long long)total) : 0ull;
+        __syncthreads();
+        if (c) dem_seg[x] = ((start + (uint64_t)before) << 32) | c;
+        __syncthreads();
+    }
+}
+
+// Request lists (chunk ids ascending) into sig, with the check for repeated
+// chunks, and the demand lists. Lists of up to kSegMax chunks take a wave
+// each, of up to kListMax a workgroup each; with a longer one, sig is left to
+// a key sort. Nothing is done once an error is known.
+__global__ __launch_bounds__(kListThreads) void k_g_lists(int m, const int64_t *__restrict__ req_off,
+                                                          const int32_t *__restrict__ req_chunks,
+                                                          const uint32_t *__restrict__ rank,
+                                                          const uint64_t *__restrict__ dem_seg,
+                                                          int32_t *__restrict__ sig, int32_t *__restrict__ sig_len,
+                                                          int32_t *__restrict__ dem, GHeader *h) {
+    __shared__ uint32_t stage[kListMax];
+    if (h->err & ~GERR_DUP) return;            // (GERR_DUP is raised in this launch: no workgroup stops for it)
+    const int64_t longest = h->max_len;
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    auto demand = [&](int64_t j, int32_t x, int i) {
+        dem[(int64_t)(dem_seg[x] >> 32) + rank[j]] = (int32_t)i;
+    };
+    if (longest <= kSegMax) {
+        const int nwaves = (int)(gridDim.x * blockDim.x) / kWave;
+        for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < m; i += nwaves) {
+            const int64_t o = req_off[i];
+            const int n = (int)(req_off[i + 1] - o);
+            const int32_t c = lane < n ? req_chunks[o + lane] : 0;
+            bool dup;
+            const int pos = seg_rank((uint32_t)c, n, dup);
+            if (lane < n) {
+                demand(o + lane, c, i);
+                sig[o + pos] = c;
+                if (dup) atomicOr(&h->err, (uint32_t)GERR_DUP);
+            }
+            if (lane == 0) sig_len[i] = n;
+        }
+        return;
+    }
+    for (int i = (int)blockIdx.x; i < m; i += (int)gridDim.x) {
+        const int64_t o = req_off[i];
+        const int64_t n = req_off[i + 1] - o;
+        for (int64_t e = threadIdx.x; e < n; e += kListThreads) demand(o + e, req_chunks[o + e], i);
+        if (threadIdx.x == 0) sig_len[i] = (int32_t)n;
+        if (longest <= kListMax) {
+            list_ranks(stage, (int)n, [&](int e) { return (uint32_t)req_chunks[o + e]; },
+                       [&](int, uint32_t c, int pos, bool dup) {
+                           sig[o + pos] = (int32_t)c;
+                           if (dup) atomicOr(&h->err, (uint32_t)GERR_DUP);
+                       });
+            __syncthreads();
+        }
+    }
+}
+
+// (request, chunk) keys of every slot (valid input)
+__global__ void k_g_keys(int m, int64_t nnz, const int64_t *req_off, const int32_t *req_chunks, uint64_t *keys) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         int lo = 0, hi = m - 1;                     // request of slot j: last i with req_off[i] <= j
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (req_off[mid] <= j) lo = mid; else hi = mid - 1;
         }
-        const int32_t x = req_chunks[j];
-        if (x < 0 || (int64_t)x >= n_chunks) {
-            atomicOr(&h->err, GERR_RANGE);
-            keys1[j] = ~0ull; keys2[j] = ~0ull;
-            continue;
-        }
-        keys1[j] = ((uint64_t)lo << 32) | (uint32_t)x;
-        keys2[j] = ((uint64_t)x << 32) | (uint32_t)lo;
-        const int64_t wx = w[x];
-        if (wx > 0 && wx <= MPT_MAX_CHUNK_WEIGHT) atomicAdd(&h->total, (unsigned long long)wx);
+        keys[j] = ((uint64_t)lo << 32) | (uint32_t)req_chunks[j];
+    }
+}
+
+// sorted keys -> request lists; a repeated chunk inside a request is two
+// equal adjacent keys
+__global__ void k_g_sig_long(int64_t nnz, const uint64_t *keys, int32_t *sig, GHeader *h) {
+    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
+        sig[j] = (int32_t)(keys[j] & 0xffffffffu);
+        if (j > 0 && keys[j] == keys[j - 1]) atomicOr(&h->err, (uint32_t)GERR_DUP);
     }
 }
 
 // ---------------------------------------------------------------------------
-// lists and pair weights
-
-// sorted keys -> request lists (chunk ids ascending inside each request),
-// demand lists (request ids ascending inside each chunk); a repeated chunk
-// inside a request is two equal adjacent (request, chunk) keys. keys1 null:
-// the request lists are already in sig (k_g_sig_short).
-__global__ void k_g_lists(int m, int64_t nnz, const uint64_t *keys1, const uint64_t *keys2, int32_t *sig,
-                          int32_t *sig_len, int32_t *dem, const int64_t *req_off, GHeader *h) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
-        dem[j] = (int32_t)(keys2[j] & 0xffffffffu);
-        if (!keys1) continue;
-        sig[j] = (int32_t)(keys1[j] & 0xffffffffu);
-        if (j > 0 && keys1[j] == keys1[j - 1]) atomicOr(&h->err, GERR_DUP);
-    }
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-        sig_len[i] = (int32_t)(req_off[i + 1] - req_off[i]);
-}
-
-// request lists when every request has at most kSegMax chunks: one wave
-// per request ranks its chunks (chunk ids validated already)
-__global__ void k_g_sig_short(int m, const int64_t *req_off, const int32_t *req_chunks, int32_t *sig, GHeader *h) {
-    const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; i < m; i += nwaves) {
-        const int64_t o = req_off[i];
-        const int n = (int)(req_off[i + 1] - o);
-        const uint32_t c = lane < n ? (uint32_t)req_chunks[o + lane] : 0u;
-        bool dup;
-        const int pos = seg_rank(c, n, dup);
-        if (lane < n) {
-            sig[o + pos] = (int32_t)c;
-            if (dup) atomicOr(&h->err, GERR_DUP);
-        }
-    }
-}
-
-// dem_off[x] = first slot of chunk x in the (chunk, request) order
-__global__ void k_g_dem_off(int64_t n_chunks, int64_t nnz, const uint64_t *keys2, int64_t *dem_off) {
-    for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x <= n_chunks; x += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t key = (uint64_t)x << 32;
-        int64_t lo = 0, hi = nnz;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (keys2[mid] < key) lo = mid + 1; else hi = mid;
-        }
-        dem_off[x] = lo;
-    }
-}
+// pair weights
 
 // row a of P, a tile of kPairTile columns per workgroup: every chunk x of
 // R_a adds w(x) to the columns of the requests in its demand list S_x (one
@@ -246,9 +348,11 @@ __global__ void k_g_dem_off(int64_t n_chunks, int64_t nnz, const uint64_t *keys2
 constexpr int kPairTile = 4096;
 constexpr int kPairThreads = 256;
 __global__ __launch_bounds__(kPairThreads) void k_g_pair_rows(int m, const int32_t *sig, const int64_t *req_off,
-                                                              const int32_t *dem, const int64_t *dem_off,
-                                                              const int64_t *w, int64_t *P) {
+                                                              const int32_t *dem, const uint64_t *dem_seg,
+                                                              const int64_t *w, int64_t *P, int sorted, const GHeader *h) {
     __shared__ unsigned long long row[kPairTile];
+    const bool lists = sorted || h->max_len <= kListMax;
+    if (h->err || !lists) return;              // (the lists are not there)
     const int tiles = (m + kPairTile - 1) / kPairTile;
     const int64_t a = blockIdx.x / tiles;
     const int c0 = (int)(blockIdx.x % tiles) * kPairTile;
@@ -260,8 +364,11 @@ __global__ __launch_bounds__(kPairThreads) void k_g_pair_rows(int m, const int32
     for (int64_t q = s0 + wid; q < s1; q += kPairThreads / kWave) {
         const int32_t x = sig[q];
         const unsigned long long wx = (unsigned long long)w[x];
-        for (int64_t f = dem_off[x] + lane; f < dem_off[x + 1]; f += kWave) {
-            const int b = dem[f] - c0;
+        const uint64_t seg = dem_seg[x];
+        const int32_t *holders = dem + (seg >> 32);
+        const int n = (int)(seg & 0xffffffffu);
+        for (int f = lane; f < n; f += kWave) {
+            const int b = holders[f] - c0;
             if (b >= 0 && b < width) atomicAdd(&row[b], wx);
         }
     }
@@ -802,52 +909,46 @@ int g_read_errors(GHeader *h, hipStream_t s, int64_t *request_total = nullptr, i
     return MPT_OK;
 }
 
-// Validate the instance and build the sorted lists, the demand lists and
-// (when P is given) the pair weights. Synchronises once to report errors.
+// Validate the instance and build the request lists, the demand lists and the
+// pair weights, with one synchronisation at the end to report errors (two with
+// requests of more than kListMax chunks, whose lists a key sort puts in order).
 int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const int64_t *req_off,
               const int32_t *req_chunks, int64_t *P, const GLayout &L, char *ws, hipStream_t s,
               int64_t *request_total = nullptr) {
     GHeader *h = (GHeader *)ws;
-    uint64_t *keys1 = (uint64_t *)(ws + L.keys1), *keys2 = (uint64_t *)(ws + L.keys2);
-    k_g_header<<<1, 64, 0, s>>>(h);
-    k_g_check_offsets<<<1, 256, 0, s>>>(m, nnz, req_off, h);
-    if (n_chunks > 0) k_g_check_weights<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, chunk_w, h);
+    int32_t *sig = (int32_t *)(ws + L.sig), *sig_len = (int32_t *)(ws + L.sig_len), *dem = (int32_t *)(ws + L.dem);
+    uint64_t *dem_seg = (uint64_t *)(ws + L.dem_seg);
+    uint32_t *rank = (uint32_t *)(ws + L.rank);
+    const int64_t blocks = (int64_t)m * ((m + kPairTile - 1) / kPairTile);
+    auto pairs = [&](int sorted) {
+        LaunchScope ls("g_pairs", 8.0 * (double)m * m, s);
+        k_g_pair_rows<<<(unsigned)blocks, kPairThreads, 0, s>>>(m, sig, req_off, dem, dem_seg, chunk_w, P, sorted, h);
+    };
     {
-        LaunchScope ls("g_keys", (double)nnz, s);
-        k_g_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, chunk_w, keys1, keys2, h);
+        LaunchScope ls("g_lists", (double)nnz, s);
+        k_g_begin<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, dem_seg, h);
+        k_g_check<<<grid_for(std::max<int64_t>(nnz, std::max<int64_t>(m, n_chunks / 4)), kCountSlice, 1024),
+                    kCountThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, chunk_w, dem_seg, rank, h);
+        if (n_chunks > 0)
+            k_g_stretches<<<grid_for(n_chunks, kCountThreads), kCountThreads, 0, s>>>(n_chunks, dem_seg, h);
+        k_g_lists<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, dem_seg, sig, sig_len,
+                                                               dem, h);
     }
+    pairs(0);
     MPT_HIP_TRY(hipGetLastError());
     int64_t max_len = 0;
-    int rc = g_read_errors(h, s, nullptr, &max_len);
-    if (rc) return rc;
-    int32_t *sig = (int32_t *)(ws + L.sig), *sig_len = (int32_t *)(ws + L.sig_len), *dem = (int32_t *)(ws + L.dem);
-    int64_t *dem_off = (int64_t *)(ws + L.dem_off);
-    // short requests: the request lists by ranks inside each request, the
-    // (request, chunk) keys unsorted and unused
-    const bool short_lists = max_len <= kSegMax;
+    int rc = g_read_errors(h, s, request_total, &max_len);
+    if (rc || max_len <= kListMax) return rc;
+    uint64_t *sorted = nullptr;
     {
-        LaunchScope ls("g_sort", 2.0 * (double)nnz, s);
-        uint64_t *tmp = (uint64_t *)(ws + L.keys3), *free1 = tmp;
-        if (short_lists) k_g_sig_short<<<std::max(1, (m + 3) / 4), 4 * kWave, 0, s>>>(m, req_off, req_chunks, sig, h);
-        else if ((rc = sort_keys(keys1, tmp, nnz, s, &free1))) return rc;
-        // (the buffer that the first sort did not end in)
-        uint64_t *tmp2 = free1 == tmp ? keys1 : tmp;
-        if (!short_lists) keys1 = free1; else tmp2 = tmp;
-        if ((rc = sort_keys(keys2, tmp2, nnz, s, &keys2))) return rc;
+        LaunchScope ls("g_sort", (double)nnz, s);
+        k_g_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, (uint64_t *)(ws + L.keys1));
+        if ((rc = sort_keys((uint64_t *)(ws + L.keys1), (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
+        k_g_sig_long<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, sig, h);
     }
-    k_g_lists<<<grid_for(std::max<int64_t>(nnz, m), 256), 256, 0, s>>>(m, nnz, short_lists ? nullptr : keys1, keys2, sig,
-                                                                        sig_len, dem, req_off, h);
-    k_g_dem_off<<<grid_for(n_chunks + 1, 256), 256, 0, s>>>(n_chunks, nnz, keys2, dem_off);
+    pairs(1);
     MPT_HIP_TRY(hipGetLastError());
-    if ((rc = g_read_errors(h, s, request_total))) return rc;
-    if (P) {
-        const int64_t mm = (int64_t)m * m;
-        LaunchScope ls("g_pairs", 8.0 * (double)mm, s);
-        const int64_t blocks = (int64_t)m * ((m + kPairTile - 1) / kPairTile);
-        k_g_pair_rows<<<(unsigned)blocks, kPairThreads, 0, s>>>(m, sig, req_off, dem, dem_off, chunk_w, P);
-        MPT_HIP_TRY(hipGetLastError());
-    }
-    return MPT_OK;
+    return g_read_errors(h, s, request_total);
 }
 
 }  // namespace
