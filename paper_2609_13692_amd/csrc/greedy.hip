@@ -388,8 +388,17 @@ __global__ void k_g_row_best(int m, const int64_t *V, int64_t *best_v, int32_t *
     if (row >= m) return;
     int64_t v = -1;
     int32_t p = -1;
-    for (int d = lane; d < m; d += kWave)
-        if (d != row && better(V[row * m + d], d, v, p)) { v = V[row * m + d]; p = d; }
+    constexpr int U = 8;                         // columns per lane in flight (128 MiB: 24 us, 42 us one at a time)
+    for (int d0 = lane; d0 < m; d0 += U * kWave) {
+        int64_t x[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) x[q] = d0 + q * kWave < m ? V[row * m + d0 + q * kWave] : -2;
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int d = d0 + q * kWave;
+            if (d < m && d != row && better(x[q], d, v, p)) { v = x[q]; p = d; }
+        }
+    }
     wave_best(v, p);
     if (lane == 0) { best_v[row] = v; best_p[row] = p; }
 }
@@ -435,17 +444,6 @@ struct Rac {
 };
 
 __device__ inline uint64_t lanes_below(int lane) { return (1ull << lane) - 1ull; }
-
-// w(p ∩ q) for ascending lists: the shorter searched in the longer
-__device__ inline int64_t inter_weight(const int32_t *p, int64_t np, const int32_t *q, int64_t nq, const int64_t *w) {
-    if (np > nq) { const int32_t *t = p; p = q; q = t; const int64_t n = np; np = nq; nq = n; }
-    int64_t s = 0;
-    for (int64_t j = 0; j < np; ++j) {
-        const int32_t y = p[j];
-        if (find_sorted(q, nq, y) >= 0) s += w[y];
-    }
-    return s;
-}
 
 // pair order (gain, a, b): true when x comes after y in the greedy's order
 // (smaller gain; equal gains, larger names)
@@ -560,6 +558,54 @@ __global__ void k_rac_pairs_merge(Rac R, int round) {
     }
 }
 
+// V[a][x] for the columns x of one wave (lane l: column x of lane l, need: the
+// values of both parts are positive and the merged list is not empty): groups
+// of G lanes, G the least power of two holding the merged list (at most 64),
+// take the wave's needed columns in turn, a lane per chunk of the list and a
+// binary search each in the column's list. The lists of a column are read by a
+// whole group at once; one lane walking its column's list alone was a chain of
+// up to kept * log2(len) dependent reads.
+__device__ inline int64_t group_weights(bool need, int32_t x, const int32_t *sa, int kept, int glog, const Rac &R) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int G = 1 << glog, grp = lane >> glog, e0 = lane & (G - 1);
+    uint64_t todo = __ballot(need);
+    int64_t mine = 0;
+    while (todo) {
+        // group q takes the q-th needed column
+        uint64_t rest = todo;
+        int src = -1;
+        for (int q = 0; q < kWave >> glog && rest; ++q) {
+            const int l = __ffsll((unsigned long long)rest) - 1;
+            rest &= rest - 1;
+            if (q == grp) src = l;
+        }
+        const int32_t c = __shfl(x, src < 0 ? 0 : src, kWave);
+        int64_t v = 0;
+        if (src >= 0) {
+            const int32_t *sx = R.sig + R.req_off[c];
+            const int64_t nx = R.sig_len[c];
+            for (int e = e0; e < kept; e += G) {
+                const int32_t y = sa[e];
+                if (find_sorted(sx, nx, y) >= 0) v += R.w[y];
+            }
+        }
+        for (int off = G >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+        // back to the columns' lanes: lane l's column was taken by the group
+        // of its place among this turn's
+        const int place = __popcll(todo & lanes_below(lane));
+        const int64_t got = __shfl(v, (place << glog) & (kWave - 1), kWave);
+        if (((todo ^ rest) >> lane) & 1ull) mine = got;
+        todo = rest;
+    }
+    return mine;
+}
+
+__device__ inline int group_log(int64_t kept) {
+    int g = 0;
+    while (g < 6 && ((int64_t)1 << g) < kept) ++g;
+    return g;
+}
+
 // the new clusters' rows against every live column. A value is positive
 // only where both old values are; the row of a is written by its own merge
 // (columns of clusters merged in the same round included: both sides
@@ -570,21 +616,22 @@ __global__ void k_rac_pairs_merge(Rac R, int round) {
 __global__ void k_rac_rows(Rac R, int round) {
     const int lo = R.h->lo, hi = min(R.h->n_rec, R.m - 1);
     const int64_t m = R.m;
-    const int64_t total = (int64_t)(hi - lo) * m;
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int64_t per = (m + kWave - 1) / kWave;                 // waves across the columns
+    const int64_t total = (int64_t)(hi - lo) * per;
     const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t f = t0; f < total; f += stride) {
-        const int64_t i = lo + f / m;
-        const int32_t x = (int32_t)(f % m);
+    for (int64_t f = t0 / kWave; f < total; f += stride / kWave) {
+        const int64_t i = lo + f / per;
+        const int64_t col = (f % per) * kWave + lane;
         const int32_t a = R.ra[i], b = R.rb[i];
-        if (x == a || !R.act[x]) continue;
-        const int64_t va = R.V[a * m + x], vb = R.V[b * m + x];
         const int64_t kept = R.sig_len[a];
-        int64_t v = 0;
-        if (va > 0 && vb > 0 && kept > 0)
-            v = inter_weight(R.sig + R.req_off[a], kept, R.sig + R.req_off[x], R.sig_len[x], R.w);
-        if (v != va) {
-            R.V[a * m + x] = v;
-            if (R.touched[x] != round) R.V[(int64_t)x * m + a] = v;
+        const bool live = col < m && col != a && R.act[col];
+        const int64_t va = live ? R.V[a * m + col] : 0, vb = live ? R.V[b * m + col] : 0;
+        const int64_t v = group_weights(va > 0 && vb > 0 && kept > 0, (int32_t)col, R.sig + R.req_off[a], (int)kept,
+                                        group_log(kept), R);
+        if (live && v != va) {
+            R.V[a * m + col] = v;
+            if (R.touched[col] != round) R.V[col * m + a] = v;
         }
     }
     if (hi <= lo) return;                        // nothing merged, nothing to rescan
@@ -792,20 +839,19 @@ __device__ inline uint32_t edge_id(int u, int v) {
 }
 
 // Borůvka's rounds after the last component has formed change nothing:
-// the hook kernel raises h->bv_done when a root finds no edge out of its
+// k_bv_merge raises h->bv_done when a root finds no edge out of its
 // component (P is complete, so that root's component holds every vertex),
 // and the later rounds' kernels return at once.
-__global__ void k_bv_init(int m, int32_t *comp, GHeader *h) {
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < m; v += gridDim.x * blockDim.x) comp[v] = v;
+__global__ void k_bv_init(int m, int32_t *comp, int64_t *cw, uint32_t *ce, GHeader *h) {
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < m; v += gridDim.x * blockDim.x) {
+        comp[v] = v;
+        cw[v] = -1;
+        ce[v] = ~0u;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         h->total = 0;
         h->bv_done = 0;
     }
-}
-
-__global__ void k_bv_reset(int m, int64_t *cw, uint32_t *ce, const GHeader *h) {
-    if (h->bv_done) return;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < m; v += gridDim.x * blockDim.x) { cw[v] = -1; ce[v] = ~0u; }
 }
 
 // best edge of every vertex to another component (one wave per vertex),
@@ -819,11 +865,23 @@ __global__ void k_bv_vertex(int m, const int64_t *P, const int32_t *comp, int64_
     const int32_t cu = comp[u];
     int64_t bw = -1;
     uint32_t be = ~0u;
-    for (int v = lane; v < m; v += kWave) {
-        if (comp[v] == cu) continue;
-        const int64_t x = P[u * m + v];
-        const uint32_t e = edge_id((int)u, v);
-        if (x > bw || (x == bw && e < be)) { bw = x; be = e; }
+    // eight columns per lane in flight (twelve rounds at m = 4096, five of
+    // them real: 219 us, one column at a time 254 us)
+    constexpr int U = 8;
+    for (int v0 = lane; v0 < m; v0 += U * kWave) {
+        int64_t x[U];
+        int32_t c[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int v = v0 + q * kWave;
+            x[q] = v < m ? P[u * m + v] : -1;
+            c[q] = v < m ? comp[v] : cu;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t e = edge_id((int)u, v0 + q * kWave);
+            if (c[q] != cu && (x[q] > bw || (x[q] == bw && e < be))) { bw = x[q]; be = e; }
+        }
     }
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) {
@@ -837,44 +895,65 @@ __global__ void k_bv_vertex(int m, const int64_t *P, const int32_t *comp, int64_
     }
 }
 
-// among the vertices that reach their component's best weight, the smallest edge
-__global__ void k_bv_edge(int m, const int32_t *comp, const int64_t *vw, const uint32_t *ve, const int64_t *cw,
-                          uint32_t *ce, const GHeader *h) {
+// The rest of a round, by one workgroup with barriers between its phases: the
+// smallest edge among the vertices that reach their component's best weight;
+// every component hooks onto the component across its best edge, except the
+// smaller one of a mutual pair, and the hooking side adds the edge weight;
+// every vertex follows the hooks to its new root; the components' best weights
+// are cleared for the next round. m <= 16384 entries per array, 16 per thread:
+// 10 us at m = 4096, where four launches took 14 us and three more gaps.
+constexpr int kBvThreads = 1024;
+__global__ __launch_bounds__(kBvThreads) void k_bv_merge(int m, int32_t *comp, const int64_t *vw, const uint32_t *ve,
+                                                         int64_t *cw, uint32_t *ce, int32_t *par, GHeader *h) {
+    __shared__ uint32_t done;
+    const int tid = (int)threadIdx.x;
     if (h->bv_done) return;
-    for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < m; u += gridDim.x * blockDim.x) {
+    if (tid == 0) done = 0;
+    __syncthreads();
+    for (int u = tid; u < m; u += kBvThreads) {
         const int32_t cu = comp[u];
         if (vw[u] >= 0 && vw[u] == cw[cu]) atomicMin(&ce[cu], ve[u]);
     }
-}
-
-// every component hooks onto the component across its best edge, except
-// the smaller one of a mutual pair; the hooking side adds the edge weight
-// (no early return here: a workgroup that saw bv_done raised by another
-// one of this launch would skip hooks; with one component there are none)
-__global__ void k_bv_hook(int m, const int32_t *comp, const int64_t *cw, const uint32_t *ce, int32_t *par,
-                          GHeader *h) {
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < m; c += gridDim.x * blockDim.x) {
-        par[c] = c;
-        if (comp[c] != c) continue;
-        if (ce[c] == ~0u) {
-            h->bv_done = 1;
-            continue;
+    __threadfence();
+    __syncthreads();
+    uint64_t sum = 0;
+    for (int c = tid; c < m; c += kBvThreads) {
+        int32_t to = c;
+        if (comp[c] == c) {
+            const uint32_t e = __hip_atomic_load(&ce[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (e == ~0u) {
+                done = 1;                              // no edge out: one component is left
+            } else {
+                const int lo = (int)(e >> 14), hi = (int)(e & 0x3fffu);
+                const int32_t d = comp[lo] == c ? comp[hi] : comp[lo];
+                const uint32_t ed = __hip_atomic_load(&ce[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!(ed == e && c < d)) {             // else d hooks onto c
+                    to = d;
+                    sum += (uint64_t)cw[c];
+                }
+            }
         }
-        const int lo = (int)(ce[c] >> 14), hi = (int)(ce[c] & 0x3fffu);
-        const int32_t d = comp[lo] == c ? comp[hi] : comp[lo];
-        if (ce[d] == ce[c] && c < d) continue;           // d hooks onto c
-        par[c] = d;
-        atomicAdd(&h->total, (unsigned long long)cw[c]);
+        par[c] = to;
     }
-}
-
-// new component of every vertex: follow the hooks to a root
-__global__ void k_bv_jump(int m, int32_t *comp, const int32_t *par, const GHeader *h) {
-    if (h->bv_done) return;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < m; v += gridDim.x * blockDim.x) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    if ((tid & (kWave - 1)) == 0 && sum) atomicAdd(&h->total, (unsigned long long)sum);
+    __threadfence();
+    __syncthreads();
+    if (done) {
+        if (tid == 0) h->bv_done = 1;
+        return;
+    }
+    for (int v = tid; v < m; v += kBvThreads) {
         int32_t r = comp[v];
-        for (int guard = 0; par[r] != r && guard < m; ++guard) r = par[r];
+        for (int guard = 0; guard < m; ++guard) {
+            const int32_t q = par[r];
+            if (q == r) break;
+            r = q;
+        }
         comp[v] = r;
+        cw[v] = -1;
+        ce[v] = ~0u;
     }
 }
 
@@ -1104,14 +1183,11 @@ extern "C" int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_wei
     int rounds = 0;
     while ((1 << rounds) < m) ++rounds;
     const int gv = grid_for(m, 256);
-    k_bv_init<<<gv, 256, 0, s>>>(m, comp, h);
+    k_bv_init<<<gv, 256, 0, s>>>(m, comp, cw, ce, h);
     for (int r = 0; r < rounds; ++r) {
         LaunchScope ls("g_boruvka", 8.0 * (double)m * m, s);
-        k_bv_reset<<<gv, 256, 0, s>>>(m, cw, ce, h);
         k_bv_vertex<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, P, comp, vw, ve, cw, h);
-        k_bv_edge<<<gv, 256, 0, s>>>(m, comp, vw, ve, cw, ce, h);
-        k_bv_hook<<<gv, 256, 0, s>>>(m, comp, cw, ce, par, h);
-        k_bv_jump<<<gv, 256, 0, s>>>(m, comp, par, h);
+        k_bv_merge<<<1, kBvThreads, 0, s>>>(m, comp, vw, ve, cw, ce, par, h);
     }
     MPT_HIP_TRY(hipGetLastError());
     unsigned long long total = 0;
