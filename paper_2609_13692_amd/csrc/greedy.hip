@@ -63,9 +63,11 @@ struct GHeader {
 static_assert(sizeof(GHeader) == 256, "header is one 256-byte block");
 
 struct GLayout {
-    size_t keys1, keys2, rank, sig, sig_len, dem, dem_seg, V, best_v, best_p, active, last, touched, resc, dbuf, d_off,
+    size_t keys1, keys2, rank, sig, sig_slot, sig_len, dem, dem_seg, V, best_v, best_p, active, last, touched, resc, live, dense, d_off,
         d_len, rec32, rec64, total;
 };
+// clusters that the greedy's last rounds, run by one workgroup, may start from
+constexpr int kTailLive = 2048;
 constexpr int kRec32 = 7;    // int32 arrays of the merge records
 constexpr int kRec64 = 3;    // int64 arrays of the merge records
 
@@ -77,7 +79,8 @@ GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     L.keys1 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
     L.keys2 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
     L.rank = take(4 * (size_t)std::max<int64_t>(nnz, 1));
-    L.sig = take(4 * (size_t)std::max<int64_t>(nnz, 1));
+    L.sig = take(8 * (size_t)std::max<int64_t>(nnz, 1));   // the lists, then the D lists of long merges
+    L.sig_slot = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig_len = take(4 * mm);
     L.dem = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.dem_seg = take(8 * (size_t)std::max<int64_t>(n_chunks, 1));
@@ -88,7 +91,9 @@ GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     L.last = take(4 * mm);
     L.touched = take(4 * mm);
     L.resc = take(4 * mm);
-    L.dbuf = take(4 * (size_t)std::max<int64_t>(nnz, 1));
+    L.live = take(4 * mm);
+    const size_t dm = std::min<size_t>(mm, kTailLive);
+    L.dense = take(8 * dm * dm);
     L.d_off = take(8 * (2 * mm));
     L.d_len = take(4 * (2 * mm));
     L.rec32 = take(4 * mm * kRec32);
@@ -268,21 +273,25 @@ __global__ __launch_bounds__(kCountThreads) void k_g_stretches(int64_t n_chunks,
 }
 
 // Request lists (chunk ids ascending) into sig, with the check for repeated
-// chunks, and the demand lists. Lists of up to kSegMax chunks take a wave
+// chunks, the demand lists, and sig_slot, where in dem a list entry's request
+// stands. Lists of up to kSegMax chunks take a wave
 // each, of up to kListMax a workgroup each; with a longer one, sig is left to
 // a key sort. Nothing is done once an error is known.
 __global__ __launch_bounds__(kListThreads) void k_g_lists(int m, const int64_t *__restrict__ req_off,
                                                           const int32_t *__restrict__ req_chunks,
                                                           const uint32_t *__restrict__ rank,
                                                           const uint64_t *__restrict__ dem_seg,
-                                                          int32_t *__restrict__ sig, int32_t *__restrict__ sig_len,
-                                                          int32_t *__restrict__ dem, GHeader *h) {
+                                                          int32_t *__restrict__ sig, int32_t *__restrict__ sig_slot,
+                                                          int32_t *__restrict__ sig_len, int32_t *__restrict__ dem,
+                                                          GHeader *h) {
     __shared__ uint32_t stage[kListMax];
     if (h->err & ~GERR_DUP) return;            // (GERR_DUP is raised in this launch: no workgroup stops for it)
     const int64_t longest = h->max_len;
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    auto demand = [&](int64_t j, int32_t x, int i) {
-        dem[(int64_t)(dem_seg[x] >> 32) + rank[j]] = (int32_t)i;
+    auto demand = [&](int64_t j, int32_t x, int i) {         // slot j's place in dem
+        const int32_t at = (int32_t)(dem_seg[x] >> 32) + (int32_t)rank[j];
+        dem[at] = (int32_t)i;
+        return at;
     };
     if (longest <= kSegMax) {
         const int nwaves = (int)(gridDim.x * blockDim.x) / kWave;
@@ -293,7 +302,7 @@ __global__ __launch_bounds__(kListThreads) void k_g_lists(int m, const int64_t *
             bool dup;
             const int pos = seg_rank((uint32_t)c, n, dup);
             if (lane < n) {
-                demand(o + lane, c, i);
+                sig_slot[o + pos] = demand(o + lane, c, i);
                 sig[o + pos] = c;
                 if (dup) atomicOr(&h->err, (uint32_t)GERR_DUP);
             }
@@ -304,12 +313,14 @@ __global__ __launch_bounds__(kListThreads) void k_g_lists(int m, const int64_t *
     for (int i = (int)blockIdx.x; i < m; i += (int)gridDim.x) {
         const int64_t o = req_off[i];
         const int64_t n = req_off[i + 1] - o;
-        for (int64_t e = threadIdx.x; e < n; e += kListThreads) demand(o + e, req_chunks[o + e], i);
         if (threadIdx.x == 0) sig_len[i] = (int32_t)n;
-        if (longest <= kListMax) {
+        if (longest > kListMax) {
+            for (int64_t e = threadIdx.x; e < n; e += kListThreads) demand(o + e, req_chunks[o + e], i);
+        } else {
             list_ranks(stage, (int)n, [&](int e) { return (uint32_t)req_chunks[o + e]; },
-                       [&](int, uint32_t c, int pos, bool dup) {
+                       [&](int e, uint32_t c, int pos, bool dup) {
                            sig[o + pos] = (int32_t)c;
+                           sig_slot[o + pos] = demand(o + e, (int32_t)c, i);
                            if (dup) atomicOr(&h->err, (uint32_t)GERR_DUP);
                        });
             __syncthreads();
@@ -330,10 +341,18 @@ __global__ void k_g_keys(int m, int64_t nnz, const int64_t *req_off, const int32
 }
 
 // sorted keys -> request lists; a repeated chunk inside a request is two
-// equal adjacent keys
-__global__ void k_g_sig_long(int64_t nnz, const uint64_t *keys, int32_t *sig, GHeader *h) {
+// equal adjacent keys. An entry's place in dem is looked for in its chunk's
+// demand list.
+__global__ void k_g_sig_long(int64_t nnz, const uint64_t *keys, const uint64_t *dem_seg, const int32_t *dem,
+                             int32_t *sig, int32_t *sig_slot, GHeader *h) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
-        sig[j] = (int32_t)(keys[j] & 0xffffffffu);
+        const int32_t x = (int32_t)(keys[j] & 0xffffffffu), i = (int32_t)(keys[j] >> 32);
+        const uint64_t seg = dem_seg[x];
+        const int32_t first = (int32_t)(seg >> 32), n = (int32_t)(seg & 0xffffffffu);
+        int32_t at = first;
+        while (at < first + n - 1 && dem[at] != i) ++at;
+        sig[j] = x;
+        sig_slot[j] = at;
         if (j > 0 && keys[j] == keys[j - 1]) atomicOr(&h->err, (uint32_t)GERR_DUP);
     }
 }
@@ -422,7 +441,10 @@ struct Rac {
     const int64_t *w;
     const int64_t *req_off;     // start of each cluster's signature in sig
     int32_t *sig;               // signatures, ascending, shrinking in place
+    int32_t *sig_slot;          // where in dem the entry's cluster stands
     int32_t *sig_len;
+    int32_t *dem;               // the clusters holding each chunk (-1: no longer); stretch of chunk x: dem_seg[x]
+    const uint64_t *dem_seg;
     int64_t *V;                 // V[a][c] = w(I(a) ∩ I(c)) for live a, c
     int64_t *best_v;
     int32_t *best_p;
@@ -433,8 +455,9 @@ struct Rac {
     // merge records, in the order the rounds produce them
     int32_t *ra, *rb, *rca, *rcb, *rpos, *rdal, *rdbl;
     int64_t *rgain, *rdao, *rdbo;
-    int32_t *dbuf;              // D(v) = I(v) \ I(parent(v)), packed
-    int64_t dcap;               // entries of dbuf (nnz: the D lists never need more)
+    int64_t nnz;                // D(v) = I(v) \ I(parent(v)) lies in sig, or from sig[nnz] on (at most nnz entries)
+    int32_t *live;              // the tail's clusters, ascending
+    int64_t *dense;             // their V
     int64_t *d_off;
     int32_t *d_len;
     int32_t *merge_a, *merge_b;
@@ -444,12 +467,6 @@ struct Rac {
 };
 
 __device__ inline uint64_t lanes_below(int lane) { return (1ull << lane) - 1ull; }
-
-// pair order (gain, a, b): true when x comes after y in the greedy's order
-// (smaller gain; equal gains, larger names)
-__device__ inline bool after(int64_t xg, int32_t xa, int32_t xb, int64_t yg, int32_t ya, int32_t yb) {
-    return xg < yg || (xg == yg && (xa > ya || (xa == ya && xb > yb)));
-}
 
 __global__ void k_rac_init(Rac R) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -466,179 +483,253 @@ __global__ void k_rac_init(Rac R) {
     }
 }
 
-// One wave per row a: if a and its best partner b > a are mutual best with
-// positive value, a new merge record i (a, b, value) is taken, and the wave
-// merges: I(C) = I(A) ∩ I(B) in place of I(A), D(B) = I(B) \ I(A) and
-// D(A) = I(A) \ I(B) to the packed lists, and the merges that formed A and
-// B. The pair test reads only values that no merge of the round writes
-// (best values and partners; a partner b that a merge deactivates fails the
-// test b > best partner as well), so merging while other waves still test
-// finds the same pairs. Record numbers within a round follow the atomic
-// order; the sequence is recovered by sorting on the pair order.
-__global__ void k_rac_pairs_merge(Rac R, int round) {
+// whether z is among the ascending values y of the wave's lanes (INT32_MAX:
+// none), by shuffles: six halvings of 64
+__device__ inline bool lane_find(int32_t y, int32_t z) {
+    int at = 0;
+#pragma unroll
+    for (int h = 32; h > 0; h >>= 1) at += __shfl(y, at + h - 1, kWave) < z ? h : 0;
+    return __shfl(y, at, kWave) == z;
+}
+
+// One wave merges clusters a and b as record i: I(C) = I(A) ∩ I(B) in place of
+// I(A), D(B) = I(B) \ I(A) and D(A) = I(A) \ I(B), and the merges that formed A
+// and B; b and what a loses leave the demand lists. Lists of up to 64 chunks
+// are read once and matched in registers, and the D lists stay where their
+// chunks were: D(A) behind what is left of A's list, D(B) in front of B's,
+// which no cluster reads any more. Longer ones search each other in memory and
+// move their D lists to sig + nnz, at reserve(entries) on lane 0. rec(): the
+// record's number, asked for once the lists' reads are under way. Returns
+// |I(C)|, or -1 (cannot happen) when there is no room.
+template <class Rec, class Reserve>
+__device__ inline int merge_pair(const Rac &R, int32_t a, int32_t b, int64_t oa, int64_t na, int64_t ob, int64_t nb,
+                                 int64_t gain, int round, Rec &&rec, Reserve &&reserve) {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t a = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; a < R.m; a += nwaves) {
-        int rec = -1;
-        int32_t b = -1;
-        if (lane == 0 && R.act[a] && R.best_v[a] > 0) {
-            b = R.best_p[a];
-            if (b > a && R.best_p[b] == (int32_t)a) {
-                const int i = atomicAdd(&R.h->n_rec, 1);
-                if (i >= R.m - 1) {
-                    atomicOr(&R.h->err, GERR_INVALID);   // cannot happen
-                } else {
-                    R.ra[i] = (int32_t)a;
-                    R.rb[i] = b;
-                    R.rgain[i] = R.best_v[a];
-                    rec = i;
-                }
-            }
+    const int32_t la = R.last[a], lb = R.last[b];
+    int32_t *sa = R.sig + oa, *sb = R.sig + ob, *ta = R.sig_slot + oa;
+    const int32_t *tb = R.sig_slot + ob;
+    int64_t kept = 0, d_a, d_b;                  // where the D lists lie in sig
+    int64_t i;
+    if (na <= kWave && nb <= kWave) {
+        int32_t x = INT32_MAX, z = INT32_MAX, xt = 0, zt = 0;
+        if (lane < na) { x = sa[lane]; xt = ta[lane]; }
+        if (lane < nb) { z = sb[lane]; zt = tb[lane]; }
+        i = rec();
+        if (i < 0) return -1;
+        const bool in_b = lane_find(z, x) && lane < na;
+        const bool in_a = lane_find(x, z) && lane < nb;
+        const uint64_t mb = __ballot(lane < nb && !in_a), mi = __ballot(in_b), mo = __ballot(lane < na && !in_b);
+        kept = __popcll(mi);
+        if (lane < nb) R.dem[zt] = -1;
+        if (lane < nb && !in_a) sb[__popcll(mb & lanes_below(lane))] = z;
+        if (in_b) {
+            const int at = __popcll(mi & lanes_below(lane));
+            sa[at] = x;
+            ta[at] = xt;
+        } else if (lane < na) {
+            sa[kept + __popcll(mo & lanes_below(lane))] = x;
+            R.dem[xt] = -1;
         }
-        rec = __shfl(rec, 0, kWave);
-        if (rec < 0) continue;
-        b = __shfl(b, 0, kWave);
-        const int64_t i = rec;
-        int32_t *sa = R.sig + R.req_off[a];
-        const int32_t *sb = R.sig + R.req_off[b];
-        const int64_t na = R.sig_len[a], nb = R.sig_len[b];
-        int64_t kept = 0;
+        d_a = oa + kept;
+        d_b = ob;
+    } else {
+        i = rec();
+        if (i < 0) return -1;
         for (int64_t base = 0; base < na; base += kWave) {
             const int64_t e = base + lane;
             kept += __popcll(__ballot(e < na && find_sorted(sb, nb, sa[e]) >= 0));
         }
         const int64_t dlen = na + nb - 2 * kept;
         unsigned long long dstart = 0;
-        if (lane == 0) dstart = atomicAdd(&R.h->dcursor, (unsigned long long)dlen);
+        if (lane == 0) dstart = reserve((unsigned long long)dlen);
         dstart = __shfl(dstart, 0, kWave);
-        if ((int64_t)dstart + dlen > R.dcap) {   // cannot happen for a valid run
-            if (lane == 0) atomicOr(&R.h->err, GERR_INVALID);
-            continue;
-        }
+        if ((int64_t)dstart + dlen > R.nnz) return -1;
+        int32_t *dbuf = R.sig + R.nnz;
         int64_t dcur = (int64_t)dstart;
+        d_b = R.nnz + dcur;
+        d_a = d_b + (nb - kept);
         for (int64_t base = 0; base < nb; base += kWave) {
             const int64_t e = base + lane;
-            int32_t x = 0;
             bool keep = false;
-            if (e < nb) { x = sb[e]; keep = find_sorted(sa, na, x) < 0; }
+            int32_t z = 0;
+            if (e < nb) { z = sb[e]; keep = find_sorted(sa, na, z) < 0; R.dem[tb[e]] = -1; }
             const uint64_t mk = __ballot(keep);
-            if (keep) R.dbuf[dcur + __popcll(mk & lanes_below(lane))] = x;
+            if (keep) dbuf[dcur + __popcll(mk & lanes_below(lane))] = z;
             dcur += __popcll(mk);
         }
-        const int64_t d_a_at = dcur;
         // in place: a lane writes at or below the entry it read, and the
         // entries above the current 64 are not written yet
         int64_t k = 0;
         for (int64_t base = 0; base < na; base += kWave) {
             const int64_t e = base + lane;
-            int32_t x = 0;
+            int32_t x = 0, xt = 0;
             bool in_b = false;
-            if (e < na) { x = sa[e]; in_b = find_sorted(sb, nb, x) >= 0; }
+            if (e < na) { x = sa[e]; xt = ta[e]; in_b = find_sorted(sb, nb, x) >= 0; }
             const uint64_t mi = __ballot(in_b);
             const uint64_t mo = __ballot(e < na && !in_b);
-            if (in_b) sa[k + __popcll(mi & lanes_below(lane))] = x;
-            else if (e < na) R.dbuf[dcur + __popcll(mo & lanes_below(lane))] = x;
+            if (in_b) {
+                const int64_t at = k + __popcll(mi & lanes_below(lane));
+                sa[at] = x;
+                ta[at] = xt;
+            } else if (e < na) {
+                dbuf[dcur + __popcll(mo & lanes_below(lane))] = x;
+                R.dem[xt] = -1;
+            }
             k += __popcll(mi);
             dcur += __popcll(mo);
         }
-        if (lane == 0) {
-            R.sig_len[a] = (int32_t)kept;
-            R.act[b] = 0;
-            R.touched[a] = round;
-            R.touched[b] = round;
-            const int32_t ca = R.last[a], cb = R.last[b];
-            R.rca[i] = ca;
-            R.rcb[i] = cb;
-            R.last[a] = (int32_t)i;
-            R.rdbo[i] = (int64_t)dstart;
-            R.rdbl[i] = (int32_t)(d_a_at - (int64_t)dstart);
-            R.rdao[i] = d_a_at;
-            R.rdal[i] = (int32_t)(dcur - d_a_at);
-        }
+    }
+    if (lane == 0) {
+        R.ra[i] = a;
+        R.rb[i] = b;
+        R.rgain[i] = gain;
+        R.sig_len[a] = (int32_t)kept;
+        R.act[b] = 0;
+        R.touched[a] = round;
+        R.touched[b] = round;
+        R.rca[i] = la;
+        R.rcb[i] = lb;
+        R.last[a] = (int32_t)i;
+        R.rdbo[i] = d_b;
+        R.rdbl[i] = (int32_t)(nb - kept);
+        R.rdao[i] = d_a;
+        R.rdal[i] = (int32_t)(na - kept);
+    }
+    return (int)kept;
+}
+
+// One wave per row a: if a and its best partner b > a are mutual best with
+// positive value, a new merge record i (a, b, value) is taken and the wave
+// merges the pair. The pair test reads only values that no merge of the round
+// writes (best values and partners; a partner b that a merge deactivates fails
+// the test b > best partner as well), so merging while other waves still test
+// finds the same pairs. Record numbers within a round follow the atomic
+// order; the sequence is recovered by sorting on the pair order.
+__global__ void k_rac_pairs_merge(Rac R, int round) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    for (int64_t a = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; a < R.m; a += nwaves) {
+        // (read together: a wave's time is its chain of dependent reads)
+        const int32_t live = R.act[a], b = R.best_p[a];
+        const int64_t v = R.best_v[a];
+        if (!live || v <= 0 || b <= (int32_t)a || R.best_p[b] != (int32_t)a) continue;
+        const int kept = merge_pair(
+            R, (int32_t)a, b, R.req_off[a], R.sig_len[a], R.req_off[b], R.sig_len[b], v, round,
+            [&]() {
+                int i = 0;
+                if (lane == 0) i = atomicAdd(&R.h->n_rec, 1);
+                i = __shfl(i, 0, kWave);
+                return i < R.m - 1 ? (int64_t)i : -1;
+            },
+            [&](unsigned long long n) { return atomicAdd(&R.h->dcursor, n); });
+        if (kept < 0 && lane == 0) atomicOr(&R.h->err, (uint32_t)GERR_INVALID);   // cannot happen
     }
 }
 
-// V[a][x] for the columns x of one wave (lane l: column x of lane l, need: the
-// values of both parts are positive and the merged list is not empty): groups
-// of G lanes, G the least power of two holding the merged list (at most 64),
-// take the wave's needed columns in turn, a lane per chunk of the list and a
-// binary search each in the column's list. The lists of a column are read by a
-// whole group at once; one lane walking its column's list alone was a chain of
-// up to kept * log2(len) dependent reads.
-__device__ inline int64_t group_weights(bool need, int32_t x, const int32_t *sa, int kept, int glog, const Rac &R) {
+// The clusters that hold the chunks of a list, walked by whole waves: add(c, w)
+// for every chunk y of list[0 .. kept) and live cluster c holding it (the
+// merged cluster itself among them), w = w(y). 64 chunks at a time, a lane
+// each; the entries of their demand lists are laid end to end and taken first,
+// first + stride, ... (first + a multiple of stride below the sum), each lane
+// finding its chunk by shuffles, four entries in flight. Entries of clusters
+// that merged away or lost the chunk read -1.
+template <class Add>
+__device__ inline void walk_holders(const Rac &R, const int32_t *list, int kept, int first, int stride, Add &&add) {
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int G = 1 << glog, grp = lane >> glog, e0 = lane & (G - 1);
-    uint64_t todo = __ballot(need);
-    int64_t mine = 0;
-    while (todo) {
-        // group q takes the q-th needed column
-        uint64_t rest = todo;
-        int src = -1;
-        for (int q = 0; q < kWave >> glog && rest; ++q) {
-            const int l = __ffsll((unsigned long long)rest) - 1;
-            rest &= rest - 1;
-            if (q == grp) src = l;
+    for (int base = 0; base < kept; base += kWave) {
+        const bool has = base + lane < kept;
+        const int32_t y = has ? list[base + lane] : 0;
+        const uint64_t seg = has ? R.dem_seg[y] : 0;
+        const int64_t wy = has ? R.w[y] : 0;
+        const int n = (int)(seg & 0xffffffffu);
+        int upto = n;                                     // entries of this lane's chunk and those before it
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int q = __shfl_up(upto, o, kWave);
+            if (lane >= o) upto += q;
         }
-        const int32_t c = __shfl(x, src < 0 ? 0 : src, kWave);
-        int64_t v = 0;
-        if (src >= 0) {
-            const int32_t *sx = R.sig + R.req_off[c];
-            const int64_t nx = R.sig_len[c];
-            for (int e = e0; e < kept; e += G) {
-                const int32_t y = sa[e];
-                if (find_sorted(sx, nx, y) >= 0) v += R.w[y];
+        const int total = __shfl(upto, kWave - 1, kWave);
+        const int shift = (int)(seg >> 32) - (upto - n);  // entry t lies at t + shift
+        constexpr int U = 4;
+        for (int t0 = 0; t0 < total; t0 += U * stride) {  // (the same turns for every lane)
+            int32_t c[U];
+            int64_t wt[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + u * stride + first;
+                int at = 0;                               // chunks that end at or before entry t
+#pragma unroll
+                for (int hlf = 32; hlf > 0; hlf >>= 1) at += __shfl(upto, at + hlf - 1, kWave) <= t ? hlf : 0;
+                const int sh = __shfl(shift, at, kWave);
+                wt[u] = __shfl(wy, at, kWave);
+                c[u] = t < total ? R.dem[t + sh] : -1;
             }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c[u] >= 0) add(c[u], wt[u]);
         }
-        for (int off = G >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-        // back to the columns' lanes: lane l's column was taken by the group
-        // of its place among this turn's
-        const int place = __popcll(todo & lanes_below(lane));
-        const int64_t got = __shfl(v, (place << glog) & (kWave - 1), kWave);
-        if (((todo ^ rest) >> lane) & 1ull) mine = got;
-        todo = rest;
     }
-    return mine;
 }
 
-__device__ inline int group_log(int64_t kept) {
-    int g = 0;
-    while (g < 6 && ((int64_t)1 << g) < kept) ++g;
-    return g;
-}
-
-// the new clusters' rows against every live column. A value is positive
-// only where both old values are; the row of a is written by its own merge
-// (columns of clusters merged in the same round included: both sides
-// compute the same value), the column entry of every other row here.
-// The same launch marks the rows whose best partner may have changed: the
-// new clusters and the rows whose best partner merged (no other row's best
-// can change: values fall).
-__global__ void k_rac_rows(Rac R, int round) {
+// The new clusters' rows: a workgroup per merge and tile of kPairTile columns
+// sums w(y) over the chunks y of the merged list into the columns of the
+// clusters that hold y, in LDS, and writes what changed: the row of a by its
+// own merge (columns of clusters merged in the same round included: both sides
+// compute the same value), the column entry of every other row here. The work
+// is the holders of the merged list, and the time a chain of seven reads, 10 to
+// 12 us whatever the lists are; intersecting the list with every column's list
+// took 33 us in the first 16 rounds of 701 requests of up to 100 chunks.
+// The same launch marks the rows whose best partner may have changed: the new
+// clusters, the rows whose best partner was merged away, and those whose value
+// with a best partner that lives on as a new cluster fell (no other row's best
+// can change: values only fall, and the partner is the smallest name at its
+// value). Of the rows whose best partner merged, that leaves a third to a half
+// at m = 4096.
+constexpr int kRowThreads = 512;
+__global__ __launch_bounds__(kRowThreads) void k_rac_rows(Rac R, int round) {
+    __shared__ unsigned long long row[kPairTile];
+    constexpr int PER = kPairTile / kRowThreads;             // columns per thread
     const int lo = R.h->lo, hi = min(R.h->n_rec, R.m - 1);
-    const int64_t m = R.m;
-    const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int64_t per = (m + kWave - 1) / kWave;                 // waves across the columns
-    const int64_t total = (int64_t)(hi - lo) * per;
-    const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t f = t0 / kWave; f < total; f += stride / kWave) {
-        const int64_t i = lo + f / per;
-        const int64_t col = (f % per) * kWave + lane;
-        const int32_t a = R.ra[i], b = R.rb[i];
-        const int64_t kept = R.sig_len[a];
-        const bool live = col < m && col != a && R.act[col];
-        const int64_t va = live ? R.V[a * m + col] : 0, vb = live ? R.V[b * m + col] : 0;
-        const int64_t v = group_weights(va > 0 && vb > 0 && kept > 0, (int32_t)col, R.sig + R.req_off[a], (int)kept,
-                                        group_log(kept), R);
-        if (live && v != va) {
-            R.V[a * m + col] = v;
-            if (R.touched[col] != round) R.V[col * m + a] = v;
-        }
-    }
     if (hi <= lo) return;                        // nothing merged, nothing to rescan
-    for (int64_t x = t0; x < m; x += stride) {
+    const int64_t m = R.m;
+    const int tid = (int)threadIdx.x;
+    const int tiles = (R.m + kPairTile - 1) / kPairTile;
+    for (int64_t f = blockIdx.x; f < (int64_t)(hi - lo) * tiles; f += gridDim.x) {
+        const int32_t a = R.ra[lo + f / tiles];
+        const int c0 = (int)(f % tiles) * kPairTile;
+        const int width = min(kPairTile, R.m - c0);
+        // the old row, on its way while the holders are walked
+        int64_t va[PER];
+        int32_t live[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int j = tid + u * kRowThreads;
+            va[u] = j < width ? R.V[a * m + c0 + j] : 0;
+            live[u] = j < width ? R.act[c0 + j] : 0;
+            row[j] = 0ull;
+        }
+        __syncthreads();
+        walk_holders(R, R.sig + R.req_off[a], R.sig_len[a], tid, kRowThreads, [&](int32_t c, int64_t w) {
+            if (c >= c0 && c < c0 + width) atomicAdd(&row[c - c0], (unsigned long long)w);
+        });
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int j = tid + u * kRowThreads;
+            if (!live[u] || c0 + j == a) continue;
+            const int64_t x = c0 + j, v = (int64_t)row[j];
+            if (v == va[u]) continue;
+            R.V[a * m + x] = v;
+            if (R.touched[x] == round) continue;
+            R.V[x * m + a] = v;
+            if (R.best_p[x] == a) R.resc[atomicAdd(&R.h->n_resc[round & 1], 1)] = (int32_t)x;
+        }
+        __syncthreads();
+    }
+    for (int64_t x = blockIdx.x * (int64_t)kRowThreads + tid; x < m; x += (int64_t)gridDim.x * kRowThreads) {
         if (!R.act[x]) continue;
         const int32_t p = R.best_p[x];
-        if (R.touched[x] == round || (p >= 0 && R.touched[p] == round))
+        if (R.touched[x] == round || (p >= 0 && !R.act[p]))
             R.resc[atomicAdd(&R.h->n_resc[round & 1], 1)] = (int32_t)x;
     }
 }
@@ -647,7 +738,7 @@ __global__ void k_rac_rows(Rac R, int round) {
 // each thread loads 8 columns before comparing them. Block 0 also closes
 // the round: the next round's records start at the current count, and its
 // rescan counter starts at 0.
-constexpr int kRescThreads = 256;
+constexpr int kRescThreads = 512;
 __global__ __launch_bounds__(kRescThreads) void k_rac_rescan(Rac R, int round) {
     __shared__ int64_t sv[kRescThreads / kWave];
     __shared__ int32_t si[kRescThreads / kWave];
@@ -693,26 +784,254 @@ __global__ __launch_bounds__(kRescThreads) void k_rac_rescan(Rac R, int round) {
     }
 }
 
+constexpr int kChainThreads = 1024;
+
+// The tail's clusters: the live ones in ascending order (one workgroup), and
+// their part of V as a dense matrix (a workgroup per row): the tail reads whole
+// rows of it from one CU, whose reads cost a line each in V's scattered columns
+// (22 us a round there, m = 4096, 500 clusters left).
+__global__ __launch_bounds__(kChainThreads) void k_rac_live(Rac R) {
+    __shared__ int scan_w[kChainThreads / kWave];
+    int done = 0;
+    for (int base = 0; base < R.m; base += kChainThreads) {
+        const int r = base + (int)threadIdx.x;
+        const int live = r < R.m && R.act[r];
+        int tot;
+        const int at = done + block_scan(live, &tot, scan_w);
+        if (live) R.live[at] = r;
+        done += tot;
+    }
+}
+
+// The demand lists without the entries that left them, a wave per chunk; the
+// clusters' lists learn their entries' new places.
+__global__ void k_rac_tidy(Rac R, int64_t n_chunks, uint64_t *dem_seg) {
+    const int lane = (int)(threadIdx.x & (kWave - 1));
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+    for (int64_t x = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; x < n_chunks; x += nwaves) {
+        const uint64_t seg = dem_seg[x];
+        const int start = (int)(seg >> 32), n = (int)(seg & 0xffffffffu);
+        int k = 0;
+        for (int base = 0; base < n; base += kWave) {
+            const int32_t c = base + lane < n ? R.dem[start + base + lane] : -1;
+            const uint64_t left = __ballot(c >= 0);
+            if (c >= 0) {
+                const int at = start + k + __popcll(left & lanes_below(lane));
+                const int64_t o = R.req_off[c], e = find_sorted(R.sig + o, R.sig_len[c], (int32_t)x);
+                R.dem[at] = c;           // (at or below the entry read)
+                if (e >= 0) R.sig_slot[o + e] = at;
+            }
+            k += __popcll(left);
+        }
+        if (lane == 0 && k != n) dem_seg[x] = ((uint64_t)start << 32) | (uint64_t)k;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_rac_dense(Rac R, int L) {
+    const int64_t i = blockIdx.x, x = R.live[i];
+    for (int j = threadIdx.x; j < L; j += 256) R.dense[i * L + j] = R.V[x * R.m + R.live[j]];
+}
+
+// All remaining rounds by one workgroup, once few clusters are left and few
+// pairs merge per round: the same rounds as the three kernels above, with the
+// live clusters' names, best partners and lists' places in LDS and barriers in
+// the place of launches. A round of one to a dozen merges spends its time in
+// dependent reads (of the lists, their holders, the rows to rescan), not in work
+// for 256 CUs: 15 us here at m = 4096 (40 rounds from 650 clusters on), 24 us
+// for three launches and as much as 10 more for their gaps, and no round is
+// launched in vain (the batches ran up to 31 empty ones).
+// Every round merges at least one pair of the live clusters, so the loop ends
+// after fewer than kTailLive rounds.
+constexpr int kTailThreads = 1024;
+// (pairs of the last round) x (live clusters) up to which the tail takes over
+// (20000: 8 rounds earlier, 270 us more in the tail and 240 us less before it at
+// m = 4096, and 415 against 200 us at 701 long requests)
+constexpr int64_t kTailWork = 8192;
+constexpr int kTailAcc = 3 * kTailLive;
+struct TailLds {
+    int64_t bv[kTailLive];               // best value
+    int64_t off[kTailLive];              // the list: sig[off .. off + len)
+    int32_t len[kTailLive];
+    int32_t stamp[kTailLive];            // round in which the cluster last merged
+    uint16_t id[kTailLive];              // names, ascending
+    uint16_t bp[kTailLive];              // place of the best partner; kNoPlace: none
+    uint16_t queue[kTailLive];           // places of the rows to rescan
+    uint16_t pa[kTailLive / 2], pb[kTailLive / 2];
+    uint8_t dead[kTailLive];
+    uint16_t place[MPT_GREEDY_MAX_M];    // name -> place
+    unsigned long long acc[kTailAcc];    // new rows in the making
+    int n_pairs, n_queue;
+    unsigned long long dcursor;
+};
+constexpr uint16_t kNoPlace = 0xffffu;
+__global__ __launch_bounds__(kTailThreads) void k_rac_tail(Rac R, int L, int round) {
+    __shared__ TailLds T;
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wv = tid / kWave;
+    constexpr int kWaves = kTailThreads / kWave;
+    for (int i = tid; i < L; i += kTailThreads) {
+        T.id[i] = (uint16_t)R.live[i];
+        T.place[R.live[i]] = (uint16_t)i;
+    }
+    __syncthreads();
+    for (int i = tid; i < L; i += kTailThreads) {
+        const int32_t x = T.id[i], p = R.best_p[x];
+        T.bp[i] = p >= 0 ? T.place[p] : kNoPlace;        // (the best partner of a live cluster is live)
+        T.bv[i] = R.best_v[x];
+        T.off[i] = R.req_off[x];
+        T.len[i] = R.sig_len[x];
+        T.stamp[i] = -1;
+        T.dead[i] = 0;
+    }
+    int n_rec = min(R.h->n_rec, R.m - 1);
+    if (tid == 0) T.dcursor = R.h->dcursor;
+    for (;; ++round) {
+        if (tid == 0) { T.n_pairs = 0; T.n_queue = 0; }
+        __syncthreads();
+        for (int i = tid; i < L; i += kTailThreads) {
+            const uint16_t p = T.bp[i];
+            if (T.dead[i] || T.bv[i] <= 0 || p == kNoPlace || (int)p <= i || (int)T.bp[p] != i) continue;
+            const int f = atomicAdd(&T.n_pairs, 1);
+            T.pa[f] = (uint16_t)i;
+            T.pb[f] = p;
+        }
+        __syncthreads();
+        const int np = T.n_pairs;
+        if (np == 0 || n_rec + np > R.m - 1) break;      // (the second cannot happen)
+        for (int f = wv; f < np; f += kWaves) {
+            const int ia = T.pa[f], ib = T.pb[f];
+            const int32_t a = T.id[ia], b = T.id[ib];
+            const int kept = merge_pair(R, a, b, T.off[ia], T.len[ia], T.off[ib], T.len[ib], T.bv[ia], round,
+                                        [&]() { return (int64_t)(n_rec + f); },
+                                        [&](unsigned long long n) { return atomicAdd(&T.dcursor, n); });
+            if (lane == 0) {
+                if (kept < 0) atomicOr(&R.h->err, (uint32_t)GERR_INVALID);       // cannot happen
+                T.len[ia] = max(kept, 0);
+                T.dead[ib] = 1;
+                T.stamp[ia] = round;
+                T.stamp[ib] = round;
+            }
+        }
+        n_rec += np;
+        __syncthreads();
+        // the new rows: as many merges at a time as the LDS holds rows for, the
+        // waves shared out among them
+        const int par = min(min(np, kWaves), kTailAcc / L), per = kWaves / par;
+        for (int f0 = 0; f0 < np; f0 += par) {
+            const int slot = wv / per, f = f0 + slot;
+            const bool mine = slot < par && f < np;
+            const int first = (wv % per) * kWave + lane, stride = per * kWave;
+            unsigned long long *acc = T.acc + (size_t)slot * L;
+            if (mine)
+                for (int c = first; c < L; c += stride) acc[c] = 0ull;
+            __syncthreads();
+            if (mine) {
+                const int ia = T.pa[f];
+                walk_holders(R, R.sig + T.off[ia], T.len[ia], first, stride, [&](int32_t c, int64_t w) {
+                    atomicAdd(&acc[T.place[c]], (unsigned long long)w);
+                });
+            }
+            __syncthreads();
+            if (mine) {
+                const int64_t ia = T.pa[f];
+                constexpr int U = 4;
+                for (int d0 = first; d0 < L; d0 += U * stride) {
+                    int64_t va[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int d = d0 + u * stride;
+                        va[u] = d < L && d != ia && !T.dead[d] ? R.dense[ia * L + d] : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (va[u] < 0) continue;
+                        const int64_t d = d0 + u * stride, v = (int64_t)acc[d];
+                        if (v == va[u]) continue;
+                        R.dense[ia * L + d] = v;
+                        if (T.stamp[d] == round) continue;
+                        R.dense[d * L + ia] = v;
+                        if ((int64_t)T.bp[d] == ia) T.queue[atomicAdd(&T.n_queue, 1)] = (uint16_t)d;
+                    }
+                }
+            }
+            __syncthreads();                             // the rows' LDS is the next merges'
+        }
+        for (int i = tid; i < L; i += kTailThreads) {
+            if (T.dead[i]) continue;
+            const uint16_t p = T.bp[i];
+            if (T.stamp[i] == round || (p != kNoPlace && T.dead[p]))
+                T.queue[atomicAdd(&T.n_queue, 1)] = (uint16_t)i;
+        }
+        __syncthreads();
+        // best partners of the queued rows, a wave each, two rows in flight
+        for (int q = wv; q < T.n_queue; q += 2 * kWaves) {
+            const int qq[2] = {q, q + kWaves < T.n_queue ? q + kWaves : q};
+            int64_t v[2] = {-1, -1};
+            int32_t p[2] = {-1, -1};
+            for (int d0 = lane; d0 < L; d0 += 8 * kWave) {
+                int64_t x[2][8];
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int d = d0 + u * kWave, i = T.queue[qq[k]];
+                        x[k][u] = d < L && d != i && !T.dead[d] ? R.dense[(int64_t)i * L + d] : -2;
+                    }
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (x[k][u] >= 0 && better(x[k][u], d0 + u * kWave, v[k], p[k])) {
+                            v[k] = x[k][u];
+                            p[k] = d0 + u * kWave;
+                        }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                wave_best(v[k], p[k]);
+                if (lane == 0) {
+                    T.bv[T.queue[qq[k]]] = v[k];
+                    T.bp[T.queue[qq[k]]] = p[k] < 0 ? kNoPlace : (uint16_t)p[k];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        R.h->n_rec = n_rec;
+        R.h->lo = n_rec;
+        R.h->last_pairs = 0;
+        R.h->dcursor = T.dcursor;
+    }
+}
+
 // position of every record in the greedy's sequence: the records before it
-// in the pair order. Blocks take a tile of records (x) against a tile of
-// others (y), held in LDS, and add their counts (positions start at 0).
+// in the pair order (gain descending, names ascending). Blocks take a tile of
+// records (x) against a tile of kRankTileY others, held in LDS, and add their
+// counts (positions start at 0). 64 others a block and four comparisons in
+// flight: with 256, one after the other, the 3700 records of m = 4096 took 28
+// us.
 constexpr int kRankThreads = 256;
+constexpr int kRankTileY = 64;
 __global__ __launch_bounds__(kRankThreads) void k_rac_rank(Rac R, int n) {
-    __shared__ int64_t tg[kRankThreads];
-    __shared__ int32_t ta[kRankThreads], tb[kRankThreads];
+    __shared__ int64_t tg[kRankTileY];
+    __shared__ uint32_t tn[kRankTileY];
     const int i = blockIdx.x * kRankThreads + threadIdx.x;
-    const int j0 = blockIdx.y * kRankThreads;
-    const int j = j0 + threadIdx.x;
-    if (j < n) { tg[threadIdx.x] = R.rgain[j]; ta[threadIdx.x] = R.ra[j]; tb[threadIdx.x] = R.rb[j]; }
+    const int j0 = blockIdx.y * kRankTileY;
+    const int j = j0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < kRankTileY) {         // a record past the end comes after every other
+        tg[threadIdx.x] = j < n ? R.rgain[j] : -1;
+        tn[threadIdx.x] = j < n ? (uint32_t)R.ra[j] << 14 | (uint32_t)R.rb[j] : ~0u;
+    }
     __syncthreads();
     if (i >= n) return;
     const int64_t g = R.rgain[i];
-    const int32_t a = R.ra[i], b = R.rb[i];
-    const int cnt = min(kRankThreads, n - j0);
+    const uint32_t names = (uint32_t)R.ra[i] << 14 | (uint32_t)R.rb[i];
     int pos = 0;
-    for (int k = 0; k < cnt; ++k) pos += after(g, a, b, tg[k], ta[k], tb[k]) ? 1 : 0;
+#pragma unroll 4
+    for (int k = 0; k < kRankTileY; ++k) pos += tg[k] > g || (tg[k] == g && tn[k] < names) ? 1 : 0;
     if (pos) atomicAdd(&R.rpos[i], pos);
 }
+static_assert(MPT_GREEDY_MAX_M <= 1 << 14, "two names in 28 bits");
 
 // tree node of merge record i is m + its position; leaves are 0 .. m - 1
 __device__ inline int32_t rec_node(const Rac &R, int32_t rec, int32_t leaf) {
@@ -743,32 +1062,22 @@ __global__ void k_rac_emit(Rac R, int n) {
 // (the root's whole signature if only one cluster is left) and the
 // chain's own nodes emit nothing. Live names in ascending order, one
 // round of the workgroup at a time.
-constexpr int kChainThreads = 1024;
 __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
     __shared__ int scan_w[kChainThreads / kWave];
     __shared__ int32_t first_name;
     const int m = R.m, tid = threadIdx.x;
     if (tid == 0) first_name = -1;
     __syncthreads();
-    int64_t dcur = (int64_t)R.h->dcursor;
     int done = 0;                                // live names ranked so far
     for (int base = 0; base < m; base += kChainThreads) {
         const int r = base + tid;
         const int live = r < m && R.act[r];
-        const int len = live ? R.sig_len[r] : 0;
-        int tot, ltot;
+        int tot;
         const int rank = done + block_scan(live, &tot, scan_w);
-        const int loff = block_scan(len, &ltot, scan_w);
-        if (dcur + ltot > R.dcap) {              // cannot happen for a valid run
-            if (tid == 0) atomicOr(&R.h->err, GERR_INVALID);
-            return;
-        }
         if (live) {
             const int32_t node = rec_node(R, R.last[r], r);
-            const int32_t *src = R.sig + R.req_off[r];
-            for (int e = 0; e < len; ++e) R.dbuf[dcur + loff + e] = src[e];
-            R.d_off[node] = dcur + loff;
-            R.d_len[node] = len;
+            R.d_off[node] = R.req_off[r];
+            R.d_len[node] = R.sig_len[r];
             if (rank == 0) {
                 first_name = r;
             } else {
@@ -781,7 +1090,6 @@ __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
             }
         }
         done += tot;
-        dcur += ltot;
         __syncthreads();
     }
     const int n_live = done;
@@ -789,7 +1097,7 @@ __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
     // node m+t0+k-1 and the name of rank k+1
     for (int k = tid; k + 1 < n_live && t0 + k < m - 1; k += kChainThreads) {
         R.merge_a[t0 + k] = first_name;
-        R.d_off[m + t0 + k] = dcur;
+        R.d_off[m + t0 + k] = 0;
         R.d_len[m + t0 + k] = 0;
         if (k > 0) R.node_parent[m + t0 + k - 1] = m + t0 + k;
     }
@@ -802,7 +1110,7 @@ __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
 // The zero-gain merges (nodes m + chain_from and up) emit nothing and
 // every node above one of them is one of them, so a walk ends there.
 __global__ void k_g_orders(int m, int64_t nnz, const int64_t *req_off, const int32_t *node_parent,
-                           const int32_t *dbuf, const int64_t *d_off, const int32_t *d_len, int32_t *order_chunks,
+                           const int32_t *sig, const int64_t *d_off, const int32_t *d_len, int32_t *order_chunks,
                            int chain_from, GHeader *h) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
@@ -814,11 +1122,11 @@ __global__ void k_g_orders(int m, int64_t nnz, const int64_t *req_off, const int
         if (v >= 2 * m - 1) { if (lane == 0) atomicOr(&h->err, GERR_INVALID); return; }
         if (v >= m + chain_from) break;
         const int64_t len = d_len[v];
-        if (len < 0 || end - len < begin || d_off[v] < 0 || d_off[v] + len > nnz) {
+        if (len < 0 || end - len < begin || d_off[v] < 0 || d_off[v] + len > 2 * nnz) {
             if (lane == 0) atomicOr(&h->err, GERR_INVALID);
             return;
         }
-        const int32_t *src = dbuf + d_off[v];
+        const int32_t *src = sig + d_off[v];
         for (int64_t e = lane; e < len; e += kWave) order_chunks[end - len + e] = src[e];
         end -= len;
     }
@@ -842,16 +1150,23 @@ __device__ inline uint32_t edge_id(int u, int v) {
 // k_bv_merge raises h->bv_done when a root finds no edge out of its
 // component (P is complete, so that root's component holds every vertex),
 // and the later rounds' kernels return at once.
-__global__ void k_bv_init(int m, int32_t *comp, int64_t *cw, uint32_t *ce, GHeader *h) {
+__global__ void k_bv_init(int m, int32_t *comp, int64_t *vw, int64_t *cw, GHeader *h) {
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < m; v += gridDim.x * blockDim.x) {
         comp[v] = v;
+        vw[v] = -1;
         cw[v] = -1;
-        ce[v] = ~0u;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         h->total = 0;
         h->bv_done = 0;
     }
+}
+
+// *p = max(*p, v) for a value that only rises: an atomic only where it would
+// still raise it (all vertices of a large component share p, and atomics on one
+// address serialise: a round of two components took 52 us, others 28)
+__device__ inline void raise_best(int64_t *p, int64_t v) {
+    if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < v) atomicMax((long long *)p, (long long)v);
 }
 
 // best edge of every vertex to another component (one wave per vertex),
@@ -863,8 +1178,16 @@ __global__ void k_bv_vertex(int m, const int64_t *P, const int32_t *comp, int64_
     const int64_t u = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
     if (u >= m) return;
     const int32_t cu = comp[u];
-    int64_t bw = -1;
-    uint32_t be = ~0u;
+    int64_t bw = vw[u];
+    uint32_t be = bw >= 0 ? ve[u] : ~0u;
+    // the vertex's best edge of an earlier round stays its best while it
+    // leaves the component (the edges to choose from only get fewer)
+    if (bw >= 0 && comp[(int64_t)(be >> 14) == u ? be & 0x3fffu : be >> 14] != cu) {
+        if (lane == 0) raise_best(&cw[cu], bw);
+        return;
+    }
+    bw = -1;
+    be = ~0u;
     // eight columns per lane in flight (twelve rounds at m = 4096, five of
     // them real: 219 us, one column at a time 254 us)
     constexpr int U = 8;
@@ -891,71 +1214,82 @@ __global__ void k_bv_vertex(int m, const int64_t *P, const int32_t *comp, int64_
     }
     if (lane == 0) {
         vw[u] = bw; ve[u] = be;
-        if (bw >= 0) atomicMax((long long *)&cw[cu], (long long)bw);
+        if (bw >= 0) raise_best(&cw[cu], bw);
     }
 }
 
-// The rest of a round, by one workgroup with barriers between its phases: the
-// smallest edge among the vertices that reach their component's best weight;
-// every component hooks onto the component across its best edge, except the
-// smaller one of a mutual pair, and the hooking side adds the edge weight;
-// every vertex follows the hooks to its new root; the components' best weights
-// are cleared for the next round. m <= 16384 entries per array, 16 per thread:
-// 10 us at m = 4096, where four launches took 14 us and three more gaps.
+// The rest of a round, by one workgroup with barriers between its phases and
+// the components, hooks and best edges in LDS: the smallest edge among the
+// vertices that reach their component's best weight; every component hooks onto
+// the component across its best edge, except the smaller one of a mutual pair,
+// and the hooking side adds the edge weight; every vertex follows the hooks to
+// its new root; the components' best weights are cleared for the next round.
+// Four launches over m entries took 14 us and three more gaps, this kernel with
+// its arrays in memory 20 us (the walks to the roots are chains of reads).
 constexpr int kBvThreads = 1024;
 __global__ __launch_bounds__(kBvThreads) void k_bv_merge(int m, int32_t *comp, const int64_t *vw, const uint32_t *ve,
-                                                         int64_t *cw, uint32_t *ce, int32_t *par, GHeader *h) {
+                                                         int64_t *cw, GHeader *h) {
+    __shared__ uint32_t ce[MPT_GREEDY_MAX_M];
+    __shared__ uint16_t cp[MPT_GREEDY_MAX_M], par[MPT_GREEDY_MAX_M];
     __shared__ uint32_t done;
     const int tid = (int)threadIdx.x;
     if (h->bv_done) return;
     if (tid == 0) done = 0;
-    __syncthreads();
-    for (int u = tid; u < m; u += kBvThreads) {
-        const int32_t cu = comp[u];
-        if (vw[u] >= 0 && vw[u] == cw[cu]) atomicMin(&ce[cu], ve[u]);
+    for (int v = tid; v < m; v += kBvThreads) {
+        cp[v] = (uint16_t)comp[v];
+        ce[v] = ~0u;
     }
-    __threadfence();
+    __syncthreads();
+    constexpr int U = 4;                               // vertices per thread in flight
+    for (int u0 = tid; u0 < m; u0 += U * kBvThreads) {
+        int64_t w[U], best[U];
+        uint32_t e[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int u = u0 + q * kBvThreads;
+            w[q] = u < m ? vw[u] : -1;
+            e[q] = u < m ? ve[u] : ~0u;
+            best[q] = u < m ? cw[cp[u]] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (w[q] >= 0 && w[q] == best[q]) atomicMin(&ce[cp[u0 + q * kBvThreads]], e[q]);
+    }
     __syncthreads();
     uint64_t sum = 0;
     for (int c = tid; c < m; c += kBvThreads) {
-        int32_t to = c;
-        if (comp[c] == c) {
-            const uint32_t e = __hip_atomic_load(&ce[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int to = c;
+        if (cp[c] == c) {
+            const uint32_t e = ce[c];
             if (e == ~0u) {
                 done = 1;                              // no edge out: one component is left
             } else {
                 const int lo = (int)(e >> 14), hi = (int)(e & 0x3fffu);
-                const int32_t d = comp[lo] == c ? comp[hi] : comp[lo];
-                const uint32_t ed = __hip_atomic_load(&ce[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (!(ed == e && c < d)) {             // else d hooks onto c
+                const int d = cp[lo] == c ? cp[hi] : cp[lo];
+                if (!(ce[d] == e && c < d)) {          // else d hooks onto c
                     to = d;
                     sum += (uint64_t)cw[c];
                 }
             }
         }
-        par[c] = to;
+        par[c] = (uint16_t)to;
     }
 #pragma unroll
     for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
     if ((tid & (kWave - 1)) == 0 && sum) atomicAdd(&h->total, (unsigned long long)sum);
-    __threadfence();
-    __syncthreads();
+    __syncthreads();                                   // (cw is read before it is cleared)
     if (done) {
         if (tid == 0) h->bv_done = 1;
         return;
     }
     for (int v = tid; v < m; v += kBvThreads) {
-        int32_t r = comp[v];
-        for (int guard = 0; guard < m; ++guard) {
-            const int32_t q = par[r];
-            if (q == r) break;
-            r = q;
-        }
+        int r = cp[v];
+        for (int guard = 0; guard < m && par[r] != r; ++guard) r = par[r];
         comp[v] = r;
         cw[v] = -1;
-        ce[v] = ~0u;
     }
 }
+static_assert(MPT_GREEDY_MAX_M <= 1 << 14, "vertices in 16 bits, edges in 28");
 
 // ---------------------------------------------------------------------------
 // host side
@@ -996,6 +1330,7 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
               int64_t *request_total = nullptr) {
     GHeader *h = (GHeader *)ws;
     int32_t *sig = (int32_t *)(ws + L.sig), *sig_len = (int32_t *)(ws + L.sig_len), *dem = (int32_t *)(ws + L.dem);
+    int32_t *sig_slot = (int32_t *)(ws + L.sig_slot);
     uint64_t *dem_seg = (uint64_t *)(ws + L.dem_seg);
     uint32_t *rank = (uint32_t *)(ws + L.rank);
     const int64_t blocks = (int64_t)m * ((m + kPairTile - 1) / kPairTile);
@@ -1010,8 +1345,8 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
                     kCountThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, chunk_w, dem_seg, rank, h);
         if (n_chunks > 0)
             k_g_stretches<<<grid_for(n_chunks, kCountThreads), kCountThreads, 0, s>>>(n_chunks, dem_seg, h);
-        k_g_lists<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, dem_seg, sig, sig_len,
-                                                               dem, h);
+        k_g_lists<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, dem_seg, sig, sig_slot,
+                                                               sig_len, dem, h);
     }
     pairs(0);
     MPT_HIP_TRY(hipGetLastError());
@@ -1023,7 +1358,7 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
         LaunchScope ls("g_sort", (double)nnz, s);
         k_g_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, (uint64_t *)(ws + L.keys1));
         if ((rc = sort_keys((uint64_t *)(ws + L.keys1), (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
-        k_g_sig_long<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, sig, h);
+        k_g_sig_long<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, dem_seg, dem, sig, sig_slot, h);
     }
     pairs(1);
     MPT_HIP_TRY(hipGetLastError());
@@ -1074,7 +1409,10 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
     R.w = chunk_w;
     R.req_off = req_off;
     R.sig = (int32_t *)(ws + L.sig);
+    R.sig_slot = (int32_t *)(ws + L.sig_slot);
     R.sig_len = (int32_t *)(ws + L.sig_len);
+    R.dem = (int32_t *)(ws + L.dem);
+    R.dem_seg = (const uint64_t *)(ws + L.dem_seg);
     R.V = V;
     R.best_v = (int64_t *)(ws + L.best_v);
     R.best_p = (int32_t *)(ws + L.best_p);
@@ -1088,8 +1426,9 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
     int64_t *r64 = (int64_t *)(ws + L.rec64);
     int64_t **f64[kRec64] = {&R.rgain, &R.rdao, &R.rdbo};
     for (int k = 0; k < kRec64; ++k) *f64[k] = r64 + (size_t)k * m;
-    R.dbuf = (int32_t *)(ws + L.dbuf);
-    R.dcap = std::max<int64_t>(nnz, 1);
+    R.nnz = std::max<int64_t>(nnz, 1);
+    R.live = (int32_t *)(ws + L.live);
+    R.dense = (int64_t *)(ws + L.dense);
     R.d_off = (int64_t *)(ws + L.d_off);
     R.d_len = (int32_t *)(ws + L.d_len);
     R.merge_a = merge_a;
@@ -1102,22 +1441,36 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
         k_g_row_best<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, V, R.best_v, R.best_p);
         k_rac_init<<<grid_for(2 * (int64_t)m, 256), 256, 0, s>>>(R);
     }
-    // rounds in batches without host synchronisation; a round that finds
-    // no pair changes nothing, so the batch's last round tells whether the
-    // rounds are over. Batches of 8, 8, 16 and then 32 rounds: few
-    // synchronisations, at most 31 empty rounds (a few µs each) at the end.
+    // Rounds in batches without host synchronisation, until the rest is the
+    // tail's (k_rac_tail, which needs no further look); a round that finds no
+    // pair changes nothing, so the batch's last round tells whether the rounds
+    // are over. The first round merges about a sixth of the clusters, so an
+    // instance whose first round would be the tail's goes there at once.
     int n_rec = 0;
     {
         LaunchScope ls("g_rounds", (double)(m - 1), s);
         const int g_rec = std::max(1, std::min(4096, (m + 3) / 4));        // waves: one per row
-        const int g_cols = grid_for((int64_t)m * std::max(1, m / 2), 256, 4096);   // (2048: 1% slower, 512: 17%)
+        const int g_cols = std::max(1, std::min(2048, m / 2 * ((m + kPairTile - 1) / kPairTile)));   // workgroups: one per merge and tile
         const int g_resc = std::max(1, std::min(m, 2048));                  // workgroups: one per marked row
+        int64_t pairs = (m + 5) / 6;
         for (int round = 0;;) {
-            const int batch = round < 16 ? 8 : round < 32 ? 16 : 32;
-            for (int k = 0; k < batch; ++k, ++round) {
-                k_rac_pairs_merge<<<g_rec, 4 * kWave, 0, s>>>(R, round);
-                k_rac_rows<<<g_cols, 256, 0, s>>>(R, round);
-                k_rac_rescan<<<g_resc, kRescThreads, 0, s>>>(R, round);
+            const int64_t live = m - n_rec;
+            const bool tail = live <= kTailLive && pairs * live <= kTailWork;
+            if (tail) {
+                k_rac_live<<<1, kChainThreads, 0, s>>>(R);
+                k_rac_dense<<<(unsigned)live, 256, 0, s>>>(R, (int)live);
+                // (one look at every chunk: not worth it for a universe far
+                // larger than the requests)
+                if (round > 0 && n_chunks <= ((int64_t)1 << 20))
+                    k_rac_tidy<<<grid_for(n_chunks, 4, 8192), 4 * kWave, 0, s>>>(R, n_chunks,
+                                                                                (uint64_t *)(ws + L.dem_seg));
+                k_rac_tail<<<1, kTailThreads, 0, s>>>(R, (int)live, round);
+            } else {
+                for (int k = 0; k < 8; ++k, ++round) {
+                    k_rac_pairs_merge<<<g_rec, 4 * kWave, 0, s>>>(R, round);
+                    k_rac_rows<<<g_cols, kRowThreads, 0, s>>>(R, round);
+                    k_rac_rescan<<<g_resc, kRescThreads, 0, s>>>(R, round);
+                }
             }
             MPT_HIP_TRY(hipGetLastError());
             GHeader hh;
@@ -1125,15 +1478,17 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
             MPT_HIP_TRY(hipStreamSynchronize(s));
             if (hh.err) return fail(MPT_E_INTERNAL, "greedy rounds left an inconsistent state");   // cannot happen
             n_rec = std::min(hh.n_rec, m - 1);
-            if (hh.last_pairs == 0) break;
-            if (round > m + 32) return fail(MPT_E_INTERNAL, "greedy rounds do not end");   // cannot happen
+            pairs = hh.last_pairs;
+            if (pairs == 0) break;
+            if (tail || round > m + 32) return fail(MPT_E_INTERNAL, "greedy rounds do not end");   // cannot happen
         }
     }
     {
         LaunchScope ls("g_sequence", (double)m, s);
         if (n_rec > 0) {
-            const unsigned tiles = (unsigned)((n_rec + kRankThreads - 1) / kRankThreads);
-            k_rac_rank<<<dim3(tiles, tiles), kRankThreads, 0, s>>>(R, n_rec);
+            const unsigned tx = (unsigned)((n_rec + kRankThreads - 1) / kRankThreads);
+            const unsigned ty = (unsigned)((n_rec + kRankTileY - 1) / kRankTileY);
+            k_rac_rank<<<dim3(tx, ty), kRankThreads, 0, s>>>(R, n_rec);
             k_rac_emit<<<grid_for(n_rec, 256), 256, 0, s>>>(R, n_rec);
         }
         k_rac_chain<<<1, kChainThreads, 0, s>>>(R, n_rec);
@@ -1141,7 +1496,7 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
     MPT_HIP_TRY(hipGetLastError());
     if (order_chunks) {
         LaunchScope ls("g_orders", 4.0 * (double)nnz, s);
-        k_g_orders<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, nnz, req_off, node_parent, R.dbuf, R.d_off, R.d_len,
+        k_g_orders<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, nnz, req_off, node_parent, R.sig, R.d_off, R.d_len,
                                                      order_chunks, n_rec, R.h);
         MPT_HIP_TRY(hipGetLastError());
     }
@@ -1168,26 +1523,26 @@ extern "C" int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_wei
     if (!P || !mst_weight) return fail(MPT_E_INVALID, "P and mst_weight must not be NULL");
     if (!workspace) return fail(MPT_E_WORKSPACE, "workspace is NULL");
     if (((uintptr_t)workspace & 255u) != 0) return fail(MPT_E_WORKSPACE, "workspace is not 256-byte aligned");
-    // header, then comp, par, vertex-best and component-best arrays
-    const size_t mm = (size_t)m;
-    const size_t off_comp = align256(sizeof(GHeader)), off_par = off_comp + align256(4 * mm),
-                 off_vw = off_par + align256(4 * mm), off_ve = off_vw + align256(8 * mm),
-                 off_cw = off_ve + align256(4 * mm), off_ce = off_cw + align256(8 * mm), need = off_ce + align256(4 * mm);
+    // header, then the vertices' components, best weights and edges and the
+    // components' best weights (24 m bytes of the documented 32 m)
+    const size_t mm = (size_t)m, a4 = align256(4 * mm), a8 = align256(8 * mm);
+    const size_t off_comp = align256(sizeof(GHeader)), off_vw = off_comp + a4, off_ve = off_vw + a8,
+                 off_cw = off_ve + a4, need = off_comp + 4 * a4 + 2 * a8;
     if (workspace_bytes < need) return fail(MPT_E_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
     hipStream_t s = (hipStream_t)stream;
     GHeader *h = (GHeader *)workspace;
     char *ws = (char *)workspace;
-    int32_t *comp = (int32_t *)(ws + off_comp), *par = (int32_t *)(ws + off_par);
+    int32_t *comp = (int32_t *)(ws + off_comp);
     int64_t *vw = (int64_t *)(ws + off_vw), *cw = (int64_t *)(ws + off_cw);
-    uint32_t *ve = (uint32_t *)(ws + off_ve), *ce = (uint32_t *)(ws + off_ce);
+    uint32_t *ve = (uint32_t *)(ws + off_ve);
     int rounds = 0;
     while ((1 << rounds) < m) ++rounds;
     const int gv = grid_for(m, 256);
-    k_bv_init<<<gv, 256, 0, s>>>(m, comp, cw, ce, h);
+    k_bv_init<<<gv, 256, 0, s>>>(m, comp, vw, cw, h);
     for (int r = 0; r < rounds; ++r) {
         LaunchScope ls("g_boruvka", 8.0 * (double)m * m, s);
         k_bv_vertex<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, P, comp, vw, ve, cw, h);
-        k_bv_merge<<<1, kBvThreads, 0, s>>>(m, comp, vw, ve, cw, ce, par, h);
+        k_bv_merge<<<1, kBvThreads, 0, s>>>(m, comp, vw, ve, cw, h);
     }
     MPT_HIP_TRY(hipGetLastError());
     unsigned long long total = 0;
