@@ -174,9 +174,9 @@ __global__ void k_g_begin(int64_t n_chunks, uint64_t *dem_seg, GHeader *h) {
 // one address serialise device-wide, so each workgroup counts its slice of the
 // slots in an LDS hash table first (linear probing; a slot that finds no entry
 // counts in memory directly) and adds each entry once.
-constexpr int kCountThreads = 256;
-constexpr int kCountSlice = 1024;              // slots per workgroup pass
-constexpr int kCountBits = 11;
+constexpr int kCountThreads = 1024;
+constexpr int kCountSlice = 4096;              // slots per workgroup pass
+constexpr int kCountBits = 13;
 constexpr int kCountEntries = 1 << kCountBits;
 constexpr int kCountProbes = 16;
 __global__ __launch_bounds__(kCountThreads) void k_g_check(int m, int64_t n_chunks, int64_t nnz,
@@ -218,7 +218,8 @@ __global__ __launch_bounds__(kCountThreads) void k_g_check(int m, int64_t n_chun
             if (wx > 0 && wx <= MPT_MAX_CHUNK_WEIGHT) total += (uint64_t)wx;
             uint32_t slot = ((uint32_t)x * 2654435761u) >> (32 - kCountBits);
             for (int p = 0; p < kCountProbes && at[q] < 0; ++p) {
-                const uint32_t k = atomicCAS(&key[slot], 0u, (uint32_t)x + 1u);
+                uint32_t k = *(volatile uint32_t *)&key[slot];      // (most find their chunk there)
+                if (k == 0u) k = atomicCAS(&key[slot], 0u, (uint32_t)x + 1u);
                 if (k == 0u || k == (uint32_t)x + 1u) {
                     at[q] = (int)slot;
                     place[q] = atomicAdd(&cnt[slot], 1u);

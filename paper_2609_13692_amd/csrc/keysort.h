@@ -64,29 +64,54 @@ template <int X, bool FLIP> __device__ inline void cross(uint64_t (&v)[kSortPer]
 }
 // (a key equal to its partner's stays on both sides: the two are the same)
 
-// the 256 keys of a wave, key lane * 4 + r in v[r]: a bitonic sort whose
+// The 256 keys of a wave, key lane * 4 + r in v[r]: a bitonic sort whose
 // merges of k keys start by pairing i with i ^ (k - 1), so that every exchange
-// leaves the smaller key at the lower index
-__device__ inline void sort_wave(uint64_t (&v)[kSortPer]) {
-    auto half2 = [&]() {                                  // strides 2, 1
-        order2(v[0], v[2]); order2(v[1], v[3]);
-        order2(v[0], v[1]); order2(v[2], v[3]);
-    };
+// leaves the smaller key at the lower index. sort_wave64 stops at runs of 64
+// (16 lanes), sort_wave256 goes on from there.
+__device__ inline void half2(uint64_t (&v)[kSortPer]) {      // strides 2, 1
+    order2(v[0], v[2]); order2(v[1], v[3]);
+    order2(v[0], v[1]); order2(v[2], v[3]);
+}
+__device__ inline void sort_wave64(uint64_t (&v)[kSortPer]) {
     order2(v[0], v[1]); order2(v[2], v[3]);               // k = 2
     order2(v[0], v[3]); order2(v[1], v[2]);               // k = 4
     order2(v[0], v[1]); order2(v[2], v[3]);
-    cross<1, true>(v); half2();                           // k = 8
-    cross<3, true>(v); cross<1, false>(v); half2();       // 16
-    cross<7, true>(v); cross<2, false>(v); cross<1, false>(v); half2();
-    cross<15, true>(v); cross<4, false>(v); cross<2, false>(v); cross<1, false>(v); half2();
-    cross<31, true>(v); cross<8, false>(v); cross<4, false>(v); cross<2, false>(v); cross<1, false>(v); half2();
+    cross<1, true>(v); half2(v);                          // k = 8
+    cross<3, true>(v); cross<1, false>(v); half2(v);      // 16
+    cross<7, true>(v); cross<2, false>(v); cross<1, false>(v); half2(v);
+    cross<15, true>(v); cross<4, false>(v); cross<2, false>(v); cross<1, false>(v); half2(v);
+}
+__device__ inline void sort_wave256(uint64_t (&v)[kSortPer]) {
+    cross<31, true>(v); cross<8, false>(v); cross<4, false>(v); cross<2, false>(v); cross<1, false>(v); half2(v);
     cross<63, true>(v); cross<16, false>(v); cross<8, false>(v); cross<4, false>(v); cross<2, false>(v);
-    cross<1, false>(v); half2();                          // 256
+    cross<1, false>(v); half2(v);                         // 256
+}
+// kSortPer consecutive outputs, from o on, of the merge of each pair of sorted
+// runs of `run` keys in t: the split of the two runs at the first output by a
+// binary search, then one comparison per output
+__device__ inline void merge_outputs(const uint64_t *t, int run, int o, uint64_t (&v)[kSortPer]) {
+    const int diag = o & (2 * run - 1);
+    const uint64_t *A = t + (o - diag), *B = A + run;
+    int lo = diag > run ? diag - run : 0, hi = diag < run ? diag : run;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (A[mid] <= B[diag - 1 - mid]) lo = mid + 1; else hi = mid;
+    }
+    int a = lo, b = diag - lo;
+    uint64_t ka = a < run ? A[a] : 0, kb = b < run ? B[b] : 0;
+#pragma unroll
+    for (int r = 0; r < kSortPer; ++r) {
+        const bool take_a = b >= run || (a < run && ka <= kb);
+        v[r] = take_a ? ka : kb;
+        a += take_a ? 1 : 0;
+        b += take_a ? 0 : 1;
+        if (take_a) ka = a < run ? A[a] : 0;
+        else kb = b < run ? B[b] : 0;
+    }
 }
 
 // tiles of kSortTile keys: 256 keys per wave in registers, then the runs
-// merged in LDS, every thread its four outputs (the split of the two runs at
-// its first output by a binary search, then one comparison per output)
+// merged in LDS, every thread its four outputs
 // (in place: a workgroup has read all of its tile before it writes)
 static __global__ __launch_bounds__(kSortThreads) void k_sort_tile(uint64_t *keys, int64_t n) {
     __shared__ __align__(16) uint64_t t[2][kSortTile];
@@ -98,31 +123,15 @@ static __global__ __launch_bounds__(kSortThreads) void k_sort_tile(uint64_t *key
         const int64_t i = base + wv * 256 + r * 64 + lane;
         v[r] = i < n ? keys[i] : ~0ull;                     // padding sorts last
     }
-    sort_wave(v);
+    sort_wave64(v);
+    sort_wave256(v);
     const int o = tid * kSortPer;                         // this thread's first output
 #pragma unroll
     for (int r = 0; r < kSortPer; ++r) t[0][o + r] = v[r];
     __syncthreads();
     int cur = 0;
     for (int run = 256; run < kSortTile; run <<= 1, cur ^= 1) {
-        const int diag = o & (2 * run - 1);
-        const uint64_t *A = &t[cur][o - diag], *B = A + run;
-        int lo = diag > run ? diag - run : 0, hi = diag < run ? diag : run;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (A[mid] <= B[diag - 1 - mid]) lo = mid + 1; else hi = mid;
-        }
-        int a = lo, b = diag - lo;
-        uint64_t ka = a < run ? A[a] : 0, kb = b < run ? B[b] : 0;
-#pragma unroll
-        for (int r = 0; r < kSortPer; ++r) {
-            const bool take_a = b >= run || (a < run && ka <= kb);
-            v[r] = take_a ? ka : kb;
-            a += take_a ? 1 : 0;
-            b += take_a ? 0 : 1;
-            if (take_a) ka = a < run ? A[a] : 0;
-            else kb = b < run ? B[b] : 0;
-        }
+        merge_outputs(t[cur], run, o, v);
 #pragma unroll
         for (int r = 0; r < kSortPer; ++r) t[cur ^ 1][o + r] = v[r];
         __syncthreads();

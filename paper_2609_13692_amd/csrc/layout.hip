@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <cstring>
 #include <vector>
 
 #include "common.h"
@@ -41,11 +42,14 @@ namespace {
 using mptlib::align256;
 using mptlib::fail;
 using mptlib::grid_for;
+using mptlib::kListMax;
+using mptlib::kListThreads;
 using mptlib::kSegMax;
+using mptlib::list_ranks;
 using mptlib::LaunchScope;
 using mptlib::seg_rank;
 using mptlib::sort_keys;
-using mptlib::kSeqSortTile;
+using mptlib::seq_recs_bytes;
 using mptlib::sort_requests;
 
 constexpr int kWave = 64;
@@ -69,8 +73,8 @@ inline int64_t pow2_at_least(int64_t n) {
 }
 
 struct LLayout {
-    size_t ord, rank, lcp, base, pn, nw, mtree, crank, cinv, keys, keys2, sched, log_off, logs, acc_start, prev, next, accw,
-        bnext, bsum, cfg_win, cfg_cap, cfg_off, cfg_list, costs, total;
+    size_t ord, rank, recs, lcp, base, pn, nw, mtree, crank, cinv, keys, keys2, sched, log_off, logs, acc_start, prev, next, wsuf,
+        snext, ssum, bnext, bsum, cfg_win, cfg_cap, cfg_off, cfg_list, costs, total;
     int64_t mpad;
 };
 
@@ -78,14 +82,15 @@ struct LLayout {
 LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     LLayout L{};
     const size_t mm = (size_t)m, nz = (size_t)std::max<int64_t>(nnz, 1), nc = (size_t)std::max(n_cfg, 0);
-    L.mpad = std::max<int64_t>(pow2_at_least(m), kSeqSortTile);
+    L.mpad = std::max<int64_t>(pow2_at_least(m), 1024);      // leaves of the segment tree
     // the most keys of one sort (two buffers)
     const size_t kn = (size_t)std::max(std::max<int64_t>(nnz, n_chunks), (int64_t)nc * std::max<int64_t>(m, nnz));
-    const size_t nblk = (nz + 255) / 256;       // sorted blocks of the access logs (kStackBlock entries)
+    const size_t nblk = (nz + 1023) / 1024;     // big sorted blocks of the access logs (kBigBlock entries)
     size_t o = align256(sizeof(LHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
-    L.ord = take(4 * (size_t)L.mpad);
+    L.ord = take(4 * mm);
     L.rank = take(4 * mm);
+    L.recs = take(2 * seq_recs_bytes(m));
     L.lcp = take(4 * mm);
     L.base = take(8 * (mm + 1));
     L.pn = take(4 * nz);
@@ -101,9 +106,11 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     L.acc_start = take(4 * nc * nz);
     L.prev = take(4 * nc * nz);
     L.next = take(4 * nc * nz);
-    L.accw = take(8 * nc * nz);
-    L.bnext = take(4 * nc * nblk * 256);
-    L.bsum = take(8 * nc * nblk * 256);
+    L.wsuf = take(8 * nc * nz);
+    L.snext = take(4 * nc * nblk * 1024);
+    L.ssum = take(8 * nc * nblk * 1024);
+    L.bnext = take(4 * nc * nblk * 1024);
+    L.bsum = take(8 * nc * nblk * 1024);
     L.cfg_win = take(8 * nc);
     L.cfg_cap = take(8 * nc);
     L.cfg_off = take(4 * (nc + 1));
@@ -116,36 +123,65 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
 // ---------------------------------------------------------------------------
 // validation
 
-__global__ void k_l_header(LHeader *h) {
-    if (threadIdx.x == 0) { h->err = 0; h->total = 0; h->cost = 0; h->max_len = 0; }
+// header and, where given, zero[0 .. n)
+__global__ void k_l_begin(LHeader *h, int32_t *zero, int64_t n) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) { h->err = 0; h->total = 0; h->cost = 0; h->max_len = 0; }
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) zero[i] = 0;
 }
 
-__global__ void k_l_check_offsets(int m, int64_t nnz, const int64_t *off, LHeader *h) {
-    bool ok = true;
-    int64_t mx = 0;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) {
+constexpr int kCheckThreads = 256;
+// the sum of v over the workgroup, on thread 0
+__device__ inline uint64_t check_block_sum(uint64_t v, uint64_t (&red)[kCheckThreads / kWave]) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
+    __syncthreads();
+    uint64_t sum = 0;
+    for (int k = 0; k < kCheckThreads / kWave; ++k) sum += red[k];
+    return sum;
+}
+
+// offsets, chunk ids and (w given) weights, the longest sequence and the total
+// weight: one addition per workgroup (one per slot on the total's address was
+// 25 us at 160088 slots, and the offsets on one workgroup 18 us)
+__global__ __launch_bounds__(kCheckThreads) void k_l_check(int m, int64_t nnz, int64_t n_chunks,
+                                                           const int64_t *__restrict__ off,
+                                                           const int32_t *__restrict__ seqs,
+                                                           const int64_t *__restrict__ w, LHeader *h) {
+    __shared__ uint64_t red[kCheckThreads / kWave];
+    const int64_t t0 = blockIdx.x * (int64_t)kCheckThreads + threadIdx.x, stride = (int64_t)gridDim.x * kCheckThreads;
+    uint32_t err = 0;
+    int64_t longest = 0;
+    for (int64_t i = t0; i < m; i += stride) {
         const int64_t len = off[i + 1] - off[i];
-        ok = ok && len >= 0;
-        mx = len > mx ? len : mx;
+        if (len < 0) err |= LERR_INVALID;
+        longest = len > longest ? len : longest;
     }
-    if (threadIdx.x == 0) ok = ok && off[0] == 0 && off[m] == nnz;
-    if (!ok) atomicOr(&h->err, LERR_INVALID);
-    if (mx > 0) atomicMax((long long *)&h->max_len, (long long)mx);
-}
-
-__global__ void k_l_check_chunks(int64_t nnz, int64_t n_chunks, const int32_t *seqs, const int64_t *w, LHeader *h) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
+    if (t0 == 0 && (off[0] != 0 || off[m] != nnz)) err |= LERR_INVALID;
+    uint64_t total = 0;
+    for (int64_t j = t0; j < nnz; j += stride) {
         const int32_t x = seqs[j];
-        if (x < 0 || (int64_t)x >= n_chunks) { atomicOr(&h->err, LERR_RANGE); continue; }
-        if (w) {
-            const int64_t wx = w[x];
-            if (wx <= 0 || wx > MPT_MAX_CHUNK_WEIGHT) atomicOr(&h->err, LERR_WEIGHT);
-            else atomicAdd(&h->total, (unsigned long long)wx);
-        }
+        if (x < 0 || (int64_t)x >= n_chunks) { err |= LERR_RANGE; continue; }
+        if (!w) continue;
+        const int64_t wx = w[x];
+        if (wx <= 0 || wx > MPT_MAX_CHUNK_WEIGHT) err |= LERR_WEIGHT;
+        else total += (uint64_t)wx;
     }
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        const int64_t l = __shfl_xor(longest, o, kWave);
+        longest = l > longest ? l : longest;
+        err |= (uint32_t)__shfl_xor((int)err, o, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        if (err) atomicOr(&h->err, err);
+        if (longest > 0) atomicMax((long long *)&h->max_len, (long long)longest);
+    }
+    total = check_block_sum(total, red);
+    if (threadIdx.x == 0 && total) atomicAdd(&h->total, (unsigned long long)total);
 }
 
-int l_read_errors(LHeader *h, hipStream_t s, int64_t *max_len = nullptr) {
+int l_read_errors(LHeader *h, hipStream_t s, int64_t *max_len = nullptr, int64_t *cost = nullptr) {
     LHeader hh;
     MPT_HIP_TRY(hipMemcpyAsync(&hh, h, sizeof hh, hipMemcpyDeviceToHost, s));
     MPT_HIP_TRY(hipStreamSynchronize(s));
@@ -154,24 +190,54 @@ int l_read_errors(LHeader *h, hipStream_t s, int64_t *max_len = nullptr) {
     if (hh.err & LERR_WEIGHT) return fail(MPT_E_WEIGHT, "a chunk weight is <= 0 or > 2^32");
     if (hh.total >= (1ull << 61)) return fail(MPT_E_OVERFLOW, "sum of sequence weights reaches 2^61");
     if (max_len) *max_len = hh.max_len;
+    if (cost) *cost = (int64_t)hh.cost;
     return MPT_OK;
 }
 
 // ---------------------------------------------------------------------------
 // global-order layouts
 
-__global__ void k_l_fill_i32(int32_t *p, int64_t n, int32_t v) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
 __global__ void k_l_fill_u64(uint64_t *p, int64_t n, uint64_t v) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// demand of every chunk (into the rank array, reused below)
-__global__ void k_l_count(int64_t nnz, const int32_t *chunks, int32_t *cnt) {
-    for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x)
-        atomicAdd(&cnt[chunks[j]], 1);
+// Demand of every chunk (into the rank array, zeroed). Popular chunks repeat
+// in a quarter of the requests, and atomics on one address serialise
+// device-wide (70 us at 160088 slots, one per slot), so each workgroup counts
+// its slice in an LDS hash table first (linear probing; a slot that finds no
+// entry is counted in memory directly).
+constexpr int kCountThreads = 1024;
+constexpr int kCountSlice = 4096;
+constexpr int kCountBits = 13;
+constexpr int kCountEntries = 1 << kCountBits;
+constexpr int kCountProbes = 16;
+__global__ __launch_bounds__(kCountThreads) void k_l_count(int64_t nnz, const int32_t *__restrict__ chunks,
+                                                           int32_t *cnt, const LHeader *h) {
+    __shared__ uint32_t key[kCountEntries], num[kCountEntries];     // chunk + 1 (0: empty), its slots
+    if (h->err) return;
+    for (int64_t s0 = (int64_t)blockIdx.x * kCountSlice; s0 < nnz; s0 += (int64_t)gridDim.x * kCountSlice) {
+        for (int e = (int)threadIdx.x; e < kCountEntries; e += kCountThreads) { key[e] = 0u; num[e] = 0u; }
+        __syncthreads();
+        for (int64_t j = s0 + threadIdx.x; j < s0 + kCountSlice && j < nnz; j += kCountThreads) {
+            const uint32_t x = (uint32_t)chunks[j];
+            uint32_t slot = (x * 2654435761u) >> (32 - kCountBits);
+            bool done = false;
+            for (int p = 0; p < kCountProbes && !done; ++p) {
+                uint32_t k = *(volatile uint32_t *)&key[slot];      // (most find their chunk there)
+                if (k == 0u) k = atomicCAS(&key[slot], 0u, x + 1u);
+                if (k == 0u || k == x + 1u) {
+                    atomicAdd(&num[slot], 1u);
+                    done = true;
+                }
+                slot = (slot + 1u) & (kCountEntries - 1u);
+            }
+            if (!done) atomicAdd(&cnt[x], 1);
+        }
+        __syncthreads();
+        for (int e = (int)threadIdx.x; e < kCountEntries; e += kCountThreads)
+            if (key[e]) atomicAdd(&cnt[key[e] - 1u], (int32_t)num[e]);
+        __syncthreads();
+    }
 }
 
 // popularity key of chunk x: demand descending, then id ascending
@@ -210,21 +276,43 @@ __global__ void k_l_layout_out(int64_t nnz, const uint64_t *keys, const int32_t 
     }
 }
 
-// the layout when every request has at most kSegMax chunks: one wave per
-// request ranks its chunks by their position in the order (the id, or the
-// popularity rank), ties by slot
-__global__ void k_l_layout_short(int m, const int64_t *req_off, const int32_t *chunks, const int32_t *rank, int kind,
-                                 int32_t *seqs) {
-    const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
-    for (int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; i < m; i += nwaves) {
+// the layout when every request has at most kListMax chunks: a wave per
+// request (up to kSegMax chunks) or a workgroup per request orders its chunks
+// by their position in the order (the id, or the popularity rank), ties by
+// slot. With longer requests, or an error, nothing is done (the key sort's).
+__global__ __launch_bounds__(kListThreads) void k_l_layout_short(int m, const int64_t *__restrict__ req_off,
+                                                                 const int32_t *chunks,
+                                                                 const int32_t *__restrict__ rank, int kind,
+                                                                 int32_t *seqs, const LHeader *h) {
+    __shared__ uint32_t stage[kListMax];
+    if (h->err || h->max_len > kListMax) return;
+    auto place = [&](int32_t x) { return kind == MPT_ORDER_ID ? (uint32_t)x : (uint32_t)rank[x]; };
+    if (h->max_len <= kSegMax) {
+        const int lane = (int)(threadIdx.x & (kWave - 1));
+        const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / kWave;
+        for (int64_t i = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; i < m; i += nwaves) {
+            const int64_t o = req_off[i];
+            const int n = (int)(req_off[i + 1] - o);
+            const int32_t x = lane < n ? chunks[o + lane] : 0;
+            bool dup;
+            const int pos = seg_rank(lane < n ? place(x) : 0u, n, dup);
+            if (lane < n) seqs[o + pos] = x;
+        }
+        return;
+    }
+    for (int64_t i = blockIdx.x; i < m; i += gridDim.x) {
         const int64_t o = req_off[i];
+        // the chunks themselves, held until all of the request's are read
+        int32_t x[kListMax / kListThreads];
         const int n = (int)(req_off[i + 1] - o);
-        const int32_t x = lane < n ? chunks[o + lane] : 0;
-        const uint32_t r = lane < n ? (kind == MPT_ORDER_ID ? (uint32_t)x : (uint32_t)rank[x]) : 0u;
-        bool dup;
-        const int pos = seg_rank(r, n, dup);
-        if (lane < n) seqs[o + pos] = x;
+        int q = 0;
+        list_ranks(stage, n,
+                   [&](int e) {
+                       x[q] = chunks[o + e];
+                       return place(x[q++]);
+                   },
+                   [&](int e, uint32_t, int pos, bool) { seqs[o + pos] = x[e / kListThreads]; });
+        __syncthreads();
     }
 }
 
@@ -236,11 +324,19 @@ __global__ void k_l_inverse(int64_t n, const int32_t *rank, int32_t *inv) {
 // ---------------------------------------------------------------------------
 // trie cost, ranks, node ids
 
-// position s of the sorted order: LCP with s-1, the weight it adds, the
-// count of its new nodes (into base[s + 1] for the scan), rank of its request
-__global__ void k_l_lcp(int m, const int32_t *ord, const int64_t *off, const int32_t *seqs, const int64_t *w,
-                        int32_t *lcp, int64_t *base, int32_t *rank, LHeader *h) {
-    for (int s = blockIdx.x * blockDim.x + threadIdx.x; s < m; s += gridDim.x * blockDim.x) {
+// position s of the sorted order: LCP with s-1, the weight it adds (one
+// addition per workgroup), the count of its new nodes (into base[s + 1] for the
+// scan), rank of its request
+__global__ __launch_bounds__(kCheckThreads) void k_l_lcp(int m, const int32_t *__restrict__ ord,
+                                                         const int64_t *__restrict__ off,
+                                                         const int32_t *__restrict__ seqs,
+                                                         const int64_t *__restrict__ w, int32_t *__restrict__ lcp,
+                                                         int64_t *__restrict__ base, int32_t *__restrict__ rank,
+                                                         LHeader *h) {
+    __shared__ uint64_t red[kCheckThreads / kWave];
+    if (h->err) return;
+    uint64_t add = 0;
+    for (int s = blockIdx.x * kCheckThreads + threadIdx.x; s < m; s += gridDim.x * kCheckThreads) {
         const int i = ord[s];
         const int64_t li = off[i + 1] - off[i];
         const int32_t *si = seqs + off[i];
@@ -251,42 +347,75 @@ __global__ void k_l_lcp(int m, const int32_t *ord, const int64_t *off, const int
             const int32_t *sp = seqs + off[p];
             while (l < li && l < lp && si[l] == sp[l]) ++l;
         }
-        unsigned long long add = 0;
-        for (int64_t j = l; j < li; ++j) add += (unsigned long long)w[si[j]];
-        if (add) atomicAdd(&h->cost, add);
+        for (int64_t j = l; j < li; ++j) add += (uint64_t)w[si[j]];
         lcp[s] = (int32_t)l;
         base[s + 1] = li - l;
         rank[i] = s;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) base[0] = 0;
+    add = check_block_sum(add, red);
+    if (threadIdx.x == 0 && add) atomicAdd(&h->cost, (unsigned long long)add);
 }
 
-// in-place inclusive scan of base[1 .. m] (one workgroup): base[s] becomes
-// the first node id of sorted position s, base[m] the node count
-__global__ __launch_bounds__(1024) void k_l_scan(int m, int64_t *base) {
-    __shared__ int64_t sw[16];
-    __shared__ int64_t carry;
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int b0 = 1; b0 <= m; b0 += blockDim.x) {
-        const int i = b0 + threadIdx.x;
-        int64_t x = i <= m ? base[i] : 0;
+// In-place scan of a[0 .. n) by one workgroup of 1024, inclusive or exclusive,
+// kScanPer * 1024 entries at a time through LDS: coalesced reads and writes,
+// kScanPer consecutive entries per thread in between. The sums stay below 2^31
+// (at most nnz). (One entry per thread at a time was a round trip per 1024
+// entries, 30 us at 20011.)
+constexpr int kScanPer = 16;
+template <bool INCL>
+__device__ inline void scan_array(int64_t n, int64_t *a) {
+    __shared__ int32_t buf[1024 * (kScanPer + 1)];       // one pad per thread's entries: no bank conflicts
+    __shared__ int32_t sw[16];
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    int32_t carry = 0;
+    for (int64_t b0 = 0; b0 < n; b0 += 1024 * kScanPer) {
+        int64_t v[kScanPer];
+#pragma unroll
+        for (int q = 0; q < kScanPer; ++q) {
+            const int e = q * 1024 + tid;
+            v[q] = b0 + e < n ? a[b0 + e] : 0;
+        }
+#pragma unroll
+        for (int q = 0; q < kScanPer; ++q) {
+            const int e = q * 1024 + tid;
+            buf[e + e / kScanPer] = (int32_t)v[q];
+        }
+        __syncthreads();
+        int32_t x = 0, in[kScanPer];
+#pragma unroll
+        for (int q = 0; q < kScanPer; ++q) {
+            const int32_t t = buf[tid * (kScanPer + 1) + q];
+            in[q] = INCL ? x + t : x;
+            x += t;
+        }
+        const int32_t own = x;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
-            const int64_t y = __shfl_up(x, o, kWave);
+            const int32_t y = __shfl_up(x, o, kWave);
             if (lane >= o) x += y;
         }
         if (lane == kWave - 1) sw[wid] = x;
         __syncthreads();
-        int64_t before = carry;
-        for (int k = 0; k < wid; ++k) before += sw[k];
-        if (i <= m) base[i] = before + x;
+        int32_t before = carry + x - own;
+        for (int k = 0; k < 16; ++k) {
+            before += k < wid ? sw[k] : 0;
+            carry += sw[k];
+        }
+#pragma unroll
+        for (int q = 0; q < kScanPer; ++q) buf[tid * (kScanPer + 1) + q] = before + in[q];
         __syncthreads();
-        if (threadIdx.x == blockDim.x - 1) carry = before + x;
+#pragma unroll
+        for (int q = 0; q < kScanPer; ++q) {
+            const int e = q * 1024 + tid;
+            if (b0 + e < n) a[b0 + e] = buf[e + e / kScanPer];
+        }
         __syncthreads();
     }
 }
+
+// base[s] becomes the first node id of sorted position s, base[m] the node count
+__global__ __launch_bounds__(1024) void k_l_scan(int m, int64_t *base) { scan_array<true>(m, base + 1); }
 
 // weight of every trie node: sorted position s creates the nodes of depths
 // LCP .. len-1 of its request, with ids base[s] + (j - LCP)
@@ -401,30 +530,7 @@ __global__ void k_l_sched_out(int m, int n_cfg, const uint64_t *keys, const int3
 // exclusive scan of the log lengths of every configuration (one workgroup
 // per configuration)
 __global__ __launch_bounds__(1024) void k_l_log_scan(int m, int64_t *log_off) {
-    __shared__ int64_t sw[16];
-    __shared__ int64_t carry;
-    int64_t *a = log_off + (int64_t)blockIdx.x * m;
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int b0 = 0; b0 < m; b0 += blockDim.x) {
-        const int i = b0 + threadIdx.x;
-        const int64_t v = i < m ? a[i] : 0;
-        int64_t x = v;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int64_t y = __shfl_up(x, o, kWave);
-            if (lane >= o) x += y;
-        }
-        if (lane == kWave - 1) sw[wid] = x;
-        __syncthreads();
-        int64_t before = carry;
-        for (int k = 0; k < wid; ++k) before += sw[k];
-        if (i < m) a[i] = before + x - v;
-        __syncthreads();
-        if (threadIdx.x == blockDim.x - 1) carry = before + x;
-        __syncthreads();
-    }
+    scan_array<false>(m, log_off + (int64_t)blockIdx.x * m);
 }
 
 // the access log of every configuration: served requests in order, each
@@ -464,8 +570,7 @@ __global__ void k_l_logs(int m, int n_cfg, int64_t nnz, const int32_t *sched, co
 // again before s (next_j >= s). D does not depend on the capacity: one pass
 // over a schedule's log bills all its capacities.
 
-constexpr int kStackBlock = 256;               // log entries per sorted block
-static_assert(kStackBlock == 256, "the lockstep searches of k_l_bill take 9 halvings");
+constexpr int kSmallBlock = 64, kBigBlock = 1024;   // log entries per sorted block
 
 // sort keys of the access logs of schedules d0 .. d0 + nd - 1: (schedule,
 // node, log position)
@@ -494,139 +599,227 @@ __global__ void k_l_prev_next(int64_t nnz, int d0, int nd, int be, const uint64_
     }
 }
 
-// one workgroup per block of 256 log entries of one schedule: the entries'
-// weights, and the block sorted by next access descending with the running
-// weight sum, so that the weight of the entries with next >= s is a prefix
-__global__ __launch_bounds__(kStackBlock) void k_l_stack_blocks(int64_t nnz, int64_t nblk, const int32_t *logs,
-                                                                const int64_t *nw, const int32_t *next,
-                                                                int64_t *accw, int32_t *bnext, int64_t *bsum) {
-    __shared__ uint64_t t[kStackBlock];
-    __shared__ int64_t ws[kStackBlock];
+// One workgroup per big block of one schedule's log. For every entry, the
+// weight of the entries from it to the end of its small block (wsuf); and the
+// small blocks, then the big one, sorted by next access descending with the
+// running weight sum, so that the weight of a block's entries with next >= s is
+// a prefix. Keys (next access inverted << 10 | entry), sorted in registers up
+// to 256 and merged in LDS.
+constexpr int kStackThreads = kBigBlock / 4;
+__device__ inline int32_t stack_next(uint64_t key) { return (int32_t)(0x7fffffffll - (int64_t)(key >> 10)); }
+__global__ __launch_bounds__(kStackThreads) void k_l_stack_blocks(int64_t nnz, int64_t nblk,
+                                                                  const int32_t *__restrict__ logs,
+                                                                  const int64_t *__restrict__ nw,
+                                                                  const int32_t *__restrict__ next,
+                                                                  int64_t *__restrict__ wsuf,
+                                                                  int32_t *__restrict__ snext,
+                                                                  int64_t *__restrict__ ssum,
+                                                                  int32_t *__restrict__ bnext,
+                                                                  int64_t *__restrict__ bsum) {
+    using namespace mptlib::keysort_detail;
+    __shared__ __align__(16) uint64_t t[2][kBigBlock];
+    __shared__ int64_t ws[kBigBlock];
+    __shared__ int64_t part[kStackThreads / kWave];
+    const int tid = (int)threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int64_t d = blockIdx.x / nblk, b = blockIdx.x % nblk;
-    const int64_t j = b * kStackBlock + threadIdx.x;
-    const int64_t at = d * nnz + j;
-    int64_t w = 0;
-    int32_t nx = -1;                                     // padding: never counted
-    if (j < nnz) {
-        w = nw[logs[at]];
-        nx = next[at];
-        accw[at] = w;
-    }
-    ws[threadIdx.x] = w;
-    // key: next access in the high half (biased so that -1 sorts lowest),
-    // entry index in the low half; sorted descending
-    t[threadIdx.x] = ((uint64_t)(uint32_t)(nx + 1) << 32) | (uint64_t)threadIdx.x;
-    __syncthreads();
-    for (int k = 2; k <= kStackBlock; k <<= 1)
-        for (int s = k >> 1; s > 0; s >>= 1) {
-            const int i = threadIdx.x, pj = i ^ s;
-            if (pj > i) {
-                const bool desc = (i & k) == 0;
-                const uint64_t a = t[i], c = t[pj];
-                if (desc ? (a < c) : (a > c)) { t[i] = c; t[pj] = a; }
-            }
-            __syncthreads();
-        }
-    const uint64_t key = t[threadIdx.x];
-    int64_t x = ws[key & 0xffffffffull];
-    // inclusive scan of the weights in sorted order
-    __shared__ int64_t sw[kStackBlock / kWave];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int64_t j0 = b * kBigBlock + tid * 4;
+    uint64_t v[4];
+    int64_t w[4];
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int64_t y = __shfl_up(x, o, kWave);
-        if (lane >= o) x += y;
+    for (int r = 0; r < 4; ++r) {
+        const int64_t at = d * nnz + j0 + r;
+        w[r] = 0;
+        int32_t nx = -1;                                 // padding: never counted
+        if (j0 + r < nnz) {
+            w[r] = nw[logs[at]];
+            nx = next[at];
+        }
+        ws[tid * 4 + r] = w[r];
+        v[r] = ((uint64_t)(0x7fffffffll - nx) << 10) | (uint64_t)(tid * 4 + r);
     }
-    if (lane == kWave - 1) sw[wid] = x;
+    {
+        // 16 lanes hold a small block
+        int64_t suf[4], x;
+        suf[3] = w[3];
+#pragma unroll
+        for (int r = 2; r >= 0; --r) suf[r] = w[r] + suf[r + 1];
+        x = suf[0];
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+            const int64_t y = __shfl_down(x, o, 16);
+            if ((lane & 15) + o < 16) x += y;
+        }
+        x -= suf[0];                                     // the lanes after this one
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (j0 + r < nnz) wsuf[d * nnz + j0 + r] = suf[r] + x;
+    }
     __syncthreads();
-    for (int k = 0; k < wid; ++k) x += sw[k];
-    const int64_t out = d * nblk * kStackBlock + j;
-    bnext[out] = (int32_t)(key >> 32) - 1;
-    bsum[out] = x;
+    const int64_t out = (d * nblk + b) * kBigBlock + tid * 4;
+    // running sums of the sorted weights over WIDTH lanes, from start on
+    auto emit = [&](int width, int64_t start, int32_t *on, int64_t *os) {
+        int64_t pre[4], x = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pre[r] = x += ws[v[r] & (kBigBlock - 1u)];
+        const int64_t own = x;
+        for (int o = 1; o < width; o <<= 1) {
+            const int64_t y = __shfl_up(x, o, width);
+            if ((lane & (width - 1)) >= o) x += y;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            on[out + r] = stack_next(v[r]);
+            os[out + r] = start + x - own + pre[r];
+        }
+    };
+    sort_wave64(v);
+    emit(16, 0, snext, ssum);
+    sort_wave256(v);
+    int cur = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t[0][tid * 4 + r] = v[r];
+    __syncthreads();
+    for (int run = 256; run < kBigBlock; run <<= 1, cur ^= 1) {
+        merge_outputs(t[cur], run, tid * 4, v);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t[cur ^ 1][tid * 4 + r] = v[r];
+        __syncthreads();
+    }
+    int64_t x = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x += ws[v[r] & (kBigBlock - 1u)];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
+    if (lane == 0) part[wid] = x;
+    __syncthreads();
+    int64_t start = 0;
+    for (int k = 0; k < wid; ++k) start += part[k];
+    emit(kWave, start, bnext, bsum);
 }
 
-// one thread per log entry of one schedule: its stack distance, then its
-// bill under every capacity of the schedule, summed per workgroup in LDS
-// and added to the configurations' costs
+// The weight of the entries with next access >= s in `count` <= 4 sorted blocks
+// of SIZE entries that end at hi, hi - SIZE, ..., their searches in lockstep
+template <int SIZE>
+__device__ inline int64_t blocks_weight(const int32_t *bn, const int64_t *bs, int64_t hi, int count, int64_t s) {
+    int lo[4], up[4];
+    int64_t first[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        first[u] = hi - (int64_t)(u + 1) * SIZE;
+        lo[u] = 0;
+        up[u] = u < count ? SIZE : 0;
+    }
+    for (int left = SIZE; left > 0; left >>= 1) {
+        int32_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = lo[u] < up[u] ? bn[first[u] + ((lo[u] + up[u]) >> 1)] : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (lo[u] >= up[u]) continue;
+            const int mid = (lo[u] + up[u]) >> 1;
+            if (v[u] >= s) lo[u] = mid + 1; else up[u] = mid;
+        }
+    }
+    int64_t sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+        if (lo[u] > 0) sum += bs[first[u] + lo[u] - 1];
+    return sum;
+}
+
+// One thread per log entry of one schedule: its stack distance, then its bill
+// under every capacity of the schedule, summed per workgroup in LDS and added
+// to the configurations' costs. The stretch (p, s) is taken from its end: the
+// part of a small block before s is the block's share less the weight of its
+// entries from s on (those are accessed at s or later themselves), then small
+// blocks down to a big block's end, big blocks, small blocks, and single
+// entries up to the first small block. A distance that already misses the
+// largest capacity misses them all, whatever is left of the stretch.
+// Bound by the searches' reads: 250 us at 20011 requests and 114 at 4096; with
+// one size of block (256), its edges entry by entry and no end to a search, 840
+// and 162.
 constexpr int kBillThreads = 256;
-__global__ __launch_bounds__(kBillThreads) void k_l_bill(int64_t nnz, int64_t nblk, const int32_t *prev,
-                                                         const int32_t *next, const int32_t *acc_start,
-                                                         const int64_t *accw, const int32_t *bnext,
-                                                         const int64_t *bsum, const int32_t *cfg_off,
-                                                         const int32_t *cfg_list, const int64_t *caps,
+constexpr int kBillSingles = 96;      // stretches up to this are added entry by entry
+__global__ __launch_bounds__(kBillThreads) void k_l_bill(int64_t nnz, int64_t nblk, const int32_t *__restrict__ prev,
+                                                         const int32_t *__restrict__ next,
+                                                         const int32_t *__restrict__ acc_start,
+                                                         const int64_t *__restrict__ wsuf,
+                                                         const int32_t *__restrict__ snext,
+                                                         const int64_t *__restrict__ ssum,
+                                                         const int32_t *__restrict__ bnext,
+                                                         const int64_t *__restrict__ bsum,
+                                                         const int32_t *__restrict__ cfg_off,
+                                                         const int32_t *__restrict__ cfg_list,
+                                                         const int64_t *__restrict__ caps,
                                                          unsigned long long *costs) {
     __shared__ unsigned long long acc[MPT_CACHE_MAX_CONFIGS];
+    __shared__ int64_t cap[MPT_CACHE_MAX_CONFIGS];
     const int d = blockIdx.y;
     const int c0 = cfg_off[d], nc = cfg_off[d + 1] - c0;
-    for (int k = threadIdx.x; k < nc; k += kBillThreads) acc[k] = 0ull;
+    for (int k = threadIdx.x; k < nc; k += kBillThreads) {
+        acc[k] = 0ull;
+        cap[k] = caps[cfg_list[c0 + k]];
+    }
     __syncthreads();
+    int64_t largest = 0;
+    for (int k = 0; k < nc; ++k) largest = cap[k] > largest ? cap[k] : largest;
     const int64_t e = blockIdx.x * (int64_t)kBillThreads + threadIdx.x;
     if (e < nnz) {
         const int64_t base = (int64_t)d * nnz;
-        const int64_t w = accw[base + e];
+        // the weight of entry q, given the suffix sums at it and after it
+        auto weight = [&](int64_t q, int64_t at, int64_t after) {
+            return at - ((q + 1) % kSmallBlock != 0 && q + 1 < nnz ? after : 0);
+        };
+        const int64_t w = weight(e, wsuf[base + e], e + 1 < nnz ? wsuf[base + e + 1] : 0);
         const int64_t p = prev[base + e];
         int64_t dist = -1;                               // -1: first access, a miss everywhere
         if (p >= 0) {
-            const int64_t s = acc_start[base + e];
+            const int64_t s = acc_start[base + e], j0 = p + 1;
             dist = 0;
-            // a range of single entries, 8 loads in flight at a time
+            // a range of single entries, 8 in flight at a time
             auto singles = [&](int64_t from, int64_t to) {
                 for (int64_t q = from; q < to; q += 8) {
                     int32_t nx[8];
-                    int64_t wq[8];
+                    int64_t wq[9];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        nx[u] = q + u < to ? next[base + q + u] : -1;
-                        wq[u] = q + u < to ? accw[base + q + u] : 0;
-                    }
+                    for (int u = 0; u < 8; ++u) nx[u] = q + u < to ? next[base + q + u] : -1;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) dist += nx[u] >= s ? wq[u] : 0;
+                    for (int u = 0; u < 9; ++u) wq[u] = q + u < nnz ? wsuf[base + q + u] : 0;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) dist += nx[u] >= s ? weight(q + u, wq[u], wq[u + 1]) : 0;
                 }
             };
-            const int64_t j0 = p + 1;
-            const int64_t first_full = (j0 + kStackBlock - 1) / kStackBlock * kStackBlock;
-            const int64_t end_full = s / kStackBlock * kStackBlock;
-            if (first_full >= end_full) {
-                singles(j0, s);                          // no whole block in between
+            if (s - j0 <= kBillSingles) {
+                singles(j0, s);
             } else {
-                singles(j0, first_full);
-                singles(end_full, s);
-                // whole blocks: the prefix of each block with next >= s, four
-                // binary searches in lockstep
-                const int64_t bbase = (int64_t)d * nblk * kStackBlock;
-                int64_t j = first_full;
-                for (; j + 4 * kStackBlock <= end_full; j += 4 * kStackBlock) {
-                    int lo[4] = {0, 0, 0, 0}, hi[4] = {kStackBlock, kStackBlock, kStackBlock, kStackBlock};
-                    for (int it = 0; it <= 8; ++it) {           // log2(kStackBlock) + 1 halvings
-                        int32_t v[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int mid = (lo[u] + hi[u]) >> 1;
-                            v[u] = lo[u] < hi[u] ? bnext[bbase + j + u * kStackBlock + mid] : 0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            if (lo[u] >= hi[u]) continue;
-                            const int mid = (lo[u] + hi[u]) >> 1;
-                            if (v[u] >= s) lo[u] = mid + 1; else hi[u] = mid;
-                        }
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (lo[u] > 0) dist += bsum[bbase + j + u * kStackBlock + lo[u] - 1];
+                const int64_t row = (int64_t)d * nblk * kBigBlock;
+                const int32_t *sn = snext + row, *bn = bnext + row;
+                const int64_t *ss = ssum + row, *bs = bsum + row;
+                const int64_t lo64 = (j0 + kSmallBlock - 1) / kSmallBlock * kSmallBlock;
+                const int64_t lo1k = (j0 + kBigBlock - 1) / kBigBlock * kBigBlock;
+                int64_t hi = s / kSmallBlock * kSmallBlock;
+                if (s > hi) dist += blocks_weight<kSmallBlock>(sn, ss, hi + kSmallBlock, 1, s) - wsuf[base + s];
+                while (hi > lo64 && hi % kBigBlock != 0 && dist + w <= largest) {
+                    const int64_t down = hi / kBigBlock * kBigBlock;
+                    const int n = (int)min<int64_t>(4, (hi - (down > lo64 ? down : lo64)) / kSmallBlock);
+                    dist += blocks_weight<kSmallBlock>(sn, ss, hi, n, s);
+                    hi -= (int64_t)n * kSmallBlock;
                 }
-                for (; j < end_full; j += kStackBlock) {
-                    int lo = 0, hi = kStackBlock;              // first sorted entry with next < s
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (bnext[bbase + j + mid] >= s) lo = mid + 1; else hi = mid;
-                    }
-                    if (lo > 0) dist += bsum[bbase + j + lo - 1];
+                while (hi > lo1k && hi % kBigBlock == 0 && dist + w <= largest) {
+                    const int n = (int)min<int64_t>(4, (hi - lo1k) / kBigBlock);
+                    dist += blocks_weight<kBigBlock>(bn, bs, hi, n, s);
+                    hi -= (int64_t)n * kBigBlock;
                 }
+                while (hi > lo64 && dist + w <= largest) {
+                    const int n = (int)min<int64_t>(4, (hi - lo64) / kSmallBlock);
+                    dist += blocks_weight<kSmallBlock>(sn, ss, hi, n, s);
+                    hi -= (int64_t)n * kSmallBlock;
+                }
+                if (dist + w <= largest) singles(j0, lo64);
             }
         }
         for (int k = 0; k < nc; ++k) {
-            const bool miss = dist < 0 || dist + w > caps[cfg_list[c0 + k]];
+            const bool miss = dist < 0 || dist + w > cap[k];
             if (miss) atomicAdd(&acc[k], (unsigned long long)w);
         }
     }
@@ -652,32 +845,32 @@ int l_check_ws(const LLayout &L, void *ws, size_t bytes) {
     return MPT_OK;
 }
 
-// validation + lexicographic order + LCPs + trie cost (+ node ids)
+// validation + lexicographic order (to dfs too, where given) + LCPs + trie
+// cost, with one synchronisation at the end; then, paths: the node ids
 int l_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *w, const int64_t *off, const int32_t *seqs,
-              const LLayout &L, char *ws, hipStream_t s, bool paths, int64_t *trie_cost, int64_t *n_nodes) {
+              const LLayout &L, char *ws, hipStream_t s, bool paths, int32_t *dfs, int64_t *trie_cost) {
     LHeader *h = (LHeader *)ws;
-    k_l_header<<<1, 64, 0, s>>>(h);
-    k_l_check_offsets<<<1, 256, 0, s>>>(m, nnz, off, h);
-    if (nnz > 0) k_l_check_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, n_chunks, seqs, w, h);
-    MPT_HIP_TRY(hipGetLastError());
-    int rc = l_read_errors(h, s);
-    if (rc) return rc;
     int32_t *ord = (int32_t *)(ws + L.ord), *rank = (int32_t *)(ws + L.rank), *lcp = (int32_t *)(ws + L.lcp);
     int64_t *base = (int64_t *)(ws + L.base);
+    int rc;
+    k_l_begin<<<grid_for(m, 256), 256, 0, s>>>(h, rank, m);
+    k_l_check<<<grid_for(std::max<int64_t>(nnz, m), 2 * kCheckThreads, 1024), kCheckThreads, 0, s>>>(
+        m, nnz, n_chunks, off, seqs, w, h);
     {
         LaunchScope ls("l_sort_requests", (double)m, s);
-        if ((rc = sort_requests(ord, rank, m, L.mpad, off, seqs, s))) return rc;
+        if ((rc = sort_requests(ord, rank, dfs, m, off, seqs, ws + L.recs, &h->err, s))) return rc;
     }
     {
         LaunchScope ls("l_lcp", (double)nnz, s);
-        k_l_lcp<<<grid_for(m, 256), 256, 0, s>>>(m, ord, off, seqs, w, lcp, base, rank, h);
-        k_l_scan<<<1, 1024, 0, s>>>(m, base);
+        k_l_lcp<<<grid_for(m, kCheckThreads, 4096), kCheckThreads, 0, s>>>(m, ord, off, seqs, w, lcp, base, rank, h);
     }
     MPT_HIP_TRY(hipGetLastError());
+    if ((rc = l_read_errors(h, s, nullptr, trie_cost))) return rc;
     if (paths) {
         int32_t *pn = (int32_t *)(ws + L.pn), *mtree = (int32_t *)(ws + L.mtree);
         int64_t *nw = (int64_t *)(ws + L.nw);
         LaunchScope ls("l_paths", (double)nnz, s);
+        k_l_scan<<<1, 1024, 0, s>>>(m, base);
         k_l_node_weights<<<grid_for(m, 256), 256, 0, s>>>(m, ord, off, seqs, w, lcp, base, nw);
         const int64_t sub = std::min<int64_t>(kTreeBlock, L.mpad);
         k_l_mtree_low<<<(unsigned)(L.mpad / sub), 1024, 0, s>>>(m, L.mpad, lcp, mtree);
@@ -686,12 +879,6 @@ int l_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *w, const int6
             k_l_paths<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, L.mpad, off, rank, lcp, base, mtree, pn);
         MPT_HIP_TRY(hipGetLastError());
     }
-    int64_t hv[2] = {0, 0};
-    MPT_HIP_TRY(hipMemcpyAsync(&hv[0], &h->cost, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipMemcpyAsync(&hv[1], &base[m], sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
-    if (trie_cost) *trie_cost = hv[0];
-    if (n_nodes) *n_nodes = hv[1];
     return MPT_OK;
 }
 
@@ -718,30 +905,28 @@ extern "C" int mpt_global_order_layout(int m, int64_t n_chunks, int64_t nnz, con
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     LHeader *h = (LHeader *)ws;
-    k_l_header<<<1, 64, 0, s>>>(h);
-    k_l_check_offsets<<<1, 256, 0, s>>>(m, nnz, req_off, h);
-    if (nnz > 0) k_l_check_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, n_chunks, req_chunks, nullptr, h);
+    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
+    int32_t *rank = (int32_t *)(ws + L.crank), *inv = (int32_t *)(ws + L.cinv);
+    const bool popular = order_kind == MPT_ORDER_POPULARITY;
+    LaunchScope ls("l_global_order", (double)nnz, s);
+    k_l_begin<<<grid_for(popular ? n_chunks : 1, 256), 256, 0, s>>>(h, rank, popular ? n_chunks : 0);
+    k_l_check<<<grid_for(std::max<int64_t>(nnz, m), 2 * kCheckThreads, 1024), kCheckThreads, 0, s>>>(
+        m, nnz, n_chunks, req_off, req_chunks, nullptr, h);
+    if (nnz > 0) {
+        if (popular) {
+            // (count, id) keys of the chunks
+            k_l_count<<<grid_for(nnz, kCountSlice, 1024), kCountThreads, 0, s>>>(nnz, req_chunks, rank, h);
+            k_l_pop_keys<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, keys);
+            if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
+            k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
+        }
+        k_l_layout_short<<<grid_for(m, 4, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs, h);
+    }
     MPT_HIP_TRY(hipGetLastError());
     int64_t max_len = 0;
     if ((rc = l_read_errors(h, s, &max_len))) return rc;
-    if (nnz == 0) return MPT_OK;
-    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
-    int32_t *rank = (int32_t *)(ws + L.crank), *inv = (int32_t *)(ws + L.cinv);
-    LaunchScope ls("l_global_order", (double)nnz, s);
-    if (order_kind == MPT_ORDER_POPULARITY) {
-        // (count, id) keys of the chunks
-        k_l_fill_i32<<<grid_for(n_chunks, 256), 256, 0, s>>>(rank, n_chunks, 0);
-        k_l_count<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, req_chunks, rank);
-        k_l_pop_keys<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, keys);
-        if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
-        k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
-        if (max_len > kSegMax) k_l_inverse<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, inv);
-    }
-    if (max_len <= kSegMax) {
-        k_l_layout_short<<<std::max(1, (m + 3) / 4), 4 * kWave, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs);
-        MPT_HIP_TRY(hipGetLastError());
-        return MPT_OK;
-    }
+    if (max_len <= kListMax) return MPT_OK;
+    if (popular) k_l_inverse<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, inv);
     k_l_layout_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, rank, order_kind, keys);
     if ((rc = sort_keys(keys, keys2, nnz, s, &sorted))) return rc;
     k_l_layout_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, inv, order_kind, seqs);
@@ -761,12 +946,7 @@ extern "C" int mpt_layout_cost(int m, int64_t n_chunks, int64_t nnz, const int64
     if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    if ((rc = l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, false, trie_cost, nullptr))) return rc;
-    if (dfs_order) {
-        MPT_HIP_TRY(hipMemcpyAsync(dfs_order, ws + L.ord, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToDevice, s));
-        MPT_HIP_TRY(hipStreamSynchronize(s));
-    }
-    return MPT_OK;
+    return l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, false, dfs_order, trie_cost);
 }
 
 extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w,
@@ -786,8 +966,8 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
     if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    int64_t tc = 0, n_nodes = 0;
-    if ((rc = l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, true, &tc, &n_nodes))) return rc;
+    int64_t tc = 0;
+    if ((rc = l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, true, nullptr, &tc))) return rc;
     if (trie_cost) *trie_cost = tc;
     // configurations: window <= 0 or > m means the whole stream. Equal
     // windows share one schedule (and log); cfg_off / cfg_list list the
@@ -808,17 +988,20 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
             if (sched_of[c] == d) cfg_list.push_back(c);
         cfg_off[d + 1] = (int32_t)cfg_list.size();
     }
-    std::vector<int64_t> capv(capacities, capacities + n_configs);
+    // windows, capacities, offsets and lists go over in one copy: the four
+    // arrays lie one after the other in the workspace
     int64_t *dev_win = (int64_t *)(ws + L.cfg_win), *dev_capacity = (int64_t *)(ws + L.cfg_cap);
     int32_t *dev_cfg_off = (int32_t *)(ws + L.cfg_off), *dev_cfg_list = (int32_t *)(ws + L.cfg_list);
-    MPT_HIP_TRY(hipMemcpyAsync(dev_win, win.data(), sizeof(int64_t) * n_sched, hipMemcpyHostToDevice, s));
-    MPT_HIP_TRY(hipMemcpyAsync(dev_capacity, capv.data(), sizeof(int64_t) * n_configs, hipMemcpyHostToDevice, s));
-    MPT_HIP_TRY(hipMemcpyAsync(dev_cfg_off, cfg_off.data(), sizeof(int32_t) * (n_sched + 1), hipMemcpyHostToDevice, s));
-    MPT_HIP_TRY(hipMemcpyAsync(dev_cfg_list, cfg_list.data(), sizeof(int32_t) * n_configs, hipMemcpyHostToDevice, s));
+    std::vector<char> image(L.cfg_list - L.cfg_win + sizeof(int32_t) * (size_t)n_configs);
+    std::memcpy(image.data(), win.data(), sizeof(int64_t) * (size_t)n_sched);
+    std::memcpy(image.data() + (L.cfg_cap - L.cfg_win), capacities, sizeof(int64_t) * (size_t)n_configs);
+    std::memcpy(image.data() + (L.cfg_off - L.cfg_win), cfg_off.data(), sizeof(int32_t) * (size_t)(n_sched + 1));
+    std::memcpy(image.data() + (L.cfg_list - L.cfg_win), cfg_list.data(), sizeof(int32_t) * (size_t)n_configs);
+    MPT_HIP_TRY(hipMemcpyAsync(dev_win, image.data(), image.size(), hipMemcpyHostToDevice, s));
     uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
     int32_t *sched = (int32_t *)(ws + L.sched), *logs = (int32_t *)(ws + L.logs);
     int32_t *acc_start = (int32_t *)(ws + L.acc_start), *prev = (int32_t *)(ws + L.prev), *next = (int32_t *)(ws + L.next);
-    int64_t *log_off = (int64_t *)(ws + L.log_off), *accw = (int64_t *)(ws + L.accw);
+    int64_t *log_off = (int64_t *)(ws + L.log_off), *wsuf = (int64_t *)(ws + L.wsuf);
     const int32_t *ord = (const int32_t *)(ws + L.ord), *rank = (const int32_t *)(ws + L.rank);
     {
         LaunchScope ls("l_schedules", (double)n_sched * m, s);
@@ -842,8 +1025,8 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
             // the 63 key bits hold
             LaunchScope ls("l_reuse", (double)n_sched * nnz, s);
             auto bits = [](int64_t n) { int b = 1; while (b < 62 && ((int64_t)1 << b) < n) ++b; return b; };
-            const int be = bits(nnz), bn = bits(std::max<int64_t>(n_nodes, 1));
-            const int gb = 63 - be - bn;                  // >= 1: nnz and the node count stay below 2^31
+            const int be = bits(nnz), bn = be;            // (nnz bounds the node count)
+            const int gb = 63 - be - bn;                  // >= 1: nnz stays below 2^31
             const int group = gb >= 8 ? n_sched : std::min(n_sched, 1 << gb);
             for (int d0 = 0; d0 < n_sched; d0 += group) {
                 const int nd = std::min(group, n_sched - d0);
@@ -854,13 +1037,13 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
             }
         }
         LaunchScope ls("l_simulate", (double)n_configs * nnz, s);
-        const int64_t nblk = (nnz + kStackBlock - 1) / kStackBlock;
-        int32_t *bnext = (int32_t *)(ws + L.bnext);
-        int64_t *bsum = (int64_t *)(ws + L.bsum);
-        k_l_stack_blocks<<<(unsigned)(n_sched * nblk), kStackBlock, 0, s>>>(nnz, nblk, logs, (const int64_t *)(ws + L.nw),
-                                                                            next, accw, bnext, bsum);
+        const int64_t nblk = (nnz + kBigBlock - 1) / kBigBlock;
+        int32_t *snext = (int32_t *)(ws + L.snext), *bnext = (int32_t *)(ws + L.bnext);
+        int64_t *ssum = (int64_t *)(ws + L.ssum), *bsum = (int64_t *)(ws + L.bsum);
+        k_l_stack_blocks<<<(unsigned)(n_sched * nblk), kStackThreads, 0, s>>>(
+            nnz, nblk, logs, (const int64_t *)(ws + L.nw), next, wsuf, snext, ssum, bnext, bsum);
         k_l_bill<<<dim3((unsigned)((nnz + kBillThreads - 1) / kBillThreads), (unsigned)n_sched), kBillThreads, 0, s>>>(
-            nnz, nblk, prev, next, acc_start, accw, bnext, bsum, dev_cfg_off, dev_cfg_list, dev_capacity,
+            nnz, nblk, prev, next, acc_start, wsuf, snext, ssum, bnext, bsum, dev_cfg_off, dev_cfg_list, dev_capacity,
             (unsigned long long *)dev_costs);
     }
     MPT_HIP_TRY(hipGetLastError());

@@ -24,7 +24,7 @@ namespace {
 using mptlib::align256;
 using mptlib::fail;
 using mptlib::grid_for;
-using mptlib::kSeqSortTile;
+using mptlib::seq_recs_bytes;
 using mptlib::LaunchScope;
 using mptlib::sort_keys;
 using mptlib::sort_requests;
@@ -40,28 +40,21 @@ struct PHeader {
 };
 static_assert(sizeof(PHeader) == 256, "header is one 256-byte block");
 
-inline int64_t pow2_at_least(int64_t n) {
-    int64_t p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
-
 struct PLayout {
-    size_t keys, keys2, rf_off, rf_chunks, ord, gstart, lead, rep, roff, total;
-    int64_t mpad;
+    size_t keys, keys2, rf_off, rf_chunks, recs, ord, gstart, lead, rep, roff, total;
 };
 
 PLayout p_layout(int m, int64_t nnz) {
     PLayout L{};
     const size_t mm = (size_t)m, nz = (size_t)std::max<int64_t>(nnz, 1);
-    L.mpad = std::max<int64_t>(pow2_at_least(m), kSeqSortTile);
     size_t o = align256(sizeof(PHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
     L.keys = take(8 * nz);
     L.keys2 = take(8 * nz);
     L.rf_off = take(8 * (mm + 1));
     L.rf_chunks = take(4 * nz);
-    L.ord = take(4 * (size_t)L.mpad);
+    L.recs = take(2 * seq_recs_bytes(m));
+    L.ord = take(4 * mm);
     L.gstart = take(4 * mm);
     L.lead = take(4 * mm);
     L.rep = take(8 * (mm + 1));
@@ -70,8 +63,9 @@ PLayout p_layout(int m, int64_t nnz) {
     return L;
 }
 
-__global__ void k_p_header(PHeader *h) {
-    if (threadIdx.x == 0) { h->err = 0; h->n_distinct = 0; }
+__global__ void k_p_header(PHeader *h, int32_t *zero, int n) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) { h->err = 0; h->n_distinct = 0; }
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) zero[i] = 0;
 }
 
 __global__ void k_p_check(int m, int64_t n_chunks, int64_t nnz, const int64_t *off, const int32_t *chunks, PHeader *h) {
@@ -270,7 +264,7 @@ extern "C" int mpt_pinned_split(int m, int64_t n_chunks, int64_t nnz, const int6
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)workspace;
     PHeader *h = (PHeader *)ws;
-    k_p_header<<<1, 64, 0, s>>>(h);
+    k_p_header<<<grid_for(m, 256), 256, 0, s>>>(h, (int32_t *)(ws + L.gstart), m);
     k_p_check<<<grid_for(std::max<int64_t>(nnz, m), 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, h);
     MPT_HIP_TRY(hipGetLastError());
     if ((rc = p_read(h, s, nullptr))) return rc;
@@ -288,8 +282,8 @@ extern "C" int mpt_pinned_split(int m, int64_t n_chunks, int64_t nnz, const int6
             if ((rc = sort_keys(keys, (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
             k_p_free_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(m, rf_off, sorted, rf_chunks);
         }
-        // (gstart, written after the sort, is its scratch)
-        if ((rc = sort_requests(ord, gstart, m, L.mpad, rf_off, rf_chunks, s))) return rc;
+        // (gstart, zeroed with the header and written after the sort, is its scratch)
+        if ((rc = sort_requests(ord, gstart, nullptr, m, rf_off, rf_chunks, ws + L.recs, nullptr, s))) return rc;
         k_p_group_starts<<<grid_for(m, 256), 256, 0, s>>>(m, ord, rf_off, rf_chunks, gstart);
         k_p_max_scan<<<1, 1024, 0, s>>>(m, gstart);
         k_p_leaders<<<grid_for(m, 256), 256, 0, s>>>(m, ord, gstart, rf_off, lead, rep, roff);
@@ -316,7 +310,7 @@ extern "C" int mpt_pinned_assemble(int m, int64_t nnz, const int64_t *req_off, c
         return fail(MPT_E_WORKSPACE, "workspace missing, misaligned or smaller than 256 bytes");
     hipStream_t s = (hipStream_t)stream;
     PHeader *h = (PHeader *)workspace;
-    k_p_header<<<1, 64, 0, s>>>(h);
+    k_p_header<<<1, 64, 0, s>>>(h, nullptr, 0);
     {
         LaunchScope ls("p_assemble", (double)nnz, s);
         k_p_assemble<<<grid_for(m, 256), 256, 0, s>>>(m, t, n_distinct, req_off, req_chunks, dmap, free_off,
