@@ -2570,6 +2570,8 @@ __global__ void k_request_total(int m, const int64_t *W, WsHeader *h) {
 }
 }  // namespace rb
 
+#include "short_rows.h"
+
 // ---------------------------------------------------------------------------
 // phase 3: one workgroup per request i. Chunk x of R_i is emitted at the
 // first node of i's root-to-leaf path that lies inside S_x; inside a node
@@ -3074,6 +3076,57 @@ int solve_rb(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, con
     return MPT_OK;
 }
 
+// Mid-sized instances (m = 13 .. 23): rows of 2^9 entries (short_rows.h).
+// Solves measured on 2^12-entry rows against these, in us, on 32-bit keys /
+// doubles: m = 13 110 / 119 against 60 / 76, m = 16 243 / 283 against 114 /
+// 139, m = 20 532 / 633 against 319 / 393, m = 22 1263 / 1653 against 1134 /
+// 1596, m = 23 2903 / 3941 against 2623 / 3747. The gain is a level's fixed
+// time and falls with m; from m = 24 on the wide rows' smaller row traffic
+// and shared block loads are kept.
+constexpr int kShortRowsMaxM = 23;
+template <class E>
+int solve_sr(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, const WsLayout &Lw, hipStream_t s) {
+    // Workgroups that run at a time: four waves each of 115 registers (four
+    // waves a SIMD) on 32-bit keys, of 148 (three) on 64-bit ones. Twice as
+    // many, shorter chunks took 347 -> 367 us at m = 20.
+    constexpr uint32_t kWorkgroups = sizeof(E) == 4 ? 1024 : 768;
+    E *T = (E *)(ws + Lw.rb_plain);
+    uint64_t *partial = (uint64_t *)(ws + Lw.rb_wrow);
+    const uint64_t slots = ((uint64_t)12 << m) / (sr::ROW * sizeof(uint64_t));   // W and split in row order: not used here
+    const char *kCrossLabel = sizeof(E) == 4 ? "rb_cross_u32" : (std::is_same<E, double>::value ? "rb_cross_f64" : "rb_cross_u64");
+    const int H = m - sr::L;
+    double pair_work = 1.0;
+    for (int i = 0; i < sr::L; ++i) pair_work *= 3.0;
+    {
+        LaunchScope ls("rb_row0", pair_work / 2, s);
+        sr::k_sr_row0<E><<<1, rb::THREADS, 0, s>>>(m, W, T, C, split);
+    }
+    for (int h = 1; h <= H; ++h) {
+        const uint32_t rows = kBinom.v[H][h], pairs = (1u << (h - 1)) - 1u;
+        // Few pairs: one launch that also completes the rows (two launches:
+        // 10 us more at m = 20 where 462 rows have 15 pairs, but 2 us less
+        // at m = 16 where 21 rows leave the chip idle). More: the pairs in
+        // chunks, then a launch that folds their keys and completes the rows.
+        uint32_t chunks = 1;
+        if (pairs > (rows >= 64u ? 15u : 7u)) {
+            const uint64_t most = std::min<uint64_t>(std::min<uint64_t>(kWorkgroups, slots) / rows, sr::kMaxChunks);
+            chunks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(most, (pairs + sr::WAVES - 1) / sr::WAVES));
+        }
+        const uint32_t per_chunk = std::max(1u, (pairs + chunks * sr::WAVES - 1) / (chunks * sr::WAVES)) * sr::WAVES;
+        if (pairs) chunks = (pairs + per_chunk - 1) / per_chunk;
+        {
+            LaunchScope ls(pairs ? kCrossLabel : "rb_final", pair_work * rows * (pairs + (chunks == 1 ? 1.0 : 0.0)), s);
+            sr::k_sr_cross<E><<<rows * chunks, sr::THREADS, 0, s>>>(m, h, pairs, chunks, per_chunk, W, T, C, split, partial);
+        }
+        if (chunks > 1) {
+            LaunchScope ls("rb_final", pair_work * rows, s);
+            sr::k_sr_final<E><<<rows, sr::THREADS, 0, s>>>(m, h, chunks, W, T, C, split, partial);
+        }
+    }
+    MPT_HIP_TRY(hipGetLastError());
+    return MPT_OK;
+}
+
 }  // namespace
 
 // ===========================================================================
@@ -3198,9 +3251,14 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             // narrow cross-pair keys while every C(A) + C(B) stays below 2^20 - 1
             // (then 2 C' < 2^52 too, for any m up to MPT_MAX_M)
             static_assert(rb::kNarrowTotal <= ((int64_t)1 << (51 - MPT_MAX_M)), "narrow keys imply double keys");
-            if (total < rb::kNarrowTotal - 1)
+            const bool narrow = total < rb::kNarrowTotal - 1, doubles = total < ((int64_t)1 << (51 - m));
+            if (m <= kShortRowsMaxM && chunk_pairs == 0)
+                rc = narrow ? solve_sr<uint32_t>(m, W, C, split, ws, L, s)
+                            : doubles ? solve_sr<double>(m, W, C, split, ws, L, s)
+                                      : solve_sr<uint64_t>(m, W, C, split, ws, L, s);
+            else if (narrow)
                 rc = solve_rb<double, true>(m, W, C, split, ws, L, chunk_pairs, s);
-            else if (total < ((int64_t)1 << (51 - m)))
+            else if (doubles)
                 rc = solve_rb<double, false>(m, W, C, split, ws, L, chunk_pairs, s);
             else
                 rc = solve_rb<uint64_t, false>(m, W, C, split, ws, L, chunk_pairs, s);
