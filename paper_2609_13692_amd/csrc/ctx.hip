@@ -9,6 +9,7 @@
 #include <cstdint>
 #include <cstring>
 #include <new>
+#include <optional>
 
 #include "common.h"
 #include "core.h"
@@ -92,8 +93,6 @@ struct mpt_ctx {
 };
 
 namespace {
-
-constexpr size_t kHostImage = 16384;    // bytes of a host instance that goes over in one copy
 
 // where memory lies, as the runtime knows it (an address it does not know is
 // ordinary host memory)
@@ -224,14 +223,14 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
         const size_t b_off = 8 * (size_t)(m + 1), b_chunks = 4 * (size_t)nnz, b_w = 8 * (size_t)n_chunks;
         // Inputs in this device's memory, outside the workspace: the build's
         // first kernel reads them in place and leaves the copies. Otherwise
-        // they are copied first; the three arrays lie one after the other in
-        // the workspace (sig follows), so a small instance in host memory goes
-        // over in one copy, from an image of that stretch.
+        // they are copied first; a small instance in host memory goes into a
+        // pinned block instead, which the build reads in place too (one kernel
+        // that reads each input once: the build of at most 16384 chunks and
+        // slots). The arrays lie in the block as they do in the workspace.
         mptcore::InputCopy copy{};
         const int64_t *in_off = d_off, *in_w = d_w;
         const int32_t *in_chunks = d_chunks;
-        char image[kHostImage];
-        bool staged = false;
+        std::optional<mptlib::HostSlot> slot;
         auto in_place = [&](const void *p) {
             const char *q = (const char *)p;
             return on_device(p, ctx->device) && (q < ctx->ws || q >= ctx->ws + ctx->ws_bytes);
@@ -241,13 +240,16 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
             in_off = req_off;
             in_w = chunk_w;
             in_chunks = req_chunks;
-        } else if (L.sig - L.req_off <= sizeof image && on_host(req_off) && (nnz == 0 || on_host(req_chunks)) &&
-                   (n_chunks == 0 || on_host(chunk_w))) {
+        } else if (L.sig - L.req_off <= mptlib::HostSlot::kBytes && on_host(req_off) &&
+                   (nnz == 0 || on_host(req_chunks)) && (n_chunks == 0 || on_host(chunk_w)) && slot.emplace().ptr()) {
+            char *image = slot->ptr();
             std::memcpy(image, req_off, b_off);
             if (nnz > 0) std::memcpy(image + (L.req_chunks - L.req_off), req_chunks, b_chunks);
             if (n_chunks > 0) std::memcpy(image + (L.chunk_w - L.req_off), chunk_w, b_w);
-            staged = true;
-            MPT_HIP_TRY(hipMemcpyAsync(d_off, image, L.chunk_w - L.req_off + b_w, hipMemcpyHostToDevice, s));
+            copy = {d_w, d_off, d_chunks};
+            in_off = (const int64_t *)image;
+            in_w = (const int64_t *)(image + (L.chunk_w - L.req_off));
+            in_chunks = (const int32_t *)(image + (L.req_chunks - L.req_off));
         } else {
             MPT_HIP_TRY(hipMemcpyAsync(d_off, req_off, b_off, hipMemcpyDefault, s));
             if (nnz > 0) MPT_HIP_TRY(hipMemcpyAsync(d_chunks, req_chunks, b_chunks, hipMemcpyDefault, s));
@@ -257,7 +259,8 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
         const int rc = mptcore::build(m, n_chunks, nnz, in_w, in_off, in_chunks, ctx->at<uint32_t>(L.sig),
                                       ctx->at<int64_t>(L.W), ctx->ws + L.core, L.core_bytes, s, &total, ctx->route,
                                       copy);
-        if (rc && staged) (void)hipStreamSynchronize(s);     // (a build that succeeds has synchronised it)
+        // (a build that succeeds has synchronised the stream)
+        if (rc && slot && slot->ptr() && hipStreamSynchronize(s) != hipSuccess) slot->abandon();
         if (rc) return rc;
         ctx->total = total;
         ctx->state = BUILT;
@@ -302,9 +305,7 @@ extern "C" int mpt_ctx_optimum(const mpt_ctx *ctx, int64_t *opt_cost, int64_t *s
         if (!dev.ok()) return fail(MPT_E_DEVICE, "cannot make device %d current", ctx->device);
         int64_t opt = 0;
         const int64_t *C = ctx->at<int64_t>(ctx->lay.C);
-        MPT_HIP_TRY(hipMemcpyAsync(&opt, C + (((int64_t)1 << ctx->m) - 1), sizeof opt, hipMemcpyDeviceToHost,
-                                   ctx->stream));
-        MPT_HIP_TRY(hipStreamSynchronize(ctx->stream));
+        MPT_HIP_TRY(mptlib::read_back(&opt, C + (((int64_t)1 << ctx->m) - 1), sizeof opt, ctx->stream));
         if (opt_cost) *opt_cost = opt;
         if (savings) *savings = ctx->total - opt;
         return MPT_OK;
@@ -328,9 +329,13 @@ extern "C" int mpt_ctx_extract_orders(mpt_ctx *ctx, int32_t *order_chunks_host) 
                                   L.core_bytes, s, false);
         if (rc) return rc;
         if (order_chunks_host && ctx->nnz > 0) {
-            MPT_HIP_TRY(hipMemcpyAsync(order_chunks_host, ctx->at<void>(L.orders), 4 * (size_t)ctx->nnz,
-                                       hipMemcpyDeviceToHost, s));
-            MPT_HIP_TRY(hipStreamSynchronize(s));
+            const size_t bytes = 4 * (size_t)ctx->nnz;
+            if (on_host(order_chunks_host)) {
+                MPT_HIP_TRY(mptlib::read_back(order_chunks_host, ctx->at<void>(L.orders), bytes, s));
+            } else {
+                MPT_HIP_TRY(hipMemcpyAsync(order_chunks_host, ctx->at<void>(L.orders), bytes, hipMemcpyDeviceToHost, s));
+                MPT_HIP_TRY(hipStreamSynchronize(s));
+            }
         }
         ctx->state = EXTRACTED;
         return MPT_OK;

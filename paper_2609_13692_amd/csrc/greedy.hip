@@ -58,7 +58,8 @@ struct GHeader {
     unsigned long long dcursor;  // next free slot of the packed D lists
     int64_t max_len;             // longest request list
     unsigned long long dem_at;   // next free slot of the demand lists
-    int64_t pad[24];
+    unsigned long long savings;  // sum of the merges' gains
+    int64_t pad[23];
 };
 static_assert(sizeof(GHeader) == 256, "header is one 256-byte block");
 
@@ -1066,9 +1067,14 @@ __global__ void k_rac_emit(Rac R, int n) {
 __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
     __shared__ int scan_w[kChainThreads / kWave];
     __shared__ int32_t first_name;
+    __shared__ unsigned long long savings;
     const int m = R.m, tid = threadIdx.x;
-    if (tid == 0) first_name = -1;
+    if (tid == 0) { first_name = -1; savings = 0ull; }
     __syncthreads();
+    // SAV(H): the gains of the merges found (k_rac_emit; the chain's are 0)
+    unsigned long long sum = 0;
+    for (int t = tid; t < t0; t += kChainThreads) sum += (unsigned long long)R.gain[t];
+    if (sum) atomicAdd(&savings, sum);
     int done = 0;                                // live names ranked so far
     for (int base = 0; base < m; base += kChainThreads) {
         const int r = base + tid;
@@ -1104,6 +1110,7 @@ __global__ __launch_bounds__(kChainThreads) void k_rac_chain(Rac R, int t0) {
     }
     if (tid == 0 && n_live >= 2) R.node_parent[rec_node(R, R.last[first_name], first_name)] = m + t0;
     if (tid == 0 && t0 + n_live - 1 != m - 1) atomicOr(&R.h->err, GERR_INVALID);
+    if (tid == 0) R.h->savings = savings;      // (added before the first barrier of the loop above: m >= 1)
 }
 
 // pi_i: walk from leaf i to the root, placing D(v) of every node on the
@@ -1309,10 +1316,10 @@ int g_check_ws(const GLayout &L, void *ws, size_t bytes) {
     return MPT_OK;
 }
 
-int g_read_errors(GHeader *h, hipStream_t s, int64_t *request_total = nullptr, int64_t *max_len = nullptr) {
+int g_read_errors(GHeader *h, hipStream_t s, int64_t *request_total = nullptr, int64_t *max_len = nullptr,
+                  int64_t *savings = nullptr) {
     GHeader hh;
-    MPT_HIP_TRY(hipMemcpyAsync(&hh, h, sizeof hh, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
     if (hh.err & GERR_INVALID) return fail(MPT_E_INVALID, "req_off is not a CSR offset array of length m+1 ending at nnz");
     if (hh.err & GERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
     if (hh.err & GERR_WEIGHT) return fail(MPT_E_WEIGHT, "a chunk weight is <= 0 or > 2^32");
@@ -1320,6 +1327,7 @@ int g_read_errors(GHeader *h, hipStream_t s, int64_t *request_total = nullptr, i
     if (hh.total >= (1ull << 61)) return fail(MPT_E_OVERFLOW, "sum of request weights reaches 2^61");
     if (request_total) *request_total = (int64_t)hh.total;
     if (max_len) *max_len = hh.max_len;
+    if (savings) *savings = (int64_t)hh.savings;
     return MPT_OK;
 }
 
@@ -1475,8 +1483,7 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
             }
             MPT_HIP_TRY(hipGetLastError());
             GHeader hh;
-            MPT_HIP_TRY(hipMemcpyAsync(&hh, R.h, sizeof hh, hipMemcpyDeviceToHost, s));
-            MPT_HIP_TRY(hipStreamSynchronize(s));
+            MPT_HIP_TRY(mptlib::read_back(&hh, R.h, sizeof hh, s));
             if (hh.err) return fail(MPT_E_INTERNAL, "greedy rounds left an inconsistent state");   // cannot happen
             n_rec = std::min(hh.n_rec, m - 1);
             pairs = hh.last_pairs;
@@ -1501,20 +1508,7 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
                                                      order_chunks, n_rec, R.h);
         MPT_HIP_TRY(hipGetLastError());
     }
-    if ((rc = g_read_errors(R.h, s))) return rc;
-    if (savings) {
-        *savings = 0;
-        if (m > 1) {
-            // the gains are copied back and summed on the host (m - 1 values)
-            int64_t *hg = new int64_t[m - 1];
-            const hipError_t e1 = hipMemcpyAsync(hg, gain, sizeof(int64_t) * (size_t)(m - 1), hipMemcpyDeviceToHost, s);
-            const hipError_t e2 = e1 == hipSuccess ? hipStreamSynchronize(s) : e1;
-            if (e2 != hipSuccess) { delete[] hg; return fail(MPT_E_DEVICE, "copy of the gains: %s", hipGetErrorString(e2)); }
-            for (int t = 0; t < m - 1; ++t) *savings += hg[t];
-            delete[] hg;
-        }
-    }
-    return MPT_OK;
+    return g_read_errors(R.h, s, nullptr, nullptr, savings);
 }
 
 extern "C" int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_weight, void *workspace,
@@ -1547,8 +1541,7 @@ extern "C" int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_wei
     }
     MPT_HIP_TRY(hipGetLastError());
     unsigned long long total = 0;
-    MPT_HIP_TRY(hipMemcpyAsync(&total, &h->total, sizeof total, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
     *mst_weight = (int64_t)total;
     return MPT_OK;
 }

@@ -183,8 +183,7 @@ __global__ __launch_bounds__(kCheckThreads) void k_l_check(int m, int64_t nnz, i
 
 int l_read_errors(LHeader *h, hipStream_t s, int64_t *max_len = nullptr, int64_t *cost = nullptr) {
     LHeader hh;
-    MPT_HIP_TRY(hipMemcpyAsync(&hh, h, sizeof hh, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
     if (hh.err & LERR_INVALID) return fail(MPT_E_INVALID, "offsets are not a CSR offset array of length m+1 ending at nnz");
     if (hh.err & LERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
     if (hh.err & LERR_WEIGHT) return fail(MPT_E_WEIGHT, "a chunk weight is <= 0 or > 2^32");
@@ -1047,7 +1046,6 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
             (unsigned long long *)dev_costs);
     }
     MPT_HIP_TRY(hipGetLastError());
-    MPT_HIP_TRY(hipMemcpyAsync(costs, dev_costs, sizeof(int64_t) * n_configs, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(costs, dev_costs, sizeof(int64_t) * n_configs, s));
     return MPT_OK;
 }

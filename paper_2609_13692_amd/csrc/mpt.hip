@@ -2945,8 +2945,7 @@ static_assert(offsetof(WsHeader, total) == offsetof(HeaderHead, total), "header 
 
 int read_errors(WsHeader *h, hipStream_t s, int64_t *total = nullptr) {
     HeaderHead hh{};
-    MPT_HIP_TRY(hipMemcpyAsync(&hh, h, sizeof hh, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
     const uint32_t err = hh.err;
     if (err & ERR_INVALID) return fail(MPT_E_INVALID, "req_off is not a CSR offset array of length m+1 ending at nnz, or split is not a hierarchy");
     if (err & ERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
@@ -3243,8 +3242,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         if (total < 0) {
             WsHeader *h = (WsHeader *)ws;
             rb::k_request_total<<<1, 64, 0, s>>>(m, W, h);
-            MPT_HIP_TRY(hipMemcpyAsync(&total, &h->total, sizeof total, hipMemcpyDeviceToHost, s));
-            MPT_HIP_TRY(hipStreamSynchronize(s));
+            MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
         }
         // doubles while 2 C' < 2^52 (Key<double>); below 2^62 keys fit uint64
         if (total < ((int64_t)1 << (61 - m))) {
@@ -3263,10 +3261,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             else
                 rc = solve_rb<uint64_t, false>(m, W, C, split, ws, L, chunk_pairs, s);
             if (rc) return rc;
-            if (opt_cost) {
-                MPT_HIP_TRY(hipMemcpyAsync(opt_cost, C + (n - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-                MPT_HIP_TRY(hipStreamSynchronize(s));
-            }
+            if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
             return MPT_OK;
         }
     }
@@ -3275,10 +3270,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         LaunchScope ls("dp_small", (std::pow(3.0, m) + 1.0) / 2.0 - (double)n, s);
         rb::k_dp_small<<<1, rb::THREADS, 0, s>>>(m, W, C, split);
         MPT_HIP_TRY(hipGetLastError());
-        if (opt_cost) {
-            MPT_HIP_TRY(hipMemcpyAsync(opt_cost, C + (n - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            MPT_HIP_TRY(hipStreamSynchronize(s));
-        }
+        if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
         return MPT_OK;
     }
     // costs too large to pack: the plain kernels, one launch per popcount layer
@@ -3307,10 +3299,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         MPT_HIP_TRY(hipGetLastError());
     }
     MPT_HIP_TRY(hipGetLastError());
-    if (opt_cost) {
-        MPT_HIP_TRY(hipMemcpyAsync(opt_cost, C + (n - 1), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        MPT_HIP_TRY(hipStreamSynchronize(s));
-    }
+    if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
     return MPT_OK;
 }
 
@@ -3484,6 +3473,66 @@ int fail(int status, const char *fmt, ...) {
 
 void clear_error() { t_last_error.clear(); }
 const char *error_text() { return t_last_error.c_str(); }
+
+// --- reading back -------------------------------------------------------------
+namespace {
+struct SlotPool {
+    static constexpr int kSlots = 32;
+    std::mutex mu;
+    char *base = nullptr;
+    bool tried = false;
+    uint32_t taken = 0;
+} g_slots;
+}  // namespace
+
+HostSlot::HostSlot() {
+    std::lock_guard<std::mutex> g(g_slots.mu);
+    if (!g_slots.tried) {
+        g_slots.tried = true;
+        // (an allocation must not break a capture that runs on another thread)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kBytes * SlotPool::kSlots, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            g_slots.base = (char *)p;
+        else
+            (void)hipGetLastError();
+        if (set) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!g_slots.base || g_slots.taken == ~0u) return;
+    const int i = __builtin_ctz(~g_slots.taken);
+    g_slots.taken |= 1u << i;
+    ptr_ = g_slots.base + (size_t)i * kBytes;
+}
+
+HostSlot::~HostSlot() {
+    if (!ptr_) return;
+    std::lock_guard<std::mutex> g(g_slots.mu);
+    g_slots.taken &= ~(1u << (int)((size_t)(ptr_ - g_slots.base) / kBytes));
+}
+
+__global__ void k_post(const uint32_t *__restrict__ src, uint32_t *__restrict__ dst, int words) {
+    for (int i = (int)threadIdx.x; i < words; i += (int)blockDim.x) dst[i] = src[i];
+}
+
+hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
+    HostSlot slot;
+    if (bytes > HostSlot::kBytes || (bytes & 3u) != 0 || ((uintptr_t)src & 3u) != 0 || !slot.ptr()) {
+        const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;
+    }
+    const int words = (int)(bytes / 4);
+    k_post<<<1, words > 64 ? 256 : 64, 0, s>>>((const uint32_t *)src, (uint32_t *)slot.ptr(), words);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;                // (not queued: the block stays ours)
+    e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        slot.abandon();
+        return e;
+    }
+    std::memcpy(dst, slot.ptr(), bytes);
+    return hipSuccess;
+}
 
 // --- event profiler ---------------------------------------------------------
 struct ProfRecord { std::string name; double work; hipEvent_t a, b; };

@@ -232,8 +232,7 @@ int p_check_ws(const PLayout &L, void *ws, size_t bytes) {
 
 int p_read(PHeader *h, hipStream_t s, int *n_distinct) {
     PHeader hh;
-    MPT_HIP_TRY(hipMemcpyAsync(&hh, h, sizeof hh, hipMemcpyDeviceToHost, s));
-    MPT_HIP_TRY(hipStreamSynchronize(s));
+    MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
     if (hh.err & PERR_INVALID) return fail(MPT_E_INVALID, "offsets are not CSR, or the set map does not match the free layout");
     if (hh.err & PERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
     if (n_distinct) *n_distinct = hh.n_distinct;
