@@ -34,8 +34,10 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
 
 // Orders read off the hierarchy. validate = false skips the offset and
 // hierarchy checks (and their synchronisation) for inputs the library made.
+// host_orders (ordinary host memory, or null) receives the orders as well,
+// after one synchronisation.
 int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const int32_t *req_chunks,
             const uint32_t *sig, const uint32_t *split, int32_t *order_chunks, void *workspace,
-            size_t workspace_bytes, hipStream_t s, bool validate);
+            size_t workspace_bytes, hipStream_t s, bool validate, int32_t *host_orders = nullptr);
 
 }  // namespace mptcore

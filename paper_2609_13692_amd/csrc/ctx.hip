@@ -323,19 +323,16 @@ extern "C" int mpt_ctx_extract_orders(mpt_ctx *ctx, int32_t *order_chunks_host) 
         hipStream_t s = ctx->stream;
         ctx->state = SOLVED;
         // offsets and chunk ids were validated by the build, split made by the solve
+        int32_t *host = order_chunks_host && ctx->nnz > 0 ? order_chunks_host : nullptr;
+        int32_t *ordinary = host && on_host(host) ? host : nullptr;
         int rc = mptcore::extract(ctx->m, ctx->n_chunks, ctx->nnz, ctx->at<int64_t>(L.req_off),
                                   ctx->at<int32_t>(L.req_chunks), ctx->at<uint32_t>(L.sig),
                                   ctx->at<uint32_t>(L.split), ctx->at<int32_t>(L.orders), ctx->ws + L.core,
-                                  L.core_bytes, s, false);
+                                  L.core_bytes, s, false, ordinary);
         if (rc) return rc;
-        if (order_chunks_host && ctx->nnz > 0) {
-            const size_t bytes = 4 * (size_t)ctx->nnz;
-            if (on_host(order_chunks_host)) {
-                MPT_HIP_TRY(mptlib::read_back(order_chunks_host, ctx->at<void>(L.orders), bytes, s));
-            } else {
-                MPT_HIP_TRY(hipMemcpyAsync(order_chunks_host, ctx->at<void>(L.orders), bytes, hipMemcpyDeviceToHost, s));
-                MPT_HIP_TRY(hipStreamSynchronize(s));
-            }
+        if (host && !ordinary) {
+            MPT_HIP_TRY(hipMemcpyAsync(host, ctx->at<void>(L.orders), 4 * (size_t)ctx->nnz, hipMemcpyDeviceToHost, s));
+            MPT_HIP_TRY(hipStreamSynchronize(s));
         }
         ctx->state = EXTRACTED;
         return MPT_OK;

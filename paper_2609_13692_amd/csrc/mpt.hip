@@ -20,6 +20,7 @@
 #include <cstddef>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -68,6 +69,9 @@ struct WsHeader {
     int64_t pad[29];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
+// the first fields of the header, as the host reads them back
+struct HeaderHead { uint32_t err; uint32_t n_list; int64_t zero_weight; int64_t total; };
+static_assert(offsetof(WsHeader, total) == offsetof(HeaderHead, total), "header prefix");
 
 // ---------------------------------------------------------------------------
 // small device helpers
@@ -557,7 +561,9 @@ void dense_zeta_high(int m, int j, int K, int64_t *W, hipStream_t s) {
 // demand sets, the compaction and, FULL (m <= 12), the W table itself, by one
 // workgroup in one launch; the masks live in LDS. off_dst, chunks_dst and
 // w_dst, where given, receive copies of the inputs (the context keeps them),
-// which saves three copies between launches.
+// which saves three copies between launches; post, where given, is host memory
+// that receives the header (as everywhere below: a kernel that writes its
+// result there itself saves the launch of one that copies it, 4 us a call).
 // Bound by latency: launches and a few dependent round trips. 4.4 us at m = 9
 // (36 slots, 64 chunks, with W) and at m = 16 (128 slots, 1000 chunks), where
 // the separate kernels took 15 us and up to eight more launches. The limit is
@@ -569,7 +575,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         int m, int n_chunks, int nnz, const int64_t *__restrict__ w, const int64_t *__restrict__ req_off,
         const int32_t *__restrict__ req_chunks, int64_t *__restrict__ w_dst, int64_t *__restrict__ off_dst,
         int32_t *__restrict__ chunks_dst, uint32_t *__restrict__ sig, uint32_t *__restrict__ list_sig,
-        int64_t *__restrict__ list_w, int64_t *__restrict__ W, WsHeader *h) {
+        int64_t *__restrict__ list_w, int64_t *__restrict__ W, WsHeader *h, HeaderHead *post) {
     __shared__ uint32_t sg[kSmallBuild];
     __shared__ __align__(16) int64_t tile[FULL ? kZetaN + kZetaN / 8 : 1];
     __shared__ int64_t off[32];
@@ -636,6 +642,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         h->n_list = n_list;
         h->zero_weight = (int64_t)zero_weight;
         h->total = (int64_t)total;
+        if (post) *post = HeaderHead{err, n_list, (int64_t)zero_weight, (int64_t)total};
         if (FULL) tile[0] += (int64_t)zero_weight;
     }
     if constexpr (FULL) {
@@ -2402,7 +2409,7 @@ __global__ __launch_bounds__(THREADS) void k_rb_row0(int m, const int64_t *__res
 // part) pairs by lane groups per subset. For m < CB the block's missing requests hold
 // nothing: they cost 0 and reach no subset that is written.
 __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__restrict__ W, int64_t *__restrict__ C,
-                                                      uint32_t *__restrict__ split) {
+                                                      uint32_t *__restrict__ split, int64_t *post) {
     __shared__ __align__(16) uint64_t t64[ROW];
     __shared__ __align__(16) uint64_t acc64[ROW];
     const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -2431,6 +2438,7 @@ __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__re
         row_dp<uint32_t>(r2, own_k, own_s2, w32, t, acc);
         for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
             C[e] = e ? (int64_t)(t[npos(slot_of(e >> CB), (int)(e & (NB - 1u)))] >> L) : kInf;
+            if (post && e == n - 1u) *post = C[e];
             split[e] = acc[e];
         }
     } else if (total < kWide) {
@@ -2440,6 +2448,7 @@ __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__re
         row_dp<uint64_t>(r2, own_k, own_s2, w64, t64, acc64);
         for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
             C[e] = e ? (int64_t)(t64[lpos(slot_of(e >> CB), (int)(e & (NB - 1u)))] >> L) : kInf;
+            if (post && e == n - 1u) *post = C[e];
             split[e] = (uint32_t)acc64[e];
         }
     } else {
@@ -2481,6 +2490,7 @@ __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__re
         }
         for (uint32_t e = threadIdx.x; e < n; e += THREADS) {
             C[e] = e ? c[e] : kInf;
+            if (post && e == n - 1u) *post = C[e];
             split[e] = spl[e];
         }
     }
@@ -2559,7 +2569,7 @@ __global__ __launch_bounds__(256) void k_transpose(const T *__restrict__ in, T *
 }
 
 // sum_i W({i}), saturated, for the packed-key eligibility test
-__global__ void k_request_total(int m, const int64_t *W, WsHeader *h) {
+__global__ void k_request_total(int m, const int64_t *W, WsHeader *h, int64_t *post) {
     if (threadIdx.x != 0) return;
     int64_t tot = 0;
     for (int i = 0; i < m; ++i) {
@@ -2567,6 +2577,7 @@ __global__ void k_request_total(int m, const int64_t *W, WsHeader *h) {
         tot = (v >= INT64_MAX - tot) ? INT64_MAX : tot + v;
     }
     h->total = tot;
+    if (post) *post = tot;
 }
 }  // namespace rb
 
@@ -2649,7 +2660,8 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
                                                                  const int32_t *__restrict__ req_chunks,
                                                                  const uint32_t *__restrict__ sig,
                                                                  const uint32_t *__restrict__ split,
-                                                                 int32_t *__restrict__ order_chunks, WsHeader *h) {
+                                                                 int32_t *__restrict__ order_chunks, WsHeader *h,
+                                                                 int32_t *post) {
     __shared__ uint64_t keys[kShortOrders];
     __shared__ int64_t off[32];
     __shared__ uint32_t path[32];
@@ -2663,7 +2675,10 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
         bool ok = off[0] == 0 && off[m] == nnz;
         for (int i = 0; i < m; ++i) ok = ok && off[i] <= off[i + 1];
         if (!ok) {                                    // (the same for every thread of every workgroup)
-            if (own == 0 && tid == 0) h->err = ERR_INVALID;
+            if (own == 0 && tid == 0) {
+                h->err = ERR_INVALID;
+                if (post) *post = (int32_t)ERR_INVALID;
+            }
             return;
         }
     }
@@ -2692,7 +2707,10 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
         }
     __syncthreads();
     const uint32_t e_all = err;
-    if (VALIDATE && own == 0 && tid == 0) h->err = e_all;
+    if (VALIDATE && own == 0 && tid == 0) {
+        h->err = e_all;
+        if (post) *post = (int32_t)e_all;
+    }
     if (e_all) return;
     const int64_t lo = off[own];
     const int len = (int)(off[own + 1] - lo);
@@ -2720,6 +2738,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
                 pos += (o < key || (o == key && f < e)) ? 1 : 0;
             }
             order_chunks[lo + pos] = (int32_t)(key & 0xffffffffu);
+            if (!VALIDATE && post) post[lo + pos] = (int32_t)(key & 0xffffffffu);
         }
         return;
     }
@@ -2732,7 +2751,10 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
             }
             __syncthreads();
         }
-    for (int e = tid; e < len; e += kOrderThreads) order_chunks[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
+    for (int e = tid; e < len; e += kOrderThreads) {
+        order_chunks[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
+        if (!VALIDATE && post) post[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
+    }
 }
 
 __global__ void k_extract_out(int64_t nnz, const uint64_t *keys, int32_t *order_chunks) {
@@ -2939,13 +2961,29 @@ int check_ws(void *ws, size_t bytes, size_t need) {
     return MPT_OK;
 }
 
-// the first fields of the header, as the host reads them back
-struct HeaderHead { uint32_t err; uint32_t n_list; int64_t zero_weight; int64_t total; };
-static_assert(offsetof(WsHeader, total) == offsetof(HeaderHead, total), "header prefix");
+// Launches whose kernels write slot are queued: their error, if any. (One of
+// several may still run then, so the block does not go back.)
+hipError_t launched(mptlib::HostSlot &slot) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) slot.abandon();
+    return e;
+}
+// waits for the stream whose kernels write slot
+hipError_t wait_for(mptlib::HostSlot &slot, hipStream_t s) {
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) slot.abandon();
+    return e;
+}
 
-int read_errors(WsHeader *h, hipStream_t s, int64_t *total = nullptr) {
+// post: the block that a kernel has written the header to, if any
+int read_errors(WsHeader *h, hipStream_t s, int64_t *total = nullptr, mptlib::HostSlot *post = nullptr) {
     HeaderHead hh{};
-    MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
+    if (post && post->ptr()) {
+        MPT_HIP_TRY(wait_for(*post, s));
+        std::memcpy(&hh, post->ptr(), sizeof hh);
+    } else {
+        MPT_HIP_TRY(mptlib::read_back(&hh, h, sizeof hh, s));
+    }
     const uint32_t err = hh.err;
     if (err & ERR_INVALID) return fail(MPT_E_INVALID, "req_off is not a CSR offset array of length m+1 ending at nnz, or split is not a hierarchy");
     if (err & ERR_RANGE) return fail(MPT_E_RANGE, "a chunk id is outside [0, n_chunks)");
@@ -3084,7 +3122,7 @@ int solve_rb(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, con
 // and shared block loads are kept.
 constexpr int kShortRowsMaxM = 23;
 template <class E>
-int solve_sr(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, const WsLayout &Lw, hipStream_t s) {
+void solve_sr(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *post, char *ws, const WsLayout &Lw, hipStream_t s) {
     // Workgroups that run at a time: four waves each of 115 registers (four
     // waves a SIMD) on 32-bit keys, of 148 (three) on 64-bit ones. Twice as
     // many, shorter chunks took 347 -> 367 us at m = 20.
@@ -3115,15 +3153,14 @@ int solve_sr(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, con
         if (pairs) chunks = (pairs + per_chunk - 1) / per_chunk;
         {
             LaunchScope ls(pairs ? kCrossLabel : "rb_final", pair_work * rows * (pairs + (chunks == 1 ? 1.0 : 0.0)), s);
-            sr::k_sr_cross<E><<<rows * chunks, sr::THREADS, 0, s>>>(m, h, pairs, chunks, per_chunk, W, T, C, split, partial);
+            sr::k_sr_cross<E><<<rows * chunks, sr::THREADS, 0, s>>>(m, h, pairs, chunks, per_chunk, W, T, C, split,
+                                                                         h == H ? post : nullptr, partial);
         }
         if (chunks > 1) {
             LaunchScope ls("rb_final", pair_work * rows, s);
-            sr::k_sr_final<E><<<rows, sr::THREADS, 0, s>>>(m, h, chunks, W, T, C, split, partial);
+            sr::k_sr_final<E><<<rows, sr::THREADS, 0, s>>>(m, h, chunks, W, T, C, split, h == H ? post : nullptr, partial);
         }
     }
-    MPT_HIP_TRY(hipGetLastError());
-    return MPT_OK;
 }
 
 }  // namespace
@@ -3159,17 +3196,24 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
     const bool dense = route == MPT_ROUTE_DENSE || (route == MPT_ROUTE_AUTO && dense_route_pays(m, nnz));
     const bool small = n_chunks <= kSmallBuild && nnz <= kSmallBuild;
     const bool full = small && m <= kZetaBits && !dense;       // the whole build in one launch
+    std::optional<mptlib::HostSlot> slot;
+    HeaderHead *post = small ? (HeaderHead *)slot.emplace().ptr() : nullptr;
+    auto finish = [&]() -> int {
+        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        return read_errors(h, s, total, slot ? &*slot : nullptr);
+    };
     if (full) {
         LaunchScope ls("weights_tile", 8.0 * (double)(1ull << m), s);
         k_build_small<true><<<1, kSmallThreads, 0, s>>>(m, (int)n_chunks, (int)nnz, chunk_w, req_off, req_chunks,
-                                                       copy.w, copy.off, copy.chunks, sig, nullptr, nullptr, W, h);
-        MPT_HIP_TRY(hipGetLastError());
-        return read_errors(h, s, total);
+                                                       copy.w, copy.off, copy.chunks, sig, nullptr, nullptr, W, h,
+                                                       post);
+        return finish();
     }
     if (small) {
         LaunchScope ls("build_small", (double)nnz, s);
         k_build_small<false><<<1, kSmallThreads, 0, s>>>(m, (int)n_chunks, (int)nnz, chunk_w, req_off, req_chunks,
-                                                        copy.w, copy.off, copy.chunks, sig, list_sig, list_w, W, h);
+                                                        copy.w, copy.off, copy.chunks, sig, list_sig, list_w, W, h,
+                                                        post);
     } else {
         if (copy.off) {
             MPT_HIP_TRY(hipMemcpyAsync(copy.off, req_off, 8 * (size_t)(m + 1), hipMemcpyDeviceToDevice, s));
@@ -3219,8 +3263,7 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
             }
         }
     }
-    MPT_HIP_TRY(hipGetLastError());
-    return read_errors(h, s, total);
+    return finish();
 }
 
 int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cost, void *workspace,
@@ -3236,13 +3279,35 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
     int64_t *part_v = (int64_t *)(ws + L.part_v);
     uint32_t *part_a = (uint32_t *)(ws + L.part_a);
     const int64_t n = (int64_t)1 << m;
+    // C of the full set: from the block that the last kernel writes (post), or
+    // read back from the table
+    std::optional<mptlib::HostSlot> slot;
+    int64_t *post = opt_cost && m <= kShortRowsMaxM ? (int64_t *)slot.emplace().ptr() : nullptr;
+    auto optimum = [&]() -> int {
+        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        if (!opt_cost) return MPT_OK;
+        if (post) {
+            MPT_HIP_TRY(wait_for(*slot, s));
+            std::memcpy(opt_cost, post, sizeof *opt_cost);
+        } else {
+            MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
+        }
+        return MPT_OK;
+    };
     if (m >= kRbMinM) {
         // packed keys need every cost below 2^(62-m): sum_i w(R_i) picks the
         // representation. Unknown (< 0): read it back from W.
         if (total < 0) {
             WsHeader *h = (WsHeader *)ws;
-            rb::k_request_total<<<1, 64, 0, s>>>(m, W, h);
-            MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
+            mptlib::HostSlot slot;
+            rb::k_request_total<<<1, 64, 0, s>>>(m, W, h, (int64_t *)slot.ptr());
+            MPT_HIP_TRY(launched(slot));
+            if (slot.ptr()) {
+                MPT_HIP_TRY(wait_for(slot, s));
+                std::memcpy(&total, slot.ptr(), sizeof total);
+            } else {
+                MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
+            }
         }
         // doubles while 2 C' < 2^52 (Key<double>); below 2^62 keys fit uint64
         if (total < ((int64_t)1 << (61 - m))) {
@@ -3250,30 +3315,30 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             // (then 2 C' < 2^52 too, for any m up to MPT_MAX_M)
             static_assert(rb::kNarrowTotal <= ((int64_t)1 << (51 - MPT_MAX_M)), "narrow keys imply double keys");
             const bool narrow = total < rb::kNarrowTotal - 1, doubles = total < ((int64_t)1 << (51 - m));
-            if (m <= kShortRowsMaxM && chunk_pairs == 0)
-                rc = narrow ? solve_sr<uint32_t>(m, W, C, split, ws, L, s)
-                            : doubles ? solve_sr<double>(m, W, C, split, ws, L, s)
-                                      : solve_sr<uint64_t>(m, W, C, split, ws, L, s);
-            else if (narrow)
+            if (m <= kShortRowsMaxM && chunk_pairs == 0) {
+                if (narrow) solve_sr<uint32_t>(m, W, C, split, post, ws, L, s);
+                else if (doubles) solve_sr<double>(m, W, C, split, post, ws, L, s);
+                else solve_sr<uint64_t>(m, W, C, split, post, ws, L, s);
+                return optimum();
+            }
+            post = nullptr;
+            if (narrow)
                 rc = solve_rb<double, true>(m, W, C, split, ws, L, chunk_pairs, s);
             else if (doubles)
                 rc = solve_rb<double, false>(m, W, C, split, ws, L, chunk_pairs, s);
             else
                 rc = solve_rb<uint64_t, false>(m, W, C, split, ws, L, chunk_pairs, s);
-            if (rc) return rc;
-            if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
-            return MPT_OK;
+            return rc ? rc : optimum();
         }
     }
     if (m < kRbMinM) {
         // at most one row of requests: one launch, which picks its key width
         LaunchScope ls("dp_small", (std::pow(3.0, m) + 1.0) / 2.0 - (double)n, s);
-        rb::k_dp_small<<<1, rb::THREADS, 0, s>>>(m, W, C, split);
-        MPT_HIP_TRY(hipGetLastError());
-        if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
-        return MPT_OK;
+        rb::k_dp_small<<<1, rb::THREADS, 0, s>>>(m, W, C, split, post);
+        return optimum();
     }
     // costs too large to pack: the plain kernels, one launch per popcount layer
+    post = nullptr;
     {
         LaunchScope ls("dp_init", 8.0 * n, s);
         k_dp_init<<<grid_for(n, 256, 16384), 256, 0, s>>>(m, W, C, split);
@@ -3298,14 +3363,12 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         }
         MPT_HIP_TRY(hipGetLastError());
     }
-    MPT_HIP_TRY(hipGetLastError());
-    if (opt_cost) MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
-    return MPT_OK;
+    return optimum();
 }
 
 int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const int32_t *req_chunks,
             const uint32_t *sig, const uint32_t *split, int32_t *order_chunks, void *workspace,
-            size_t workspace_bytes, hipStream_t s, bool validate) {
+            size_t workspace_bytes, hipStream_t s, bool validate, int32_t *host_orders) {
     mptlib::Range range("mpt extract_orders");
     int rc = check_common(m, n_chunks, nnz);
     if (rc) return rc;
@@ -3316,16 +3379,35 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
     if ((rc = check_ws(workspace, workspace_bytes, L.extract_end))) return rc;
     char *ws = (char *)workspace;
     WsHeader *h = (WsHeader *)ws;
+    auto orders_to_host = [&]() -> int {
+        MPT_HIP_TRY(mptlib::read_back(host_orders, order_chunks, sizeof(int32_t) * (size_t)nnz, s));
+        return MPT_OK;
+    };
     if (nnz <= kShortOrders) {
-        LaunchScope ls("extract", (double)nnz, s);
-        if (validate)
-            k_extract_short<true><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
-                                                              order_chunks, h);
-        else
-            k_extract_short<false><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
-                                                               order_chunks, h);
-        MPT_HIP_TRY(hipGetLastError());
-        return validate ? read_errors(h, s) : MPT_OK;
+        static_assert(kShortOrders * sizeof(int32_t) <= mptlib::HostSlot::kBytes, "a block holds the orders");
+        // a block for the error bits, or for the orders
+        std::optional<mptlib::HostSlot> slot;
+        if (validate || host_orders) slot.emplace();
+        int32_t *post = slot ? (int32_t *)slot->ptr() : nullptr;
+        {
+            LaunchScope ls("extract", (double)nnz, s);
+            if (validate)
+                k_extract_short<true><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
+                                                                  order_chunks, h, post);
+            else
+                k_extract_short<false><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
+                                                                   order_chunks, h, post);
+        }
+        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        if (validate) {
+            if ((rc = read_errors(h, s, nullptr, slot ? &*slot : nullptr))) return rc;
+            return host_orders ? orders_to_host() : MPT_OK;
+        }
+        if (!host_orders) return MPT_OK;
+        if (!post) return orders_to_host();
+        MPT_HIP_TRY(wait_for(*slot, s));
+        std::memcpy(host_orders, post, sizeof(int32_t) * (size_t)nnz);
+        return MPT_OK;
     }
     if (validate) {
         k_header_init<<<1, 64, 0, s>>>(h);
@@ -3344,7 +3426,7 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
         k_extract_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, order_chunks);
     }
     MPT_HIP_TRY(hipGetLastError());
-    return MPT_OK;
+    return host_orders ? orders_to_host() : MPT_OK;
 }
 
 }  // namespace mptcore
@@ -3493,7 +3575,8 @@ HostSlot::HostSlot() {
         hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
         const bool set = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
         void *p = nullptr;
-        if (hipHostMalloc(&p, kBytes * SlotPool::kSlots, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+        if (hipHostMalloc(&p, kBytes * SlotPool::kSlots, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) ==
+            hipSuccess)
             g_slots.base = (char *)p;
         else
             (void)hipGetLastError();
@@ -3524,8 +3607,7 @@ hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
     const int words = (int)(bytes / 4);
     k_post<<<1, words > 64 ? 256 : 64, 0, s>>>((const uint32_t *)src, (uint32_t *)slot.ptr(), words);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;                // (not queued: the block stays ours)
-    e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         slot.abandon();
         return e;

@@ -174,7 +174,8 @@ template <class E> __device__ inline void load_w(int m, uint32_t sh, const int64
     }
 }
 
-// Completes row S_H (non-empty): s.acc holds its cross-pair keys.
+// Completes row S_H (non-empty): s.acc holds its cross-pair keys. post, given
+// for the row of the full set alone, receives C of the full set (host memory).
 // A level's lanes convolve one or two block pairs, take the minima over the
 // lanes of their S2 in registers and go on, all of them, with the block's own
 // chain; the group's first lane writes the block. One barrier per level.
@@ -184,7 +185,7 @@ template <class E> __device__ inline void load_w(int m, uint32_t sh, const int64
 // level and 64-bit integers in place of doubles in the chain).
 template <class E>
 __device__ inline void finish_row(int m, uint32_t sh, const Weight<E> (&w_in)[W_PER], Lds<E> &s, E *__restrict__ T,
-                                  int64_t *__restrict__ C, uint32_t *__restrict__ split) {
+                                  int64_t *__restrict__ C, uint32_t *__restrict__ split, int64_t *post) {
     constexpr bool NARROW = sizeof(E) == 4;
     const int tid = (int)threadIdx.x, H = m - L;
     E *rS = s.own(), *r0 = s.zero();
@@ -314,9 +315,12 @@ __device__ inline void finish_row(int m, uint32_t sh, const Weight<E> (&w_in)[W_
     for (uint32_t e = (uint32_t)tid; e < (uint32_t)ROW; e += THREADS) {
         const E v = rS[pos<E>(slot_of(e >> CB), (int)(e & (NB - 1u)))];
         const uint32_t at = sh | (e << H);
-        if constexpr (NARROW) C[at] = (int64_t)(v >> L);
-        else C[at] = (int64_t)(Key<E>::entry_value(v) >> m);
+        int64_t c;
+        if constexpr (NARROW) c = (int64_t)(v >> L);
+        else c = (int64_t)(Key<E>::entry_value(v) >> m);
+        C[at] = c;
         split[at] = spl[e];
+        if (post && e == (uint32_t)ROW - 1u) *post = c;
     }
 }
 
@@ -335,7 +339,7 @@ template <class E>
 __global__ __launch_bounds__(THREADS) void k_sr_cross(int m, int h, uint32_t n_pairs, uint32_t chunks,
                                                       uint32_t per_chunk, const int64_t *__restrict__ W,
                                                       E *__restrict__ T, int64_t *__restrict__ C,
-                                                      uint32_t *__restrict__ split, uint64_t *__restrict__ partial) {
+                                                      uint32_t *__restrict__ split, int64_t *post, uint64_t *__restrict__ partial) {
     __shared__ Lds<E> s;
     constexpr int PIECES = ROW * (int)sizeof(E) / 16;
     constexpr int PER = PIECES / kWave;          // 16-byte pieces of a row per lane
@@ -434,7 +438,7 @@ __global__ __launch_bounds__(THREADS) void k_sr_cross(int m, int h, uint32_t n_p
     }
     lds_barrier();
     if (chunks == 1) {
-        finish_row<E>(m, sh, w, s, T, C, split);
+        finish_row<E>(m, sh, w, s, T, C, split, post);
     } else {
         for (uint32_t e = tid; e < (uint32_t)ROW; e += THREADS) partial[(size_t)id * ROW + e] = s.acc[e];
     }
@@ -444,7 +448,7 @@ __global__ __launch_bounds__(THREADS) void k_sr_cross(int m, int h, uint32_t n_p
 template <class E>
 __global__ __launch_bounds__(THREADS) void k_sr_final(int m, int h, uint32_t chunks, const int64_t *__restrict__ W,
                                                       E *__restrict__ T, int64_t *__restrict__ C,
-                                                      uint32_t *__restrict__ split,
+                                                      uint32_t *__restrict__ split, int64_t *post,
                                                       const uint64_t *__restrict__ partial) {
     __shared__ Lds<E> s;
     const uint32_t sh = unrank_colex(blockIdx.x, h, m - L);
@@ -466,7 +470,7 @@ __global__ __launch_bounds__(THREADS) void k_sr_final(int m, int h, uint32_t chu
         }
         reinterpret_cast<ulonglong2 *>(s.acc)[p] = v;
     }
-    finish_row<E>(m, sh, w, s, T, C, split);
+    finish_row<E>(m, sh, w, s, T, C, split, post);
 }
 
 // row 0, the DP over the 9 in-row requests alone, by one workgroup
