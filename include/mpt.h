@@ -20,7 +20,10 @@
  * Conventions shared by every entry point
  *  - Subsets of requests are m-bit masks: bit i set = request i is in the set.
  *  - Every array argument is DEVICE memory (HBM) owned by the caller; the
- *    library allocates nothing and keeps no pointer after a call returns.
+ *    library allocates no device memory and keeps no pointer after a call
+ *    returns. It allocates 512 KiB of pinned host memory once per process,
+ *    in the first call that reads a result back (mpt_solve_exact_noalloc
+ *    never does), for those results; threads share it safely.
  *  - `stream` is a hipStream_t (NULL = the null stream). All device work of a
  *    call is enqueued on it. Calls that return a host value synchronise it.
  *  - `workspace` is caller-owned device scratch of at least

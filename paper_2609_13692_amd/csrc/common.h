@@ -72,7 +72,8 @@ class HostSlot {
 // through a pinned block that a kernel writes: launch and wait take 15 us on
 // an idle stream where hipMemcpyAsync to pageable memory and the wait take 22
 // (11 is the launch and the wait alone).
-hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s);
+// pinned = false: a plain copy and wait, for calls that must not allocate.
+hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s, bool pinned = true);
 
 inline int grid_for(int64_t n, int threads, int cap = 8192) {
     int64_t g = (n + threads - 1) / threads;

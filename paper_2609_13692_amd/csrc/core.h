@@ -29,8 +29,9 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
 // The Section 3.1 DP. total: sum_i w(R_i) of the instance that W belongs to,
 // or < 0 to read it back from W (one stream synchronisation). chunk_pairs > 0
 // overrides the level plan (cross pairs in chunks of at most that many pairs).
+// pinned = false: no pinned host blocks (which the first use allocates).
 int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cost, void *workspace,
-          size_t workspace_bytes, hipStream_t s, int64_t total, int64_t chunk_pairs);
+          size_t workspace_bytes, hipStream_t s, int64_t total, int64_t chunk_pairs, bool pinned = true);
 
 // Orders read off the hierarchy. validate = false skips the offset and
 // hierarchy checks (and their synchronisation) for inputs the library made.

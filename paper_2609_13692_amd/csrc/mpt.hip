@@ -3267,7 +3267,7 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
 }
 
 int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cost, void *workspace,
-          size_t workspace_bytes, hipStream_t s, int64_t total, int64_t chunk_pairs) {
+          size_t workspace_bytes, hipStream_t s, int64_t total, int64_t chunk_pairs, bool pinned) {
     mptlib::Range range("mpt solve_exact");
     int rc = check_common(m, 0, 0);
     if (rc) return rc;
@@ -3282,7 +3282,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
     // C of the full set: from the block that the last kernel writes (post), or
     // read back from the table
     std::optional<mptlib::HostSlot> slot;
-    int64_t *post = opt_cost && m <= kShortRowsMaxM ? (int64_t *)slot.emplace().ptr() : nullptr;
+    int64_t *post = pinned && opt_cost && m <= kShortRowsMaxM ? (int64_t *)slot.emplace().ptr() : nullptr;
     auto optimum = [&]() -> int {
         MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
         if (!opt_cost) return MPT_OK;
@@ -3290,7 +3290,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             MPT_HIP_TRY(wait_for(*slot, s));
             std::memcpy(opt_cost, post, sizeof *opt_cost);
         } else {
-            MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s));
+            MPT_HIP_TRY(mptlib::read_back(opt_cost, C + (n - 1), sizeof(int64_t), s, pinned));
         }
         return MPT_OK;
     };
@@ -3299,14 +3299,15 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         // representation. Unknown (< 0): read it back from W.
         if (total < 0) {
             WsHeader *h = (WsHeader *)ws;
-            mptlib::HostSlot slot;
-            rb::k_request_total<<<1, 64, 0, s>>>(m, W, h, (int64_t *)slot.ptr());
-            MPT_HIP_TRY(launched(slot));
-            if (slot.ptr()) {
-                MPT_HIP_TRY(wait_for(slot, s));
-                std::memcpy(&total, slot.ptr(), sizeof total);
+            std::optional<mptlib::HostSlot> at;
+            int64_t *host = pinned ? (int64_t *)at.emplace().ptr() : nullptr;
+            rb::k_request_total<<<1, 64, 0, s>>>(m, W, h, host);
+            MPT_HIP_TRY(at ? launched(*at) : hipGetLastError());
+            if (host) {
+                MPT_HIP_TRY(wait_for(*at, s));
+                std::memcpy(&total, host, sizeof total);
             } else {
-                MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
+                MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s, pinned));
             }
         }
         // doubles while 2 C' < 2^52 (Key<double>); below 2^62 keys fit uint64
@@ -3534,7 +3535,8 @@ extern "C" int mpt_solve_exact_noalloc(int m, const int64_t *W, int64_t *C, uint
         void *ws = nullptr;
         int rc = scratch_address(&ws);
         if (rc) return rc;
-        return mptcore::solve(m, W, C, split, opt_cost, ws, sizeof(scratch), (hipStream_t)stream, -1, 0);
+        // (no pinned blocks: the first one allocates)
+        return mptcore::solve(m, W, C, split, opt_cost, ws, sizeof(scratch), (hipStream_t)stream, -1, 0, false);
     });
 }
 
@@ -3598,12 +3600,14 @@ __global__ void k_post(const uint32_t *__restrict__ src, uint32_t *__restrict__ 
     for (int i = (int)threadIdx.x; i < words; i += (int)blockDim.x) dst[i] = src[i];
 }
 
-hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s) {
-    HostSlot slot;
-    if (bytes > HostSlot::kBytes || (bytes & 3u) != 0 || ((uintptr_t)src & 3u) != 0 || !slot.ptr()) {
+hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s, bool pinned) {
+    std::optional<HostSlot> taken;
+    if (pinned && bytes <= HostSlot::kBytes && (bytes & 3u) == 0 && ((uintptr_t)src & 3u) == 0) taken.emplace();
+    if (!taken || !taken->ptr()) {
         const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
+    HostSlot &slot = *taken;
     const int words = (int)(bytes / 4);
     k_post<<<1, words > 64 ? 256 : 64, 0, s>>>((const uint32_t *)src, (uint32_t *)slot.ptr(), words);
     hipError_t e = hipGetLastError();
