@@ -151,8 +151,20 @@ __global__ void k_build_init(int m, int64_t n_chunks, int64_t nnz, const int64_t
 
 // S_x: every request slot sets bit i of its chunk's mask; a bit that was
 // already set means the chunk is repeated inside request i.
+// Bound by its device-scope atomics (26 G/s: 87 us for 2.25M slots), which
+// leave HBM idle, so for the dense route (ZERO) the same launch zeroes W, each
+// workgroup its share before its slots: 108 us at m = 25, where the two
+// launches took 87 and 34.
+template <bool ZERO>
 __global__ void k_demand_sets(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off,
-                              const int32_t *req_chunks, uint32_t *sig, WsHeader *h) {
+                              const int32_t *req_chunks, uint32_t *sig, WsHeader *h, int64_t n, int64_t *W) {
+    if constexpr (ZERO) {
+        longlong2 *p = reinterpret_cast<longlong2 *>(W);     // (W is 16-byte aligned)
+        const longlong2 z = make_longlong2(0, 0);
+        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n / 2; i += (int64_t)gridDim.x * blockDim.x)
+            p[i] = z;
+        if (n == 1 && blockIdx.x == 0 && threadIdx.x == 0) W[0] = 0;
+    }
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         // request of slot j: the last i with req_off[i] <= j
         int lo = 0, hi = m - 1;
@@ -384,8 +396,10 @@ __global__ __launch_bounds__(kZetaThreads) void k_weights_tile(
 // once per tile, tiles x entries in all): f(S) = the weight of the chunks
 // with S_x = S, scattered into a zeroed W, then the superset zeta
 // W(S) = sum_{T superset of S} f(T) in place, in read-write passes of up to
-// 11 bits (low bits) and 5 bits (the others) that keep every subset a
-// thread touches in registers: at m = 25, the zeroing plus four passes.
+// 11 bits (low bits) and 7 bits (the others) that keep every subset a
+// thread touches in registers: at m = 25, the zeroing plus three passes. Long
+// lists are zeroed by the demand sets' launch; k_dense_zero is for forced
+// dense builds of small instances and for empty lists.
 __global__ void k_dense_zero(int64_t n, int64_t *W) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
         W[i] = 0;
@@ -3195,6 +3209,7 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
 
     const bool dense = route == MPT_ROUTE_DENSE || (route == MPT_ROUTE_AUTO && dense_route_pays(m, nnz));
     const bool small = n_chunks <= kSmallBuild && nnz <= kSmallBuild;
+    bool zeroed = false;                                       // W, by the demand sets' launch
     const bool full = small && m <= kZetaBits && !dense;       // the whole build in one launch
     std::optional<mptlib::HostSlot> slot;
     HeaderHead *post = small ? (HeaderHead *)slot.emplace().ptr() : nullptr;
@@ -3232,7 +3247,13 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
         if (n_chunks > 0) {
             if (nnz > 0) {
                 LaunchScope ls("demand_sets", (double)nnz, s);
-                k_demand_sets<<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, h);
+                if (dense)
+                    k_demand_sets<true><<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig,
+                                                                           h, (int64_t)1 << m, W);
+                else
+                    k_demand_sets<false><<<grid_for(nnz, 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig,
+                                                                            h, 0, nullptr);
+                zeroed = dense;
             }
             LaunchScope ls("compact", (double)n_chunks, s);
             k_compact<<<grid_for(n_chunks, kCompactTile, kCompactMaxBlocks), kCompactThreads, 0, s>>>(
@@ -3249,7 +3270,7 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
         const int64_t n = (int64_t)1 << m;
         const uint32_t cap = (uint32_t)std::max<int64_t>(nnz, 1);
         LaunchScope ls("weights_dense", 8.0 * (double)n, s);
-        k_dense_zero<<<grid_for(n, 256, 16384), 256, 0, s>>>(n, W);
+        if (!zeroed) k_dense_zero<<<grid_for(n, 256, 16384), 256, 0, s>>>(n, W);
         k_dense_scatter<<<(uint32_t)std::min<int64_t>((cap + kScatterSlice - 1) / kScatterSlice, 1024),
                           kScatterThreads, 0, s>>>(cap, list_sig, list_w, h, W);
         const int64_t waves = (n + (1 << kLowPassBits) - 1) >> kLowPassBits;
