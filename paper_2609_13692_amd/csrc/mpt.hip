@@ -462,13 +462,45 @@ __device__ inline void zeta_reg_bits(int64_t (&v)[1 << K]) {
 }
 
 // the low min(m, 11) bits: a wave owns 2^11 consecutive subsets, lane l
-// holds subsets l + 64 r (r < 32), so every load and store is 64
-// consecutive values; bits 6..10 are register bits, bits 0..5 lane bits
-// (lane l adds lane l + 2^b when its bit b is clear). Subsets past 2^m read
-// as 0 and are not stored: adding them changes nothing.
+// holds subsets l + 64 r (r < 32), so every load is 64 consecutive values.
+// Bits 6..10 are register bits. Lane bits 5 and 4 trade places with register
+// bits 4 and 3 by the half and row swaps, so that their additions use all
+// lanes; they stay traded in the stores (runs of 16 values, one line each).
+// Lane bits 0..3 are moves within a row of 16 lanes: lane l adds lane l + 2^b
+// when its bit b is clear. Subsets past 2^m read as 0 and are not stored:
+// adding them changes nothing.
+// Bound by HBM: the lane bits by 12 LDS shuffles per value took 91 us at
+// m = 25 (a plain read-write pass of the table: 64).
 constexpr int kLaneRegBits = 5;
 constexpr int kLowPassBits = 6 + kLaneRegBits;
 constexpr int kDenseThreads = 256;
+// lanes with bit B of their number clear: the value of lane + 2^B; others 0
+template <int B> __device__ inline uint32_t lane_up32(uint32_t v, uint32_t clear) {
+    if constexpr (B == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xF5, 0xF, 0xF, false) & clear;   // quad_perm [1,1,3,3]
+    else if constexpr (B == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xEE, 0xF, 0xF, false) & clear;   // quad_perm [2,3,2,3]
+    else if constexpr (B == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0x5, false);     // row_shl 4, quads 0 and 2
+    else return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x108, 0xF, 0x3, false);                           // row_shl 8, quads 0 and 1
+}
+template <int B, int R> __device__ inline void zeta_lane_bit(int64_t (&v)[R], int lane) {
+    const uint32_t clear = lane & (1 << B) ? 0u : ~0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint64_t x = (uint64_t)v[r];
+        v[r] += (int64_t)(((uint64_t)lane_up32<B>((uint32_t)(x >> 32), clear) << 32) | lane_up32<B>((uint32_t)x, clear));
+    }
+}
+// lane bit 5 (HALF) or 4 and the register bit that tells a from b trade places
+template <bool HALF> __device__ inline void swap_lane_bit(int64_t &a, int64_t &b) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    auto sw = [](uint32_t x, uint32_t y) -> u2 {
+        if constexpr (HALF) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        else return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    };
+    const u2 lo = sw((uint32_t)(uint64_t)a, (uint32_t)(uint64_t)b);
+    const u2 hi = sw((uint32_t)((uint64_t)a >> 32), (uint32_t)((uint64_t)b >> 32));
+    a = (int64_t)(((uint64_t)hi[0] << 32) | lo[0]);
+    b = (int64_t)(((uint64_t)hi[1] << 32) | lo[1]);
+}
 __global__ __launch_bounds__(kDenseThreads) void k_dense_zeta_low(int64_t n, int64_t *W) {
     constexpr int R = 1 << kLaneRegBits;
     const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -481,18 +513,27 @@ __global__ __launch_bounds__(kDenseThreads) void k_dense_zeta_low(int64_t n, int
         v[r] = i < n ? W[i] : 0;
     }
     zeta_reg_bits<kLaneRegBits>(v);
+    // the value of register r, lane l is then that of subset r4 << 5 | r3 << 4
+    // in the place of lane bits 5 and 4, and l5, l4 of register bits 4 and 3
 #pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        const bool add = !(lane & (1 << b));
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t up = __shfl_down(v[r], 1u << b, kWave);
-            if (add) v[r] += up;
-        }
+    for (int r = 0; r < R / 2; ++r) {
+        swap_lane_bit<true>(v[r], v[r + R / 2]);
+        v[r] += v[r + R / 2];
     }
 #pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (!(r & (R / 4))) {
+            swap_lane_bit<false>(v[r], v[r + R / 4]);
+            v[r] += v[r + R / 4];
+        }
+    zeta_lane_bit<3>(v, lane);
+    zeta_lane_bit<2>(v, lane);
+    zeta_lane_bit<1>(v, lane);
+    zeta_lane_bit<0>(v, lane);
+    const int low = (lane & 15) | ((lane & 32) << 5) | ((lane & 16) << 5);     // lane bits 5 and 4: subset bits 10 and 9
+#pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int64_t i = base + lane + ((int64_t)r << 6);
+        const int64_t i = base + low + ((r & (R / 4 - 1)) << 6) + ((r & (R / 2)) << 1) + ((r & (R / 4)) << 1);   // register bits 4 and 3: subset bits 5 and 4
         if (i < n) W[i] = v[r];
     }
 }
