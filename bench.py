@@ -52,6 +52,16 @@ DP_KEYS = {
     "rb_cross_u64": ("k_rb_cross<unsigned long, false>", 4.0,
                      "u64 keys (v_lshl_add_u64 + v_cmp_lt_u64 + 2 v_cndmask_b32)"),
 }
+# m = 13 .. 23 run rows of 2^9 entries (the 32-bit keys are cost << 9 | ...)
+SHORT_ROWS_MAX_M = 23
+SHORT_ROWS_KERNEL = {"rb_cross_u32": "k_sr_cross<unsigned int>", "rb_cross_f64": "k_sr_cross<double>",
+                     "rb_cross_u64": "k_sr_cross<unsigned long>"}
+
+
+def dp_key(label: str, m: int):
+    key = DP_KEYS.get(label)
+    return (SHORT_ROWS_KERNEL[label], *key[1:]) if key and m <= SHORT_ROWS_MAX_M else key
+
 
 WORKLOADS = {
     1: "tiny random, m=12, u=64, k=4, w~U{1..32}, seed 0",
@@ -202,8 +212,8 @@ def dense_w_bench(steps: int, warmup: int) -> dict:
     superset zeta in read-write passes of 11 bits and of up to 7) on the long-
     list instance (m = 25 requests of 90000 chunks over 2^20), inputs
     resident in HBM. One step = one mpt_ctx_build_weights (demand sets,
-    compaction, W). `roofline` prices the route's own table traffic (the
-    zeroing write plus a read and a write per pass) against HBM; the
+    compaction, W). `roofline` prices the passes' own table traffic (a
+    read and a write each) against HBM; the
     algorithmic minimum is one write of the table."""
     import torch
     from paper_2609_13692_amd import mpt
@@ -230,7 +240,7 @@ def dense_w_bench(steps: int, warmup: int) -> dict:
     ctx.close()
     dense = prof.get("weights_dense")
     passes = 1 + max(0, -(-(m - 11) // 7))        # the low 11 bits, then high passes of at most 7 bits
-    route_bytes = 8 * (1 << m) * (1 + 2 * passes)
+    route_bytes = 8 * (1 << m) * 2 * passes       # (the zeroing write is in the demand sets' launch)
     out = {
         "workload": f"long lists: m={m} requests of 90000 chunks drawn uniformly from u={inst.n_chunks}, "
                     f"w~U{{1..999}}, seed 12, nnz={inst.nnz}",
@@ -297,7 +307,7 @@ def wide_keys_bench(inst, steps: int, golden_opt) -> dict:
         d = mpt.profile_end()[dom]
         ctx.close()
         ms = (t1 - t0) * 1000.0 / steps
-        kernel, ops, keys = DP_KEYS[dom]
+        kernel, ops, keys = dp_key(dom, inst.m)
         tops = d["work"] * ops / (d["total_ms"] / 1000.0) / 1e12
         out[f"x{scale}"] = {
             "request_total": int(sc.weights[sc.req_chunks].sum()),
@@ -496,7 +506,7 @@ def main() -> int:
             golden_opt = json.load(f)["opt"]
 
     d = prof_dom[dom]
-    key = DP_KEYS.get(dom)
+    key = dp_key(dom, inst.m)
     z = prof.get("weights_tile")
     zeta = None
     if z:

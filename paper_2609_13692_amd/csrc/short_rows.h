@@ -2,7 +2,7 @@
 // 2^9 entries (included by mpt.hip, which describes the scheme and the keys).
 //
 // With 2^12-entry rows an instance of m = 13 .. 21 requests has few rows per
-// level and a level's time is the finishing of one row (10 in-row levels and
+// level (at most 126 for 256 CUs) and a level's time is the finishing of one row (10 in-row levels and
 // 3^9 block convolutions on one CU, 30 us on 32-bit keys, 41 us on 64-bit
 // ones), whatever the number of CUs. With 2^9 entries a row has 7 in-row
 // levels and 3^6 convolutions, there are eight times as many rows, and one
@@ -30,6 +30,9 @@ constexpr int L = 9;                       // row bits
 constexpr int R2 = L - CB;                 // middle bits
 constexpr int ROW = 1 << L;
 constexpr int NS2 = 1 << R2;               // blocks per row
+// Four waves: three (192) took 570 us where four take 544 (m = 21, 32-bit keys;
+// on doubles 786 and 757), six and eight 664 and 541 (doubles 1041 and 960: 148
+// registers leave three waves a SIMD, which they do not fill).
 constexpr int THREADS = 256;
 constexpr int kMaxChunks = 32;             // chunks of one row's pairs
 
