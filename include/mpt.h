@@ -85,7 +85,8 @@ size_t mpt_workspace_bytes(int m, int64_t nnz);
  *   sig        [n_chunks]  out: uint32 S_x masks
  *   W          [2^m]       out: int64 table, 16-byte aligned
  * Validates the device inputs (MPT_E_INVALID / RANGE / DUP / WEIGHT /
- * OVERFLOW) and synchronises `stream` to report the result.
+ * OVERFLOW) and synchronises `stream` to report the result. With n_chunks = 0
+ * the chunk ids are not looked at: W is 0 everywhere.
  */
 int mpt_build_weights(int m, int64_t n_chunks, int64_t nnz,
                       const int64_t *chunk_w, const int64_t *req_off,

@@ -656,7 +656,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_build_small(
         }
         const int32_t x = req_chunks[j];
         if (chunks_dst) chunks_dst[j] = x;
-        if (x < 0 || x >= n_chunks) { atomicOr(&err, (uint32_t)ERR_RANGE); continue; }
+        if (x < 0 || x >= n_chunks) {                // (no chunks at all: nothing to check the ids against)
+            if (n_chunks > 0) atomicOr(&err, (uint32_t)ERR_RANGE);
+            continue;
+        }
         const uint32_t bit = 1u << lo;
         if (atomicOr(&sg[x], bit) & bit) atomicOr(&err, (uint32_t)ERR_DUP);
     }
@@ -2773,9 +2776,9 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
     int n2 = 1;
     while (n2 < len) n2 <<= 1;
     for (int e = tid; e < n2; e += kOrderThreads) {
-        uint64_t key = ~0ull;                         // padding of the sort
-        if (e < len) {
-            const uint32_t x = (uint32_t)req_chunks[lo + e];
+        uint64_t key = ~0ull;                         // padding of the sort, ids without a chunk
+        const uint32_t x = e < len ? (uint32_t)req_chunks[lo + e] : ~0u;
+        if ((int64_t)x < n_chunks) {
             const uint32_t s = sig[x];
             int d = 0;
             while (d < dn - 1 && (path[d] & ~s)) ++d;

@@ -57,6 +57,34 @@ def test_tables(m, u, nnz):
     ctx.close()
 
 
+@pytest.mark.parametrize("m", [7, 13])
+@pytest.mark.parametrize("nnz", [6, 4097, LIMIT, LIMIT + 1])
+def test_slots_without_chunks(m, nnz):
+    """An empty universe: request slots name no chunk. The build takes them on
+    every route and W is 0; the stateless read-off refuses the ids, the
+    context's, which looks at none, gives -1 for each."""
+    off = np.minimum(np.arange(m + 1) * (nnz // 4), nnz)
+    off[m] = nnz
+    inst = wl.Instance(0, np.zeros(0, dtype=np.int64), off, np.arange(nnz, dtype=np.int32))
+    print(f"[gpu] build without chunks m={m} nnz={nnz}", flush=True)
+    p = mpt.Problem(inst)
+    p.build()
+    assert not p.W.any()
+    assert p.solve() == 0
+    with pytest.raises(mpt.MptError) as e:
+        p.extract()
+    assert e.value.name == "MPT_E_RANGE"
+    for up in (lambda t: t, lambda t: t.cuda()):
+        ctx = mpt.Context("cuda")
+        ctx.reserve(m, 0, nnz)
+        ctx.build_weights(m, 0, up(torch.as_tensor(inst.weights)), up(torch.as_tensor(inst.req_off)),
+                          up(torch.as_tensor(inst.req_chunks)))
+        assert not ctx.copy_table(mpt.MPT_TABLE_W).any()
+        assert ctx.solve_exact()[:2] == (0, 0)
+        assert (ctx.extract_orders() == -1).all()
+        ctx.close()
+
+
 def test_inputs_inside_the_workspace():
     """A rebuild on the context's own orders as request lists."""
     inst = family(9, 300, 200, 4)
