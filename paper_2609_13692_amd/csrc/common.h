@@ -51,15 +51,19 @@ class Range {
 // fixed pool (32 blocks, one allocation, made at the first use and kept: a
 // block goes back when its HostSlot ends); a mutex guards the pool, so that
 // calls on any threads, streams and devices may hold one each. ptr() is null
-// when all are taken or the allocation failed: callers then copy.
+// when all are taken, when the allocation failed and while s is being captured
+// (a recorded kernel must not keep the block's address): callers then copy.
 class HostSlot {
   public:
     static constexpr size_t kBytes = 16384;
-    HostSlot();
+    explicit HostSlot(hipStream_t s);
     ~HostSlot();
     char *ptr() const { return ptr_; }
-    // the device may still use the block: it never goes back
-    void abandon() { ptr_ = nullptr; }
+    // after an error, launches that use the block may be queued on s: it goes
+    // back when they are over, or never if that cannot be waited for
+    void settle(hipStream_t s) {
+        if (ptr_ && hipStreamSynchronize(s) != hipSuccess) ptr_ = nullptr;
+    }
     HostSlot(const HostSlot &) = delete;
     HostSlot &operator=(const HostSlot &) = delete;
 

@@ -241,7 +241,7 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
             in_w = chunk_w;
             in_chunks = req_chunks;
         } else if (L.sig - L.req_off <= mptlib::HostSlot::kBytes && on_host(req_off) &&
-                   (nnz == 0 || on_host(req_chunks)) && (n_chunks == 0 || on_host(chunk_w)) && slot.emplace().ptr()) {
+                   (nnz == 0 || on_host(req_chunks)) && (n_chunks == 0 || on_host(chunk_w)) && slot.emplace(s).ptr()) {
             char *image = slot->ptr();
             std::memcpy(image, req_off, b_off);
             if (nnz > 0) std::memcpy(image + (L.req_chunks - L.req_off), req_chunks, b_chunks);
@@ -260,7 +260,7 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
                                       ctx->at<int64_t>(L.W), ctx->ws + L.core, L.core_bytes, s, &total, ctx->route,
                                       copy);
         // (a build that succeeds has synchronised the stream)
-        if (rc && slot && slot->ptr() && hipStreamSynchronize(s) != hipSuccess) slot->abandon();
+        if (rc && slot) slot->settle(s);
         if (rc) return rc;
         ctx->total = total;
         ctx->state = BUILT;

@@ -3019,17 +3019,17 @@ int check_ws(void *ws, size_t bytes, size_t need) {
     return MPT_OK;
 }
 
-// Launches whose kernels write slot are queued: their error, if any. (One of
-// several may still run then, so the block does not go back.)
-hipError_t launched(mptlib::HostSlot &slot) {
+// Launches whose kernels write slot are queued: their error, if any (one of
+// several may still run then, and an error left by an earlier call stops none).
+hipError_t launched(mptlib::HostSlot &slot, hipStream_t s) {
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) slot.abandon();
+    if (e != hipSuccess) slot.settle(s);
     return e;
 }
 // waits for the stream whose kernels write slot
 hipError_t wait_for(mptlib::HostSlot &slot, hipStream_t s) {
     const hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess) slot.abandon();
+    if (e != hipSuccess) slot.settle(s);
     return e;
 }
 
@@ -3256,9 +3256,9 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
     bool zeroed = false;                                       // W, by the demand sets' launch
     const bool full = small && m <= kZetaBits && !dense;       // the whole build in one launch
     std::optional<mptlib::HostSlot> slot;
-    HeaderHead *post = small ? (HeaderHead *)slot.emplace().ptr() : nullptr;
+    HeaderHead *post = small ? (HeaderHead *)slot.emplace(s).ptr() : nullptr;
     auto finish = [&]() -> int {
-        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        MPT_HIP_TRY(slot ? launched(*slot, s) : hipGetLastError());
         return read_errors(h, s, total, slot ? &*slot : nullptr);
     };
     if (full) {
@@ -3347,9 +3347,9 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
     // C of the full set: from the block that the last kernel writes (post), or
     // read back from the table
     std::optional<mptlib::HostSlot> slot;
-    int64_t *post = pinned && opt_cost && m <= kShortRowsMaxM ? (int64_t *)slot.emplace().ptr() : nullptr;
+    int64_t *post = pinned && opt_cost && m <= kShortRowsMaxM ? (int64_t *)slot.emplace(s).ptr() : nullptr;
     auto optimum = [&]() -> int {
-        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        MPT_HIP_TRY(slot ? launched(*slot, s) : hipGetLastError());
         if (!opt_cost) return MPT_OK;
         if (post) {
             MPT_HIP_TRY(wait_for(*slot, s));
@@ -3365,9 +3365,9 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
         if (total < 0) {
             WsHeader *h = (WsHeader *)ws;
             std::optional<mptlib::HostSlot> at;
-            int64_t *host = pinned ? (int64_t *)at.emplace().ptr() : nullptr;
+            int64_t *host = pinned ? (int64_t *)at.emplace(s).ptr() : nullptr;
             rb::k_request_total<<<1, 64, 0, s>>>(m, W, h, host);
-            MPT_HIP_TRY(at ? launched(*at) : hipGetLastError());
+            MPT_HIP_TRY(at ? launched(*at, s) : hipGetLastError());
             if (host) {
                 MPT_HIP_TRY(wait_for(*at, s));
                 std::memcpy(&total, host, sizeof total);
@@ -3453,7 +3453,7 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
         static_assert(kShortOrders * sizeof(int32_t) <= mptlib::HostSlot::kBytes, "a block holds the orders");
         // a block for the error bits, or for the orders
         std::optional<mptlib::HostSlot> slot;
-        if (validate || host_orders) slot.emplace();
+        if (validate || host_orders) slot.emplace(s);
         int32_t *post = slot ? (int32_t *)slot->ptr() : nullptr;
         {
             LaunchScope ls("extract", (double)nnz, s);
@@ -3464,7 +3464,7 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
                 k_extract_short<false><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
                                                                    order_chunks, h, post);
         }
-        MPT_HIP_TRY(slot ? launched(*slot) : hipGetLastError());
+        MPT_HIP_TRY(slot ? launched(*slot, s) : hipGetLastError());
         if (validate) {
             if ((rc = read_errors(h, s, nullptr, slot ? &*slot : nullptr))) return rc;
             return host_orders ? orders_to_host() : MPT_OK;
@@ -3634,7 +3634,13 @@ struct SlotPool {
 } g_slots;
 }  // namespace
 
-HostSlot::HostSlot() {
+HostSlot::HostSlot(hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {      // (the null stream while another one is captured)
+        (void)hipGetLastError();
+        return;
+    }
+    if (capture != hipStreamCaptureStatusNone) return;
     std::lock_guard<std::mutex> g(g_slots.mu);
     if (!g_slots.tried) {
         g_slots.tried = true;
@@ -3667,7 +3673,7 @@ __global__ void k_post(const uint32_t *__restrict__ src, uint32_t *__restrict__ 
 
 hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s, bool pinned) {
     std::optional<HostSlot> taken;
-    if (pinned && bytes <= HostSlot::kBytes && (bytes & 3u) == 0 && ((uintptr_t)src & 3u) == 0) taken.emplace();
+    if (pinned && bytes <= HostSlot::kBytes && (bytes & 3u) == 0 && ((uintptr_t)src & 3u) == 0) taken.emplace(s);
     if (!taken || !taken->ptr()) {
         const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
@@ -3678,7 +3684,7 @@ hipError_t read_back(void *dst, const void *src, size_t bytes, hipStream_t s, bo
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
-        slot.abandon();
+        slot.settle(s);
         return e;
     }
     std::memcpy(dst, slot.ptr(), bytes);

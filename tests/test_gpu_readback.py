@@ -1,7 +1,10 @@
 """Results and small host instances that travel through the pinned blocks
 (16 KiB each, a pool of 32): at the block's size, just past it, and from
-several threads and streams at a time. Compared exactly with the oracle."""
+several threads and streams at a time; with every block taken, and after calls
+that a stream capture refuses. Compared exactly with the oracle."""
+import ctypes
 import threading
+from types import SimpleNamespace
 
 import numpy as np
 import pytest
@@ -66,3 +69,87 @@ def test_threads_and_streams():
     for t in threads:
         t.join()
     assert not failed
+
+
+class Blocks:
+    """Takes every block that is left, for as long as it lives (the library's
+    own mptlib::HostSlot, a class of one pointer)."""
+
+    def __init__(self):
+        lib = mpt.load()
+        self._end = lib._ZN6mptlib8HostSlotD1Ev
+        self.slots = []
+        while True:
+            slot = ctypes.c_void_p()
+            lib._ZN6mptlib8HostSlotC1EP12ihipStream_t(ctypes.byref(slot), None)
+            if not slot.value:
+                break
+            self.slots.append(slot)
+
+    def close(self):
+        for slot in self.slots:
+            self._end(ctypes.byref(slot))
+        self.slots = []
+
+
+def everything(inst):
+    """The results of one call of every kind that reads something back."""
+    ctx, p, g = mpt.Context("cuda"), mpt.Problem(inst), mpt.Greedy(inst)
+    out = [mpt.Context.run(ctx, inst), p.run(), p.orders.cpu().numpy(), g.run(), g.orders.cpu().numpy()]
+    L = mpt.Layouts(inst, n_configs=2)
+    pop = L.global_order(mpt.MPT_ORDER_POPULARITY)
+    out += [L.cost(pop), L.simulate(pop, [0, 1], [500, 2000])]
+    r = mpt.pinned_layout(inst, 1, "greedy")
+    out += [r["orders"].cpu().numpy(), r["cost"], r["n_distinct"]]
+    ctx.close()
+    return out
+
+
+def equal(a, b):
+    if isinstance(a, dict):
+        return a.keys() == b.keys() and all(equal(a[k], b[k]) for k in a)
+    if isinstance(a, (list, tuple)):
+        return len(a) == len(b) and all(equal(x, y) for x, y in zip(a, b))
+    return np.array_equal(a, b)
+
+
+def test_every_block_taken():
+    insts = [instance(9, 60, 4, 2), instance(12, 300, 9, 2), instance(14, 900, 12, 3), instance(5, 20000, 800, 4)]
+    want = [everything(inst) for inst in insts]
+    held = Blocks()
+    try:
+        assert held.slots
+        for inst, ref in zip(insts, want):
+            print(f"[gpu] no blocks left, m={inst.m}", flush=True)
+            assert equal(everything(inst), ref)
+            check(mpt.Context("cuda").run(inst), inst)
+    finally:
+        held.close()
+
+
+def test_refused_captures_keep_the_blocks():
+    """A call that returns a host value cannot be captured: it fails, and the
+    block it would have used is there for the next one."""
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    inst = instance(6, 60, 4, 5)
+    p = mpt.Problem(inst)
+    want = p.run()
+    free = Blocks()
+    n = len(free.slots)
+    free.close()
+    torch.cuda.synchronize()
+    for i in range(4):
+        graph, handle = ctypes.c_void_p(), ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(handle)) == 0     # (a stream whose capture failed takes no other)
+        assert hip.hipStreamBeginCapture(handle, 2) == 0          # 2: relaxed
+        with pytest.raises(mpt.MptError) as e:
+            p.solve(stream=SimpleNamespace(cuda_stream=handle.value))
+        assert e.value.name == "MPT_E_DEVICE"
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) != 0 and not graph.value
+        hip.hipGetLastError()
+        assert hip.hipStreamDestroy(handle) == 0
+    print("[gpu] captures refused", flush=True)
+    assert p.solve() == want
+    free = Blocks()
+    assert len(free.slots) == n
+    free.close()
