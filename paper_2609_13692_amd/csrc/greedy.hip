@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kListThreads) void k_g_lists(int m, const int64_t *
                                                           int32_t *__restrict__ sig, int32_t *__restrict__ sig_slot,
                                                           int32_t *__restrict__ sig_len, int32_t *__restrict__ dem,
                                                           GHeader *h) {
-    __shared__ uint32_t stage[kListMax];
+    __shared__ __align__(16) uint32_t stage[kListMax];
     if (h->err & ~GERR_DUP) return;            // (GERR_DUP is raised in this launch: no workgroup stops for it)
     const int64_t longest = h->max_len;
     const int lane = (int)(threadIdx.x & (kWave - 1));

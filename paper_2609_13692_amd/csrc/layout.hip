@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kListThreads) void k_l_layout_short(int m, const in
                                                                  const int32_t *chunks,
                                                                  const int32_t *__restrict__ rank, int kind,
                                                                  int32_t *seqs, const LHeader *h) {
-    __shared__ uint32_t stage[kListMax];
+    __shared__ __align__(16) uint32_t stage[kListMax];
     if (h->err || h->max_len > kListMax) return;
     auto place = [&](int32_t x) { return kind == MPT_ORDER_ID ? (uint32_t)x : (uint32_t)rank[x]; };
     if (h->max_len <= kSegMax) {
@@ -919,7 +919,10 @@ extern "C" int mpt_global_order_layout(int m, int64_t n_chunks, int64_t nnz, con
             if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
             k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
         }
-        k_l_layout_short<<<grid_for(m, 4, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs, h);
+        // (workgroups for requests of more than kSegMax chunks, whose length the
+        // host does not know; four requests each took 217 us for 100 of 512
+        // chunks, where a wave per request does not notice the difference)
+        k_l_layout_short<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs, h);
     }
     MPT_HIP_TRY(hipGetLastError());
     int64_t max_len = 0;

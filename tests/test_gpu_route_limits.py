@@ -1,0 +1,44 @@
+"""Where one route hands over to another, the call does not get slower: each
+test times a call just inside a route against the same call on the route
+beyond its limit (or on inputs that the route should not notice). The best of
+many passes, and bounds well above what runs differ by."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_13692_amd import mpt
+from paper_2609_13692_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def best(call, passes=30):
+    for _ in range(3):
+        call()
+    torch.cuda.synchronize()
+    took = []
+    for _ in range(passes):
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        took.append(time.perf_counter() - t)
+    return min(took) * 1e6
+
+
+def uniform(lens, u, seed=0):
+    rng = np.random.default_rng(seed)
+    return wl.from_sets([rng.choice(u, size=k, replace=False).tolist() for k in lens],
+                        rng.integers(1, 300, size=u).tolist(), u)
+
+
+@pytest.mark.parametrize("m", [10, 100, 600])
+def test_layouts_of_requests_up_to_the_rank_limit(m):
+    """512 chunks per request: ranks; 513: the key sort."""
+    took = {}
+    for k in (512, 513):
+        L = mpt.Layouts(uniform([k] * m, 5000, m))
+        took[k] = best(lambda: L.global_order(mpt.MPT_ORDER_ID))
+    print(f"[gpu] layouts m={m}: 512 chunks {took[512]:.0f} us, 513 {took[513]:.0f} us", flush=True)
+    assert took[512] < 1.3 * took[513]
