@@ -2697,30 +2697,34 @@ __global__ __launch_bounds__(256) void k_extract(int m, int64_t n_chunks, int64_
 }
 
 // Up to kShortOrders request slots, in one launch: a workgroup per request
-// takes its keys to LDS, orders them there and writes the request's range.
-// With VALIDATE every workgroup checks the whole input (offsets, one lane per
-// request walking its path, all chunk ids), so that none writes before all of
-// it is known to be sound; workgroup 0 reports the error bits. Positions by
-// counting smaller keys (ties by slot) up to kRankOrders chunks, a bitonic
-// sort in LDS above.
+// orders its keys and writes the request's range. With VALIDATE every workgroup
+// checks the whole input (offsets, one lane per request walking its path, all
+// chunk ids), so that none writes before all of it is known to be sound;
+// workgroup 0 reports the error bits. Positions by counting smaller keys (ties
+// by slot) up to kRankOrders chunks; above, the key sort's tile (256 keys per
+// wave in registers, then merges in LDS) with four keys per thread, so that
+// THREADS is 256 up to 1024 slots and 1024 above.
 // Bound by latency: the walk is up to m - 1 dependent reads of split. The
 // sort of all nnz keys that it replaces for these sizes padded them to one
 // tile of 4096 keys and took four launches: 33 us in the tile sort whatever
 // nnz was and 12 us in the others, against 7 us here (m = 16, 128 slots). A
 // limit on nnz and not on the longest request, because only nnz is known on
-// the host.
+// the host: a call takes 33 us on one request of 4096 chunks and 54 on 4097, by
+// the key sort (with a bitonic sort in LDS by 256 threads 95 on 4096). Ranks and
+// tile sort meet at about 100 chunks (eight requests of 65: 25.0 and 26.0 us a
+// call, of 100: 26.2 both, of 128: 26.6 and 26.2).
 constexpr int kShortOrders = 4096;
-constexpr int kRankOrders = 512;      // 512^2 comparisons on one CU take about 7 us, the sort's 45 stages as long
-constexpr int kOrderThreads = 256;
-template <bool VALIDATE>
-__global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t n_chunks, int64_t nnz,
-                                                                 const int64_t *__restrict__ req_off,
-                                                                 const int32_t *__restrict__ req_chunks,
-                                                                 const uint32_t *__restrict__ sig,
-                                                                 const uint32_t *__restrict__ split,
-                                                                 int32_t *__restrict__ order_chunks, WsHeader *h,
-                                                                 int32_t *post) {
-    __shared__ uint64_t keys[kShortOrders];
+constexpr int kRankOrders = 128;
+template <bool VALIDATE, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_extract_short(int m, int64_t n_chunks, int64_t nnz,
+                                                           const int64_t *__restrict__ req_off,
+                                                           const int32_t *__restrict__ req_chunks,
+                                                           const uint32_t *__restrict__ sig,
+                                                           const uint32_t *__restrict__ split,
+                                                           int32_t *__restrict__ order_chunks, WsHeader *h,
+                                                           int32_t *post) {
+    constexpr int PER = mptlib::kSortPer;
+    __shared__ __align__(16) uint64_t keys[2][THREADS * PER];
     __shared__ int64_t off[32];
     __shared__ uint32_t path[32];
     __shared__ int depth_n;
@@ -2759,7 +2763,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
         if (bad) atomicOr(&err, (uint32_t)ERR_INVALID);
     }
     if (VALIDATE)
-        for (int64_t j = tid; j < nnz; j += kOrderThreads) {
+        for (int64_t j = tid; j < nnz; j += THREADS) {
             const int32_t x = req_chunks[j];
             if (x < 0 || (int64_t)x >= n_chunks) atomicOr(&err, (uint32_t)ERR_RANGE);
         }
@@ -2773,46 +2777,52 @@ __global__ __launch_bounds__(kOrderThreads) void k_extract_short(int m, int64_t 
     const int64_t lo = off[own];
     const int len = (int)(off[own + 1] - lo);
     const int dn = depth_n;
-    int n2 = 1;
-    while (n2 < len) n2 <<= 1;
-    for (int e = tid; e < n2; e += kOrderThreads) {
-        uint64_t key = ~0ull;                         // padding of the sort, ids without a chunk
+    auto key_of = [&](int e) {                        // ~0: none, or an id without a chunk
         const uint32_t x = e < len ? (uint32_t)req_chunks[lo + e] : ~0u;
-        if ((int64_t)x < n_chunks) {
-            const uint32_t s = sig[x];
-            int d = 0;
-            while (d < dn - 1 && (path[d] & ~s)) ++d;
-            key = ((uint64_t)d << 32) | x;
-        }
-        keys[e] = key;
-    }
-    __syncthreads();
+        if ((int64_t)x >= n_chunks) return ~0ull;
+        const uint32_t s = sig[x];
+        int d = 0;
+        while (d < dn - 1 && (path[d] & ~s)) ++d;
+        return ((unsigned long long)d << 32) | x;
+    };
+    auto put = [&](int pos, uint64_t key) {
+        order_chunks[lo + pos] = (int32_t)(key & 0xffffffffu);
+        if (!VALIDATE && post) post[lo + pos] = (int32_t)(key & 0xffffffffu);
+    };
     if (len <= kRankOrders) {
-        for (int e = tid; e < len; e += kOrderThreads) {
-            const uint64_t key = keys[e];
-            int pos = 0;
-            for (int f = 0; f < len; ++f) {
-                const uint64_t o = keys[f];
-                pos += (o < key || (o == key && f < e)) ? 1 : 0;
-            }
-            order_chunks[lo + pos] = (int32_t)(key & 0xffffffffu);
-            if (!VALIDATE && post) post[lo + pos] = (int32_t)(key & 0xffffffffu);
+        static_assert(kRankOrders <= THREADS, "a thread per chunk");
+        const uint64_t key = key_of(tid);
+        if (tid < len) keys[0][tid] = key;
+        __syncthreads();
+        if (tid >= len) return;
+        int pos = 0;
+        for (int f = 0; f < len; ++f) {
+            const uint64_t o = keys[0][f];
+            pos += (o < key || (o == key && f < tid)) ? 1 : 0;
         }
+        put(pos, key);
         return;
     }
-    for (int k = 2; k <= n2; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int p = tid; p < n2 / 2; p += kOrderThreads) {
-                const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), l = i + j;
-                const uint64_t x = keys[i], y = keys[l];
-                if ((x > y) == ((i & k) == 0)) { keys[i] = y; keys[l] = x; }
-            }
-            __syncthreads();
-        }
-    for (int e = tid; e < len; e += kOrderThreads) {
-        order_chunks[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
-        if (!VALIDATE && post) post[lo + e] = (int32_t)(keys[e] & 0xffffffffu);
+    // four keys per thread; the waves past the last key have nothing to sort
+    uint64_t v[PER];
+    const int first = tid / kWave * (kWave * PER) + (tid & (kWave - 1));
+#pragma unroll
+    for (int r = 0; r < PER; ++r) v[r] = key_of(first + r * kWave);
+    if (first - (tid & (kWave - 1)) < len) {
+        mptlib::keysort_detail::sort_wave64(v);
+        mptlib::keysort_detail::sort_wave256(v);
     }
+    int cur = 0;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) keys[0][tid * PER + r] = v[r];
+    __syncthreads();
+    for (int run = kWave * PER; run < len; run <<= 1, cur ^= 1) {
+        mptlib::keysort_detail::merge_outputs(keys[cur], run, tid * PER, v);
+#pragma unroll
+        for (int r = 0; r < PER; ++r) keys[cur ^ 1][tid * PER + r] = v[r];
+        __syncthreads();
+    }
+    for (int e = tid; e < len; e += THREADS) put(e, keys[cur][e]);
 }
 
 __global__ void k_extract_out(int64_t nnz, const uint64_t *keys, int32_t *order_chunks) {
@@ -3457,12 +3467,13 @@ int extract(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off, const 
         int32_t *post = slot ? (int32_t *)slot->ptr() : nullptr;
         {
             LaunchScope ls("extract", (double)nnz, s);
-            if (validate)
-                k_extract_short<true><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
-                                                                  order_chunks, h, post);
-            else
-                k_extract_short<false><<<m, kOrderThreads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split,
-                                                                   order_chunks, h, post);
+            const int threads = nnz <= 256 * mptlib::kSortPer ? 256 : 1024;
+            static_assert(1024 * mptlib::kSortPer == kShortOrders, "four keys per thread hold any request");
+            auto launch = [&](auto kernel) {
+                kernel<<<m, threads, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, sig, split, order_chunks, h, post);
+            };
+            if (validate) launch(threads == 256 ? k_extract_short<true, 256> : k_extract_short<true, 1024>);
+            else launch(threads == 256 ? k_extract_short<false, 256> : k_extract_short<false, 1024>);
         }
         MPT_HIP_TRY(slot ? launched(*slot, s) : hipGetLastError());
         if (validate) {

@@ -1,6 +1,8 @@
 """The order read-off at the edges of its one-launch route (at most 4096
-request slots): 4095, 4096 and 4097 slots; requests of 0, 1, 512 (ranks),
-513 (LDS sort) and 4096 chunks; the stateless call and the context. Orders
+request slots; 256 threads per request up to 1024, 1024 above): 1023 to 1025 and
+4095 to 4097 slots; requests of 0, 1, 128 (ranks), 129 (tile sort), a wave's 256
+keys and the merges' 512 and 1024, and of 4096 chunks; the stateless call and the
+context. Orders
 against the oracle's, and nothing written when the input is refused."""
 import numpy as np
 import pytest
@@ -20,6 +22,7 @@ def family(lens, u, seed):
 
 
 LENS = [[0], [1], [0, 0, 3], [512, 513, 1, 0], [511, 512, 513, 514, 700, 1, 2], [4095], [4096], [4097],
+        [127, 128, 129, 130], [255, 256, 257], [511, 512], [511, 513], [1023, 0, 1], [1024], [1025], [1026, 128, 129], [3000],
         [2048, 2048], [2048, 2049], [1500, 0, 1500, 1000, 96], [63] * 12 + [900]]
 
 

@@ -42,3 +42,15 @@ def test_layouts_of_requests_up_to_the_rank_limit(m):
         took[k] = best(lambda: L.global_order(mpt.MPT_ORDER_ID))
     print(f"[gpu] layouts m={m}: 512 chunks {took[512]:.0f} us, 513 {took[513]:.0f} us", flush=True)
     assert took[512] < 1.3 * took[513]
+
+
+@pytest.mark.parametrize("m", [1, 2])
+def test_orders_of_long_requests_up_to_the_slot_limit(m):
+    """4096 slots: one launch; 4097: keys, their sort and the copy out."""
+    took = {}
+    for nnz in (4096, 4097):
+        p = mpt.Problem(uniform([nnz - (m - 1) * (4096 // m)] + [4096 // m] * (m - 1), 5000, m))
+        p.run()
+        took[nnz] = best(p.extract)
+    print(f"[gpu] orders m={m}: 4096 slots {took[4096]:.0f} us, 4097 {took[4097]:.0f} us", flush=True)
+    assert took[4096] < 1.2 * took[4097]
