@@ -2464,7 +2464,7 @@ __global__ __launch_bounds__(THREADS) void k_rb_row0(int m, const int64_t *__res
 // order, in one launch. The total sum_i w(R_i) picks the width inside the
 // kernel, so that nothing is read back: 32-bit keys below 2^20 - 1 (C(A) +
 // C(B) <= total, shifted by L = 12 bits), 64-bit keys below 2^50; above, (cost,
-// part) pairs by lane groups per subset. For m < CB the block's missing requests hold
+// part) pairs by lane groups per subset. Calls at m = 12: 40, 54 and 84 us. For m < CB the block's missing requests hold
 // nothing: they cost 0 and reach no subset that is written.
 __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__restrict__ W, int64_t *__restrict__ C,
                                                       uint32_t *__restrict__ split, int64_t *post) {
@@ -2519,18 +2519,22 @@ __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__re
         lds_barrier();
         const uint32_t wv = threadIdx.x / kWave;
         for (int p = 2; p <= m; ++p) {
-            // one lane per subset while it has at most 63 candidates, a wave
-            // above; lane li takes candidates li, li + G, ... in ascending A
-            const uint32_t G = p <= 7 ? 1u : (uint32_t)kWave, per_wave = (uint32_t)kWave / G;
-            const uint32_t n_sub = c_binom.v[m][p], gl = (uint32_t)lane / G, li = (uint32_t)lane % G;
+            // as many lanes per subset as keep the level within one pass of the
+            // workgroup (m = 12: at most 64 candidates per lane; a wave per
+            // subset from p = 8 on was 31 turns there); lane li takes candidates
+            // li, li + G, ... in ascending A
+            const uint32_t n_sub = c_binom.v[m][p], n_a = (1u << (p - 1)) - 1u;
+            uint32_t G = 1;
+            while (G < (uint32_t)kWave && G <= n_a / 2u && 2u * G * n_sub <= (uint32_t)THREADS) G <<= 1;
+            const uint32_t per_wave = (uint32_t)kWave / G, gl = (uint32_t)lane / G, li = (uint32_t)lane % G;
             for (uint32_t r0 = wv * per_wave; r0 < n_sub; r0 += (uint32_t)(THREADS / kWave) * per_wave) {
                 const uint32_t r = r0 + gl;
-                int64_t best = INT64_MAX;
+                int64_t best = INT64_MAX, w_s = 0;
                 uint32_t best_a = ~0u, S = 0;
                 if (r < n_sub) {
                     S = c_subsets.v[c_subsets.begin[p] + (int)r];
+                    w_s = W[S];
                     const uint32_t lb = S & (0u - S), rest = S ^ lb;
-                    const uint32_t n_a = (1u << (p - 1)) - 1u;
                     const uint32_t step = deposit(G, rest);
                     uint32_t ap = deposit(li, rest);
                     for (uint32_t q = li; q < n_a; q += G) {
@@ -2538,9 +2542,13 @@ __global__ __launch_bounds__(THREADS) void k_dp_small(int m, const int64_t *__re
                         ap = ((ap | ~rest) + step) & rest;
                     }
                 }
-                if (G > 1u) wave_lex_min(best, best_a);
+                for (uint32_t off = G / 2u; off > 0u; off >>= 1) {
+                    const int64_t ov = __shfl_xor(best, (int)off, kWave);
+                    const uint32_t oa = __shfl_xor(best_a, (int)off, kWave);
+                    lex_min(best, best_a, ov, oa);
+                }
                 if (r < n_sub && li == 0) {
-                    c[S] = best - W[S];
+                    c[S] = best - w_s;
                     spl[S] = best_a;
                 }
             }

@@ -54,3 +54,22 @@ def test_orders_of_long_requests_up_to_the_slot_limit(m):
         took[nnz] = best(p.extract)
     print(f"[gpu] orders m={m}: 4096 slots {took[4096]:.0f} us, 4097 {took[4097]:.0f} us", flush=True)
     assert took[4096] < 1.2 * took[4097]
+
+
+@pytest.mark.parametrize("m", [10, 12])
+def test_small_solves_of_large_totals(m):
+    """sum_i w(R_i) of 2^49 (64-bit keys) and of 2^55 ((cost, part) pairs)."""
+    took = {}
+    for total in (1 << 49, 1 << 55):
+        n = 1 << m
+        f = np.zeros(n, dtype=np.int64)
+        f[1 << np.arange(m)] = total // (2 * m)
+        f[np.random.default_rng(m).integers(1, n, size=3 * m)] += total // (6 * m * m)
+        for b in range(m):
+            v = f.reshape(-1, 2, 1 << b)
+            v[:, 0] += v[:, 1]
+        W, ws = torch.as_tensor(f).cuda(), mpt.alloc_workspace(m, 0)
+        C, S = torch.empty(n, dtype=torch.int64, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+        took[total] = best(lambda: mpt.mpt_solve_exact(m, W, C, S, ws))
+    print(f"[gpu] small solves m={m}: {took[1 << 49]:.0f} us, large totals {took[1 << 55]:.0f} us", flush=True)
+    assert took[1 << 55] < 2.2 * took[1 << 49]

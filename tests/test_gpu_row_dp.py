@@ -55,6 +55,22 @@ def test_every_small_m_at_every_width(total):
         assert np.array_equal(S.cpu().numpy().view(np.uint32), split), (m, total)
 
 
+def test_ties_of_large_totals():
+    """Costs that are small multiples of 2^48: (cost, part) pairs, many equal
+    costs, the smallest part of each."""
+    for m in range(2, 13):
+        W = table(m, 40, 5, sparse=True) << 48
+        W[: 1 << (m - 1)] += 1 << 48                  # (one chunk that all but the last request hold)
+        print(f"[gpu] row dp ties m={m}", flush=True)
+        dev = torch.as_tensor(W).cuda()
+        C = torch.empty(W.size, dtype=torch.int64, device="cuda")
+        S = torch.empty(W.size, dtype=torch.int32, device="cuda")
+        mpt.mpt_solve_exact(m, dev, C, S, mpt.alloc_workspace(m, 0))
+        M, split = oracle.exact_dp(m, W)
+        assert np.array_equal(C.cpu().numpy()[1:], oracle.cost_table(m, W, M)[1:]), m
+        assert np.array_equal(S.cpu().numpy().view(np.uint32), split), m
+
+
 @pytest.mark.parametrize("m", [13, 14])
 @pytest.mark.parametrize("total", [700, (1 << 20) - 1, (1 << 46) + 3])
 def test_row0_of_larger_instances(m, total):
