@@ -343,19 +343,31 @@ __global__ void k_g_keys(int m, int64_t nnz, const int64_t *req_off, const int32
 }
 
 // sorted keys -> request lists; a repeated chunk inside a request is two
-// equal adjacent keys. An entry's place in dem is looked for in its chunk's
-// demand list.
-__global__ void k_g_sig_long(int64_t nnz, const uint64_t *keys, const uint64_t *dem_seg, const int32_t *dem,
-                             int32_t *sig, int32_t *sig_slot, GHeader *h) {
+// equal adjacent keys. Slot j's entry stands in dem at its chunk's stretch +
+// rank[j] (as k_g_lists wrote it), and in its list where the sorted keys of its
+// request have it: a binary search in them, whatever the chunk's demand. (A
+// look through the chunk's demand list took up to m reads: the pair weights of
+// 1000 nested requests of 1001 to 2000 chunks took 4649 us with it, 2245 now.)
+__global__ void k_g_sig_long(int m, int64_t nnz, const int64_t *req_off, const int32_t *req_chunks,
+                             const uint64_t *keys, const uint64_t *dem_seg, const uint32_t *rank, int32_t *sig,
+                             int32_t *sig_slot, GHeader *h) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t x = (int32_t)(keys[j] & 0xffffffffu), i = (int32_t)(keys[j] >> 32);
-        const uint64_t seg = dem_seg[x];
-        const int32_t first = (int32_t)(seg >> 32), n = (int32_t)(seg & 0xffffffffu);
-        int32_t at = first;
-        while (at < first + n - 1 && dem[at] != i) ++at;
-        sig[j] = x;
-        sig_slot[j] = at;
-        if (j > 0 && keys[j] == keys[j - 1]) atomicOr(&h->err, (uint32_t)GERR_DUP);
+        const uint64_t key = keys[j];
+        sig[j] = (int32_t)(key & 0xffffffffu);
+        if (j > 0 && key == keys[j - 1]) atomicOr(&h->err, (uint32_t)GERR_DUP);
+        int a = 0, b = m - 1;                       // request of slot j: last i with req_off[i] <= j
+        while (a < b) {
+            const int mid = (a + b + 1) >> 1;
+            if (req_off[mid] <= j) a = mid; else b = mid - 1;
+        }
+        const int32_t x = req_chunks[j];
+        const uint64_t own = ((uint64_t)a << 32) | (uint32_t)x;
+        int64_t lo = req_off[a], hi = req_off[a + 1];
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if (keys[mid] < own) lo = mid + 1; else hi = mid;
+        }
+        sig_slot[lo] = (int32_t)(dem_seg[x] >> 32) + (int32_t)rank[j];
     }
 }
 
@@ -1367,7 +1379,8 @@ int g_prepare(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, cons
         LaunchScope ls("g_sort", (double)nnz, s);
         k_g_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, (uint64_t *)(ws + L.keys1));
         if ((rc = sort_keys((uint64_t *)(ws + L.keys1), (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
-        k_g_sig_long<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, dem_seg, dem, sig, sig_slot, h);
+        k_g_sig_long<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, sorted, dem_seg, rank, sig,
+                                                           sig_slot, h);
     }
     pairs(1);
     MPT_HIP_TRY(hipGetLastError());

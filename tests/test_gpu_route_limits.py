@@ -73,3 +73,25 @@ def test_small_solves_of_large_totals(m):
         took[total] = best(lambda: mpt.mpt_solve_exact(m, W, C, S, ws))
     print(f"[gpu] small solves m={m}: {took[1 << 49]:.0f} us, large totals {took[1 << 55]:.0f} us", flush=True)
     assert took[1 << 55] < 2.2 * took[1 << 49]
+
+
+def test_lists_of_long_requests_with_popular_chunks():
+    """4000 requests of 30 chunks and one of 600, whose lists a key sort puts in
+    order: four of the chunks held by everyone, or none by more than a few. The
+    pair weights differ (their work is the demand), the lists must not."""
+    took = {}
+    rng = np.random.default_rng(1)
+    for popular in (0, 4):
+        u = 60000
+        sets = [np.concatenate([np.arange(popular), popular + rng.choice(u - popular, size=k - popular, replace=False)])
+                for k in [30] * 4000 + [600]]
+        g = mpt.Greedy(wl.from_sets([s.tolist() for s in sets], rng.integers(1, 300, size=u).tolist(), u))
+        g.pair_weights()
+        spent = []
+        for _ in range(10):
+            mpt.profile_begin()
+            g.pair_weights()
+            spent.append(mpt.profile_end()["g_sort"]["total_ms"])
+        took[popular] = min(spent) * 1e3
+    print(f"[gpu] lists: {took[0]:.0f} us, with popular chunks {took[4]:.0f} us", flush=True)
+    assert took[4] < 1.5 * took[0]
