@@ -60,7 +60,8 @@ SHORT_ROWS_KERNEL = {"rb_cross_u32": "k_sr_cross<unsigned int>", "rb_cross_f64":
 
 def dp_key(label: str, m: int):
     key = DP_KEYS.get(label)
-    return (SHORT_ROWS_KERNEL[label], *key[1:]) if key and m <= SHORT_ROWS_MAX_M else key
+    short = m <= SHORT_ROWS_MAX_M and not (label == "rb_cross_u64" and m == 22)
+    return (SHORT_ROWS_KERNEL[label], *key[1:]) if key and short else key
 
 
 WORKLOADS = {

@@ -3190,13 +3190,16 @@ int solve_rb(int m, const int64_t *W, int64_t *C, uint32_t *split, char *ws, con
 }
 
 // Mid-sized instances (m = 13 .. 23): rows of 2^9 entries (short_rows.h).
-// Solves measured on 2^12-entry rows against these, in us, on 32-bit keys /
-// doubles: m = 13 110 / 119 against 60 / 76, m = 16 243 / 283 against 114 /
-// 139, m = 20 532 / 633 against 319 / 393, m = 22 1263 / 1653 against 1134 /
-// 1596, m = 23 2903 / 3941 against 2623 / 3747. The gain is a level's fixed
-// time and falls with m; from m = 24 on the wide rows' smaller row traffic
-// and shared block loads are kept.
+// Calls measured on 2^12-entry rows against these, in us, on 32-bit keys /
+// doubles / 64-bit integers: m = 16 319 / 354 / 406 against 146 / 171 / 198, m =
+// 20 611 / 710 / 884 against 356 / 432 / 594, m = 21 799 / 967 / 1333 against
+// 584 / 754 / 1178, m = 22 1341 / 1733 / 2750 against 1165 / 1628 / 2808, m = 23
+// 2988 / 4020 / 6858 against 2662 / 3839 / 6774. The gain is a level's fixed time
+// and falls with m, for 64-bit integers (four instructions a candidate) fastest:
+// m = 22 keeps the wide rows for them, and from m = 24 on the wide rows' smaller
+// row traffic and shared block loads are kept for all.
 constexpr int kShortRowsMaxM = 23;
+inline bool short_rows_pay(int m, bool doubles) { return m <= kShortRowsMaxM && (doubles || m != 22); }
 template <class E>
 void solve_sr(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *post, char *ws, const WsLayout &Lw, hipStream_t s) {
     // Workgroups that run at a time: four waves each of 115 registers (four
@@ -3399,7 +3402,7 @@ int solve(int m, const int64_t *W, int64_t *C, uint32_t *split, int64_t *opt_cos
             // (then 2 C' < 2^52 too, for any m up to MPT_MAX_M)
             static_assert(rb::kNarrowTotal <= ((int64_t)1 << (51 - MPT_MAX_M)), "narrow keys imply double keys");
             const bool narrow = total < rb::kNarrowTotal - 1, doubles = total < ((int64_t)1 << (51 - m));
-            if (m <= kShortRowsMaxM && chunk_pairs == 0) {
+            if (short_rows_pay(m, doubles) && chunk_pairs == 0) {
                 if (narrow) solve_sr<uint32_t>(m, W, C, split, post, ws, L, s);
                 else if (doubles) solve_sr<double>(m, W, C, split, post, ws, L, s);
                 else solve_sr<uint64_t>(m, W, C, split, post, ws, L, s);

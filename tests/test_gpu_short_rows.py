@@ -61,7 +61,7 @@ def test_against_the_oracle(m, width, ties):
     assert np.array_equal(split, ref["split"].astype(np.uint32))
 
 
-@pytest.mark.parametrize("m", [18, 20, 21, 23])
+@pytest.mark.parametrize("m", [18, 20, 21, 22, 23])
 @pytest.mark.parametrize("width", WIDTHS)
 @pytest.mark.parametrize("ties", [False, True])
 def test_against_the_long_rows(m, width, ties):
@@ -71,6 +71,22 @@ def test_against_the_long_rows(m, width, ties):
     assert a[0] == b[0]
     assert np.array_equal(a[1], b[1])
     assert np.array_equal(a[2], b[2])
+
+
+def test_where_the_long_rows_are_faster():
+    """64-bit keys at m = 22 (2750 us on 2^12-entry rows, 2808 on short ones):
+    the kernels that ran, by their labels."""
+    for m, width, wide in ((21, "u64", False), (22, "u64", True), (22, "f64", False), (23, "u64", False),
+                           (24, "u32", True)):
+        inst = instance(m, width, 5)
+        prob = mpt.Problem(inst)
+        prob.build()
+        print(f"[gpu] rows m={m} width={width}", flush=True)
+        mpt.profile_begin()
+        prob.solve()
+        labels = mpt.profile_end()
+        assert f"rb_cross_{width}" in labels
+        assert ("rb_unpack" in labels) == wide, (m, width)
 
 
 @pytest.mark.parametrize("m", [13, 15])
