@@ -1398,15 +1398,17 @@ extern "C" int mpt_pair_weights(int m, int64_t n_chunks, int64_t nnz, const int6
                                 const int32_t *req_chunks, int64_t *P, int64_t *request_total, void *workspace,
                                 size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    int rc = g_check_common(m, n_chunks, nnz);
-    if (rc) return rc;
-    if (!req_off || !P) return fail(MPT_E_INVALID, "req_off and P must not be NULL");
-    if (n_chunks > 0 && !chunk_w) return fail(MPT_E_INVALID, "chunk_w must not be NULL");
-    if (nnz > 0 && !req_chunks) return fail(MPT_E_INVALID, "req_chunks must not be NULL");
-    const GLayout L = g_layout(m, n_chunks, nnz);
-    if ((rc = g_check_ws(L, workspace, workspace_bytes))) return rc;
-    return g_prepare(m, n_chunks, nnz, chunk_w, req_off, req_chunks, P, L, (char *)workspace, (hipStream_t)stream,
-                     request_total);
+    return mptlib::guarded(__func__, [&]() -> int {
+        int rc = g_check_common(m, n_chunks, nnz);
+        if (rc) return rc;
+        if (!req_off || !P) return fail(MPT_E_INVALID, "req_off and P must not be NULL");
+        if (n_chunks > 0 && !chunk_w) return fail(MPT_E_INVALID, "chunk_w must not be NULL");
+        if (nnz > 0 && !req_chunks) return fail(MPT_E_INVALID, "req_chunks must not be NULL");
+        const GLayout L = g_layout(m, n_chunks, nnz);
+        if ((rc = g_check_ws(L, workspace, workspace_bytes))) return rc;
+        return g_prepare(m, n_chunks, nnz, chunk_w, req_off, req_chunks, P, L, (char *)workspace, (hipStream_t)stream,
+                         request_total);
+    });
 }
 
 extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w,
@@ -1414,147 +1416,151 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
                                     int32_t *merge_b, int64_t *gain, int32_t *node_parent, int32_t *order_chunks,
                                     int64_t *savings, void *workspace, size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    int rc = g_check_common(m, n_chunks, nnz);
-    if (rc) return rc;
-    if (!req_off || !node_parent) return fail(MPT_E_INVALID, "req_off and node_parent must not be NULL");
-    if (m > 1 && (!merge_a || !merge_b || !gain)) return fail(MPT_E_INVALID, "merge_a, merge_b and gain must not be NULL");
-    if (n_chunks > 0 && !chunk_w) return fail(MPT_E_INVALID, "chunk_w must not be NULL");
-    if (nnz > 0 && !req_chunks) return fail(MPT_E_INVALID, "req_chunks must not be NULL");
-    const GLayout L = g_layout(m, n_chunks, nnz);
-    if ((rc = g_check_ws(L, workspace, workspace_bytes))) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)workspace;
-    int64_t *V = (int64_t *)(ws + L.V);
-    if ((rc = g_prepare(m, n_chunks, nnz, chunk_w, req_off, req_chunks, V, L, ws, s))) return rc;
-    Rac R{};
-    R.m = m;
-    R.w = chunk_w;
-    R.req_off = req_off;
-    R.sig = (int32_t *)(ws + L.sig);
-    R.sig_slot = (int32_t *)(ws + L.sig_slot);
-    R.sig_len = (int32_t *)(ws + L.sig_len);
-    R.dem = (int32_t *)(ws + L.dem);
-    R.dem_seg = (const uint64_t *)(ws + L.dem_seg);
-    R.V = V;
-    R.best_v = (int64_t *)(ws + L.best_v);
-    R.best_p = (int32_t *)(ws + L.best_p);
-    R.act = (int32_t *)(ws + L.active);
-    R.last = (int32_t *)(ws + L.last);
-    R.touched = (int32_t *)(ws + L.touched);
-    R.resc = (int32_t *)(ws + L.resc);
-    int32_t *r32 = (int32_t *)(ws + L.rec32);
-    int32_t **f32[kRec32] = {&R.ra, &R.rb, &R.rca, &R.rcb, &R.rpos, &R.rdal, &R.rdbl};
-    for (int k = 0; k < kRec32; ++k) *f32[k] = r32 + (size_t)k * m;
-    int64_t *r64 = (int64_t *)(ws + L.rec64);
-    int64_t **f64[kRec64] = {&R.rgain, &R.rdao, &R.rdbo};
-    for (int k = 0; k < kRec64; ++k) *f64[k] = r64 + (size_t)k * m;
-    R.nnz = std::max<int64_t>(nnz, 1);
-    R.live = (int32_t *)(ws + L.live);
-    R.dense = (int64_t *)(ws + L.dense);
-    R.d_off = (int64_t *)(ws + L.d_off);
-    R.d_len = (int32_t *)(ws + L.d_len);
-    R.merge_a = merge_a;
-    R.merge_b = merge_b;
-    R.gain = gain;
-    R.node_parent = node_parent;
-    R.h = (GHeader *)ws;
-    {
-        LaunchScope ls("g_row_best", 8.0 * (double)m * m, s);
-        k_g_row_best<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, V, R.best_v, R.best_p);
-        k_rac_init<<<grid_for(2 * (int64_t)m, 256), 256, 0, s>>>(R);
-    }
-    // Rounds in batches without host synchronisation, until the rest is the
-    // tail's (k_rac_tail, which needs no further look); a round that finds no
-    // pair changes nothing, so the batch's last round tells whether the rounds
-    // are over. The first round merges about a sixth of the clusters, so an
-    // instance whose first round would be the tail's goes there at once.
-    int n_rec = 0;
-    {
-        LaunchScope ls("g_rounds", (double)(m - 1), s);
-        const int g_rec = std::max(1, std::min(4096, (m + 3) / 4));        // waves: one per row
-        const int g_cols = std::max(1, std::min(2048, m / 2 * ((m + kPairTile - 1) / kPairTile)));   // workgroups: one per merge and tile
-        const int g_resc = std::max(1, std::min(m, 2048));                  // workgroups: one per marked row
-        int64_t pairs = (m + 5) / 6;
-        for (int round = 0;;) {
-            const int64_t live = m - n_rec;
-            const bool tail = live <= kTailLive && pairs * live <= kTailWork;
-            if (tail) {
-                k_rac_live<<<1, kChainThreads, 0, s>>>(R);
-                k_rac_dense<<<(unsigned)live, 256, 0, s>>>(R, (int)live);
-                // (one look at every chunk: not worth it for a universe far
-                // larger than the requests)
-                if (round > 0 && n_chunks <= ((int64_t)1 << 20))
-                    k_rac_tidy<<<grid_for(n_chunks, 4, 8192), 4 * kWave, 0, s>>>(R, n_chunks,
-                                                                                (uint64_t *)(ws + L.dem_seg));
-                k_rac_tail<<<1, kTailThreads, 0, s>>>(R, (int)live, round);
-            } else {
-                for (int k = 0; k < 8; ++k, ++round) {
-                    k_rac_pairs_merge<<<g_rec, 4 * kWave, 0, s>>>(R, round);
-                    k_rac_rows<<<g_cols, kRowThreads, 0, s>>>(R, round);
-                    k_rac_rescan<<<g_resc, kRescThreads, 0, s>>>(R, round);
+    return mptlib::guarded(__func__, [&]() -> int {
+        int rc = g_check_common(m, n_chunks, nnz);
+        if (rc) return rc;
+        if (!req_off || !node_parent) return fail(MPT_E_INVALID, "req_off and node_parent must not be NULL");
+        if (m > 1 && (!merge_a || !merge_b || !gain)) return fail(MPT_E_INVALID, "merge_a, merge_b and gain must not be NULL");
+        if (n_chunks > 0 && !chunk_w) return fail(MPT_E_INVALID, "chunk_w must not be NULL");
+        if (nnz > 0 && !req_chunks) return fail(MPT_E_INVALID, "req_chunks must not be NULL");
+        const GLayout L = g_layout(m, n_chunks, nnz);
+        if ((rc = g_check_ws(L, workspace, workspace_bytes))) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        char *ws = (char *)workspace;
+        int64_t *V = (int64_t *)(ws + L.V);
+        if ((rc = g_prepare(m, n_chunks, nnz, chunk_w, req_off, req_chunks, V, L, ws, s))) return rc;
+        Rac R{};
+        R.m = m;
+        R.w = chunk_w;
+        R.req_off = req_off;
+        R.sig = (int32_t *)(ws + L.sig);
+        R.sig_slot = (int32_t *)(ws + L.sig_slot);
+        R.sig_len = (int32_t *)(ws + L.sig_len);
+        R.dem = (int32_t *)(ws + L.dem);
+        R.dem_seg = (const uint64_t *)(ws + L.dem_seg);
+        R.V = V;
+        R.best_v = (int64_t *)(ws + L.best_v);
+        R.best_p = (int32_t *)(ws + L.best_p);
+        R.act = (int32_t *)(ws + L.active);
+        R.last = (int32_t *)(ws + L.last);
+        R.touched = (int32_t *)(ws + L.touched);
+        R.resc = (int32_t *)(ws + L.resc);
+        int32_t *r32 = (int32_t *)(ws + L.rec32);
+        int32_t **f32[kRec32] = {&R.ra, &R.rb, &R.rca, &R.rcb, &R.rpos, &R.rdal, &R.rdbl};
+        for (int k = 0; k < kRec32; ++k) *f32[k] = r32 + (size_t)k * m;
+        int64_t *r64 = (int64_t *)(ws + L.rec64);
+        int64_t **f64[kRec64] = {&R.rgain, &R.rdao, &R.rdbo};
+        for (int k = 0; k < kRec64; ++k) *f64[k] = r64 + (size_t)k * m;
+        R.nnz = std::max<int64_t>(nnz, 1);
+        R.live = (int32_t *)(ws + L.live);
+        R.dense = (int64_t *)(ws + L.dense);
+        R.d_off = (int64_t *)(ws + L.d_off);
+        R.d_len = (int32_t *)(ws + L.d_len);
+        R.merge_a = merge_a;
+        R.merge_b = merge_b;
+        R.gain = gain;
+        R.node_parent = node_parent;
+        R.h = (GHeader *)ws;
+        {
+            LaunchScope ls("g_row_best", 8.0 * (double)m * m, s);
+            k_g_row_best<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, V, R.best_v, R.best_p);
+            k_rac_init<<<grid_for(2 * (int64_t)m, 256), 256, 0, s>>>(R);
+        }
+        // Rounds in batches without host synchronisation, until the rest is the
+        // tail's (k_rac_tail, which needs no further look); a round that finds no
+        // pair changes nothing, so the batch's last round tells whether the rounds
+        // are over. The first round merges about a sixth of the clusters, so an
+        // instance whose first round would be the tail's goes there at once.
+        int n_rec = 0;
+        {
+            LaunchScope ls("g_rounds", (double)(m - 1), s);
+            const int g_rec = std::max(1, std::min(4096, (m + 3) / 4));        // waves: one per row
+            const int g_cols = std::max(1, std::min(2048, m / 2 * ((m + kPairTile - 1) / kPairTile)));   // workgroups: one per merge and tile
+            const int g_resc = std::max(1, std::min(m, 2048));                  // workgroups: one per marked row
+            int64_t pairs = (m + 5) / 6;
+            for (int round = 0;;) {
+                const int64_t live = m - n_rec;
+                const bool tail = live <= kTailLive && pairs * live <= kTailWork;
+                if (tail) {
+                    k_rac_live<<<1, kChainThreads, 0, s>>>(R);
+                    k_rac_dense<<<(unsigned)live, 256, 0, s>>>(R, (int)live);
+                    // (one look at every chunk: not worth it for a universe far
+                    // larger than the requests)
+                    if (round > 0 && n_chunks <= ((int64_t)1 << 20))
+                        k_rac_tidy<<<grid_for(n_chunks, 4, 8192), 4 * kWave, 0, s>>>(R, n_chunks,
+                                                                                    (uint64_t *)(ws + L.dem_seg));
+                    k_rac_tail<<<1, kTailThreads, 0, s>>>(R, (int)live, round);
+                } else {
+                    for (int k = 0; k < 8; ++k, ++round) {
+                        k_rac_pairs_merge<<<g_rec, 4 * kWave, 0, s>>>(R, round);
+                        k_rac_rows<<<g_cols, kRowThreads, 0, s>>>(R, round);
+                        k_rac_rescan<<<g_resc, kRescThreads, 0, s>>>(R, round);
+                    }
                 }
+                MPT_HIP_TRY(hipGetLastError());
+                GHeader hh;
+                MPT_HIP_TRY(mptlib::read_back(&hh, R.h, sizeof hh, s));
+                if (hh.err) return fail(MPT_E_INTERNAL, "greedy rounds left an inconsistent state");   // cannot happen
+                n_rec = std::min(hh.n_rec, m - 1);
+                pairs = hh.last_pairs;
+                if (pairs == 0) break;
+                if (tail || round > m + 32) return fail(MPT_E_INTERNAL, "greedy rounds do not end");   // cannot happen
             }
-            MPT_HIP_TRY(hipGetLastError());
-            GHeader hh;
-            MPT_HIP_TRY(mptlib::read_back(&hh, R.h, sizeof hh, s));
-            if (hh.err) return fail(MPT_E_INTERNAL, "greedy rounds left an inconsistent state");   // cannot happen
-            n_rec = std::min(hh.n_rec, m - 1);
-            pairs = hh.last_pairs;
-            if (pairs == 0) break;
-            if (tail || round > m + 32) return fail(MPT_E_INTERNAL, "greedy rounds do not end");   // cannot happen
         }
-    }
-    {
-        LaunchScope ls("g_sequence", (double)m, s);
-        if (n_rec > 0) {
-            const unsigned tx = (unsigned)((n_rec + kRankThreads - 1) / kRankThreads);
-            const unsigned ty = (unsigned)((n_rec + kRankTileY - 1) / kRankTileY);
-            k_rac_rank<<<dim3(tx, ty), kRankThreads, 0, s>>>(R, n_rec);
-            k_rac_emit<<<grid_for(n_rec, 256), 256, 0, s>>>(R, n_rec);
+        {
+            LaunchScope ls("g_sequence", (double)m, s);
+            if (n_rec > 0) {
+                const unsigned tx = (unsigned)((n_rec + kRankThreads - 1) / kRankThreads);
+                const unsigned ty = (unsigned)((n_rec + kRankTileY - 1) / kRankTileY);
+                k_rac_rank<<<dim3(tx, ty), kRankThreads, 0, s>>>(R, n_rec);
+                k_rac_emit<<<grid_for(n_rec, 256), 256, 0, s>>>(R, n_rec);
+            }
+            k_rac_chain<<<1, kChainThreads, 0, s>>>(R, n_rec);
         }
-        k_rac_chain<<<1, kChainThreads, 0, s>>>(R, n_rec);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    if (order_chunks) {
-        LaunchScope ls("g_orders", 4.0 * (double)nnz, s);
-        k_g_orders<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, nnz, req_off, node_parent, R.sig, R.d_off, R.d_len,
-                                                     order_chunks, n_rec, R.h);
         MPT_HIP_TRY(hipGetLastError());
-    }
-    return g_read_errors(R.h, s, nullptr, nullptr, savings);
+        if (order_chunks) {
+            LaunchScope ls("g_orders", 4.0 * (double)nnz, s);
+            k_g_orders<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, nnz, req_off, node_parent, R.sig, R.d_off, R.d_len,
+                                                         order_chunks, n_rec, R.h);
+            MPT_HIP_TRY(hipGetLastError());
+        }
+        return g_read_errors(R.h, s, nullptr, nullptr, savings);
+    });
 }
 
 extern "C" int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_weight, void *workspace,
                                        size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    if (m < 1 || m > MPT_GREEDY_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_GREEDY_MAX_M);
-    if (!P || !mst_weight) return fail(MPT_E_INVALID, "P and mst_weight must not be NULL");
-    if (!workspace) return fail(MPT_E_WORKSPACE, "workspace is NULL");
-    if (((uintptr_t)workspace & 255u) != 0) return fail(MPT_E_WORKSPACE, "workspace is not 256-byte aligned");
-    // header, then the vertices' components, best weights and edges and the
-    // components' best weights (24 m bytes of the documented 32 m)
-    const size_t mm = (size_t)m, a4 = align256(4 * mm), a8 = align256(8 * mm);
-    const size_t off_comp = align256(sizeof(GHeader)), off_vw = off_comp + a4, off_ve = off_vw + a8,
-                 off_cw = off_ve + a4, need = off_comp + 4 * a4 + 2 * a8;
-    if (workspace_bytes < need) return fail(MPT_E_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
-    hipStream_t s = (hipStream_t)stream;
-    GHeader *h = (GHeader *)workspace;
-    char *ws = (char *)workspace;
-    int32_t *comp = (int32_t *)(ws + off_comp);
-    int64_t *vw = (int64_t *)(ws + off_vw), *cw = (int64_t *)(ws + off_cw);
-    uint32_t *ve = (uint32_t *)(ws + off_ve);
-    int rounds = 0;
-    while ((1 << rounds) < m) ++rounds;
-    const int gv = grid_for(m, 256);
-    k_bv_init<<<gv, 256, 0, s>>>(m, comp, vw, cw, h);
-    for (int r = 0; r < rounds; ++r) {
-        LaunchScope ls("g_boruvka", 8.0 * (double)m * m, s);
-        k_bv_vertex<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, P, comp, vw, ve, cw, h);
-        k_bv_merge<<<1, kBvThreads, 0, s>>>(m, comp, vw, ve, cw, h);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    unsigned long long total = 0;
-    MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
-    *mst_weight = (int64_t)total;
-    return MPT_OK;
+    return mptlib::guarded(__func__, [&]() -> int {
+        if (m < 1 || m > MPT_GREEDY_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_GREEDY_MAX_M);
+        if (!P || !mst_weight) return fail(MPT_E_INVALID, "P and mst_weight must not be NULL");
+        if (!workspace) return fail(MPT_E_WORKSPACE, "workspace is NULL");
+        if (((uintptr_t)workspace & 255u) != 0) return fail(MPT_E_WORKSPACE, "workspace is not 256-byte aligned");
+        // header, then the vertices' components, best weights and edges and the
+        // components' best weights (24 m bytes of the documented 32 m)
+        const size_t mm = (size_t)m, a4 = align256(4 * mm), a8 = align256(8 * mm);
+        const size_t off_comp = align256(sizeof(GHeader)), off_vw = off_comp + a4, off_ve = off_vw + a8,
+                     off_cw = off_ve + a4, need = off_comp + 4 * a4 + 2 * a8;
+        if (workspace_bytes < need) return fail(MPT_E_WORKSPACE, "workspace has %zu bytes, needs %zu", workspace_bytes, need);
+        hipStream_t s = (hipStream_t)stream;
+        GHeader *h = (GHeader *)workspace;
+        char *ws = (char *)workspace;
+        int32_t *comp = (int32_t *)(ws + off_comp);
+        int64_t *vw = (int64_t *)(ws + off_vw), *cw = (int64_t *)(ws + off_cw);
+        uint32_t *ve = (uint32_t *)(ws + off_ve);
+        int rounds = 0;
+        while ((1 << rounds) < m) ++rounds;
+        const int gv = grid_for(m, 256);
+        k_bv_init<<<gv, 256, 0, s>>>(m, comp, vw, cw, h);
+        for (int r = 0; r < rounds; ++r) {
+            LaunchScope ls("g_boruvka", 8.0 * (double)m * m, s);
+            k_bv_vertex<<<(m + 3) / 4, 4 * kWave, 0, s>>>(m, P, comp, vw, ve, cw, h);
+            k_bv_merge<<<1, kBvThreads, 0, s>>>(m, comp, vw, ve, cw, h);
+        }
+        MPT_HIP_TRY(hipGetLastError());
+        unsigned long long total = 0;
+        MPT_HIP_TRY(mptlib::read_back(&total, &h->total, sizeof total, s));
+        *mst_weight = (int64_t)total;
+        return MPT_OK;
+    });
 }

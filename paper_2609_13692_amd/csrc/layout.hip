@@ -894,61 +894,65 @@ extern "C" int mpt_global_order_layout(int m, int64_t n_chunks, int64_t nnz, con
                                        const int32_t *req_chunks, int order_kind, int32_t *seqs, void *workspace,
                                        size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    int rc = l_check(m, n_chunks, nnz);
-    if (rc) return rc;
-    if (order_kind != MPT_ORDER_ID && order_kind != MPT_ORDER_POPULARITY)
-        return fail(MPT_E_INVALID, "order_kind = %d is not MPT_ORDER_ID or MPT_ORDER_POPULARITY", order_kind);
-    if (!req_off || (nnz > 0 && (!req_chunks || !seqs))) return fail(MPT_E_INVALID, "req_off, req_chunks and seqs must not be NULL");
-    const LLayout L = l_layout(m, n_chunks, nnz, 0);
-    if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)workspace;
-    LHeader *h = (LHeader *)ws;
-    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
-    int32_t *rank = (int32_t *)(ws + L.crank), *inv = (int32_t *)(ws + L.cinv);
-    const bool popular = order_kind == MPT_ORDER_POPULARITY;
-    LaunchScope ls("l_global_order", (double)nnz, s);
-    k_l_begin<<<grid_for(popular ? n_chunks : 1, 256), 256, 0, s>>>(h, rank, popular ? n_chunks : 0);
-    k_l_check<<<grid_for(std::max<int64_t>(nnz, m), 2 * kCheckThreads, 1024), kCheckThreads, 0, s>>>(
-        m, nnz, n_chunks, req_off, req_chunks, nullptr, h);
-    if (nnz > 0) {
-        if (popular) {
-            // (count, id) keys of the chunks
-            k_l_count<<<grid_for(nnz, kCountSlice, 1024), kCountThreads, 0, s>>>(nnz, req_chunks, rank, h);
-            k_l_pop_keys<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, keys);
-            if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
-            k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
+    return mptlib::guarded(__func__, [&]() -> int {
+        int rc = l_check(m, n_chunks, nnz);
+        if (rc) return rc;
+        if (order_kind != MPT_ORDER_ID && order_kind != MPT_ORDER_POPULARITY)
+            return fail(MPT_E_INVALID, "order_kind = %d is not MPT_ORDER_ID or MPT_ORDER_POPULARITY", order_kind);
+        if (!req_off || (nnz > 0 && (!req_chunks || !seqs))) return fail(MPT_E_INVALID, "req_off, req_chunks and seqs must not be NULL");
+        const LLayout L = l_layout(m, n_chunks, nnz, 0);
+        if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        char *ws = (char *)workspace;
+        LHeader *h = (LHeader *)ws;
+        uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
+        int32_t *rank = (int32_t *)(ws + L.crank), *inv = (int32_t *)(ws + L.cinv);
+        const bool popular = order_kind == MPT_ORDER_POPULARITY;
+        LaunchScope ls("l_global_order", (double)nnz, s);
+        k_l_begin<<<grid_for(popular ? n_chunks : 1, 256), 256, 0, s>>>(h, rank, popular ? n_chunks : 0);
+        k_l_check<<<grid_for(std::max<int64_t>(nnz, m), 2 * kCheckThreads, 1024), kCheckThreads, 0, s>>>(
+            m, nnz, n_chunks, req_off, req_chunks, nullptr, h);
+        if (nnz > 0) {
+            if (popular) {
+                // (count, id) keys of the chunks
+                k_l_count<<<grid_for(nnz, kCountSlice, 1024), kCountThreads, 0, s>>>(nnz, req_chunks, rank, h);
+                k_l_pop_keys<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, keys);
+                if ((rc = sort_keys(keys, keys2, n_chunks, s, &sorted))) return rc;
+                k_l_pop_rank<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, sorted, rank);
+            }
+            // (workgroups for requests of more than kSegMax chunks, whose length the
+            // host does not know; four requests each took 217 us for 100 of 512
+            // chunks, where a wave per request does not notice the difference)
+            k_l_layout_short<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs, h);
         }
-        // (workgroups for requests of more than kSegMax chunks, whose length the
-        // host does not know; four requests each took 217 us for 100 of 512
-        // chunks, where a wave per request does not notice the difference)
-        k_l_layout_short<<<grid_for(m, 1, 4096), kListThreads, 0, s>>>(m, req_off, req_chunks, rank, order_kind, seqs, h);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    int64_t max_len = 0;
-    if ((rc = l_read_errors(h, s, &max_len))) return rc;
-    if (max_len <= kListMax) return MPT_OK;
-    if (popular) k_l_inverse<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, inv);
-    k_l_layout_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, rank, order_kind, keys);
-    if ((rc = sort_keys(keys, keys2, nnz, s, &sorted))) return rc;
-    k_l_layout_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, inv, order_kind, seqs);
-    MPT_HIP_TRY(hipGetLastError());
-    return MPT_OK;
+        MPT_HIP_TRY(hipGetLastError());
+        int64_t max_len = 0;
+        if ((rc = l_read_errors(h, s, &max_len))) return rc;
+        if (max_len <= kListMax) return MPT_OK;
+        if (popular) k_l_inverse<<<grid_for(n_chunks, 256), 256, 0, s>>>(n_chunks, rank, inv);
+        k_l_layout_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, nnz, req_off, req_chunks, rank, order_kind, keys);
+        if ((rc = sort_keys(keys, keys2, nnz, s, &sorted))) return rc;
+        k_l_layout_out<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, sorted, inv, order_kind, seqs);
+        MPT_HIP_TRY(hipGetLastError());
+        return MPT_OK;
+    });
 }
 
 extern "C" int mpt_layout_cost(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const int64_t *seq_off,
                                const int32_t *seqs, int32_t *dfs_order, int64_t *trie_cost, void *workspace,
                                size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    int rc = l_check(m, n_chunks, nnz);
-    if (rc) return rc;
-    if (!seq_off || !trie_cost || (nnz > 0 && !seqs) || (n_chunks > 0 && !chunk_w))
-        return fail(MPT_E_INVALID, "seq_off, seqs, chunk_w and trie_cost must not be NULL");
-    const LLayout L = l_layout(m, n_chunks, nnz, 0);
-    if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)workspace;
-    return l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, false, dfs_order, trie_cost);
+    return mptlib::guarded(__func__, [&]() -> int {
+        int rc = l_check(m, n_chunks, nnz);
+        if (rc) return rc;
+        if (!seq_off || !trie_cost || (nnz > 0 && !seqs) || (n_chunks > 0 && !chunk_w))
+            return fail(MPT_E_INVALID, "seq_off, seqs, chunk_w and trie_cost must not be NULL");
+        const LLayout L = l_layout(m, n_chunks, nnz, 0);
+        if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        char *ws = (char *)workspace;
+        return l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, false, dfs_order, trie_cost);
+    });
 }
 
 extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w,
@@ -956,99 +960,101 @@ extern "C" int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const in
                                   const int64_t *windows, const int64_t *capacities, int64_t *costs,
                                   int64_t *trie_cost, void *workspace, size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    int rc = l_check(m, n_chunks, nnz);
-    if (rc) return rc;
-    if (n_configs < 1 || n_configs > MPT_CACHE_MAX_CONFIGS)
-        return fail(MPT_E_INVALID, "n_configs = %d outside [1, %d]", n_configs, MPT_CACHE_MAX_CONFIGS);
-    if (!seq_off || !windows || !capacities || !costs || (nnz > 0 && !seqs) || (n_chunks > 0 && !chunk_w))
-        return fail(MPT_E_INVALID, "seq_off, seqs, chunk_w, windows, capacities and costs must not be NULL");
-    for (int c = 0; c < n_configs; ++c)
-        if (capacities[c] < 0) return fail(MPT_E_INVALID, "capacity %d is negative", c);
-    const LLayout L = l_layout(m, n_chunks, nnz, n_configs);
-    if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)workspace;
-    int64_t tc = 0;
-    if ((rc = l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, true, nullptr, &tc))) return rc;
-    if (trie_cost) *trie_cost = tc;
-    // configurations: window <= 0 or > m means the whole stream. Equal
-    // windows share one schedule (and log); cfg_off / cfg_list list the
-    // configurations of every schedule.
-    std::vector<int64_t> win;
-    std::vector<int> sched_of(n_configs);
-    for (int c = 0; c < n_configs; ++c) {
-        const int64_t wc = (windows[c] <= 0 || windows[c] > m) ? m : windows[c];
-        int d = 0;
-        while (d < (int)win.size() && win[d] != wc) ++d;
-        if (d == (int)win.size()) win.push_back(wc);
-        sched_of[c] = d;
-    }
-    const int n_sched = (int)win.size();
-    std::vector<int32_t> cfg_off(n_sched + 1, 0), cfg_list;
-    for (int d = 0; d < n_sched; ++d) {
+    return mptlib::guarded(__func__, [&]() -> int {
+        int rc = l_check(m, n_chunks, nnz);
+        if (rc) return rc;
+        if (n_configs < 1 || n_configs > MPT_CACHE_MAX_CONFIGS)
+            return fail(MPT_E_INVALID, "n_configs = %d outside [1, %d]", n_configs, MPT_CACHE_MAX_CONFIGS);
+        if (!seq_off || !windows || !capacities || !costs || (nnz > 0 && !seqs) || (n_chunks > 0 && !chunk_w))
+            return fail(MPT_E_INVALID, "seq_off, seqs, chunk_w, windows, capacities and costs must not be NULL");
         for (int c = 0; c < n_configs; ++c)
-            if (sched_of[c] == d) cfg_list.push_back(c);
-        cfg_off[d + 1] = (int32_t)cfg_list.size();
-    }
-    // windows, capacities, offsets and lists go over in one copy: the four
-    // arrays lie one after the other in the workspace
-    int64_t *dev_win = (int64_t *)(ws + L.cfg_win), *dev_capacity = (int64_t *)(ws + L.cfg_cap);
-    int32_t *dev_cfg_off = (int32_t *)(ws + L.cfg_off), *dev_cfg_list = (int32_t *)(ws + L.cfg_list);
-    std::vector<char> image(L.cfg_list - L.cfg_win + sizeof(int32_t) * (size_t)n_configs);
-    std::memcpy(image.data(), win.data(), sizeof(int64_t) * (size_t)n_sched);
-    std::memcpy(image.data() + (L.cfg_cap - L.cfg_win), capacities, sizeof(int64_t) * (size_t)n_configs);
-    std::memcpy(image.data() + (L.cfg_off - L.cfg_win), cfg_off.data(), sizeof(int32_t) * (size_t)(n_sched + 1));
-    std::memcpy(image.data() + (L.cfg_list - L.cfg_win), cfg_list.data(), sizeof(int32_t) * (size_t)n_configs);
-    MPT_HIP_TRY(hipMemcpyAsync(dev_win, image.data(), image.size(), hipMemcpyHostToDevice, s));
-    uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
-    int32_t *sched = (int32_t *)(ws + L.sched), *logs = (int32_t *)(ws + L.logs);
-    int32_t *acc_start = (int32_t *)(ws + L.acc_start), *prev = (int32_t *)(ws + L.prev), *next = (int32_t *)(ws + L.next);
-    int64_t *log_off = (int64_t *)(ws + L.log_off), *wsuf = (int64_t *)(ws + L.wsuf);
-    const int32_t *ord = (const int32_t *)(ws + L.ord), *rank = (const int32_t *)(ws + L.rank);
-    {
-        LaunchScope ls("l_schedules", (double)n_sched * m, s);
-        const int64_t sn = (int64_t)n_sched * m;
-        k_l_sched_keys<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, dev_win, rank, keys);
-        if ((rc = sort_keys(keys, keys2, sn, s, &sorted))) return rc;
-        k_l_sched_out<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, sorted, ord, seq_off, sched,
-                                                                          log_off);
-        k_l_log_scan<<<n_sched, 1024, 0, s>>>(m, log_off);
-        if (nnz > 0)
-            k_l_logs<<<grid_for((int64_t)n_sched * m, 256), 256, 0, s>>>(m, n_sched, nnz, sched, log_off, seq_off,
-                                                                         (const int32_t *)(ws + L.pn), logs, acc_start);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    int64_t *dev_costs = (int64_t *)(ws + L.costs);
-    k_l_fill_u64<<<1, 256, 0, s>>>((uint64_t *)dev_costs, n_configs, 0ull);
-    if (nnz > 0) {
-        {
-            // previous and next access of every log entry: a sort of
-            // (schedule, node, position) keys, as many schedules per sort as
-            // the 63 key bits hold
-            LaunchScope ls("l_reuse", (double)n_sched * nnz, s);
-            auto bits = [](int64_t n) { int b = 1; while (b < 62 && ((int64_t)1 << b) < n) ++b; return b; };
-            const int be = bits(nnz), bn = be;            // (nnz bounds the node count)
-            const int gb = 63 - be - bn;                  // >= 1: nnz stays below 2^31
-            const int group = gb >= 8 ? n_sched : std::min(n_sched, 1 << gb);
-            for (int d0 = 0; d0 < n_sched; d0 += group) {
-                const int nd = std::min(group, n_sched - d0);
-                const int64_t an = (int64_t)nd * nnz;
-                k_l_acc_keys<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, bn, logs, keys);
-                if ((rc = sort_keys(keys, keys2, an, s, &sorted))) return rc;
-                k_l_prev_next<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, sorted, prev, next);
-            }
+            if (capacities[c] < 0) return fail(MPT_E_INVALID, "capacity %d is negative", c);
+        const LLayout L = l_layout(m, n_chunks, nnz, n_configs);
+        if ((rc = l_check_ws(L, workspace, workspace_bytes))) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        char *ws = (char *)workspace;
+        int64_t tc = 0;
+        if ((rc = l_prepare(m, n_chunks, nnz, chunk_w, seq_off, seqs, L, ws, s, true, nullptr, &tc))) return rc;
+        if (trie_cost) *trie_cost = tc;
+        // configurations: window <= 0 or > m means the whole stream. Equal
+        // windows share one schedule (and log); cfg_off / cfg_list list the
+        // configurations of every schedule.
+        std::vector<int64_t> win;
+        std::vector<int> sched_of(n_configs);
+        for (int c = 0; c < n_configs; ++c) {
+            const int64_t wc = (windows[c] <= 0 || windows[c] > m) ? m : windows[c];
+            int d = 0;
+            while (d < (int)win.size() && win[d] != wc) ++d;
+            if (d == (int)win.size()) win.push_back(wc);
+            sched_of[c] = d;
         }
-        LaunchScope ls("l_simulate", (double)n_configs * nnz, s);
-        const int64_t nblk = (nnz + kBigBlock - 1) / kBigBlock;
-        int32_t *snext = (int32_t *)(ws + L.snext), *bnext = (int32_t *)(ws + L.bnext);
-        int64_t *ssum = (int64_t *)(ws + L.ssum), *bsum = (int64_t *)(ws + L.bsum);
-        k_l_stack_blocks<<<(unsigned)(n_sched * nblk), kStackThreads, 0, s>>>(
-            nnz, nblk, logs, (const int64_t *)(ws + L.nw), next, wsuf, snext, ssum, bnext, bsum);
-        k_l_bill<<<dim3((unsigned)((nnz + kBillThreads - 1) / kBillThreads), (unsigned)n_sched), kBillThreads, 0, s>>>(
-            nnz, nblk, prev, next, acc_start, wsuf, snext, ssum, bnext, bsum, dev_cfg_off, dev_cfg_list, dev_capacity,
-            (unsigned long long *)dev_costs);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    MPT_HIP_TRY(mptlib::read_back(costs, dev_costs, sizeof(int64_t) * n_configs, s));
-    return MPT_OK;
+        const int n_sched = (int)win.size();
+        std::vector<int32_t> cfg_off(n_sched + 1, 0), cfg_list;
+        for (int d = 0; d < n_sched; ++d) {
+            for (int c = 0; c < n_configs; ++c)
+                if (sched_of[c] == d) cfg_list.push_back(c);
+            cfg_off[d + 1] = (int32_t)cfg_list.size();
+        }
+        // windows, capacities, offsets and lists go over in one copy: the four
+        // arrays lie one after the other in the workspace
+        int64_t *dev_win = (int64_t *)(ws + L.cfg_win), *dev_capacity = (int64_t *)(ws + L.cfg_cap);
+        int32_t *dev_cfg_off = (int32_t *)(ws + L.cfg_off), *dev_cfg_list = (int32_t *)(ws + L.cfg_list);
+        std::vector<char> image(L.cfg_list - L.cfg_win + sizeof(int32_t) * (size_t)n_configs);
+        std::memcpy(image.data(), win.data(), sizeof(int64_t) * (size_t)n_sched);
+        std::memcpy(image.data() + (L.cfg_cap - L.cfg_win), capacities, sizeof(int64_t) * (size_t)n_configs);
+        std::memcpy(image.data() + (L.cfg_off - L.cfg_win), cfg_off.data(), sizeof(int32_t) * (size_t)(n_sched + 1));
+        std::memcpy(image.data() + (L.cfg_list - L.cfg_win), cfg_list.data(), sizeof(int32_t) * (size_t)n_configs);
+        MPT_HIP_TRY(hipMemcpyAsync(dev_win, image.data(), image.size(), hipMemcpyHostToDevice, s));
+        uint64_t *keys = (uint64_t *)(ws + L.keys), *keys2 = (uint64_t *)(ws + L.keys2), *sorted = nullptr;
+        int32_t *sched = (int32_t *)(ws + L.sched), *logs = (int32_t *)(ws + L.logs);
+        int32_t *acc_start = (int32_t *)(ws + L.acc_start), *prev = (int32_t *)(ws + L.prev), *next = (int32_t *)(ws + L.next);
+        int64_t *log_off = (int64_t *)(ws + L.log_off), *wsuf = (int64_t *)(ws + L.wsuf);
+        const int32_t *ord = (const int32_t *)(ws + L.ord), *rank = (const int32_t *)(ws + L.rank);
+        {
+            LaunchScope ls("l_schedules", (double)n_sched * m, s);
+            const int64_t sn = (int64_t)n_sched * m;
+            k_l_sched_keys<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, dev_win, rank, keys);
+            if ((rc = sort_keys(keys, keys2, sn, s, &sorted))) return rc;
+            k_l_sched_out<<<grid_for(sn, 256), 256, 0, s>>>(m, n_sched, sorted, ord, seq_off, sched,
+                                                                              log_off);
+            k_l_log_scan<<<n_sched, 1024, 0, s>>>(m, log_off);
+            if (nnz > 0)
+                k_l_logs<<<grid_for((int64_t)n_sched * m, 256), 256, 0, s>>>(m, n_sched, nnz, sched, log_off, seq_off,
+                                                                             (const int32_t *)(ws + L.pn), logs, acc_start);
+        }
+        MPT_HIP_TRY(hipGetLastError());
+        int64_t *dev_costs = (int64_t *)(ws + L.costs);
+        k_l_fill_u64<<<1, 256, 0, s>>>((uint64_t *)dev_costs, n_configs, 0ull);
+        if (nnz > 0) {
+            {
+                // previous and next access of every log entry: a sort of
+                // (schedule, node, position) keys, as many schedules per sort as
+                // the 63 key bits hold
+                LaunchScope ls("l_reuse", (double)n_sched * nnz, s);
+                auto bits = [](int64_t n) { int b = 1; while (b < 62 && ((int64_t)1 << b) < n) ++b; return b; };
+                const int be = bits(nnz), bn = be;            // (nnz bounds the node count)
+                const int gb = 63 - be - bn;                  // >= 1: nnz stays below 2^31
+                const int group = gb >= 8 ? n_sched : std::min(n_sched, 1 << gb);
+                for (int d0 = 0; d0 < n_sched; d0 += group) {
+                    const int nd = std::min(group, n_sched - d0);
+                    const int64_t an = (int64_t)nd * nnz;
+                    k_l_acc_keys<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, bn, logs, keys);
+                    if ((rc = sort_keys(keys, keys2, an, s, &sorted))) return rc;
+                    k_l_prev_next<<<grid_for(an, 256), 256, 0, s>>>(nnz, d0, nd, be, sorted, prev, next);
+                }
+            }
+            LaunchScope ls("l_simulate", (double)n_configs * nnz, s);
+            const int64_t nblk = (nnz + kBigBlock - 1) / kBigBlock;
+            int32_t *snext = (int32_t *)(ws + L.snext), *bnext = (int32_t *)(ws + L.bnext);
+            int64_t *ssum = (int64_t *)(ws + L.ssum), *bsum = (int64_t *)(ws + L.bsum);
+            k_l_stack_blocks<<<(unsigned)(n_sched * nblk), kStackThreads, 0, s>>>(
+                nnz, nblk, logs, (const int64_t *)(ws + L.nw), next, wsuf, snext, ssum, bnext, bsum);
+            k_l_bill<<<dim3((unsigned)((nnz + kBillThreads - 1) / kBillThreads), (unsigned)n_sched), kBillThreads, 0, s>>>(
+                nnz, nblk, prev, next, acc_start, wsuf, snext, ssum, bnext, bsum, dev_cfg_off, dev_cfg_list, dev_capacity,
+                (unsigned long long *)dev_costs);
+        }
+        MPT_HIP_TRY(hipGetLastError());
+        MPT_HIP_TRY(mptlib::read_back(costs, dev_costs, sizeof(int64_t) * n_configs, s));
+        return MPT_OK;
+    });
 }

@@ -3743,41 +3743,45 @@ using mptlib::ProfRecord;
 extern "C" int mpt_profile_begin(void) { return mpt_profile_begin_prefix(""); }
 
 extern "C" int mpt_profile_begin_prefix(const char *prefix) {
-    std::lock_guard<std::mutex> g(g_prof.mu);
-    for (auto &r : g_prof.recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
-    g_prof.recs.clear();
-    g_prof.prefix = prefix ? prefix : "";
-    g_prof.on = true;
-    return MPT_OK;
+    return mptlib::guarded(__func__, [&]() -> int {
+        std::lock_guard<std::mutex> g(g_prof.mu);
+        for (auto &r : g_prof.recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
+        g_prof.recs.clear();
+        g_prof.prefix = prefix ? prefix : "";
+        g_prof.on = true;
+        return MPT_OK;
+    });
 }
 
 extern "C" int mpt_profile_end(mpt_profile_row *rows, int max_entries) {
-    std::vector<ProfRecord> recs;
-    {
-        std::lock_guard<std::mutex> g(g_prof.mu);
-        g_prof.on = false;
-        recs.swap(g_prof.recs);
-    }
-    std::vector<mpt_profile_row> agg;
-    int status = MPT_OK;
-    for (auto &r : recs) {
-        float ms = 0.f;
-        if (hipEventSynchronize(r.b) != hipSuccess || hipEventElapsedTime(&ms, r.a, r.b) != hipSuccess)
-            status = fail(MPT_E_DEVICE, "profiling event failed");
-        (void)hipEventDestroy(r.a);
-        (void)hipEventDestroy(r.b);
-        auto it = std::find_if(agg.begin(), agg.end(), [&](const mpt_profile_row &x) { return r.name == x.kernel; });
-        if (it == agg.end()) {
-            mpt_profile_row row{};
-            snprintf(row.kernel, sizeof row.kernel, "%s", r.name.c_str());
-            agg.push_back(row);
-            it = agg.end() - 1;
+    return mptlib::guarded(__func__, [&]() -> int {
+        std::vector<ProfRecord> recs;
+        {
+            std::lock_guard<std::mutex> g(g_prof.mu);
+            g_prof.on = false;
+            recs.swap(g_prof.recs);
         }
-        it->launches += 1;
-        it->total_ms += ms;
-        it->work += r.work;
-    }
-    if (status != MPT_OK) return status;
-    for (int i = 0; i < (int)agg.size() && i < max_entries; ++i) rows[i] = agg[i];
-    return (int)agg.size();
+        std::vector<mpt_profile_row> agg;
+        int status = MPT_OK;
+        for (auto &r : recs) {
+            float ms = 0.f;
+            if (hipEventSynchronize(r.b) != hipSuccess || hipEventElapsedTime(&ms, r.a, r.b) != hipSuccess)
+                status = fail(MPT_E_DEVICE, "profiling event failed");
+            (void)hipEventDestroy(r.a);
+            (void)hipEventDestroy(r.b);
+            auto it = std::find_if(agg.begin(), agg.end(), [&](const mpt_profile_row &x) { return r.name == x.kernel; });
+            if (it == agg.end()) {
+                mpt_profile_row row{};
+                snprintf(row.kernel, sizeof row.kernel, "%s", r.name.c_str());
+                agg.push_back(row);
+                it = agg.end() - 1;
+            }
+            it->launches += 1;
+            it->total_ms += ms;
+            it->work += r.work;
+        }
+        if (status != MPT_OK) return status;
+        for (int i = 0; i < (int)agg.size() && i < max_entries; ++i) rows[i] = agg[i];
+        return (int)agg.size();
+    });
 }

@@ -251,49 +251,51 @@ extern "C" int mpt_pinned_split(int m, int64_t n_chunks, int64_t nnz, const int6
                                 int32_t *free_chunks, int *n_distinct, void *workspace, size_t workspace_bytes,
                                 void *stream) {
     mptlib::clear_error();
-    if (m < 1 || m > MPT_LAYOUT_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_LAYOUT_MAX_M);
-    if (n_chunks < 0 || n_chunks > MPT_MAX_CHUNKS || nnz < 0 || nnz > (int64_t)INT32_MAX)
-        return fail(MPT_E_INVALID, "n_chunks or nnz out of range");
-    if (t < 0) return fail(MPT_E_INVALID, "t = %d is negative", t);
-    if (!req_off || !dmap || !free_off || !n_distinct || (nnz > 0 && (!req_chunks || !free_chunks)))
-        return fail(MPT_E_INVALID, "req_off, req_chunks, dmap, free_off, free_chunks and n_distinct must not be NULL");
-    const PLayout L = p_layout(m, nnz);
-    int rc = p_check_ws(L, workspace, workspace_bytes);
-    if (rc) return rc;
-    hipStream_t s = (hipStream_t)stream;
-    char *ws = (char *)workspace;
-    PHeader *h = (PHeader *)ws;
-    k_p_header<<<grid_for(m, 256), 256, 0, s>>>(h, (int32_t *)(ws + L.gstart), m);
-    k_p_check<<<grid_for(std::max<int64_t>(nnz, m), 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, h);
-    MPT_HIP_TRY(hipGetLastError());
-    if ((rc = p_read(h, s, nullptr))) return rc;
-    uint64_t *keys = (uint64_t *)(ws + L.keys);
-    int64_t *rf_off = (int64_t *)(ws + L.rf_off), *rep = (int64_t *)(ws + L.rep), *roff = (int64_t *)(ws + L.roff);
-    int32_t *rf_chunks = (int32_t *)(ws + L.rf_chunks), *ord = (int32_t *)(ws + L.ord);
-    int32_t *gstart = (int32_t *)(ws + L.gstart), *lead = (int32_t *)(ws + L.lead);
-    {
-        LaunchScope ls("p_split", (double)nnz, s);
-        k_p_counts<<<grid_for(m, 256), 256, 0, s>>>(m, t, req_off, rf_off);
-        k_p_scan<<<1, 1024, 0, s>>>(m, rf_off);
-        if (nnz > 0) {
-            uint64_t *sorted = nullptr;
-            k_p_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, t, nnz, req_off, req_chunks, keys);
-            if ((rc = sort_keys(keys, (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
-            k_p_free_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(m, rf_off, sorted, rf_chunks);
+    return mptlib::guarded(__func__, [&]() -> int {
+        if (m < 1 || m > MPT_LAYOUT_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_LAYOUT_MAX_M);
+        if (n_chunks < 0 || n_chunks > MPT_MAX_CHUNKS || nnz < 0 || nnz > (int64_t)INT32_MAX)
+            return fail(MPT_E_INVALID, "n_chunks or nnz out of range");
+        if (t < 0) return fail(MPT_E_INVALID, "t = %d is negative", t);
+        if (!req_off || !dmap || !free_off || !n_distinct || (nnz > 0 && (!req_chunks || !free_chunks)))
+            return fail(MPT_E_INVALID, "req_off, req_chunks, dmap, free_off, free_chunks and n_distinct must not be NULL");
+        const PLayout L = p_layout(m, nnz);
+        int rc = p_check_ws(L, workspace, workspace_bytes);
+        if (rc) return rc;
+        hipStream_t s = (hipStream_t)stream;
+        char *ws = (char *)workspace;
+        PHeader *h = (PHeader *)ws;
+        k_p_header<<<grid_for(m, 256), 256, 0, s>>>(h, (int32_t *)(ws + L.gstart), m);
+        k_p_check<<<grid_for(std::max<int64_t>(nnz, m), 256), 256, 0, s>>>(m, n_chunks, nnz, req_off, req_chunks, h);
+        MPT_HIP_TRY(hipGetLastError());
+        if ((rc = p_read(h, s, nullptr))) return rc;
+        uint64_t *keys = (uint64_t *)(ws + L.keys);
+        int64_t *rf_off = (int64_t *)(ws + L.rf_off), *rep = (int64_t *)(ws + L.rep), *roff = (int64_t *)(ws + L.roff);
+        int32_t *rf_chunks = (int32_t *)(ws + L.rf_chunks), *ord = (int32_t *)(ws + L.ord);
+        int32_t *gstart = (int32_t *)(ws + L.gstart), *lead = (int32_t *)(ws + L.lead);
+        {
+            LaunchScope ls("p_split", (double)nnz, s);
+            k_p_counts<<<grid_for(m, 256), 256, 0, s>>>(m, t, req_off, rf_off);
+            k_p_scan<<<1, 1024, 0, s>>>(m, rf_off);
+            if (nnz > 0) {
+                uint64_t *sorted = nullptr;
+                k_p_keys<<<grid_for(nnz, 256), 256, 0, s>>>(m, t, nnz, req_off, req_chunks, keys);
+                if ((rc = sort_keys(keys, (uint64_t *)(ws + L.keys2), nnz, s, &sorted))) return rc;
+                k_p_free_chunks<<<grid_for(nnz, 256), 256, 0, s>>>(m, rf_off, sorted, rf_chunks);
+            }
+            // (gstart, zeroed with the header and written after the sort, is its scratch)
+            if ((rc = sort_requests(ord, gstart, nullptr, m, rf_off, rf_chunks, ws + L.recs, nullptr, s))) return rc;
+            k_p_group_starts<<<grid_for(m, 256), 256, 0, s>>>(m, ord, rf_off, rf_chunks, gstart);
+            k_p_max_scan<<<1, 1024, 0, s>>>(m, gstart);
+            k_p_leaders<<<grid_for(m, 256), 256, 0, s>>>(m, ord, gstart, rf_off, lead, rep, roff);
+            // exclusive positions: rep[i] = number of representatives before i
+            k_p_scan<<<1, 1024, 0, s>>>(m, rep);
+            k_p_scan<<<1, 1024, 0, s>>>(m, roff);
+            k_p_distinct<<<grid_for(m, 256), 256, 0, s>>>(m, lead, rep, roff, rf_off, rf_chunks, dmap, free_off,
+                                                          free_chunks, h);
         }
-        // (gstart, zeroed with the header and written after the sort, is its scratch)
-        if ((rc = sort_requests(ord, gstart, nullptr, m, rf_off, rf_chunks, ws + L.recs, nullptr, s))) return rc;
-        k_p_group_starts<<<grid_for(m, 256), 256, 0, s>>>(m, ord, rf_off, rf_chunks, gstart);
-        k_p_max_scan<<<1, 1024, 0, s>>>(m, gstart);
-        k_p_leaders<<<grid_for(m, 256), 256, 0, s>>>(m, ord, gstart, rf_off, lead, rep, roff);
-        // exclusive positions: rep[i] = number of representatives before i
-        k_p_scan<<<1, 1024, 0, s>>>(m, rep);
-        k_p_scan<<<1, 1024, 0, s>>>(m, roff);
-        k_p_distinct<<<grid_for(m, 256), 256, 0, s>>>(m, lead, rep, roff, rf_off, rf_chunks, dmap, free_off,
-                                                      free_chunks, h);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    return p_read(h, s, n_distinct);
+        MPT_HIP_TRY(hipGetLastError());
+        return p_read(h, s, n_distinct);
+    });
 }
 
 extern "C" int mpt_pinned_assemble(int m, int64_t nnz, const int64_t *req_off, const int32_t *req_chunks, int t,
@@ -301,20 +303,22 @@ extern "C" int mpt_pinned_assemble(int m, int64_t nnz, const int64_t *req_off, c
                                    const int32_t *free_layout, int32_t *seqs, void *workspace,
                                    size_t workspace_bytes, void *stream) {
     mptlib::clear_error();
-    if (m < 1 || m > MPT_LAYOUT_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_LAYOUT_MAX_M);
-    if (nnz < 0 || t < 0 || n_distinct < 1 || n_distinct > m) return fail(MPT_E_INVALID, "nnz, t or n_distinct out of range");
-    if (!req_off || !dmap || !free_off || (nnz > 0 && (!req_chunks || !seqs || !free_layout)))
-        return fail(MPT_E_INVALID, "array arguments must not be NULL");
-    if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < sizeof(PHeader))
-        return fail(MPT_E_WORKSPACE, "workspace missing, misaligned or smaller than 256 bytes");
-    hipStream_t s = (hipStream_t)stream;
-    PHeader *h = (PHeader *)workspace;
-    k_p_header<<<1, 64, 0, s>>>(h, nullptr, 0);
-    {
-        LaunchScope ls("p_assemble", (double)nnz, s);
-        k_p_assemble<<<grid_for(m, 256), 256, 0, s>>>(m, t, n_distinct, req_off, req_chunks, dmap, free_off,
-                                                      free_layout, seqs, h);
-    }
-    MPT_HIP_TRY(hipGetLastError());
-    return p_read(h, s, nullptr);
+    return mptlib::guarded(__func__, [&]() -> int {
+        if (m < 1 || m > MPT_LAYOUT_MAX_M) return fail(MPT_E_INVALID, "m = %d outside [1, %d]", m, MPT_LAYOUT_MAX_M);
+        if (nnz < 0 || t < 0 || n_distinct < 1 || n_distinct > m) return fail(MPT_E_INVALID, "nnz, t or n_distinct out of range");
+        if (!req_off || !dmap || !free_off || (nnz > 0 && (!req_chunks || !seqs || !free_layout)))
+            return fail(MPT_E_INVALID, "array arguments must not be NULL");
+        if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < sizeof(PHeader))
+            return fail(MPT_E_WORKSPACE, "workspace missing, misaligned or smaller than 256 bytes");
+        hipStream_t s = (hipStream_t)stream;
+        PHeader *h = (PHeader *)workspace;
+        k_p_header<<<1, 64, 0, s>>>(h, nullptr, 0);
+        {
+            LaunchScope ls("p_assemble", (double)nnz, s);
+            k_p_assemble<<<grid_for(m, 256), 256, 0, s>>>(m, t, n_distinct, req_off, req_chunks, dmap, free_off,
+                                                          free_layout, seqs, h);
+        }
+        MPT_HIP_TRY(hipGetLastError());
+        return p_read(h, s, nullptr);
+    });
 }

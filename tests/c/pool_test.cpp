@@ -3,15 +3,26 @@
 // symbols come first), so that a stream that is being captured, a stale error
 // and a failing allocation can be played without a device. Kernels do not run;
 // what is checked is which way the results would have come back: through a
-// block (no copy is enqueued) or by a copy (the way without a block).
+// block (no copy is enqueued) or by a copy (the way without a block); and that a
+// call which runs out of host memory returns an error.
 // Exit status 0 when every check passed.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 
 #include "mpt.h"
+
+static bool no_memory = false;
+void *operator new(size_t n) {
+    void *p = no_memory ? nullptr : malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 static bool capturing = false, device_lost = false;
 static int stale = 0, copies = 0, allocations = 0;
@@ -100,6 +111,15 @@ int main() {
     const int before = copies;
     CHECK(calls() == 5 && copies == before + 5);
     CHECK(allocations == 1);
+    // host memory that runs out inside a call is an error of that call: no C++
+    // exception crosses the interface
+    int64_t window = 2, capacity = 5, cost = 0;
+    no_memory = true;
+    const int rc = mpt_cache_simulate(4, 8, 8, (int64_t *)arrays[0], (int64_t *)arrays[1], (int32_t *)arrays[2], 1,
+                                      &window, &capacity, &cost, nullptr, workspace, sizeof workspace, nullptr);
+    no_memory = false;
+    CHECK(rc == MPT_E_INTERNAL);
+    CHECK(strstr(mpt_last_error(), "mpt_cache_simulate") != nullptr);
     if (!failures) puts("all checks hold");
     return failures ? 1 : 0;
 }

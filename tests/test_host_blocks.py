@@ -1,5 +1,6 @@
-"""The pool of pinned host blocks when calls fail (tests/c/pool_test.cpp: the
-built libmpt.so on the CPU, with stand-ins for the HIP calls it makes)."""
+"""The pool of pinned host blocks when calls fail, and calls that run out of host
+memory (tests/c/pool_test.cpp: the built libmpt.so on the CPU, with stand-ins for
+the HIP calls it makes)."""
 import os
 import subprocess
 
