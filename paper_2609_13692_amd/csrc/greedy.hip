@@ -859,8 +859,17 @@ __global__ __launch_bounds__(256) void k_rac_dense(Rac R, int L) {
 constexpr int kTailThreads = 1024;
 // (pairs of the last round) x (live clusters) up to which the tail takes over
 // (20000: 8 rounds earlier, 270 us more in the tail and 240 us less before it at
-// m = 4096, and 415 against 200 us at 701 long requests)
+// m = 4096, and 415 against 200 us at 701 long requests), and (pairs of the last
+// round)^2 x (mean request length), for long lists: a round's merges share the
+// waves, so a merge takes the longer the more there are, where the chip's rounds
+// take as long as one merge. Whole hierarchies of m requests of k chunks over u
+// by the tail alone and by the chip's rounds alone, in us: m = 40, k = 500, u =
+// 2000 (24500) 629 and 690; 100, 100, 400 (28900) 351 and 391; 100, 150, 500
+// (43350) 461 and 614, with the tail after eight rounds of the chip 430; 200,
+// 100, 400 (115600) 626 and 548, so 478; 200, 500, 1000 3081 and 1495, so 1428;
+// 200, 5000, 10000 29700 and 12500, so 12500.
 constexpr int64_t kTailWork = 8192;
+constexpr int64_t kTailEntries = 40000;
 constexpr int kTailAcc = 3 * kTailLive;
 struct TailLds {
     int64_t bv[kTailLive];               // best value
@@ -1480,7 +1489,8 @@ extern "C" int mpt_greedy_hierarchy(int m, int64_t n_chunks, int64_t nnz, const 
             int64_t pairs = (m + 5) / 6;
             for (int round = 0;;) {
                 const int64_t live = m - n_rec;
-                const bool tail = live <= kTailLive && pairs * live <= kTailWork;
+                const bool tail = live <= kTailLive && pairs * live <= kTailWork &&
+                                  pairs * pairs * nnz <= kTailEntries * m;
                 if (tail) {
                     k_rac_live<<<1, kChainThreads, 0, s>>>(R);
                     k_rac_dense<<<(unsigned)live, 256, 0, s>>>(R, (int)live);

@@ -95,3 +95,15 @@ def test_lists_of_long_requests_with_popular_chunks():
         took[popular] = min(spent) * 1e3
     print(f"[gpu] lists: {took[0]:.0f} us, with popular chunks {took[4]:.0f} us", flush=True)
     assert took[4] < 1.5 * took[0]
+
+
+@pytest.mark.parametrize("k", [500, 2000])
+def test_hierarchies_of_long_requests(k):
+    """200 requests, few enough for one workgroup's rounds if they were short,
+    and 230, which start on the whole chip."""
+    took = {}
+    for m in (200, 230):
+        g = mpt.Greedy(uniform([k] * m, 2 * k, 3))
+        took[m] = best(g.hierarchy, passes=8)
+    print(f"[gpu] hierarchies k={k}: m=200 {took[200]:.0f} us, m=230 {took[230]:.0f} us", flush=True)
+    assert took[200] < 1.2 * took[230]
