@@ -224,9 +224,9 @@ extern "C" int mpt_ctx_build_weights(mpt_ctx *ctx, int m, int64_t n_chunks, int6
         // Inputs in this device's memory, outside the workspace: the build's
         // first kernel reads them in place and leaves the copies. Otherwise
         // they are copied first; a small instance in host memory goes into a
-        // pinned block instead, which the build reads in place too (one kernel
-        // that reads each input once: the build of at most 16384 chunks and
-        // slots). The arrays lie in the block as they do in the workspace.
+        // pinned block instead, which the build reads in place too (instances that
+        // fit one are built by one kernel that reads each input once). The arrays
+        // lie in the block as they do in the workspace.
         mptcore::InputCopy copy{};
         const int64_t *in_off = d_off, *in_w = d_w;
         const int32_t *in_chunks = d_chunks;

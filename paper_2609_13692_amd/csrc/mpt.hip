@@ -612,7 +612,7 @@ void dense_zeta_high(int m, int j, int K, int64_t *W, hipStream_t s) {
     }
 }
 
-// Small instances (n_chunks and nnz up to kSmallBuild): the checks, the
+// Small instances (kSmallBuild, kSmallSum): the checks, the
 // demand sets, the compaction and, FULL (m <= 12), the W table itself, by one
 // workgroup in one launch; the masks live in LDS. off_dst, chunks_dst and
 // w_dst, where given, receive copies of the inputs (the context keeps them),
@@ -621,9 +621,14 @@ void dense_zeta_high(int m, int j, int K, int64_t *W, hipStream_t s) {
 // result there itself saves the launch of one that copies it, 4 us a call).
 // Bound by latency: launches and a few dependent round trips. 4.4 us at m = 9
 // (36 slots, 64 chunks, with W) and at m = 16 (128 slots, 1000 chunks), where
-// the separate kernels took 15 us and up to eight more launches. The limit is
-// the LDS for the masks (64 KiB).
+// the separate kernels took 15 us and up to eight more launches. FULL it is the
+// faster side up to the LDS for the masks (64 KiB): a build of 16384 chunks and
+// 16384 slots takes 42 us at m = 12, by the separate kernels 63. Without W one
+// workgroup's work meets three wide launches at kSmallSum chunks and slots
+// together: m = 16, 10000 + 4000 38 and 40 us, 10000 + 8000 45 both, 16384 +
+// 16384 64 and 58; m = 23, 6000 + 8000 65 both, 10000 + 8000 71 and 69.
 constexpr int kSmallBuild = 16384;
+constexpr int kSmallSum = 16384;
 constexpr int kSmallThreads = 1024;
 template <bool FULL>
 __global__ __launch_bounds__(kSmallThreads) void k_build_small(
@@ -3273,9 +3278,10 @@ int build(int m, int64_t n_chunks, int64_t nnz, const int64_t *chunk_w, const in
     int64_t *list_w = (int64_t *)(ws + L.list_w);
 
     const bool dense = route == MPT_ROUTE_DENSE || (route == MPT_ROUTE_AUTO && dense_route_pays(m, nnz));
-    const bool small = n_chunks <= kSmallBuild && nnz <= kSmallBuild;
+    const bool with_w = m <= kZetaBits && !dense;              // one launch can do the whole build
+    const bool small = n_chunks <= kSmallBuild && nnz <= kSmallBuild && (with_w || n_chunks + nnz <= kSmallSum);
+    const bool full = small && with_w;
     bool zeroed = false;                                       // W, by the demand sets' launch
-    const bool full = small && m <= kZetaBits && !dense;       // the whole build in one launch
     std::optional<mptlib::HostSlot> slot;
     HeaderHead *post = small ? (HeaderHead *)slot.emplace(s).ptr() : nullptr;
     auto finish = [&]() -> int {

@@ -1,5 +1,6 @@
 """The builds at the edges of their routes: one workgroup up to 16384 chunks
-and slots (with the W table up to m = 12), several launches above; inputs in
+and 16384 slots with the W table (m up to 12), up to 16384 of both together
+without it, several launches above; inputs in
 device memory, in host memory (small and large) and inside the context's own
 workspace. W and the demand sets against the oracle's; every refused input is
 refused on either side of the limit."""
@@ -34,7 +35,8 @@ def check(inst, W, sig):
 
 
 SIZES = [(1, 1, 1), (2, 5, 0), (5, 0, 0), (12, LIMIT, LIMIT), (13, LIMIT, LIMIT), (12, LIMIT + 1, 100),
-         (12, 9000, LIMIT + 1), (14, LIMIT + 1, LIMIT), (13, 9000, LIMIT + 1), (6, 70, 300), (16, 4095, 64), (17, 40000, 900)]
+         (12, 9000, LIMIT + 1), (14, LIMIT + 1, LIMIT), (13, 9000, LIMIT + 1), (6, 70, 300), (16, 4095, 64), (17, 40000, 900),
+         (13, LIMIT - 300, 300), (13, LIMIT - 299, 300), (19, 6000, LIMIT - 6000), (19, 6000, LIMIT - 5999)]
 
 
 @pytest.mark.parametrize("m,u,nnz", SIZES)
@@ -55,6 +57,19 @@ def test_tables(m, u, nnz):
     ref = oracle.solve(inst)
     assert opt == ref["opt"] and np.array_equal(ctx.extract_orders(), ref["orders"])
     ctx.close()
+
+
+@pytest.mark.parametrize("m,u,nnz,one", [(12, LIMIT, LIMIT, True), (13, 8000, LIMIT - 8000, True),
+                                         (13, 8000, LIMIT - 7999, False), (20, LIMIT, LIMIT, False)])
+def test_one_workgroup_where_it_is_the_faster_side(m, u, nnz, one):
+    """20 requests over 16384 chunks and slots: 65 us by one workgroup, 58 by
+    the wide launches. The launches that ran, by their labels."""
+    p = mpt.Problem(family(m, u, nnz, 1))
+    p.build()
+    mpt.profile_begin()
+    p.build()
+    labels = mpt.profile_end()
+    assert ("build_init" not in labels) == one, labels
 
 
 @pytest.mark.parametrize("m", [7, 13])
