@@ -16,17 +16,20 @@ pytestmark = pytest.mark.gpu
 
 def instance(m, width, seed, ties=False):
     """Weights scaled by a power of two until sum_i w(R_i) is in the range of
-    the width (as far as a weight of at most 2^32 reaches)."""
+    the width; at the smallest m, where weights of at most 2^32 reach 64-bit
+    keys only so, with longer requests."""
     rng = np.random.default_rng([seed, m])
-    u = 10 if ties else 12 * m
-    sets = [rng.choice(u, size=int(rng.integers(0 if ties else 1, min(u, 14))), replace=False).tolist()
-            for _ in range(m)]
+    long = width == "u64" and m < 15
+    u = (20 if long else 10) if ties else 12 * m
+    longest = min(u, 70 if long else 14)
+    sets = [rng.choice(u, size=int(rng.integers(0 if ties else 1, longest)), replace=False).tolist() for _ in range(m)]
     w = np.ones(u, dtype=np.int64) if ties else rng.integers(1, 400, size=u, dtype=np.int64)
     total = int(sum(w[s].sum() for s in sets))
-    least = {"u32": 0, "f64": (1 << 20) - 1, "u64": 1 << (51 - m)}[width]
+    least, most = {"u32": (0, (1 << 20) - 1), "f64": ((1 << 20) - 1, 1 << (51 - m)), "u64": (1 << (51 - m), 1 << (61 - m))}[width]
     scale = 1
-    while total * scale < least and int(w.max()) * scale < 1 << 31:
+    while total * scale < least and int(w.max()) * scale <= 1 << 31:
         scale *= 2
+    assert least <= total * scale < most, (m, width, ties)
     return wl.from_sets(sets, w * scale, u)
 
 
