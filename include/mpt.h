@@ -274,8 +274,9 @@ int mpt_table_device(const mpt_ctx *ctx, int which, const void **dev_ptr, size_t
  *
  * These calls take any m in [1, MPT_GREEDY_MAX_M]; requests are identified
  * by index. Same conventions as above; they share one workspace of
- * mpt_greedy_workspace_bytes(m, n_chunks, nnz) bytes (about 8 m^2 + 32 nnz
- * + 8 n_chunks + 110 m bytes). Instances are validated as for
+ * mpt_greedy_workspace_bytes(m, n_chunks, nnz) bytes: 8 m^2 + max(8 min(m,
+ * 2048)^2, 16 nnz) + 20 nnz + 8 n_chunks + 112 m, and less than 8 KiB of
+ * padding. Instances are validated as for
  * mpt_build_weights.
  */
 #define MPT_GREEDY_MAX_M 16384
@@ -351,7 +352,11 @@ int mpt_spanning_tree_bound(int m, const int64_t *P, int64_t *mst_weight,
  * mpt_extract_orders or mpt_greedy_hierarchy with the request offsets.
  * Chunk ids must lie in [0, n_chunks); weights as above. The calls share one
  * workspace of mpt_layout_workspace_bytes(m, n_chunks, nnz, n_configs) bytes
- * (n_configs = 0 for the first two calls).
+ * (n_configs = 0 for the first two calls): 12 nnz + 8 n_chunks + 20 m, 8 per
+ * leaf of a tree of at least m and 1024 leaves (a power of two), per
+ * configuration 16 nnz + 12 m, and the largest of 16 max(nnz, n_chunks), 72 m
+ * past 4096 requests and, per configuration, 16 max(m, nnz) and 8 nnz + 24 (nnz
+ * rounded up to 1024); and less than 16 KiB of padding.
  */
 #define MPT_LAYOUT_MAX_M (1 << 24)
 #define MPT_CACHE_MAX_CONFIGS 256
@@ -423,6 +428,8 @@ int mpt_cache_simulate(int m, int64_t n_chunks, int64_t nnz, const int64_t *chun
  * sequence, then its pinned suffix. Requests with equal free sets thereby
  * share one free sequence, and their suffixes can share trie nodes.
  */
+/* 20 nnz + 36 m bytes (past 4096 requests at least 4 nnz + 108 m), and less
+ * than 8 KiB of padding. */
 size_t mpt_pinned_workspace_bytes(int m, int64_t nnz);
 
 /*

@@ -77,8 +77,14 @@ GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     const size_t mm = (size_t)m;
     size_t o = align256(sizeof(GHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
+    // the sort of long lists is over before the tail's dense matrix is written
+    const size_t shared = o, dm = std::min<size_t>(mm, kTailLive);
     L.keys1 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
     L.keys2 = take(8 * (size_t)std::max<int64_t>(nnz, 1));
+    const size_t keys_end = o;
+    o = shared;
+    L.dense = take(8 * dm * dm);
+    o = std::max(o, keys_end);
     L.rank = take(4 * (size_t)std::max<int64_t>(nnz, 1));
     L.sig = take(8 * (size_t)std::max<int64_t>(nnz, 1));   // the lists, then the D lists of long merges
     L.sig_slot = take(4 * (size_t)std::max<int64_t>(nnz, 1));
@@ -93,8 +99,6 @@ GLayout g_layout(int m, int64_t n_chunks, int64_t nnz) {
     L.touched = take(4 * mm);
     L.resc = take(4 * mm);
     L.live = take(4 * mm);
-    const size_t dm = std::min<size_t>(mm, kTailLive);
-    L.dense = take(8 * dm * dm);
     L.d_off = take(8 * (2 * mm));
     L.d_len = take(4 * (2 * mm));
     L.rec32 = take(4 * mm * kRec32);

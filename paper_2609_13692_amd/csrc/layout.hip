@@ -90,7 +90,6 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
     L.ord = take(4 * mm);
     L.rank = take(4 * mm);
-    L.recs = take(2 * seq_recs_bytes(m));
     L.lcp = take(4 * mm);
     L.base = take(8 * (mm + 1));
     L.pn = take(4 * nz);
@@ -98,19 +97,28 @@ LLayout l_layout(int m, int64_t n_chunks, int64_t nnz, int n_cfg) {
     L.mtree = take(8 * (size_t)L.mpad);          // min segment tree over the LCPs
     L.crank = take(4 * (size_t)n_chunks);
     L.cinv = take(4 * (size_t)n_chunks);
-    L.keys = take(8 * kn);
-    L.keys2 = take(8 * kn);
     L.sched = take(4 * nc * mm);
     L.log_off = take(8 * nc * mm);
     L.logs = take(4 * nc * nz);
     L.acc_start = take(4 * nc * nz);
     L.prev = take(4 * nc * nz);
     L.next = take(4 * nc * nz);
+    // the request sort is over before the first key sort, and those before the
+    // sorted blocks of the logs are written
+    const size_t shared = o;
+    L.recs = take(2 * seq_recs_bytes(m));
+    const size_t recs_end = o;
+    o = shared;
+    L.keys = take(8 * kn);
+    L.keys2 = take(8 * kn);
+    const size_t sorts_end = std::max(o, recs_end);
+    o = shared;
     L.wsuf = take(8 * nc * nz);
     L.snext = take(4 * nc * nblk * 1024);
     L.ssum = take(8 * nc * nblk * 1024);
     L.bnext = take(4 * nc * nblk * 1024);
     L.bsum = take(8 * nc * nblk * 1024);
+    o = std::max(o, sorts_end);
     L.cfg_win = take(8 * nc);
     L.cfg_cap = take(8 * nc);
     L.cfg_off = take(4 * (nc + 1));

@@ -49,11 +49,16 @@ PLayout p_layout(int m, int64_t nnz) {
     const size_t mm = (size_t)m, nz = (size_t)std::max<int64_t>(nnz, 1);
     size_t o = align256(sizeof(PHeader));
     auto take = [&](size_t bytes) { size_t at = o; o = align256(o + std::max<size_t>(bytes, 1)); return at; };
+    // the sort of the free slots is over before the requests are sorted
+    const size_t shared = o;
     L.keys = take(8 * nz);
     L.keys2 = take(8 * nz);
+    const size_t keys_end = o;
+    o = shared;
+    L.recs = take(2 * seq_recs_bytes(m));
+    o = std::max(o, keys_end);
     L.rf_off = take(8 * (mm + 1));
     L.rf_chunks = take(4 * nz);
-    L.recs = take(2 * seq_recs_bytes(m));
     L.ord = take(4 * mm);
     L.gstart = take(4 * mm);
     L.lead = take(4 * mm);

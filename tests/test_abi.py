@@ -194,3 +194,25 @@ def test_layout_workspace_and_host_validation(lib):
     assert lib.mpt_cache_simulate(3, 5, 4, dummy, dummy, dummy, 0, win, cap, out, None, ws, 1 << 30, None) == -1
     assert lib.mpt_cache_simulate(3, 5, 4, dummy, dummy, dummy, 1, win, cap, out, None, ws, 1 << 30, None) == -1
     assert b"negative" in lib.mpt_last_error()
+
+
+def test_workspace_sizes_are_the_documented_ones(lib):
+    """The header's formulas for the greedy, layout and pinned workspaces; the
+    buffers that are never live at the same time share their bytes."""
+    from paper_2609_13692_amd import mpt
+    pad = 16384
+    for m, u, nnz in ((1, 1, 0), (300, 900, 2400), (2048, 6000, 16384), (4096, 12288, 32768), (4097, 9000, 40000),
+                      (16384, 60000, 500000), (200, 10000, 1000000)):
+        want = 8 * m * m + max(8 * min(m, 2048) ** 2, 16 * nnz) + 20 * nnz + 8 * u + 112 * m
+        assert want <= mpt.mpt_greedy_workspace_bytes(m, u, nnz) < want + pad // 2, (m, u, nnz)
+        leaves = 1024
+        while leaves < m:
+            leaves *= 2
+        for c in (0, 1, 30):
+            slots = -(-max(nnz, 1) // 1024) * 1024
+            per = c * (16 * nnz + 12 * m)
+            shared = max(16 * max(nnz, u, c * max(m, nnz)), 72 * m if m > 4096 else 0, c * (8 * nnz + 24 * slots))
+            want = 12 * nnz + 8 * u + 20 * m + 8 * leaves + per + shared
+            assert want <= mpt.mpt_layout_workspace_bytes(m, u, nnz, c) < want + pad, (m, u, nnz, c)
+        want = 4 * nnz + 36 * m + max(16 * nnz, 72 * m if m > 4096 else 0)
+        assert want <= lib.mpt_pinned_workspace_bytes(m, nnz) < want + pad // 2, (m, nnz)
