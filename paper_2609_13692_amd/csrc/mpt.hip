@@ -2,10 +2,14 @@
 //
 // Phases (declared in include/mpt.h):
 //   1. mpt_build_weights: demand sets S_x, then W(B) = w(I(B)) for all 2^m
-//      request subsets in ONE pass over HBM (each output element is written
-//      once and the dense table is never read back).
-//   2. mpt_solve_exact: the Section 3.1 subset DP in cost form, one launch
-//      per popcount layer, with argmin splits.
+//      request subsets, from the list of held chunks in one pass over HBM (each
+//      output element is written once and never read back), or for long lists
+//      by a scatter and an in-place superset zeta.
+//   2. mpt_solve_exact: the Section 3.1 subset DP in cost form with argmin
+//      splits: up to 12 requests by one workgroup, above by rows of the table,
+//      level by level in the row's request count (2^9-entry rows up to 23
+//      requests: short_rows.h); costs too large to pack one popcount layer at a
+//      time.
 //   3. mpt_extract_orders: per-request chunk orders from the hierarchy.
 //
 // Everything here is integer arithmetic (int64 weights and costs, uint32
@@ -65,7 +69,7 @@ struct WsHeader {
     uint32_t err;          // OR of ERR_* bits
     uint32_t n_list;       // entries of the compact (S_x, w) list
     int64_t zero_weight;   // total weight of chunks that no request holds
-    int64_t total;         // sum_i w(R_i) = sum_i W({i}) (saturated)
+    int64_t total;         // sum_i w(R_i) = sum_i W({i}) (a solve that reads it off W saturates)
     int64_t pad[29];
 };
 static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
@@ -159,11 +163,10 @@ template <bool ZERO>
 __global__ void k_demand_sets(int m, int64_t n_chunks, int64_t nnz, const int64_t *req_off,
                               const int32_t *req_chunks, uint32_t *sig, WsHeader *h, int64_t n, int64_t *W) {
     if constexpr (ZERO) {
-        longlong2 *p = reinterpret_cast<longlong2 *>(W);     // (W is 16-byte aligned)
+        longlong2 *p = reinterpret_cast<longlong2 *>(W);     // (W is 16-byte aligned, n = 2^m even)
         const longlong2 z = make_longlong2(0, 0);
         for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n / 2; i += (int64_t)gridDim.x * blockDim.x)
             p[i] = z;
-        if (n == 1 && blockIdx.x == 0 && threadIdx.x == 0) W[0] = 0;
     }
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < nnz; j += (int64_t)gridDim.x * blockDim.x) {
         // request of slot j: the last i with req_off[i] <= j
@@ -268,12 +271,12 @@ __global__ __launch_bounds__(kCompactThreads) void k_compact(int64_t n_chunks, i
     }
 }
 
-// W table, one workgroup per tile of 2^13 consecutive subsets that share the
-// high bits H = tile id (for m < 13 one tile whose missing request bits no
+// W table, one workgroup per tile of 2^12 consecutive subsets that share the
+// high bits H = tile id (for m < 12 one tile whose missing request bits no
 // chunk holds). A chunk reaches W(H|L) iff H|L is inside S_x, i.e. iff S_x's
 // high part contains H and its low part contains L. So the tile keeps
 // f(L) = sum of w(x) over chunks whose high part contains H and whose low
-// part equals L, and a superset-sum (zeta) over the 13 low bits turns f into
+// part equals L, and a superset-sum (zeta) over the 12 low bits turns f into
 // W. The zeta over the high bits is thereby done on the sparse list, and the
 // dense table is written exactly once and never read.
 // The zeta over the low bits: bits 0..4 are also summed on the sparse list

@@ -38,8 +38,11 @@ __device__ inline bool seq_less_tail(int a, int b, const int64_t *off, const int
 // are validated to lie in [0, n_chunks)), so that the word order is the
 // sequence order on those chunks with a proper prefix first; sequences equal
 // there are ordered by length, or by index, or, when both go on past them, by
-// seq_less_tail. m^2 comparisons with no dependent stages: 16 us at m = 4096
-// and four times that at 8192, where the merges take three launches of 11 us.
+// seq_less_tail. m^2 comparisons with no dependent stages, 16 us at m = 4096. A
+// layout cost takes, by ranks and by merges: 51 and 62 us at m = 4096, 57 and 65
+// at 5000, 64 and 65 at 6000, 76 and 66 at 8192; where all requests share their
+// first 16 chunks, so that most comparisons read the sequences, 217 and 306 at
+// 4096, 637 and 329 at 5000. The line keeps clear of the latter.
 constexpr int kSeqRankMax = 4096;
 constexpr int kSeqRankTile = 256;         // requests i per workgroup, one per thread
 constexpr int kSeqRankTileY = 64;         // requests j per workgroup, staged in LDS

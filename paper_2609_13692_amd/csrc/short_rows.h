@@ -2,14 +2,14 @@
 // 2^9 entries (included by mpt.hip, which describes the scheme and the keys).
 //
 // With 2^12-entry rows an instance of m = 13 .. 21 requests has few rows per
-// level (at most 126 for 256 CUs) and a level's time is the finishing of one row (10 in-row levels and
-// 3^9 block convolutions on one CU, 30 us on 32-bit keys, 41 us on 64-bit
-// ones), whatever the number of CUs. With 2^9 entries a row has 7 in-row
+// level (at most 126 for 256 CUs) and a level's time is the finishing of one row
+// (10 in-row levels and 3^9 block convolutions on one CU, 30 us on 32-bit keys,
+// 41 us on 64-bit ones), whatever the number of CUs. With 2^9 entries a row has 7 in-row
 // levels and 3^6 convolutions, there are eight times as many rows, and one
 // wave takes a row pair by itself in four steps (lifted on the top middle
 // bit: 3^5 = 243 base steps in 64 lanes of at most 4), so that the pairs need
 // no barrier. Against that, a row pair carries 3^9 candidates for two rows of
-// traffic instead of 3^12, which is what counts for large m (kShortRowsMaxM).
+// traffic instead of 3^12, which is what counts for large m (short_rows_pay).
 //
 // Tables: one row-major table T of tagged entries (C(X) << m | X in the
 // representation of Key<E>; E = uint32_t, the narrow keys: C(X) << 9 | X_L).
@@ -166,7 +166,7 @@ template <class E> __device__ inline Piece clear_tags(Piece v, uint32_t keep) {
     return v;
 }
 
-// W of row S_H, three entries per thread (in entry order), before the work
+// W of row S_H, two entries per thread (in entry order), before the work
 // whose waits then cover these loads
 constexpr int W_PER = (ROW + THREADS - 1) / THREADS;
 template <class E> __device__ inline void load_w(int m, uint32_t sh, const int64_t *__restrict__ W, Weight<E> (&w)[W_PER]) {

@@ -229,11 +229,12 @@ def order_edge_instance(m, seed):
     return wl.from_sets(sets, [int(x) for x in rng.integers(1, 9, 64)], 64)
 
 
-@pytest.mark.parametrize("m", [300, 4096, 17000])
+@pytest.mark.parametrize("m", [300, 4096, 4097, 17000])
 def test_request_order_edge_cases(m):
     """The request order behind the trie cost and the DFS order, on ties,
-    prefixes and sequences equal on their first 8 chunks: up to 16384
-    requests it comes from all-pairs ranks, above from the bitonic sort."""
+    prefixes and sequences equal on their first 8 chunks: up to 4096
+    requests it comes from all-pairs ranks, above from tiles merged eight runs
+    at a time."""
     inst = order_edge_instance(m, seed=m)
     lay = np.asarray(inst.req_chunks, dtype=np.int32)
     L = mpt.Layouts(inst)
