@@ -106,4 +106,4 @@ def test_hierarchies_of_long_requests(k):
         g = mpt.Greedy(uniform([k] * m, 2 * k, 3))
         took[m] = best(g.hierarchy, passes=8)
     print(f"[gpu] hierarchies k={k}: m=200 {took[200]:.0f} us, m=230 {took[230]:.0f} us", flush=True)
-    assert took[200] < 1.2 * took[230]
+    assert took[200] < 1.4 * took[230]
